@@ -338,3 +338,179 @@ def tolerance(case):
     if kind == "loss_fwd" or not bf16:          # fp32 results: 1.7e-7 / 1.9e-6 at most (convolution weight gradients)
         return {"rel": 1e-6, "max": 1e-5}
     return {"rel": 7e-3, "max": 1.6e-2}         # one rounding to bf16: 1.9e-3 / 3.9e-3
+
+
+# ---- the same results in 64 bits, by plain torch -------------------------------------------------
+
+def _exact_attn(case, s):
+    """Node by node: the queries of a node see the tokens of its ancestors (and the visible cached keys) whole and its own
+    tokens causally."""
+    n, hq, hkv, d = case["n"], case["hq"], case["hkv"], case["d"]
+    parent, seg = _tree(case["shape"], n, case["tree_seed"])
+    n_prefix = case.get("n_prefix", 0)
+    if work(case)["flops"] > 1e14:
+        return None
+    q, k, v = (x.double().transpose(0, 1) for x in s["qkv"])                   # [heads, tokens, d]
+    d_o = None if s["d_o"] is None else s["d_o"].double().transpose(0, 1)
+    seen = []
+    if n_prefix:
+        kp, vp = (x.double().transpose(0, 1) for x in s["prefix"])
+        k, v = torch.cat([kp, k], 1), torch.cat([vp, v], 1)
+        seen = [_cuda(np.flatnonzero(_prefix_visible(n_prefix, case["tree_seed"])))]
+    start = np.concatenate([[0], np.cumsum(seg)])
+    o, dq = torch.empty_like(q), torch.zeros_like(q)
+    lse = torch.empty(hq, n, dtype=torch.float64, device="cuda")
+    dk, dv = torch.zeros_like(k), torch.zeros_like(v)
+    scale, g = d ** -0.5, hq // hkv
+    for i in range(len(seg)):
+        up, a = [], i
+        while a >= 0:
+            up.append(torch.arange(n_prefix + start[a], n_prefix + start[a + 1], device="cuda"))
+            a = int(parent[a])
+        keys = torch.cat(seen + up[::-1])
+        past = len(keys) - int(seg[i])                                         # keys in front of the node
+        step = max(1, (1 << 26) // max(1, len(keys)))
+        for h in range(hkv):
+            kh, vh, hs = k[h, keys], v[h, keys], slice(h * g, (h + 1) * g)
+            dkh, dvh = torch.zeros_like(kh), torch.zeros_like(vh)
+            for a in range(int(start[i]), int(start[i + 1]), step):
+                b = min(a + step, int(start[i + 1]))
+                last = past + torch.arange(a, b, device="cuda") - int(start[i])
+                hidden = torch.arange(len(keys), device="cuda")[None, :] > last[:, None]
+                for hh in range(hs.start, hs.stop):
+                    p = (q[hh, a:b] @ kh.T).mul_(scale).masked_fill_(hidden, -float("inf"))
+                    lse[hh, a:b] = p.logsumexp(1)
+                    p = p.sub_(lse[hh, a:b, None]).exp_()
+                    o[hh, a:b] = p @ vh
+                    if d_o is None:
+                        continue
+                    up_o = d_o[hh, a:b]
+                    dvh += p.T @ up_o
+                    ds = (up_o @ vh.T).sub_((up_o * o[hh, a:b]).sum(1, keepdim=True)).mul_(p).mul_(scale)
+                    dq[hh, a:b] = ds @ kh
+                    dkh += ds.T @ q[hh, a:b]
+            dk[h].index_add_(0, keys, dkh)
+            dv[h].index_add_(0, keys, dvh)
+    out = (o.transpose(0, 1), lse)
+    if d_o is not None:
+        dq, dk, dv = (x.transpose(0, 1) for x in (dq, dk, dv))
+        out += (dq, dk[n_prefix:], dv[n_prefix:]) + ((dk[:n_prefix], dv[:n_prefix]) if n_prefix else ())
+    return tuple(x.contiguous() for x in out)
+
+
+def _exact_loss(case, s):
+    z, target, w = s["logits"], s["target"].long(), s["weight"].double()
+    logp, lse, grad = [], [], []
+    for a in range(0, len(z), 512):
+        zr, t = z[a:a + 512].double(), target[a:a + 512, None]
+        lse.append(zr.logsumexp(1))
+        logp.append(zr.gather(1, t)[:, 0] - lse[-1])
+        if case["kind"] == "loss_train":
+            zr.sub_(lse[-1][:, None]).exp_().scatter_add_(1, t, torch.full(t.shape, -1.0, dtype=zr.dtype, device="cuda"))
+            grad.append(zr.mul_(w[a:a + 512, None]))
+    logp, lse = torch.cat(logp), torch.cat(lse)
+    out = (logp, lse, -(w * logp).sum().reshape(1))
+    return out + (torch.cat(grad),) if grad else out
+
+
+def _exact_rope(s, base=1.0e6):
+    out = []
+    for x in (s["q"].double(), s["k"].double()):
+        half = x.shape[2] // 2
+        freq = base ** (-torch.arange(half, dtype=torch.float64, device="cuda") / half)
+        ang = (s["pos"].double()[:, None] * freq)[:, None] * (-1.0 if s["inverse"] else 1.0)
+        lo, hi, c, sn = x[..., :half], x[..., half:], ang.cos(), ang.sin()
+        out.append(torch.cat([lo * c - hi * sn, hi * c + lo * sn], -1))
+    return tuple(out)
+
+
+def _exact_conv(s):
+    x, w, dy, pred = s["x"].double(), s["w"].double(), s["dy"].double(), s["pred"].long()
+    n, taps = len(x), w.shape[1]
+    at, back = [], torch.arange(n, device="cuda")
+    for _ in range(taps):                                                      # tokens that have an m-th predecessor, and which
+        rows = torch.nonzero(back >= 0)[:, 0]
+        at.append((rows, back[rows]))
+        back = torch.where(back >= 0, pred[back.clamp(min=0)], back)
+    pre = torch.zeros_like(x) if s["b"] is None else s["b"].double().expand_as(x).clone()
+    for m, (rows, src) in enumerate(at):
+        pre.index_add_(0, rows, x[src] * w[:, taps - 1 - m])
+    sig = torch.sigmoid(pre)
+    g = dy * sig * (1 + pre * (1 - sig)) if s["silu"] else dy
+    dx, dw = torch.zeros_like(x), torch.zeros_like(w)
+    for m, (rows, src) in enumerate(at):
+        dx.index_add_(0, src, g[rows] * w[:, taps - 1 - m])
+        dw[:, taps - 1 - m] = (g[rows] * x[src]).sum(0)
+    return pre * sig if s["silu"] else pre, dx, dw, None if s["b"] is None else g.sum(0)
+
+
+def _exact_gdn(case, s):
+    """The token recurrence, and its reverse with the states of one node at a time."""
+    n, hk, hv, dim = case["n"], case["hk"], case["hv"], 128
+    if n > (24576 if case["kind"] == "gdn_fwd" else 17000):
+        return None
+    parent, seg = _tree(case["shape"], n, case["tree_seed"])
+    start = np.concatenate([[0], np.cumsum(seg)])
+    heads = torch.arange(hv, device="cuda") // (hv // hk)
+    q, k, v, decay, beta = s["q"].double()[:, heads], s["k"].double()[:, heads], s["v"].double(), s["g"].double().exp(), s["beta"].double()
+    scale = dim ** -0.5
+    first = torch.zeros(hv, dim, dim, dtype=torch.float64, device="cuda") if s["state"] is None else s["state"].double()
+
+    def walk(i, state):
+        states = torch.empty(int(seg[i]) + 1, hv, dim, dim, dtype=torch.float64, device="cuda")
+        states[0] = state
+        for j in range(int(seg[i])):
+            t = int(start[i]) + j
+            nxt = torch.mul(states[j], decay[t, :, None, None], out=states[j + 1])
+            delta = beta[t, :, None] * (v[t] - torch.bmm(k[t, :, None], nxt)[:, 0])
+            nxt.baddbmm_(k[t, :, :, None], delta[:, None])
+        return states
+
+    ends, o = [], torch.empty_like(v)
+    for i in range(len(seg)):
+        states = walk(i, first if parent[i] < 0 else ends[parent[i]])
+        a, b = int(start[i]), int(start[i + 1])
+        o[a:b] = scale * torch.matmul(q[a:b, :, None], states[1:])[:, :, 0]
+        ends.append(states[-1].clone())
+    if case["kind"] == "gdn_fwd":
+        return o if s["state"] is None else (o, ends[-1][None])
+    d_o = s["d_o"].double()
+    d_end = [torch.zeros_like(first) for _ in seg]
+    if s["d_state"] is not None:
+        d_end[-1] += s["d_state"][0].double()
+    d_first = torch.zeros_like(first)
+    dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
+    dg, dbeta = torch.empty_like(beta), torch.empty_like(beta)
+    for i in reversed(range(len(seg))):
+        states, r = walk(i, first if parent[i] < 0 else ends[parent[i]]), d_end[i]
+        for j in reversed(range(int(seg[i]))):
+            t = int(start[i]) + j
+            bt, kt = beta[t, :, None], k[t, :, :, None]
+            old = states[j] * decay[t, :, None, None]
+            miss = v[t] - torch.bmm(kt.mT, old)[:, 0]
+            r = torch.baddbmm(r, scale * q[t, :, :, None], d_o[t, :, None])
+            dq[t] = scale * torch.bmm(states[j + 1], d_o[t, :, :, None])[:, :, 0]
+            dd = torch.bmm(kt.mT, r)[:, 0]
+            dv[t], dbeta[t] = bt * dd, (dd * miss).sum(1)
+            dk[t] = torch.bmm(r, (bt * miss)[:, :, None])[:, :, 0] - bt * torch.bmm(old, dd[:, :, None])[:, :, 0]
+            r = r - kt * (bt * dd)[:, None]
+            dg[t] = (r * old).sum((1, 2))
+            r = r * decay[t, :, None, None]
+        if parent[i] < 0:
+            d_first += r
+        else:
+            d_end[parent[i]] += r
+    dq, dk = (x.unflatten(1, (hk, hv // hk)).sum(2) for x in (dq, dk))
+    return (dq, dk, dv, dg, dbeta) + (() if s["state"] is None else (d_first,))
+
+
+def exact(case, seed):
+    """What run returns for these inputs, in float64; None where it would take too long."""
+    s, kind = prepare(case, seed), case["kind"]
+    if kind.startswith("attn"):
+        return _exact_attn(case, s)
+    if kind.startswith("loss"):
+        return _exact_loss(case, s)
+    if kind == "rope":
+        return _exact_rope(s)
+    return _exact_conv(s) if kind == "conv_train" else _exact_gdn(case, s)
