@@ -185,8 +185,6 @@ __global__ __launch_bounds__(G_THREADS) void gdn_prepare_kernel(GdnArgs a) {
         const float a0 = j < i ? kk[r] * dec : 0.f;
         am[i][j] = bet[i] * a0;
         if constexpr (BWD) {
-          a.f32.a0[op * (GC * GC) + i * GC + j] = a0;
-          a.f32.p[op * (GC * GC) + i * GC + j] = a.scale * qk[r] * dec;
           // element (row jt, column it) of the transposed tile: key token jt, query token it
           const int jt = jb * 32 + (r >> 2) * 8 + hf * 4 + (r & 3), it = ib * 32 + c;
           a.rev[op * REV_ELEMS + REV_PT + jt * GC + it] = (__bf16)(jt <= it ? a.scale * kq[r] * __expf(gam[it] - gam[jt]) : 0.f);
@@ -202,8 +200,6 @@ __global__ __launch_bounds__(G_THREADS) void gdn_prepare_kernel(GdnArgs a) {
         const int i = ib * 32 + (r >> 2) * 8 + hf * 4 + (r & 3);
         am[i][j] = 0.f;
         if constexpr (BWD) {
-          a.f32.a0[op * (GC * GC) + i * GC + j] = 0.f;
-          a.f32.p[op * (GC * GC) + i * GC + j] = 0.f;
           a.rev[op * REV_ELEMS + REV_PT + (jb * 32 + (r >> 2) * 8 + hf * 4 + (r & 3)) * GC + ib * 32 + c] = (__bf16)0.f;
         } else {
           pout[i * GC + j] = (__bf16)0.f;
@@ -299,16 +295,12 @@ __global__ __launch_bounds__(G_THREADS) void gdn_prepare_kernel(GdnArgs a) {
 #pragma unroll
     for (int r = 0; r < 16; r++) t21[r] = -t21[r];
     if constexpr (BWD) {
-      // T itself, for the finish kernel's transposed solve: the diagonal blocks (row 32 hf + i, column lane), T21, and
-      // the zero block
-      float* tg = a.f32.t + op * (GC * GC);
+      // T itself, for the finish kernel's transposed solve: the diagonal blocks and T21
+      float* tg = a.f32.t + op * GDN_T_ELEMS;
 #pragma unroll
-      for (int i = 0; i < 32; i++) tg[(32 * hf + i) * GC + lane] = x[i];
+      for (int i = 0; i < 32; i++) tg[2048 * hf + 32 * i + c] = x[i];
 #pragma unroll
-      for (int r = 0; r < 16; r++) {
-        tg[(32 + (r >> 2) * 8 + 4 * hf + (r & 3)) * GC + c] = t21[r];
-        tg[(2 * r + hf) * GC + 32 + c] = 0.f;
-      }
+      for (int r = 0; r < 16; r++) tg[1024 + 32 * ((r >> 2) * 8 + 4 * hf + (r & 3)) + c] = t21[r];
     }
     if constexpr (!BWD) stage_v_rows();
   } else {

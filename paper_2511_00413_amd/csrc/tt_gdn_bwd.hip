@@ -16,15 +16,15 @@
 //
 // Kernels (the first three live in tt_gdn.hip with the forward's):
 //   gdn_prepare_kernel<true>   per (chunk, head): the forward walk's bf16 record, the reverse walk's bf16 record
-//                              (Kd, -W^T, Qg^T, P^T, dO^T) and gamma, A0, P unrounded
+//                              (Kd, -W^T, Qg^T, P^T, dO^T) and gamma and (I + A)^-1 unrounded
 //   gdn_scan_kernel<true>      (32 value columns, head): the forward scan without its output; saves S0 and Vn
 //                              of every chunk (bf16)
 //   gdn_rscan_kernel           (32 value columns, head): reverse walk in the forward scan's form (bf16 matrix
 //                              instruction, fp32 state gradient in accumulators); saves dS1 and dVn (bf16)
-//   gdn_bwd_finish_kernel      per (chunk, head): everything else: products on the bf16 matrix instruction (fp32
-//                              accumulation) through LDS slabs, the transposed solve with one lane per column
-//                              and all element-wise work in fp32; dq / dk per value head in fp32
-//   gdn_bwd_group_sum_kernel   sums dq / dk over the value heads that share a key head, rounds to bf16
+//   gdn_bwd_finish_kernel      per (chunk, key head): everything else: products on the bf16 matrix instruction (fp32
+//                              accumulation), the transposed solve as a product with the inverse and all element-wise
+//                              work in fp32; dq / dk summed over the key head's value heads in registers
+//   gdn_bwd_group_sum_kernel   calls with few chunks: sums fp32 dq / dk over the value heads, rounds to bf16
 #include <hip/hip_runtime.h>
 #include <algorithm>
 #include "tt_internal.h"
@@ -37,13 +37,11 @@ namespace {
 constexpr int GC = TT_GDN_CHUNK;     // 64
 constexpr int GD = 128;
 constexpr int BT = 256;
-constexpr int KS = 64;               // k-values per LDS slab of the finish kernel's products
 
 struct BwdWs {
   GdnChunkOps ops;
   GdnBwdSaved sv;
-  __bf16* x;         // per (head, chunk) [64][256]: [dW] on the way in, [dVb | dKb] after the transposed solve
-  float* dqh;        // [N][hv_n][128] per-value-head dq, dk (the heads of the pass)
+  float* dqh;        // split calls only: [N][hv_n][128] per-value-head dq, dk (the heads of the pass)
   float* dkh;
 };
 struct KArgs {
@@ -57,553 +55,527 @@ __device__ __forceinline__ float4 ld4(const float* p) { return *(const float4*)p
 __device__ __forceinline__ int tile_row(int r, int hf) { return (r >> 2) * 8 + 4 * hf + (r & 3); }
 
 // ---- per-chunk finish ----------------------------------------------------------------------------------
-// Products C (64 x N) += A (64 x K) B (K x N) of a workgroup on the bf16 matrix instruction, fp32 accumulation
-// (slab_product below).  Nearly every operand is bf16 in memory already; only the two 64 x 64 matrices that the
-// kernel forms itself (dP scale D and dA beta D) are rounded here.  The operands go through LDS slabs of KS
-// k-values, brought in by the loaders that follow.  Wave w holds, in accumulator layout, N = 128: tiles (row
-// block t, column block w), t = 0, 1;  N = 64: the tile (row block w & 1, column block w >> 1).
-template <int N>
-struct TileMap {
-  static constexpr int TPW = N / 64;                     // tiles per wave
-  __device__ static int ib(int w, int t) { return N == 128 ? t : (w & 1); }
-  __device__ static int jb(int w) { return N == 128 ? w : (w >> 1); }
-};
+// One workgroup of four waves per (chunk, key head); it goes through the value heads of the key head one after the
+// other and keeps dq and dk, which are sums over them, in accumulator registers (SPLIT: one value head per workgroup, dq /
+// dk of every head in fp32 to memory, summed by gdn_bwd_group_sum_kernel).  What bounds it is memory: about 190 KB of
+// operands per (chunk, value head), of which every byte is read once.  To that end everything that shares an operand is
+// done while that operand is on chip:
+//   1. one pass over the four blocks of 32 value columns with S0, dS1, dO, Vn and dVn of the block in LDS:
+//      dW = -dVn S0^T, dQg = dO S0^T, dKd = Vn dS1^T, dP = dO Vn^T and <dS1, S0>
+//   2. [dVb | dKb]^T = [dVn | dW]^T T on both halves of the split T; the result stays in LDS.  A wave's dW
+//      accumulators are, as bf16, the A fragments of its own column block
+//   3. dA = -[dVb | dKb] [U | W]^T, dv and dbeta's part from dVb
+//   4. K K^T and Q K^T again (K and Q stay in LDS for all heads; cheaper than 32 KB of A0 and P per head out and in):
+//      row and column sums of dP o P + dA o A in registers, dP scale D and dA beta D as bf16 to LDS
+//   5. dq += (dP scale D) K;  dk += (dP scale D)^T Q + (dA beta D) K + (dA beta D)^T K + beta eg dKb
+// LDS 80 KB: two workgroups per compute unit, one's loads beside the other's products.  16406 tokens, 16 / 32 heads: 0.49
+// ms at 2.3 GB (4.7 TB/s; a large copy reaches 5.1).  With one value head per workgroup, fp32 dq / dk through memory,
+// A0 and P from memory and S0, dS1, dO, Vn read once per product it was 0.86 ms at 4.9 GB and 0.12 ms for the sum.
+// Register r of a wave's tile (row block t, column block w) of a 64 x 128 result: row 32 t + tile_row(r), column
+// 32 w + lane % 32; of a 64 x 64 result: row block w & 1, column block w >> 1.
+constexpr int PG = GD + 8;                               // LDS pitches (elements): rows 16-byte aligned, 8 elements of
+constexpr int PK = GC + 8;                               // padding against bank conflicts
 
-// LDS slab layouts (bf16).  "k-major": [k][row or column], the orientation in which most operands arrive (a
-// 16-byte piece of memory holds 8 rows / columns of one k); fragments come out of it through the transposing LDS
-// read.  "row-major": [row][k] for A operands whose memory has k contiguous; fragments are plain 16-byte reads.
-// Pitches (elements): rows 16-byte aligned, 8 elements of padding against bank conflicts.
-constexpr int PK_A = GC + 8;                              // k-major A slab: KS rows of 64 (+8)
-constexpr int PR_A = KS + 8;                              // row-major A slab: 64 rows of KS (+8)
-template <int N> constexpr int pitch_b() { return N + 8; } // k-major B slab: KS rows of N (+8)
-constexpr int AS_ELEMS = KS * PK_A > GC * PR_A ? KS * PK_A : GC * PR_A;
-
-// ---- operand loaders ---------------------------------------------------------------------------------------
-// A loader brings one KS-wide slab of an operand from memory into registers (load) and from there into the LDS
-// slab (store).  Memory is read in 16-byte pieces.  KMAJOR tells the layout of an A loader's slab.
-
-// Vn / dVn in fragment order, element (token, value column).  As A (k-major): (i = token, k = column).  As B:
-// (k = column, j = token).  One piece = 8 tokens of one column: tokens base .. base + 3 and base + 8 .. base + 11.
-template <int PITCH>
-struct FragLoader {
-  static constexpr bool KMAJOR = true;
-  const __bf16* p;
-  struct Regs { bf16x8 v[KS * GC / 8 / BT]; };
-  __device__ __forceinline__ void load(int k0, int tid, Regs& r) const {
-#pragma unroll
-    for (int q = 0; q < KS * GC / 8 / BT; q++) {
-      const int piece = tid + q * BT, cl = piece % KS, g = piece / KS;     // column inside the slab; (half, t, hf)
-      const int col = k0 + cl;
-      r.v[q] = *(const bf16x8*)(p + ((((size_t)(col >> 5) * 4 + (g >> 1)) * 64 + (g & 1) * 32 + (col & 31)) << 3));
-    }
-  }
-  __device__ __forceinline__ void store(__bf16* lds, int tid, const Regs& r, int = 0) const {
-#pragma unroll
-    for (int q = 0; q < KS * GC / 8 / BT; q++) {
-      const int piece = tid + q * BT, cl = piece % KS, g = piece / KS;
-      const int base = 32 * (g >> 2) + 16 * ((g >> 1) & 1) + 4 * (g & 1);
-      __bf16* d = lds + cl * PITCH + base;
-      *(bf16x4*)d = __builtin_shufflevector(r.v[q], r.v[q], 0, 1, 2, 3);
-      *(bf16x4*)(d + 8) = __builtin_shufflevector(r.v[q], r.v[q], 4, 5, 6, 7);
-    }
-  }
+struct FinishSmem {
+  __bf16 k[GC * PG], q[GC * PG];                         // rows of K and Q, zero past the chunk's length
+  // step 1: slabs S0^T, dS1^T [32 columns][128], Vn, dVn [32 columns][64 tokens];  step 2: T as hi and lo halves;  from
+  // there on dVb and dKb [token][128];  after step 3 dP scale D in dVb's place, and the closing sums behind it
+  __bf16 x[2 * GC * PG];
+  __bf16 r2[GC * PK];                                    // dO, 64 columns; [U | W]^T, 64 columns; dA beta D
+  float gam[GC], bet[GC], eg[GC], el[GC], db_v[GC];
+  float dg_row[2][GC], dg_col[2][GC], db_a[2][GC];       // per column / row block
 };
-// bf16 rows with the contraction index contiguous, as A (row-major): (i, k) = p[i * pitch + k]; rows >= len are zero
-struct RowsKLoaderA {
-  static constexpr bool KMAJOR = false;
-  const __bf16* p;
-  int pitch, len;
-  struct Regs { bf16x8 v[GC * KS / 8 / BT]; };
-  __device__ __forceinline__ void load(int k0, int tid, Regs& r) const {
-#pragma unroll
-    for (int q = 0; q < GC * KS / 8 / BT; q++) {
-      const int piece = tid + q * BT, i = piece / (KS / 8), k8 = (piece % (KS / 8)) * 8;
-      r.v[q] = *(const bf16x8*)(p + (size_t)min(i, len - 1) * pitch + k0 + k8);
-    }
-  }
-  __device__ __forceinline__ void store(__bf16* lds, int tid, const Regs& r) const {
-    bf16x8 zero;
-#pragma unroll
-    for (int e = 0; e < 8; e++) zero[e] = (__bf16)0.f;
-#pragma unroll
-    for (int q = 0; q < GC * KS / 8 / BT; q++) {
-      const int piece = tid + q * BT, i = piece / (KS / 8), k8 = (piece % (KS / 8)) * 8;
-      *(bf16x8*)(lds + i * PR_A + k8) = i < len ? r.v[q] : zero;
-    }
-  }
-};
-// any A given element by element as fp32 (the LDS-resident 64 x 64 matrices), row-major slab; a thread takes 8
-// consecutive k of one row
-template <class F>
-struct FnLoaderA {
-  static constexpr bool KMAJOR = false;
-  F f;
-  struct Regs { bf16x8 v[GC * KS / 8 / BT]; };
-  __device__ __forceinline__ void load(int k0, int tid, Regs& r) const {
-#pragma unroll
-    for (int q = 0; q < GC * KS / 8 / BT; q++) {
-      const int piece = tid + q * BT, i = piece % GC, k8 = (piece / GC) * 8;
-      r.v[q] = cvt8(f(i, k0 + k8), f(i, k0 + k8 + 1), f(i, k0 + k8 + 2), f(i, k0 + k8 + 3), f(i, k0 + k8 + 4), f(i, k0 + k8 + 5),
-                    f(i, k0 + k8 + 6), f(i, k0 + k8 + 7));
-    }
-  }
-  __device__ __forceinline__ void store(__bf16* lds, int tid, const Regs& r) const {
-#pragma unroll
-    for (int q = 0; q < GC * KS / 8 / BT; q++) {
-      const int piece = tid + q * BT, i = piece % GC, k8 = (piece / GC) * 8;
-      *(bf16x8*)(lds + i * PR_A + k8) = r.v[q];
-    }
-  }
-};
-template <class F> __device__ __forceinline__ FnLoaderA<F> fn_loader_a(F f) { return FnLoaderA<F>{f}; }
-// bf16 rows of 128 with the output index contiguous, as B (N = 128): (k, j) = p[k * pitch + j]; rows >= len are zero
-struct RowsJLoaderB {
-  const __bf16* p;
-  int pitch, len;
-  struct Regs { bf16x8 v[KS * GD / 8 / BT]; };
-  __device__ __forceinline__ void load(int k0, int tid, Regs& r) const {
-#pragma unroll
-    for (int q = 0; q < KS * GD / 8 / BT; q++) {
-      const int piece = tid + q * BT, kk = piece >> 4, j8 = (piece & 15) * 8;
-      r.v[q] = *(const bf16x8*)(p + (size_t)min(k0 + kk, len - 1) * pitch + j8);
-    }
-  }
-  __device__ __forceinline__ void store(__bf16* lds, int tid, const Regs& r, int k0) const {
-    bf16x8 zero;
-#pragma unroll
-    for (int e = 0; e < 8; e++) zero[e] = (__bf16)0.f;
-#pragma unroll
-    for (int q = 0; q < KS * GD / 8 / BT; q++) {
-      const int piece = tid + q * BT, kk = piece >> 4, j8 = (piece & 15) * 8;
-      *(bf16x8*)(lds + kk * pitch_b<GD>() + j8) = k0 + kk < len ? r.v[q] : zero;
-    }
-  }
-};
-// [U | W]^T from the walks' bf16 records, as B (N = 64): (k, j) = k < 128 ? U^T[k][j] : -(-W^T)[k - 128][j]
-struct UwLoaderB {
-  const __bf16 *ut, *wtn;
-  struct Regs { bf16x8 v[KS * GC / 8 / BT]; };
-  __device__ __forceinline__ void load(int k0, int tid, Regs& r) const {
-    const __bf16* src = k0 < GD ? ut + (size_t)k0 * GC : wtn + (size_t)(k0 - GD) * GC;     // a slab lies in one half
-#pragma unroll
-    for (int q = 0; q < KS * GC / 8 / BT; q++) {
-      const int piece = tid + q * BT, kk = piece >> 3, j8 = (piece & 7) * 8;
-      r.v[q] = *(const bf16x8*)(src + (size_t)kk * GC + j8);
-    }
-  }
-  __device__ __forceinline__ void store(__bf16* lds, int tid, const Regs& r, int k0) const {
-#pragma unroll
-    for (int q = 0; q < KS * GC / 8 / BT; q++) {
-      const int piece = tid + q * BT, kk = piece >> 3, j8 = (piece & 7) * 8;
-      typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
-      const u16x8 flipped = __builtin_bit_cast(u16x8, r.v[q]) ^ (unsigned short)0x8000;      // -x: the sign bit
-      *(bf16x8*)(lds + kk * pitch_b<GC>() + j8) = k0 < GD ? r.v[q] : __builtin_bit_cast(bf16x8, flipped);
-    }
-  }
-};
-typedef FragLoader<pitch_b<GC>()> FragLoaderB;             // Vn as B (N = 64)
+static_assert(sizeof(FinishSmem) <= 80 * 1024, "two workgroups per compute unit");
+constexpr int SLAB = 32;                                 // value columns per slab of step 1
+constexpr int X_S0 = 0, X_DS1 = SLAB * PG, X_VN = 2 * SLAB * PG, X_DVN = 2 * SLAB * PG + SLAB * PK;
+constexpr int X_TLO = GC * PK;
+constexpr int X_KB = GC * PG;                            // dKb
+constexpr int X_SUMS = GC * PK;                          // 9 x 64 floats
+static_assert(X_DVN + SLAB * PK <= 2 * GC * PG && X_SUMS % 8 == 0 && X_SUMS + 2 * 9 * GC <= X_KB && GC * PK <= X_SUMS, "LDS areas");
 
 // Barrier that waits for this wave's LDS traffic only (a __syncthreads also waits for every global load in flight,
-// i.e. for the slabs that were requested ahead).  Not for global data written by other threads of the workgroup.
+// i.e. for what was requested ahead).  Not for global data written by other threads of the workgroup.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-template <int N, int K, class LA, class LB>
-__device__ __forceinline__ void slab_product(const LA& la, const LB& lb, f32x16 (&acc)[N / 64], __bf16* as, __bf16* bs, int tid_in) {
-  constexpr int PB = pitch_b<N>(), NS = K / KS;
-  // The fetch offsets are functions of the thread id alone.  Hidden behind an opaque copy they are computed at each
-  // call; otherwise the compiler computes those of all calls at the top of the kernel and keeps them in registers
-  // throughout (measured: 174 spilled registers at two waves per SIMD).
-  int tid = tid_in;
-  asm volatile("" : "+v"(tid));
-  typedef TileMap<N> TM;
-  const int lane = tid & 63, c = lane & 31, hf = lane >> 5, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  auto multiply = [&]() {
+// Sums 16 values over the 32 lanes of a half wave (the lanes that hold one row of an accumulator tile in register r): every
+// step folds the lane positions on each other and hands half of the values to either side, so that 16 sums take 16
+// additions instead of 80.  Lane c of the half gets the total of v[c % 16].
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float half_wave_sums(float (&v)[16], int c) {
+  const bool b3 = c & 8, b2 = c & 4, b1 = c & 2, b0 = c & 1;
 #pragma unroll
-    for (int s = 0; s < KS / 16; s++) {
-      const bf16x8 b = kmajor_frag(bs, PB, 16 * s + 8 * hf, 32 * TM::jb(w) + 16 * (c >> 4), lane);
+  for (int r = 0; r < 8; r++) v[r] = (b3 ? v[r + 8] : v[r]) + dpp_move<0x140>(b3 ? v[r] : v[r + 8]);     // row_mirror: lane ^ 15
 #pragma unroll
-      for (int t = 0; t < TM::TPW; t++) {
-        const int ib = TM::ib(w, t);
-        const bf16x8 a = LA::KMAJOR ? kmajor_frag(as, PK_A, 16 * s + 8 * hf, 32 * ib + 16 * (c >> 4), lane)
-                                    : *(const bf16x8*)(as + (32 * ib + c) * PR_A + 16 * s + 8 * hf);
-        acc[t] = mfma32(a, b, acc[t]);
+  for (int r = 0; r < 4; r++) v[r] = (b2 ? v[r + 4] : v[r]) + dpp_move<0x141>(b2 ? v[r] : v[r + 4]);     // row_half_mirror: lane ^ 7
+#pragma unroll
+  for (int r = 0; r < 2; r++) v[r] = (b1 ? v[r + 2] : v[r]) + dpp_move<0x4e>(b1 ? v[r] : v[r + 2]);      // quad_perm: lane ^ 2
+  const float x = (b0 ? v[1] : v[0]) + dpp_move<0xb1>(b0 ? v[0] : v[1]);                                   // quad_perm: lane ^ 1
+  const auto o = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);   // lane ^ 16
+  return __uint_as_float(o[0]) + __uint_as_float(o[1]);
+}
+
+// The value is formed at this point of the program.  (The compiler moves additions to their use two steps later and keeps
+// both operands in registers until then: 94 spilled registers, 1.3 GB of scratch traffic and 0.82 ms at 16 K tokens.)
+template <class T> __device__ __forceinline__ void form_here(T& x) { asm volatile("" : "+v"(x)); }
+
+template <bool SPLIT>
+__global__ __launch_bounds__(BT, 2) void gdn_bwd_finish_kernel(KArgs a) {
+  __shared__ __attribute__((aligned(16))) FinishSmem sm;
+  const int nc = a.b.n_chunks, hv = a.b.hv, rep = hv / a.b.hk;
+  int chunk, unit;                                       // unit: key head (SPLIT: value head) inside this pass
+  if (!gdn_group_order(blockIdx.x, nc, SPLIT ? a.b.hv_n : a.b.hv_n / rep, SPLIT ? rep : 1, chunk, unit)) return;
+  const int kh = SPLIT ? unit / rep : unit;
+  const int tok0 = a.b.chunk_tok0[chunk], len = a.b.chunk_len[chunk];
+  const float scale = a.b.scale;
+  const size_t qrow = (size_t)a.b.hk * GD, vrow = (size_t)hv * GD;
+  bf16x8 zero8;
+#pragma unroll
+  for (int e = 0; e < 8; e++) zero8[e] = (__bf16)0.f;
+
+  // Thread positions (ib, jb: this wave's tile of a 64 x 64 result).  LDS and memory offsets are functions of these alone:
+  // taken from an opaque copy per step, they are formed where they are used; otherwise the compiler forms those of all
+  // steps in front of the loop over the heads and keeps them.
+  int tid, lane, c, hf, c16, w, ib, jb;
+  auto place = [&]() {
+    int t = threadIdx.x & (BT - 1);
+    asm volatile("" : "+v"(t)::"memory");
+    tid = t; lane = t & 63; c = lane & 31; hf = lane >> 5; c16 = 16 * (c >> 4);
+    w = __builtin_amdgcn_readfirstlane(t >> 6);
+    ib = w & 1; jb = w >> 1;
+  };
+  // The pieces of a slab, and what a head starts with (slab 0 and the chunk's scalars): requested one slab ahead, a head's
+  // first ones during the last step of the head in front of it.
+  bf16x8 s0r[2], ds1r[2], vnr, dvnr, dor[2];
+  float glast, gv, bv;
+  auto load_slab = [&](int h, int cb) {
+    // saved by the walks (bf16): S0 and dS1 transposed [value col][key dim], Vn and dVn in fragment order
+    const size_t op = (size_t)h * nc + chunk;
+    const __bf16* s0t = (const __bf16*)a.w.sv.s0t + op * (GD * GD) + cb * (SLAB * GD);
+    const __bf16* ds1t = (const __bf16*)a.w.sv.ds1t + op * (GD * GD) + cb * (SLAB * GD);
+#pragma unroll
+    for (int p = 0; p < 2; p++) {
+      s0r[p] = *(const bf16x8*)(s0t + 8 * (tid + p * BT));
+      ds1r[p] = *(const bf16x8*)(ds1t + 8 * (tid + p * BT));
+    }
+    vnr = *(const bf16x8*)((const __bf16*)a.w.sv.vns + op * (GC * GD) + cb * (SLAB * GC) + 8 * tid);
+    dvnr = *(const bf16x8*)((const __bf16*)a.w.sv.dvns + op * (GC * GD) + cb * (SLAB * GC) + 8 * tid);
+    if ((cb & 1) == 0) {
+      const __bf16* dob = (const __bf16*)a.b.d_o + (size_t)tok0 * vrow + (size_t)h * GD + cb * SLAB;
+#pragma unroll
+      for (int p = 0; p < 2; p++) {
+        const int piece = tid + p * BT, i = piece >> 3, k8 = (piece & 7) * 8;
+        dor[p] = *(const bf16x8*)(dob + (size_t)min(i, len - 1) * vrow + k8);
       }
     }
   };
-  // Up to two slabs are in flight: while slab s is multiplied, s + 1 is on its way and s + 2 has just been
-  // requested.  Two register sets take turns; the last steps request nothing (a branch around loads would put
-  // their wait at its end, so the steps are peeled).
-  typename LA::Regs ra[2];
-  typename LB::Regs rb[2];
-  static_assert(NS == 1 || NS % 2 == 0, "one slab or an even number of slabs");
-  la.load(0, tid, ra[0]);
-  lb.load(0, tid, rb[0]);
-  if constexpr (NS > 1) {
-    la.load(KS, tid, ra[1]);
-    lb.load(KS, tid, rb[1]);
-#pragma unroll 1
-    for (int k0 = 0; k0 < K - 2 * KS; k0 += 2 * KS) {
+  auto load_head = [&](int h) {
+    const float* gam = a.w.ops.gam + ((size_t)h * nc + chunk) * GC;
+    glast = gam[GC - 1];
+    gv = gam[lane];
+    bv = a.b.beta[(size_t)(tok0 + min(lane, len - 1)) * hv + h];
+    load_slab(h, 0);
+  };
+  {
+    place();
+    const __bf16* qb = (const __bf16*)a.b.q + (size_t)tok0 * qrow + (size_t)kh * GD;
+    const __bf16* kb = (const __bf16*)a.b.k + (size_t)tok0 * qrow + (size_t)kh * GD;
+    bf16x8 kr[4], qr[4];
 #pragma unroll
-      for (int set = 0; set < 2; set++) {
-        lds_barrier();                 // the previous slab (or whatever used the slab arrays before) has been read
-        la.store(as, tid, ra[set]);
-        lb.store(bs, tid, rb[set], k0 + set * KS);
+    for (int p = 0; p < 4; p++) {
+      const int piece = tid + p * BT, i = piece >> 4, c8 = (piece & 15) * 8;
+      const size_t at = (size_t)min(i, len - 1) * qrow + c8;
+      kr[p] = *(const bf16x8*)(kb + at);
+      qr[p] = *(const bf16x8*)(qb + at);
+    }
+    load_head(SPLIT ? unit : kh * rep);
+#pragma unroll
+    for (int p = 0; p < 4; p++) {
+      const int piece = tid + p * BT, i = piece >> 4, c8 = (piece & 15) * 8;
+      *(bf16x8*)(sm.k + i * PG + c8) = i < len ? kr[p] : zero8;
+      *(bf16x8*)(sm.q + i * PG + c8) = i < len ? qr[p] : zero8;
+    }
+  }
+
+  f32x16 dq[2] = {zero16(), zero16()}, dk[2] = {zero16(), zero16()};
+#pragma unroll 1
+  for (int r_h = 0; r_h < (SPLIT ? 1 : rep); r_h++) {
+    const int h = SPLIT ? unit : kh * rep + r_h;
+    const size_t op = (size_t)h * nc + chunk;
+    const __bf16* dvns = (const __bf16*)a.w.sv.dvns + op * (GC * GD);
+    const __bf16* ut = (const __bf16*)a.w.sv.fwd_rec + op * GDN_REC_ELEMS + GDN_REC_UT;
+    const __bf16* wtn = (const __bf16*)a.w.sv.rev_rec + op * GDN_REC_ELEMS + GDN_REV_WTN;
+    const __bf16* vb = (const __bf16*)a.b.v + (size_t)tok0 * vrow + (size_t)h * GD;
+
+    // ---- 1. everything that contracts over value columns ----
+    place();
+    const float el_last = __expf(glast);
+    if (tid < GC) {
+      sm.gam[tid] = gv;
+      sm.bet[tid] = tid < len ? bv : 0.f;
+      sm.eg[tid] = __expf(gv);
+      sm.el[tid] = __expf(glast - gv);
+    }
+    float s_dot = 0.f;                                   // this thread's part of <dS1, S0>
+    bf16x8 xf[2][GC / 16];                               // A fragments of the right-hand sides of step 2
+    float4 t_in[3];
+    f32x16 dp = zero16();
+    float row_qk[2], s_kd = 0.f;                         // row sums of dQg o Qg - dKd o Kd;  this thread's part of <dKd, Kd>
+    {
+      f32x16 dw[2] = {zero16(), zero16()}, dqg[2] = {zero16(), zero16()}, dkd[2] = {zero16(), zero16()};
+#pragma unroll
+      for (int cb = 0; cb < GD / SLAB; cb++) {
+        place();
+        lds_barrier();                                   // the previous slab (or whatever was here before) has been read
+#pragma unroll
+        for (int p = 0; p < 2; p++) {
+          const int piece = tid + p * BT, at = (piece >> 4) * PG + (piece & 15) * 8;
+          *(bf16x8*)(sm.x + X_S0 + at) = s0r[p];
+          *(bf16x8*)(sm.x + X_DS1 + at) = ds1r[p];
+#pragma unroll
+          for (int e = 0; e < 8; e++) s_dot += (float)s0r[p][e] * (float)ds1r[p][e];
+        }
+        form_here(s_dot);
+        {
+          // one piece of a fragment-ordered array = 8 tokens of one column: base .. base + 3 and base + 8 .. base + 11
+          const int f = tid >> 6, at = c * PK + 16 * f + 4 * hf;
+          *(bf16x4*)(sm.x + X_VN + at) = __builtin_shufflevector(vnr, vnr, 0, 1, 2, 3);
+          *(bf16x4*)(sm.x + X_VN + at + 8) = __builtin_shufflevector(vnr, vnr, 4, 5, 6, 7);
+          *(bf16x4*)(sm.x + X_DVN + at) = __builtin_shufflevector(dvnr, dvnr, 0, 1, 2, 3);
+          *(bf16x4*)(sm.x + X_DVN + at + 8) = __builtin_shufflevector(dvnr, dvnr, 4, 5, 6, 7);
+        }
+        if ((cb & 1) == 0) {
+#pragma unroll
+          for (int p = 0; p < 2; p++) {
+            const int piece = tid + p * BT, i = piece >> 3, k8 = (piece & 7) * 8;
+            *(bf16x8*)(sm.r2 + i * PK + k8) = i < len ? dor[p] : zero8;
+          }
+        }
         lds_barrier();
-        la.load(k0 + (2 + set) * KS, tid, ra[set]);
-        lb.load(k0 + (2 + set) * KS, tid, rb[set]);
-        multiply();
+        if (cb + 1 < GD / SLAB) {
+          load_slab(h, cb + 1);
+        } else {
+          // for step 2: T (three 32 x 32 blocks, the fourth is zero) and the dVn fragments of this wave's column block
+          const float* tg = a.w.ops.t + op * GDN_T_ELEMS;
+#pragma unroll
+          for (int p = 0; p < 3; p++) t_in[p] = ld4(tg + 4 * (tid + p * BT));
+#pragma unroll
+          for (int s = 0; s < GC / 16; s++) xf[0][s] = ((const bf16x8*)dvns)[(w * 4 + s) * 64 + lane];
+        }
+#pragma unroll
+        for (int s = 0; s < SLAB / 16; s++) {
+          const int k0 = 16 * s + 8 * hf;
+          const bf16x8 b_s0 = kmajor_frag(sm.x + X_S0, PG, k0, 32 * w + c16, lane);
+          const bf16x8 b_ds1 = kmajor_frag(sm.x + X_DS1, PG, k0, 32 * w + c16, lane);
+#pragma unroll
+          for (int t = 0; t < 2; t++) {
+            dw[t] = mfma32(kmajor_frag(sm.x + X_DVN, PK, k0, 32 * t + c16, lane), b_s0, dw[t]);
+            dqg[t] = mfma32(*(const bf16x8*)(sm.r2 + (32 * t + c) * PK + (cb & 1) * SLAB + k0), b_s0, dqg[t]);
+            dkd[t] = mfma32(kmajor_frag(sm.x + X_VN, PK, k0, 32 * t + c16, lane), b_ds1, dkd[t]);
+          }
+          dp = mfma32(*(const bf16x8*)(sm.r2 + (32 * ib + c) * PK + (cb & 1) * SLAB + k0),
+                      kmajor_frag(sm.x + X_VN, PK, k0, 32 * jb + c16, lane), dp);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int t = 0; t < 2; t++) {
+        place();
+#pragma unroll
+        for (int u = 0; u < 2; u++)
+          xf[1][2 * t + u] = cvt8(-dw[t][8 * u], -dw[t][8 * u + 1], -dw[t][8 * u + 2], -dw[t][8 * u + 3], -dw[t][8 * u + 4],
+                                  -dw[t][8 * u + 5], -dw[t][8 * u + 6], -dw[t][8 * u + 7]);
+        // dq_i = scale exp(gamma_i) dQg_i + ...;  dk_j = exp(gamma_last - gamma_j) dKd_j + ...;  their dot products with
+        // q_i and k_j go into dgamma.  (A k-major fragment in accumulator order holds the rows of 8 registers.)
+        float dot[16];
+#pragma unroll
+        for (int u = 0; u < 2; u++) {
+          const bf16x8 qf = kmajor_frag_acc_order(sm.q, PG, 32 * t + 16 * u + 4 * hf, 32 * w + c16, lane);
+          const bf16x8 kf = kmajor_frag_acc_order(sm.k, PG, 32 * t + 16 * u + 4 * hf, 32 * w + c16, lane);
+#pragma unroll
+          for (int v4 = 0; v4 < 2; v4++) {
+            const int i4 = 32 * t + 16 * u + 8 * v4 + 4 * hf;
+            const f32x4 eg4 = *(const f32x4*)(sm.eg + i4), el4 = *(const f32x4*)(sm.el + i4);
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+              const int r = 8 * u + 4 * v4 + e;
+              const float vq = scale * eg4[e] * dqg[t][r], vk = el4[e] * dkd[t][r], vkk = vk * (float)kf[4 * v4 + e];
+              dot[r] = vq * (float)qf[4 * v4 + e] - vkk;
+              s_kd += vkk;
+              dq[t][r] += vq;
+              dk[t][r] += vk;
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        row_qk[t] = half_wave_sums(dot, c);
+        form_here(dq[t]);
+        form_here(dk[t]);
       }
     }
-  }
+
+    place();
+    // ---- 2. (I + A)^T [dVb | dKb] = [dVn | dW]: X^T = rhs^T T ----
+    bf16x8 ur[2][2], vv[4];
+    auto load_uw = [&](int s) {                          // two slabs ahead
+      const __bf16* src = s < 2 ? ut + s * (GC * GC) : wtn + (s - 2) * (GC * GC);
 #pragma unroll
-  for (int set = 0; set < (NS > 1 ? 2 : 1); set++) {
-    lds_barrier();
-    la.store(as, tid, ra[set]);
-    lb.store(bs, tid, rb[set], K - ((NS > 1 ? 2 : 1) - set) * KS);
-    lds_barrier();
-    multiply();
-  }
-}
-
-// Sum over the 32 lanes of a half wave (the lanes that hold one row of an accumulator tile), with data-parallel
-// lane moves instead of LDS-routed shuffles (the kernel forms 96 such sums per lane).  The total arrives in the
-// upper 16 lanes of the half (lanes 16 .. 31 and 48 .. 63).
-template <int CTRL, int ROW_MASK = 0xf>
-__device__ __forceinline__ float dpp_move(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, ROW_MASK, 0xf, false));
-}
-__device__ __forceinline__ float half_wave_sum(float x) {
-  x += dpp_move<0xb1>(x);          // quad_perm [1,0,3,2]: lane ^ 1
-  x += dpp_move<0x4e>(x);          // quad_perm [2,3,0,1]: lane ^ 2
-  x += dpp_move<0x141>(x);         // row_half_mirror: the other quad of each group of 8
-  x += dpp_move<0x140>(x);         // row_mirror: the other group of 8 of each row of 16
-  x += dpp_move<0x142, 0xa>(x);    // row_bcast15 into rows 1 and 3: adds the total of the row below
-  return x;
-}
-constexpr int HALF_SUM_LANE = 16;  // a lane position (inside its half wave) that holds half_wave_sum's result
-
-constexpr int AP = GC + 1;     // row pitch of the 64 x 64 LDS matrices that are read along rows and columns
-constexpr int TP = GC + 4;     // pitch of the transposed A during the solve (rows read as float4)
-
-__global__ __launch_bounds__(BT, 2) void gdn_bwd_finish_kernel(KArgs a) {
-  __shared__ __attribute__((aligned(16))) __bf16 as[AS_ELEMS];
-  constexpr int BS_FLOATS = GC * AP > KS * pitch_b<GD>() / 2 ? GC * AP : KS * pitch_b<GD>() / 2;
-  __shared__ __attribute__((aligned(16))) float bs_f[BS_FLOATS];  // B slabs (bf16); between products also dA o A0 (fp32)
-  __bf16* bs = (__bf16*)bs_f;
-  __shared__ __attribute__((aligned(16))) float dam[GC * TP];     // A^T during the solve, then dA, then dA beta D
-  __shared__ float dpm[GC * AP];                                  // dP, then dP scale D
-  __shared__ float gm[GC * AP];                                   // dP o P + dA o A
-  __shared__ float gam[GC], bet[GC], eg[GC], el[GC];
-  __shared__ float dg_row[GC], dg_col[GC], db_a[GC], db_v[GC], dgam[GC];
-  // per-wave parts of row dot products: they live in gm, which is dead by the time they are formed
-  float(*dot_q)[GC] = (float(*)[GC])gm;
-  float(*dot_kd)[GC] = (float(*)[GC])(gm + 4 * GC);
-  float(*dot_kb)[GC] = (float(*)[GC])(gm + 8 * GC);
-  float* red = (float*)as;                                        // [BT], after the last product
-
-  int chunk, h;
-  if (!gdn_group_order(blockIdx.x, a.b.n_chunks, a.b.hv_n, a.b.hv / a.b.hk, chunk, h)) return;
-  const int tid = threadIdx.x & (BT - 1), lane = tid & 63, c = lane & 31, hf = lane >> 5;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int nc = a.b.n_chunks, hv = a.b.hv, kh = h / (hv / a.b.hk);
-  const size_t op = (size_t)h * nc + chunk;
-  const int tok0 = a.b.chunk_tok0[chunk], len = a.b.chunk_len[chunk];
-  const float scale = a.b.scale;
-  const __bf16* ut = (const __bf16*)a.w.sv.fwd_rec + op * GDN_REC_ELEMS + GDN_REC_UT;
-  const __bf16* wtn = (const __bf16*)a.w.sv.rev_rec + op * GDN_REC_ELEMS + GDN_REV_WTN;
-  const float* A0 = a.w.ops.a0 + op * (GC * GC);
-  const float* Pm = a.w.ops.p + op * (GC * GC);
-  // saved by the walks (bf16): S0 and dS1 transposed [value col][key dim], Vn and dVn in fragment order
-  const __bf16* s0t = (const __bf16*)a.w.sv.s0t + op * (GD * GD);
-  const __bf16* ds1t = (const __bf16*)a.w.sv.ds1t + op * (GD * GD);
-  const __bf16* vns = (const __bf16*)a.w.sv.vns + op * (GC * GD);
-  const __bf16* dvns = (const __bf16*)a.w.sv.dvns + op * (GC * GD);
-  __bf16* X = a.w.x + op * (GC * 2 * GD);
-  const size_t qrow = (size_t)a.b.hk * GD, vrow = (size_t)hv * GD;
-  const __bf16* qb = (const __bf16*)a.b.q + (size_t)tok0 * qrow + (size_t)kh * GD;
-  const __bf16* kb = (const __bf16*)a.b.k + (size_t)tok0 * qrow + (size_t)kh * GD;
-  const __bf16* vb = (const __bf16*)a.b.v + (size_t)tok0 * vrow + (size_t)h * GD;
-  const __bf16* dob = (const __bf16*)a.b.d_o + (size_t)tok0 * vrow + (size_t)h * GD;
-  // rows past the chunk's length read a valid row and are then zeroed (no load sits inside a branch)
-  // (32-bit offsets: a chunk spans at most 64 rows of at most 65535 * 128 elements)
-  const int qrow32 = (int)qrow, vrow32 = (int)vrow;
-  auto q_at = [&](int i, int d) { const float x = (float)qb[min(i, len - 1) * qrow32 + d]; return i < len ? x : 0.f; };
-  auto k_at = [&](int i, int d) { const float x = (float)kb[min(i, len - 1) * qrow32 + d]; return i < len ? x : 0.f; };
-
-  const float glast = a.w.ops.gam[op * GC + GC - 1];
-  const float el_last = __expf(glast);
-  if (tid < GC) {
-    const float gv = a.w.ops.gam[op * GC + tid];
-    gam[tid] = gv;
-    bet[tid] = tid < len ? a.b.beta[(size_t)(tok0 + tid) * hv + h] : 0.f;
-    eg[tid] = __expf(gv);
-    el[tid] = __expf(glast - gv);
-  }
-  typedef TileMap<GD> T128;
-  typedef TileMap<GC> T64;
-
-  // dW = -dVn S0^T, kept in fragment order (the registers of an accumulator tile, eight at a time, are exactly the
-  // fragment of its column) in the first 16 KB of X: it is the second half of the right-hand side below
-  {
-    f32x16 acc[2] = {zero16(), zero16()};
-    slab_product<GD, GD>(FragLoader<PK_A>{dvns}, RowsJLoaderB{s0t, GD, GD}, acc, as, bs, tid);
+      for (int p = 0; p < 2; p++) ur[s & 1][p] = *(const bf16x8*)(src + 8 * (tid + p * BT));
+    };
+    const int v_i = tid >> 2, v_c0 = (tid & 3) * 32;     // step 3: this thread's row and columns of dVb
+    lds_barrier();                                       // the last slab has been read
 #pragma unroll
-    for (int t = 0; t < 2; t++)                        // tile (row block t, column block w)
-#pragma unroll
-      for (int tt = 0; tt < 2; tt++)
-        ((bf16x8*)X)[(((w * 2 + T128::ib(w, t)) * 2 + tt) * 64 + lane)] =
-            cvt8(-acc[t][8 * tt], -acc[t][8 * tt + 1], -acc[t][8 * tt + 2], -acc[t][8 * tt + 3], -acc[t][8 * tt + 4],
-                 -acc[t][8 * tt + 5], -acc[t][8 * tt + 6], -acc[t][8 * tt + 7]);
-  }
-  // (I + A)^T x = rhs for the 256 columns of [dVn | dW]: x = T^T rhs with T = (I + A)^-1 from the prepare kernel,
-  // computed transposed, X^T = rhs^T T, on the matrix cores.  rhs^T comes straight from the fragment-ordered
-  // arrays (a fragment is the A operand of its column block for one k-step, its 8 tokens in accumulator order);
-  // T is split into two bf16 halves (hi + lo) in LDS, k-major, read in the same token order.
-  {
-    __bf16* th = as;                                   // [token][i], pitch PK_A
-    __bf16* tl = (__bf16*)dam;
-    const float* Tg = a.w.ops.t + op * (GC * GC);
-    lds_barrier();                                     // the last slab of the product above has been read
-#pragma unroll
-    for (int p = 0; p < GC * GC / 4 / BT; p++) {
-      const int e4 = tid + p * BT, k = e4 >> 4, i4 = (e4 & 15) * 4;
-      const float4 v = ld4(Tg + e4 * 4);
+    for (int p = 0; p < 3; p++) {
+      const int k = (p > 0 ? 32 : 0) + (tid >> 3), i4 = (p == 2 ? 32 : 0) + (tid & 7) * 4;
+      const float4 v = t_in[p];
       const bf16x4 h4 = cvt4(v.x, v.y, v.z, v.w);
-      *(bf16x4*)(th + k * PK_A + i4) = h4;
-      *(bf16x4*)(tl + k * PK_A + i4) = cvt4(v.x - (float)h4[0], v.y - (float)h4[1], v.z - (float)h4[2], v.w - (float)h4[3]);
+      *(bf16x4*)(sm.x + k * PK + i4) = h4;
+      *(bf16x4*)(sm.x + X_TLO + k * PK + i4) = cvt4(v.x - (float)h4[0], v.y - (float)h4[1], v.z - (float)h4[2], v.w - (float)h4[3]);
     }
-    // wave w: right-hand-side column blocks 2 w and 2 w + 1 (blocks 0 .. 3: dVn, 4 .. 7: dW)
-    bf16x8 af[2][GC / 16];
-    __syncthreads();                                   // T in LDS; the dW fragments written above are visible
+    lds_barrier();
+    load_uw(0);
+    load_uw(1);
 #pragma unroll
-    for (int rbi = 0; rbi < 2; rbi++) {
-      const int rb = 2 * w + rbi;
-      const bf16x8* src = rb < 4 ? (const bf16x8*)dvns + (size_t)rb * 4 * 64 : (const bf16x8*)X + (size_t)(rb - 4) * 4 * 64;
-#pragma unroll
-      for (int s4 = 0; s4 < GC / 16; s4++) af[rbi][s4] = src[s4 * 64 + lane];      // (half, t) = (s4 / 2, s4 % 2)
-    }
-    f32x16 xa[2][2] = {{zero16(), zero16()}, {zero16(), zero16()}};
-#pragma unroll
-    for (int s4 = 0; s4 < GC / 16; s4++)
+    for (int q = 0; q < 4; q++) vv[q] = *(const bf16x8*)(vb + (size_t)min(v_i, len - 1) * vrow + v_c0 + 8 * q);
+    {
+      bf16x4 xo[2][2][4];                                // the result as bf16, one column block of T at a time (registers)
 #pragma unroll
       for (int cb = 0; cb < 2; cb++) {
-        const bf16x8 bh = kmajor_frag_acc_order(th, PK_A, 16 * s4 + 4 * hf, 32 * cb + 16 * (c >> 4), lane);
-        const bf16x8 bl = kmajor_frag_acc_order(tl, PK_A, 16 * s4 + 4 * hf, 32 * cb + 16 * (c >> 4), lane);
+        f32x16 xa[2] = {zero16(), zero16()};
 #pragma unroll
-        for (int rbi = 0; rbi < 2; rbi++) {
-          xa[rbi][cb] = mfma32(af[rbi][s4], bh, xa[rbi][cb]);
-          xa[rbi][cb] = mfma32(af[rbi][s4], bl, xa[rbi][cb]);
+        for (int s = 2 * cb; s < GC / 16; s++) {         // (rows 0 .. 31 of T are zero from column 32 on)
+          const bf16x8 th = kmajor_frag_acc_order(sm.x, PK, 16 * s + 4 * hf, 32 * cb + c16, lane);
+          const bf16x8 tl = kmajor_frag_acc_order(sm.x + X_TLO, PK, 16 * s + 4 * hf, 32 * cb + c16, lane);
+#pragma unroll
+          for (int m = 0; m < 2; m++) {
+            xa[m] = mfma32(xf[m][s], th, xa[m]);
+            xa[m] = mfma32(xf[m][s], tl, xa[m]);
+          }
+        }
+#pragma unroll
+        for (int m = 0; m < 2; m++)
+#pragma unroll
+          for (int r4 = 0; r4 < 4; r4++)
+            xo[m][cb][r4] = cvt4(xa[m][4 * r4], xa[m][4 * r4 + 1], xa[m][4 * r4 + 2], xa[m][4 * r4 + 3]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      lds_barrier();                                     // T has been read
+      // a lane holds row i = 32 cb + c and, per register group, 4 consecutive columns
+#pragma unroll
+      for (int m = 0; m < 2; m++)
+#pragma unroll
+        for (int cb = 0; cb < 2; cb++)
+#pragma unroll
+          for (int r4 = 0; r4 < 4; r4++)
+            *(bf16x4*)(sm.x + m * X_KB + (32 * cb + c) * PG + 32 * w + 8 * r4 + 4 * hf) = xo[m][cb][r4];
+    }
+
+    // ---- 3. dA = strictly-lower(-[dVb | dKb] [U | W]^T);  dv_i = beta_i dVb_i,  dbeta_i += dVb_i . v_i ----
+    f32x16 da = zero16();
+#pragma unroll
+    for (int s = 0; s < 4; s++) {
+      place();
+      lds_barrier();                                     // the previous slab has been read (first time: dVb, dKb are there)
+#pragma unroll
+      for (int p = 0; p < 2; p++) {
+        const int piece = tid + p * BT;
+        *(bf16x8*)(sm.r2 + (piece >> 3) * PK + (piece & 7) * 8) = ur[s & 1][p];
+      }
+      lds_barrier();
+      if (s < 2) load_uw(s + 2);
+      if (s == 2) {                                      // from the second half on the records hold -W
+#pragma unroll
+        for (int r = 0; r < 16; r++) da[r] = -da[r];
+      }
+#pragma unroll
+      for (int ss = 0; ss < 4; ss++)
+        da = mfma32(*(const bf16x8*)(sm.x + (s >> 1) * X_KB + (32 * ib + c) * PG + (s & 1) * 64 + 16 * ss + 8 * hf),
+                    kmajor_frag(sm.r2, PK, 16 * ss + 8 * hf, 32 * jb + c16, lane), da);
+      if (s == 0) {
+        float dot = 0.f;
+        const float b = sm.bet[v_i];
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+          const bf16x8 xb = *(const bf16x8*)(sm.x + v_i * PG + v_c0 + 8 * q);
+          float xv[8];
+#pragma unroll
+          for (int e = 0; e < 8; e++) {
+            xv[e] = (float)xb[e];
+            dot += xv[e] * (float)vv[q][e];
+          }
+          if (v_i < len)
+            *(bf16x8*)((__bf16*)a.b.dv + ((size_t)(tok0 + v_i) * hv + h) * GD + v_c0 + 8 * q) =
+                cvt8(b * xv[0], b * xv[1], b * xv[2], b * xv[3], b * xv[4], b * xv[5], b * xv[6], b * xv[7]);
+        }
+        dot += __shfl_xor(dot, 1);
+        dot += __shfl_xor(dot, 2);
+        if ((tid & 3) == 0) sm.db_v[v_i] = v_i < len ? dot : 0.f;
+      }
+    }
+
+    // ---- 4. G = dP o P + dA o A: its row sums minus its column sums are the part of dgamma that comes through D ----
+    {
+      place();
+      f32x16 kk = zero16(), qk = zero16();
+#pragma unroll
+      for (int s = 0; s < GD / 16; s++) {
+        const bf16x8 kj = *(const bf16x8*)(sm.k + (32 * jb + c) * PG + 16 * s + 8 * hf);
+        kk = mfma32(*(const bf16x8*)(sm.k + (32 * ib + c) * PG + 16 * s + 8 * hf), kj, kk);
+        qk = mfma32(*(const bf16x8*)(sm.q + (32 * ib + c) * PG + 16 * s + 8 * hf), kj, qk);
+      }
+      const int j = 32 * jb + c;
+      const float gj = sm.gam[j];
+      float col = 0.f;
+      lds_barrier();                                     // dVb and the last slab have been read: dP scale D, dA beta D go there
+      float g[16], ga[16];
+#pragma unroll
+      for (int r4 = 0; r4 < 4; r4++) {
+        const int i4 = 32 * ib + 8 * r4 + 4 * hf;
+        const f32x4 gi4 = *(const f32x4*)(sm.gam + i4), b4 = *(const f32x4*)(sm.bet + i4);
+        f32x4 mp, ma;
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+          const int r = 4 * r4 + e, i = i4 + e;
+          const float dec = j <= i ? __expf(gi4[e] - gj) : 0.f;
+          const float vp = j <= i ? dp[r] : 0.f, va = j < i ? da[r] : 0.f;
+          mp[e] = vp * (scale * dec);
+          ma[e] = va * dec;
+          ga[r] = ma[e] * (j < i ? kk[r] : 0.f);         // its row sums are the part of dbeta that comes through A
+          ma[e] *= b4[e];
+          g[r] = mp[e] * (j <= i ? qk[r] : 0.f) + b4[e] * ga[r];
+          col += g[r];
+        }
+        *(bf16x4*)(sm.x + j * PK + i4) = cvt4(mp[0], mp[1], mp[2], mp[3]);
+        *(bf16x4*)(sm.r2 + j * PK + i4) = cvt4(ma[0], ma[1], ma[2], ma[3]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      const float row_g = half_wave_sums(g, c), row_a = half_wave_sums(ga, c);
+      if (c < 16) {
+        sm.dg_row[jb][32 * ib + tile_row(c, hf)] = row_g;
+        sm.db_a[jb][32 * ib + tile_row(c, hf)] = row_a;
+      }
+      col = half_swap_sum(col);
+      if (hf == 0) sm.dg_col[ib][j] = col;
+    }
+    lds_barrier();
+
+    // ---- 5. what is left of dq and dk (the 64 x 64 matrices are lower triangular) ----
+    place();
+    if (!SPLIT && r_h + 1 < rep) load_head(h + 1);
+    float row_kb[2];
+#pragma unroll
+    for (int s = 0; s < GC / 16; s++) {
+      const int k0 = 16 * s + 8 * hf;
+      const bf16x8 b_k = kmajor_frag(sm.k, PG, k0, 32 * w + c16, lane);
+      const bf16x8 b_q = kmajor_frag(sm.q, PG, k0, 32 * w + c16, lane);
+#pragma unroll
+      for (int t = 0; t < 2; t++) {
+        if (s < 2 * t + 2) {                             // rows of block t: columns up to its diagonal
+          dq[t] = mfma32(kmajor_frag(sm.x, PK, k0, 32 * t + c16, lane), b_k, dq[t]);
+          dk[t] = mfma32(kmajor_frag(sm.r2, PK, k0, 32 * t + c16, lane), b_k, dk[t]);
+        }
+        if (s >= 2 * t) {                                // transposed
+          dk[t] = mfma32(*(const bf16x8*)(sm.x + (32 * t + c) * PK + k0), b_q, dk[t]);
+          dk[t] = mfma32(*(const bf16x8*)(sm.r2 + (32 * t + c) * PK + k0), b_k, dk[t]);
         }
       }
-    __syncthreads();                                   // every wave holds its dW fragments: X may be overwritten
-    // X[i][column]: a lane holds row i = 32 cb + c and, per register group, 4 consecutive columns
-#pragma unroll
-    for (int rbi = 0; rbi < 2; rbi++)
-#pragma unroll
-      for (int cb = 0; cb < 2; cb++)
-#pragma unroll
-        for (int r4 = 0; r4 < 4; r4++)
-          *(bf16x4*)(X + (size_t)(32 * cb + c) * (2 * GD) + 32 * (2 * w + rbi) + r4 * 8 + 4 * hf) =
-              cvt4(xa[rbi][cb][4 * r4], xa[rbi][cb][4 * r4 + 1], xa[rbi][cb][4 * r4 + 2], xa[rbi][cb][4 * r4 + 3]);
-  }
-  __syncthreads();
-
-  // dA = strictly-lower( -[dVb | dKb] [U | W]^T ),  dP = tril( dO Vn^T )
-  {
-    f32x16 acc[1] = {zero16()};
-    slab_product<GC, 2 * GD>(RowsKLoaderA{X, 2 * GD, GC}, UwLoaderB{ut, wtn}, acc, as, bs, tid);
-#pragma unroll
-    for (int r = 0; r < 16; r++) {
-      const int i = 32 * T64::ib(w, 0) + tile_row(r, hf), j = 32 * T64::jb(w) + c;
-      dam[i * AP + j] = i > j ? -acc[0][r] : 0.f;
     }
-    acc[0] = zero16();
-    slab_product<GC, GD>(RowsKLoaderA{dob, vrow32, len}, FragLoaderB{vns}, acc, as, bs, tid);
-#pragma unroll
-    for (int r = 0; r < 16; r++) {
-      const int i = 32 * T64::ib(w, 0) + tile_row(r, hf), j = 32 * T64::jb(w) + c;
-      dpm[i * AP + j] = i >= j ? acc[0][r] : 0.f;
-    }
-  }
-  __syncthreads();
-
-  // G = dP o P + dA o A: its row sums minus its column sums are the part of dgamma that comes through D
-#pragma unroll
-  for (int p = 0; p < GC * GC / BT; p++) {
-    const int e = tid + p * BT, i = e / GC, j = e % GC;
-    const float ga = dam[i * AP + j] * A0[e];
-    bs_f[i * AP + j] = ga;                   // its row sums are the part of dbeta that comes through A
-    gm[i * AP + j] = dpm[i * AP + j] * Pm[e] + bet[i] * ga;
-  }
-  __syncthreads();
-  {
-    // row sums and column sums of G, row sums of dA o A0: four threads per row / column, 16 independent LDS reads
-    // each (a single thread walking all 64 waits for every read in turn), then two lane exchanges
-    const int n = tid >> 2, part = (tid & 3) * 16;
-    float s_row = 0.f, s_col = 0.f, s_a = 0.f;
-#pragma unroll
-    for (int e = 0; e < 16; e++) {
-      s_row += gm[n * AP + part + e];
-      s_col += gm[(part + e) * AP + n];
-      s_a += bs_f[n * AP + part + e];
-    }
-    s_row += __shfl_xor(s_row, 1); s_row += __shfl_xor(s_row, 2);
-    s_col += __shfl_xor(s_col, 1); s_col += __shfl_xor(s_col, 2);
-    s_a += __shfl_xor(s_a, 1); s_a += __shfl_xor(s_a, 2);
-    if ((tid & 3) == 0) {
-      dg_row[n] = s_row;
-      dg_col[n] = s_col;
-      db_a[n] = s_a;
-    }
-  }
-  __syncthreads();
-  // dP -> dP scale D,  dA -> dA beta_i D   (the factors that multiply k_j, q_i, k_i in the products below)
-#pragma unroll
-  for (int p = 0; p < GC * GC / BT; p++) {
-    const int e = tid + p * BT, i = e / GC, j = e % GC;
-    const float dec = i >= j ? __expf(gam[i] - gam[j]) : 0.f;
-    dpm[i * AP + j] *= scale * dec;
-    dam[i * AP + j] *= bet[i] * dec;
-  }
-  // (the first slab_product below starts with a barrier)
-
-  // dq_i = scale exp(gamma_i) (dO S0^T)_i + sum_j (dP scale D)_ij k_j
-  {
-    f32x16 acc[2] = {zero16(), zero16()};
-    slab_product<GD, GD>(RowsKLoaderA{dob, vrow32, len}, RowsJLoaderB{s0t, GD, GD}, acc, as, bs, tid);
-    const int j = 32 * T128::jb(w) + c;
+    __builtin_amdgcn_sched_barrier(0);
+    place();
 #pragma unroll
     for (int t = 0; t < 2; t++) {
-      // One tile at a time (register pressure); its 16 loads in one straight-line block in front of the sums: the
-      // conditional LDS write below ends a basic block per row, and a load left inside would be waited for there,
-      // one memory latency per row (measured: a quarter of the kernel's time).
+      float dot[16];
+#pragma unroll
+      for (int u = 0; u < 2; u++) {
+        const bf16x8 xf = kmajor_frag_acc_order(sm.x + X_KB, PG, 32 * t + 16 * u + 4 * hf, 32 * w + c16, lane);
+        const bf16x8 kf = kmajor_frag_acc_order(sm.k, PG, 32 * t + 16 * u + 4 * hf, 32 * w + c16, lane);
+#pragma unroll
+        for (int v4 = 0; v4 < 2; v4++) {
+          const int i4 = 32 * t + 16 * u + 8 * v4 + 4 * hf;
+          const f32x4 b4 = *(const f32x4*)(sm.bet + i4), eg4 = *(const f32x4*)(sm.eg + i4);
+#pragma unroll
+          for (int e = 0; e < 4; e++) {
+            const float dkb = (float)xf[4 * v4 + e];
+            dot[8 * u + 4 * v4 + e] = dkb * (float)kf[4 * v4 + e];
+            dk[t][8 * u + 4 * v4 + e] += b4[e] * eg4[e] * dkb;
+          }
+        }
+      }
+      row_kb[t] = half_wave_sums(dot, c);
       __builtin_amdgcn_sched_barrier(0);
-      float qv[16];
+    }
+
+    // ---- dg, dbeta ----
+    float(*sum_qk)[GC] = (float(*)[GC])(sm.x + X_SUMS);  // per-wave parts of the row sums (a quarter of the columns each)
+    float(*sum_kb)[GC] = sum_qk + 4, *part = &sum_qk[8][0];
+    if (c < 16) {
 #pragma unroll
-      for (int r = 0; r < 16; r++) qv[r] = q_at(32 * T128::ib(w, t) + tile_row(r, hf), j);
-#pragma unroll
-      for (int r = 0; r < 16; r++) {
-        const int i = 32 * T128::ib(w, t) + tile_row(r, hf);
-        acc[t][r] *= scale * eg[i];                                 // scale eg dQg_i: its contribution to dq_i
-        const float dot = half_wave_sum(acc[t][r] * qv[r]);         // dQg_i . Qg_i = (scale eg dQg_i) . q_i
-        if (c == HALF_SUM_LANE) dot_q[w][i] = dot;
+      for (int t = 0; t < 2; t++) {
+        sum_qk[w][32 * t + tile_row(c, hf)] = row_qk[t];
+        sum_kb[w][32 * t + tile_row(c, hf)] = row_kb[t];
       }
     }
-    slab_product<GD, GC>(fn_loader_a([&](int i, int k) { return dpm[i * AP + k]; }), RowsJLoaderB{kb, qrow32, len}, acc, as, bs, tid);
+    // what goes through gamma_last: <dKd, Kd>, and exp(gamma_last) <dS1, S0> (it also scales the state that is carried over)
+    float s_last = s_kd + el_last * s_dot;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) s_last += __shfl_xor(s_last, d);
+    if (lane == 0) part[w] = s_last;
+    lds_barrier();
+    if (tid < GC) {
+      const float dkb = sm.eg[tid] * ((sum_kb[0][tid] + sum_kb[1][tid]) + (sum_kb[2][tid] + sum_kb[3][tid]));       // eg dKb_i . k_i
+      float s = (sm.dg_row[0][tid] + sm.dg_row[1][tid]) - (sm.dg_col[0][tid] + sm.dg_col[1][tid]) +
+                ((sum_qk[0][tid] + sum_qk[1][tid]) + (sum_qk[2][tid] + sum_qk[3][tid])) + sm.bet[tid] * dkb;
+      // gamma_i = sum of g_j over j <= i: a sum over the rows from this one on; gamma_last reaches every g
+#pragma unroll
+      for (int d = 1; d < GC; d <<= 1) {
+        const float down = __shfl_down(s, d);
+        s += tid + d < GC ? down : 0.f;
+      }
+      const float last = (part[0] + part[1]) + (part[2] + part[3]);
+      if (tid < len) {
+        a.b.dg[(size_t)(tok0 + tid) * hv + h] = s + last;
+        a.b.dbeta[(size_t)(tok0 + tid) * hv + h] = sm.db_a[0][tid] + sm.db_a[1][tid] + dkb + sm.db_v[tid];
+      }
+    }
+  }
+
+  place();
+  if constexpr (SPLIT) {
 #pragma unroll
     for (int t = 0; t < 2; t++)
 #pragma unroll
       for (int r = 0; r < 16; r++) {
-        const int i = 32 * T128::ib(w, t) + tile_row(r, hf);
-        if (i < len) a.w.dqh[((size_t)(tok0 + i) * a.b.hv_n + h) * GD + j] = acc[t][r];
-      }
-  }
-  __builtin_amdgcn_sched_barrier(0);
-  // dk_j = el_j (Vn dS1^T)_j + beta_j eg_j dKb_j + sum_i (dP scale D)_ij q_i + sum_i (MA_ij + MA_ji) k_i
-  {
-    f32x16 acc[2] = {zero16(), zero16()};
-    slab_product<GD, GD>(FragLoader<PK_A>{vns}, RowsJLoaderB{ds1t, GD, GD}, acc, as, bs, tid);
-    int zz = 0;
-    asm volatile("" : "+v"(zz));          // row offsets are recomputed here, not kept in registers since the dq block
-    const int d = 32 * T128::jb(w) + c + zz;
-#pragma unroll
-    for (int t = 0; t < 2; t++) {
-      __builtin_amdgcn_sched_barrier(0);
-      float kvs[16], dkbs[16];              // loads first, as above
-#pragma unroll
-      for (int r = 0; r < 16; r++) {
-        const int i = 32 * T128::ib(w, t) + tile_row(r, hf);
-        kvs[r] = k_at(i, d);
-        dkbs[r] = (float)X[i * (2 * GD) + GD + d];
-      }
-#pragma unroll
-      for (int r = 0; r < 16; r++) {
-        const int i = 32 * T128::ib(w, t) + tile_row(r, hf);
-        const float fe = el[i], fkb = bet[i] * eg[i];
-        const float kv = kvs[r], dkb = dkbs[r];
-        const float s_kd = half_wave_sum(acc[t][r] * kv), s_kb = half_wave_sum(dkb * kv);
-        if (c == HALF_SUM_LANE) {
-          dot_kd[w][i] = s_kd;
-          dot_kb[w][i] = s_kb;
+        const int i = 32 * t + tile_row(r, hf);
+        const size_t at = ((size_t)(tok0 + i) * a.b.hv_n + unit) * GD + 32 * w + c;
+        if (i < len) {
+          a.w.dqh[at] = dq[t][r];
+          a.w.dkh[at] = dk[t][r];
         }
-        acc[t][r] = fe * acc[t][r] + fkb * dkb;
       }
-    }
-    slab_product<GD, GC>(fn_loader_a([&](int i, int k) { return dpm[k * AP + i]; }), RowsJLoaderB{qb, qrow32, len}, acc, as, bs, tid);
-    slab_product<GD, GC>(fn_loader_a([&](int i, int k) { return dam[i * AP + k] + dam[k * AP + i]; }), RowsJLoaderB{kb, qrow32, len}, acc, as, bs,
-                         tid);
+  } else {
+    // through LDS, so that rows leave in 16-byte pieces
+    lds_barrier();                                       // K and Q have been read
 #pragma unroll
     for (int t = 0; t < 2; t++)
 #pragma unroll
       for (int r = 0; r < 16; r++) {
-        const int i = 32 * T128::ib(w, t) + tile_row(r, hf);
-        if (i < len) a.w.dkh[((size_t)(tok0 + i) * a.b.hv_n + h) * GD + d] = acc[t][r];
+        const int at = (32 * t + tile_row(r, hf)) * PG + 32 * w + c;
+        sm.q[at] = (__bf16)dq[t][r];
+        sm.k[at] = (__bf16)dk[t][r];
       }
-  }
-  // dv_i = beta_i dVb_i,  dbeta_i += dVb_i . v_i
-  {
-    const int i = tid >> 2, c0 = (tid & 3) * 32;
-    float dot = 0.f;
-    bf16x8 xb[4], vv[4];
+    lds_barrier();
 #pragma unroll
-    for (int q = 0; q < 4; q++) {
-      xb[q] = *(const bf16x8*)(X + i * (2 * GD) + c0 + 8 * q);
-      vv[q] = *(const bf16x8*)(vb + (size_t)min(i, len - 1) * vrow + c0 + 8 * q);
-    }
-    const float b = bet[i];
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-      float xv[8];
-#pragma unroll
-      for (int e = 0; e < 8; e++) {
-        xv[e] = (float)xb[q][e];
-        dot += xv[e] * (float)vv[q][e];
+    for (int p = 0; p < 4; p++) {
+      const int piece = tid + p * BT, i = piece >> 4, c8 = (piece & 15) * 8;
+      const size_t at = (size_t)(tok0 + i) * qrow + (size_t)kh * GD + c8;
+      if (i < len) {
+        *(bf16x8*)((__bf16*)a.b.dq + at) = *(const bf16x8*)(sm.q + i * PG + c8);
+        *(bf16x8*)((__bf16*)a.b.dk + at) = *(const bf16x8*)(sm.k + i * PG + c8);
       }
-      if (i < len)
-        *(bf16x8*)((__bf16*)a.b.dv + ((size_t)(tok0 + i) * hv + h) * GD + c0 + 8 * q) =
-            cvt8(b * xv[0], b * xv[1], b * xv[2], b * xv[3], b * xv[4], b * xv[5], b * xv[6], b * xv[7]);
     }
-    dot += __shfl_xor(dot, 1);
-    dot += __shfl_xor(dot, 2);
-    if ((tid & 3) == 0) db_v[i] = i < len ? dot : 0.f;
-  }
-  // <dS1, S0>: gamma_last also scales the state that is carried over
-  __syncthreads();                     // every wave is done with the slab arrays (red lives there)
-  {
-    float s = 0.f;
-#pragma unroll
-    for (int p = 0; p < (GD * GD / 8) / BT; p++) {
-      const bf16x8 x = *(const bf16x8*)(ds1t + 8 * (tid + p * BT)), y = *(const bf16x8*)(s0t + 8 * (tid + p * BT));
-#pragma unroll
-      for (int e = 0; e < 8; e++) s += (float)x[e] * (float)y[e];
-    }
-    red[tid] = s;
-  }
-  __syncthreads();
-  if (tid < GC) {
-    // state inner product: 256 partial sums -> 64 (fixed order), the rest below
-    red[tid] = (red[tid] + red[tid + 64]) + (red[tid + 128] + red[tid + 192]);
-  }
-  __syncthreads();
-  if (tid < GC) {
-    // row dot products: the four waves hold a quarter of the columns each
-    const float dq_ = dot_q[0][tid] + dot_q[1][tid] + dot_q[2][tid] + dot_q[3][tid];
-    const float dkd = el[tid] * (dot_kd[0][tid] + dot_kd[1][tid] + dot_kd[2][tid] + dot_kd[3][tid]);      // dKd_i . Kd_i
-    const float dkb = dot_kb[0][tid] + dot_kb[1][tid] + dot_kb[2][tid] + dot_kb[3][tid];                  // dKb_i . k_i
-    dgam[tid] = dg_row[tid] - dg_col[tid] + dq_ - dkd + bet[tid] * eg[tid] * dkb;
-    red[64 + tid] = dkd + el_last * red[tid];             // what reaches every g through gamma_last, 64 parts
-    red[128 + tid] = db_a[tid] + eg[tid] * dkb + db_v[tid];
-  }
-  __syncthreads();
-  if (tid < len) {
-    float s = 0.f, last = 0.f;
-#pragma unroll
-    for (int i = 0; i < GC; i++) {                        // independent reads, fixed order
-      s += i >= tid ? dgam[i] : 0.f;                      // gamma_i = sum of g_j over j <= i
-      last += red[64 + i];
-    }
-    a.b.dg[(size_t)(tok0 + tid) * hv + h] = s + last;
-    a.b.dbeta[(size_t)(tok0 + tid) * hv + h] = red[128 + tid];
   }
 }
 
@@ -635,7 +607,7 @@ size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 // carves the workspace; returns the total size (with p == nullptr: only the size)
 // (hv_n: value heads of one pass; the saved states and their gradients keep the tensors' head stride hv)
-size_t carve(char* p, int64_t n_tokens, int n_chunks, int n_slots, int n_segments, int hv, int hv_n, BwdWs* w) {
+size_t carve(char* p, int64_t n_tokens, int n_chunks, int n_slots, int n_segments, int hv, int hv_n, bool split, BwdWs* w) {
   const size_t per = (size_t)n_chunks * hv_n;
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -645,9 +617,7 @@ size_t carve(char* p, int64_t n_tokens, int n_chunks, int n_slots, int n_segment
   };
   BwdWs t{};
   t.ops.gam = (float*)take(per * GC * 4);
-  t.ops.a0 = (float*)take(per * GC * GC * 4);
-  t.ops.p = (float*)take(per * GC * GC * 4);
-  t.ops.t = (float*)take(per * GC * GC * 4);
+  t.ops.t = (float*)take(per * GDN_T_ELEMS * 4);
   t.sv.fwd_rec = take(per * GDN_REC_ELEMS * 2);
   t.sv.rev_rec = take(per * GDN_REC_ELEMS * 2);
   t.sv.glast = (float*)take(per * 4);
@@ -658,17 +628,26 @@ size_t carve(char* p, int64_t n_tokens, int n_chunks, int n_slots, int n_segment
   t.sv.slots = (float*)take((size_t)n_slots * hv * GD * GD * 4);
   t.sv.slot_grad = (float*)take((size_t)n_slots * hv * GD * GD * 4);
   t.sv.seg_grad = (float*)take((size_t)n_segments * hv * GD * GD * 4);
-  t.x = (__bf16*)take(per * GC * 2 * GD * 2);
-  t.dqh = (float*)take((size_t)n_tokens * hv_n * GD * 4);
-  t.dkh = (float*)take((size_t)n_tokens * hv_n * GD * 4);
+  if (split) {
+    t.dqh = (float*)take((size_t)n_tokens * hv_n * GD * 4);
+    t.dkh = (float*)take((size_t)n_tokens * hv_n * GD * 4);
+  }
   if (w) *w = t;
   return off + 256;
 }
 
+// One value head per workgroup of the finish kernel where a call has few (chunk, key head) pairs (the chip holds 512
+// workgroups): there the value heads side by side are worth more than the fp32 dq / dk saved.  Whole backward, two value
+// heads per key head, one by one / in one workgroup: 164 pairs 200 / 208 us, 328 pairs 221 / 225, 332 pairs (longer walk)
+// 317 / 316, 408 pairs 279 / 265, 664 pairs 443 / 430, 1328 pairs 636 / 610.  The whole call decides, not the pass: results do not depend on how much workspace there is.
+constexpr int64_t FINISH_SPLIT_BELOW = 384;
+bool finish_split(int n_chunks, int hk, int hv) { return hv > hk && (int64_t)n_chunks * hk < FINISH_SPLIT_BELOW; }
+
 }  // namespace
 
 size_t gdn_bwd_workspace(int64_t n_tokens, int n_chunks, int n_slots, int n_segments, int hk, int hv, int key_heads_per_pass) {
-  return carve(nullptr, n_tokens, n_chunks, n_slots, n_segments, hv, key_heads_per_pass * (hv / hk), nullptr);
+  return carve(nullptr, n_tokens, n_chunks, n_slots, n_segments, hv, key_heads_per_pass * (hv / hk),
+               finish_split(n_chunks, hk, hv), nullptr);
 }
 
 // The value heads are independent of each other up to the final sum over the value heads of a key head, so the
@@ -682,6 +661,7 @@ hipError_t gdn_bwd(const GdnBwdArgs& b0, hipStream_t st) {
     per_pass--;
   if (gdn_bwd_workspace(b0.n_tokens, b0.n_chunks, b0.n_slots, n_seg, b0.hk, b0.hv, per_pass) > b0.workspace_bytes)
     return hipErrorInvalidValue;
+  const bool split = finish_split(b0.n_chunks, b0.hk, b0.hv);
   auto zero = [&](float* p, size_t floats) {
     if (floats == 0) return;
     const size_t n4 = floats / 4;
@@ -701,7 +681,7 @@ hipError_t gdn_bwd(const GdnBwdArgs& b0, hipStream_t st) {
     if (b0.d_initial_state) b.d_initial_state = b0.d_initial_state + so;
     KArgs a{};
     a.b = b;
-    carve((char*)b.workspace, b.n_tokens, b.n_chunks, b.n_slots, n_seg, b.hv, b.hv_n, &a.w);
+    carve((char*)b.workspace, b.n_tokens, b.n_chunks, b.n_slots, n_seg, b.hv, b.hv_n, split, &a.w);
     // walking all chunks in sequence order, readers add into the slot gradients and into d_initial_state; with a
     // schedule every segment stores its own gradient and nothing has to start from zero
     if (!b.sched) {
@@ -715,10 +695,11 @@ hipError_t gdn_bwd(const GdnBwdArgs& b0, hipStream_t st) {
     if (hipError_t e = gdn_bwd_prepare_and_walks(b, a.w.ops, a.w.sv, st); e != hipSuccess) return e;
     {
       KernelTimer t(TT_KERNEL_GDN_BWD_FINISH, st);
-      gdn_bwd_finish_kernel<<<gdn_group_order_grid(b.n_chunks, b.hv_n, b.hv / b.hk), BT, 0, st>>>(a);
+      if (split) gdn_bwd_finish_kernel<true><<<gdn_group_order_grid(b.n_chunks, b.hv_n, rep), BT, 0, st>>>(a);
+      else gdn_bwd_finish_kernel<false><<<gdn_group_order_grid(b.n_chunks, hk_n, 1), BT, 0, st>>>(a);
     }
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-    {
+    if (split) {
       const size_t n4 = (size_t)b.n_tokens * hk_n * (GD / 4);
       gdn_bwd_group_sum_kernel<<<dim3((unsigned)std::min<size_t>((n4 + BT - 1) / BT, 8192)), BT, 0, st>>>(a);
     }

@@ -96,10 +96,10 @@ size_t gdn_workspace(int n_chunks, int n_slots, int hv);
 // finish kernel):
 struct GdnChunkOps {
   float* gam;      // [64]       running sum of the log-decays inside the chunk
-  float* a0;       // [64][64]   strictly-lower (k_i . k_j) exp(gamma_i - gamma_j)   (A without beta_i)
-  float* p;        // [64][64]   scale tril((q_i . k_j) exp(gamma_i - gamma_j))
-  float* t;        // [64][64]   (I + A)^-1, A = diag(beta) a0: the inverse both triangular solves are products with
+  float* t;        // [3][32][32] the blocks T11, T21, T22 of (I + A)^-1 (T12 is zero), A = strictly-lower(beta_i
+                   //            (k_i . k_j) exp(gamma_i - gamma_j)): the inverse both triangular solves are products with
 };
+constexpr size_t GDN_T_ELEMS = 3 * 32 * 32;
 // bf16 operands of the two walks and what they save for the finish kernel:
 constexpr size_t GDN_REC_ELEMS = 4 * 64 * 128 + 64 * 64;     // elements of one walk record (forward and reverse alike)
 constexpr size_t GDN_REC_UT = 64 * 128;      // forward record: U^T [128 value cols][64 tokens], U = (I + A)^-1 (beta V)

@@ -146,3 +146,23 @@ def test_chunk_boundary_lengths():
     parent = [-1, 0, 0, 1, 1, 2, -1, 6, 7]
     seg = [64, 63, 65, 128, 1, 0, 129, 0, 2]
     _check(W._mk(parent, seg, [1] * len(seg), "boundaries"), 1, 2, 77)
+
+
+@pytest.mark.parametrize("n_nodes,hk,hv", [(11, 32, 64), (12, 32, 64), (16, 32, 96), (3, 171, 171)])
+def test_value_heads_of_a_workgroup(n_nodes, hk, hv):
+    """From 384 (chunk, key head) pairs on, one workgroup takes all value heads of a key head and sums dq and dk on chip;
+    below, every value head has a workgroup of its own.  Both sides of that line, two and three value heads per key head
+    and one; passes over a part of the key heads give the same bits."""
+    parent = [-1] + [(i - 1) // 2 for i in range(1, n_nodes)]
+    tree = W._mk(parent, [1 + (5 * i) % 9 for i in range(n_nodes)], [1] * n_nodes, "short nodes")
+    _check(tree, hk, hv, 55)
+    plan = T.tree_gdn_plan(tree.parent, tree.seg_len).to_device()
+    assert plan.n_chunks == n_nodes
+    n = sum(tree.seg_len)
+    ins = [x.cuda() for x in _inputs(n, hk, hv, 56)]
+    outs = []
+    for smallest in (False, True):
+        ws = torch.empty(T.tree_gdn_bwd_workspace(n, hk, hv, plan, smallest=smallest), dtype=torch.uint8, device="cuda")
+        outs.append(T.tree_gdn_bwd(*ins, plan, workspace=ws))
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(*outs))
