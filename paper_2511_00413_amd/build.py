@@ -10,7 +10,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtreetrain.so")
 
-SOURCES = ["tt_error.cpp", "tt_meta.cpp", "tt_api.hip", "tt_timing.hip", "tt_attn_ref.hip", "tt_loss.hip",
+SOURCES = ["tt_error.cpp", "tt_meta.cpp", "tt_api.hip", "tt_timing.hip", "tt_attn_ref.hip", "tt_attn_f32.hip", "tt_loss.hip",
            "tt_attn_fwd.hip", "tt_attn_bwd.hip", "tt_attn_dkdv.hip", "tt_rope.hip", "tt_partition.cpp",
            "tt_partition_run.hip", "tt_conv.hip", "tt_gdn.hip", "tt_gdn_bwd.hip"]
 

@@ -15,6 +15,7 @@ struct Checked {
   tt::AttnArgs a;
   bool bf16;
   bool use_mfma;
+  bool use_f32;       // fp32 tensors with a head dim of 64 or 128: the fp32 matrix instruction
 };
 
 size_t delta_bytes(const tt_attn_desc* d) {
@@ -72,6 +73,7 @@ tt_status check_common(const tt_attn_desc* d, const void* q, const void* k_own, 
   a.kend = kend; a.kt_min = kt_min; a.kt_max = kt_max;
   c.bf16 = d->dtype == TT_DTYPE_BF16;
   c.use_mfma = mfma_supported(d);
+  c.use_f32 = !c.bf16 && !(d->flags & TT_FLAG_REFERENCE_KERNELS) && tt::f32_attn_supported(a);
   return TT_OK;
 }
 
@@ -107,6 +109,7 @@ extern "C" tt_status tt_tree_attn_fwd(const tt_attn_desc* desc, const void* q, c
   c.a.workspace = workspace; c.a.workspace_bytes = workspace_bytes;
   hipStream_t st = (hipStream_t)stream;
   if (c.use_mfma) return hip_result(tt::mfma_attn_fwd(c.a, st), "tree_attn_fwd");
+  if (c.use_f32) return hip_result(tt::f32_attn_fwd(c.a, st), "tree_attn_fwd (fp32)");
   return hip_result(tt::ref_attn_fwd(c.a, c.bf16, st), "tree_attn_fwd (reference kernels)");
 }
 
@@ -138,6 +141,7 @@ extern "C" tt_status tt_tree_attn_bwd(const tt_attn_desc* desc, const void* q, c
   c.a.workspace_bytes = workspace_bytes - delta_bytes(desc);
   hipStream_t st = (hipStream_t)stream;
   if (c.use_mfma) return hip_result(tt::mfma_attn_bwd(c.a, st), "tree_attn_bwd");
+  if (c.use_f32) return hip_result(tt::f32_attn_bwd(c.a, st), "tree_attn_bwd (fp32)");
   return hip_result(tt::ref_attn_bwd(c.a, c.bf16, st), "tree_attn_bwd (reference kernels)");
 }
 

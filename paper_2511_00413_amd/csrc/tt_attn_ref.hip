@@ -1,7 +1,6 @@
 // Reference-grade tree attention kernels: plain fp32 arithmetic, one wavefront per query row
-// (forward, dQ) or per key (dK/dV), no matrix cores.  This is the TT_DTYPE_FP32 path of the
-// library (the paper verifies its gradients in float32, Appendix "Numerical Verification"); the
-// same code also runs on bf16 tensors for cross-checking the MFMA kernels.
+// (forward, dQ) or per key (dK/dV), no matrix cores.  Head dims other than 64 and 128 in fp32 and
+// other than 128 in bf16, and any of them for cross-checking the matrix kernels (TT_FLAG_REFERENCE_KERNELS).
 //
 // Mask (Section "Attention Mask"): key j is visible to query i  <=>  j <= i + P < kend[j].
 // Deterministic: every output element is produced by one wavefront in a fixed order.

@@ -46,6 +46,11 @@ typedef RefArgs AttnArgs;
 hipError_t ref_attn_fwd(const RefArgs& a, bool bf16, hipStream_t st);
 hipError_t ref_attn_bwd(const RefArgs& a, bool bf16, hipStream_t st);
 
+// fp32 kernels on the fp32 matrix instruction, d = 64 and 128 (tt_attn_f32.hip)
+bool f32_attn_supported(const RefArgs& a);
+hipError_t f32_attn_fwd(const RefArgs& a, hipStream_t st);
+hipError_t f32_attn_bwd(const RefArgs& a, hipStream_t st);
+
 // bf16 MFMA kernels, d = 128 (tt_attn_fwd.hip / tt_attn_bwd.hip)
 hipError_t mfma_attn_fwd(const AttnArgs& a, hipStream_t st);
 hipError_t mfma_attn_bwd(const AttnArgs& a, hipStream_t st);

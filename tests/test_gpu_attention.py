@@ -203,3 +203,38 @@ def test_token_strides_of_a_fused_qkv_buffer():
     o, lse = T.tree_attn_fwd(qv, kv, vv, kend, kmin, kmax)
     dq, dk, dv = T.tree_attn_bwd(qv, kv, vv, kend, kmin, kmax, o, dev(do), lse)
     assert np.array_equal(f64(o), plain["o"]) and np.array_equal(f64(dk), plain["dk"]) and np.array_equal(f64(dq), plain["dq"])
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(2, 2, 64), (6, 2, 128)])
+def test_fp32_matrix_kernels_block_edges(hq, hkv, d):
+    """Token counts around the 16-wide blocks and the 128 keys of one round of the waves, nodes that start inside a block,
+    and cached keys that end inside one."""
+    dims = W.AttnDims(hq, hkv, d, "fp32", 1.0)
+    # (a single token has dq = dk = 0 by cancellation, <dO, V> - <dO, O> with O = V: nothing to be relative to)
+    for segs in ([2], [15], [16], [17], [128], [129], [40, 1, 3, 88], [500, 13]):
+        _full_parity(W.chain_tree(segs), dims, sum(segs), label="fp32-chain")
+    _full_parity(W.random_tree(641, n_nodes=24, lo=1, hi=30, n_roots=2, p_zero=0.1), dims, 8, label="fp32-short-nodes")
+    vis = np.ones(37, dtype=np.uint8)
+    vis[5:20] = 0
+    _prefix_case("fp32", 22, 37, vis, W.random_tree(642, n_nodes=6, lo=1, hi=50), hq, hkv, d, False)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_non_finite_values_reach_only_who_sees_them(d):
+    """Infinities and NaN in one branch stay out of the rows of every token that does not see it: finite in exactly the
+    places where the row-by-row kernels are."""
+    from gpu_util import gpu_attention
+    tree = W._mk([-1, 0, 0, 1], [21, 30, 45, 9], [1] * 4, "four nodes")
+    meta = T.tree_build_meta(tree.parent, tree.seg_len)
+    n = meta.n_tokens
+    q, k, v, do = W.attn_inputs(n, n, W.AttnDims(2, 1, d, "fp32", 1.0), 3)
+    v[25, 0, 3] = float("inf")
+    k[30, 0, 1] = float("nan")
+    q[70, 1, 2] = float("nan")
+    do[90, 0, 5] = float("inf")
+    got, ref = (gpu_attention(meta, q, k, v, do, reference_kernels=r) for r in (False, True))
+    for key in ("o", "lse", "dq", "dk", "dv"):
+        fin = np.isfinite(ref[key])
+        assert np.array_equal(np.isfinite(got[key]), fin), key
+        # one wave's sums in another order: 1e-5 of the largest entry
+        assert fin.any() and not fin.all() and np.abs(got[key][fin] - ref[key][fin]).max() <= 1e-5 * np.abs(ref[key][fin]).max(), key
