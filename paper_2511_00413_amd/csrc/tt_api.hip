@@ -214,7 +214,7 @@ extern "C" tt_status tt_tree_weighted_logprob_fwd_bwd(int64_t n_rows, int32_t vo
     return hip_result(tt::weighted_logprob_fused(n_rows, vocab, bf16, logits, row_stride, target, weight, grad_scale, logp, lse,
                                                  loss_acc, dlogits, dlogits_row_stride, st),
                       "tree_weighted_logprob_fwd_bwd");
-  // rows off the 16-byte grid: the two passes one after the other
+  // logits and gradient rows at different distances from the 16-byte grid: the two passes one after the other
   if (tt_status s = hip_result(tt::weighted_logprob(n_rows, vocab, bf16, logits, row_stride, target, weight, logp, lse, loss_acc, st),
                                "tree_weighted_logprob_fwd_bwd (forward pass)"))
     return s;

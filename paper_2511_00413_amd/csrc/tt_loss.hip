@@ -8,6 +8,7 @@
 // loss is bit-reproducible.
 #include <hip/hip_runtime.h>
 #include <algorithm>
+#include <type_traits>
 #include <hip/hip_bf16.h>
 #include "tt_kernels.h"
 
@@ -246,16 +247,28 @@ row_dlogits_kernel(int vocab, const T* logits, int64_t row_stride, const int32_t
 
 // ---- forward and backward in one pass ----------------------------------------------------------------
 // When the gradient is wanted together with the loss (the usual training step), a row is read from memory
-// once: the workgroup streams it, keeps its first `lds_vecs` 16-byte vectors in LDS while it accumulates
-// (max, sum of exp), and then forms the gradient from that copy; what did not fit (a vocabulary beyond
-// FUSED_LDS_BYTES per row) is read a second time, right behind the first read, so that it mostly comes out of
-// the caches.  Both the row and the gradient row must start on a 16-byte boundary (the host checks that and
-// uses the two separate kernels otherwise).  Same arithmetic per element as the separate kernels.
+// once: the workgroup streams it, keeps what it can on chip while it accumulates (max, sum of exp), and then forms
+// the gradient from that copy; what did not fit is read a second time, right behind the first read.
+//   NREG = 0: the first `lds_vecs` 16-byte vectors of the row are kept in LDS.
+//   NREG > 0: the first NREG * FUSED_THREADS vectors are kept in registers, the next ones in LDS.
+// A row may start anywhere on the element grid as long as logits and gradient row are the same distance from a
+// 16-byte boundary (the host checks that and uses the two separate kernels otherwise): the elements in front of the
+// first boundary and behind the last whole vector are done one by one.  Same arithmetic per element as the separate
+// kernels.
 constexpr int FUSED_THREADS = 512;
 constexpr int FUSED_LDS_BYTES = 64 * 1024;             // two workgroups per compute unit
+// The register form, for rows longer than 96 KB.  Bound by HBM with the exponentials' issue slots close behind, so two
+// workgroups share a compute unit (one streams in while the other stores), which leaves 128 registers per lane: 12
+// vectors in registers and 72 KB of LDS keep 168 KB of a row.  4096 rows: 151936 bf16 entries 499 -> 474 us, 100352
+// 315 -> 294 us, 40064 fp32 260 -> 244 us; 8 / 16 / 18 / 20 vectors: within 2 % of that, some sizes to either side.  Rows
+// of up to 96 KB measured the same in both forms (65536 bf16: 196 against 198 us) and stay with the first one.
+// Rows off the 16-byte grid ran the two separate kernels before, the gradient element by element: 32003 bf16 entries
+// 254 -> 114 us, 151935 1127 -> 520 us.
+constexpr int FUSED_BIG_NREG = 12;
+constexpr int FUSED_BIG_LDS_BYTES = 72 * 1024;
 
-template <typename T>
-__global__ void __launch_bounds__(FUSED_THREADS)
+template <typename T, int NREG>
+__global__ void __launch_bounds__(FUSED_THREADS, 4)
 row_logprob_dlogits_kernel(int vocab, const T* logits, int64_t row_stride, const int32_t* __restrict__ target,
                            const float* __restrict__ weight, float grad_scale, float* __restrict__ logp,
                            float* __restrict__ lse_out, T* dlogits, int64_t out_stride, int lds_vecs) {
@@ -267,14 +280,17 @@ row_logprob_dlogits_kernel(int vocab, const T* logits, int64_t row_stride, const
   const T* row = logits + r * row_stride;
   T* out = dlogits + r * out_stride;
   const int t = threadIdx.x;
-  const int nvec = vocab / EPV;
-  const u32x4* vp = reinterpret_cast<const u32x4*>(row);
-  u32x4* op = reinterpret_cast<u32x4*>(out);
+  // [0, head) one by one, [head, head + nvec * EPV) in vectors, the rest one by one
+  const int head = min((int)(((16 - (reinterpret_cast<uintptr_t>(row) & 15)) & 15) / sizeof(T)), vocab);
+  const int nvec = (vocab - head) / EPV;
+  const int tail0 = head + nvec * EPV;
+  const u32x4* vp = reinterpret_cast<const u32x4*>(row + head);
+  u32x4* op = reinterpret_cast<u32x4*>(out + head);
   const int y = target[r];
   const bool used = y >= 0 && y < vocab;
   const float w = used ? grad_scale * (weight ? weight[r] : 1.f) : 0.f;
 
-  // ---- pass 1: statistics; the part of the row that is kept goes to LDS ----
+  // ---- pass 1: statistics ----
   MS st = {-INFINITY, 0.f};
   auto push_vec = [&](const u32x4& v) {
     if constexpr (sizeof(T) == 2) {
@@ -286,20 +302,30 @@ row_logprob_dlogits_kernel(int vocab, const T* logits, int64_t row_stride, const
       push1(st, __uint_as_float(v.z)); push1(st, __uint_as_float(v.w));
     }
   };
-  const int n_kept = min(nvec, lds_vecs);
+  [[maybe_unused]] u32x4 kept[NREG > 0 ? NREG : 1];
+  if constexpr (NREG > 0) {
+    // (the host picks this form only for rows of more than NREG * FUSED_THREADS vectors)
+#pragma unroll
+    for (int j = 0; j < NREG; j++) kept[j] = __builtin_nontemporal_load(vp + j * FUSED_THREADS + t);
+#pragma unroll
+    for (int j = 0; j < NREG; j++) { push_vec(kept[j]); __builtin_amdgcn_sched_barrier(0); }
+  }
+  constexpr int reg_vecs = NREG * FUSED_THREADS;
+  const int n_kept = min(nvec, reg_vecs + lds_vecs);   // vectors kept on chip
   {
-    int i = t;
+    int i = reg_vecs + t;
     for (; i + 3 * FUSED_THREADS < n_kept; i += 4 * FUSED_THREADS) {      // 4 loads in flight per thread
       const u32x4 v0 = __builtin_nontemporal_load(vp + i);
       const u32x4 v1 = __builtin_nontemporal_load(vp + i + FUSED_THREADS);
       const u32x4 v2 = __builtin_nontemporal_load(vp + i + 2 * FUSED_THREADS);
       const u32x4 v3 = __builtin_nontemporal_load(vp + i + 3 * FUSED_THREADS);
-      rowbuf[i] = v0; rowbuf[i + FUSED_THREADS] = v1; rowbuf[i + 2 * FUSED_THREADS] = v2; rowbuf[i + 3 * FUSED_THREADS] = v3;
+      u32x4* l = rowbuf + (i - reg_vecs);
+      l[0] = v0; l[FUSED_THREADS] = v1; l[2 * FUSED_THREADS] = v2; l[3 * FUSED_THREADS] = v3;
       push_vec(v0); push_vec(v1); push_vec(v2); push_vec(v3);
     }
     for (; i < n_kept; i += FUSED_THREADS) {
       const u32x4 v0 = __builtin_nontemporal_load(vp + i);
-      rowbuf[i] = v0;
+      rowbuf[i - reg_vecs] = v0;
       push_vec(v0);
     }
   }
@@ -311,7 +337,8 @@ row_logprob_dlogits_kernel(int vocab, const T* logits, int64_t row_stride, const
     }
     for (; i < nvec; i += FUSED_THREADS) push_vec(vp[i]);
   }
-  for (int e = nvec * EPV + t; e < vocab; e += FUSED_THREADS) push1(st, elem(row, e));
+  for (int e = t; e < head; e += FUSED_THREADS) push1(st, elem(row, e));
+  for (int e = tail0 + t; e < vocab; e += FUSED_THREADS) push1(st, elem(row, e));
   for (int o = 32; o > 0; o >>= 1) {
     MS other = {__shfl_xor(st.m, o), __shfl_xor(st.s, o)};
     st = merge(st, other);
@@ -332,10 +359,18 @@ row_logprob_dlogits_kernel(int vocab, const T* logits, int64_t row_stride, const
 
   // ---- pass 2: gradient ----
   auto grad = [&](const u32x4& v, int i) {
-    if constexpr (sizeof(T) == 2) return grad_vec_bf16(v, lse, w, i * EPV, y);
-    else return grad_vec_f32(v, lse, w, i * EPV, y);
+    if constexpr (sizeof(T) == 2) return grad_vec_bf16(v, lse, w, head + i * EPV, y);
+    else return grad_vec_f32(v, lse, w, head + i * EPV, y);
   };
-  for (int i = t; i < n_kept; i += FUSED_THREADS) __builtin_nontemporal_store(grad(rowbuf[i], i), op + i);
+  if constexpr (NREG > 0) {
+#pragma unroll
+    for (int j = 0; j < NREG; j++) {
+      asm volatile("" : "+v"(kept[j]));                 // (else its unpacked form is kept from pass 1, in twice the registers)
+      const int i = j * FUSED_THREADS + t;
+      __builtin_nontemporal_store(grad(kept[j], i), op + i);
+    }
+  }
+  for (int i = reg_vecs + t; i < n_kept; i += FUSED_THREADS) __builtin_nontemporal_store(grad(rowbuf[i - reg_vecs], i), op + i);
   {
     int i = n_kept + t;
     for (; i + 3 * FUSED_THREADS < nvec; i += 4 * FUSED_THREADS) {
@@ -353,45 +388,52 @@ row_logprob_dlogits_kernel(int vocab, const T* logits, int64_t row_stride, const
       __builtin_nontemporal_store(grad(v0, i), op + i);
     }
   }
-  for (int e = nvec * EPV + t; e < vocab; e += FUSED_THREADS) {
+  auto single = [&](int e) {
     const float g = w * ex2((elem(row, e) - lse) * LOG2E) - (e == y ? w : 0.f);
     store_elem(out, e, g);
-  }
+  };
+  for (int e = t; e < head; e += FUSED_THREADS) single(e);
+  for (int e = tail0 + t; e < vocab; e += FUSED_THREADS) single(e);
+}
+
+template <typename T, int NREG>
+hipError_t launch_fused(int64_t n_rows, int vocab, const T* logits, int64_t row_stride, const int32_t* target, const float* weight,
+                        float grad_scale, float* logp, float* lse, T* dlogits, int64_t out_stride, hipStream_t st) {
+  constexpr int cap = NREG > 0 ? FUSED_BIG_LDS_BYTES : FUSED_LDS_BYTES;
+  const int nvec = vocab / (int)(16 / sizeof(T));                        // of a row that starts on a boundary; others have fewer
+  const int lds_vecs = std::min(std::max(nvec - NREG * FUSED_THREADS, 0), cap / 16);
+  if (hipError_t e = hipFuncSetAttribute((const void*)row_logprob_dlogits_kernel<T, NREG>,
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, cap))
+    return e;
+  row_logprob_dlogits_kernel<T, NREG><<<(unsigned)n_rows, FUSED_THREADS, (size_t)lds_vecs * 16, st>>>(
+      vocab, logits, row_stride, target, weight, grad_scale, logp, lse, dlogits, out_stride, lds_vecs);
+  return hipGetLastError();
 }
 
 }  // namespace
 
 bool weighted_logprob_fused_ok(bool bf16, const void* logits, int64_t row_stride, const void* dlogits, int64_t out_stride) {
-  const int esz = bf16 ? 2 : 4;
-  return ((reinterpret_cast<uintptr_t>(logits) | reinterpret_cast<uintptr_t>(dlogits)) & 15) == 0 && (row_stride * esz) % 16 == 0 &&
-         (out_stride * esz) % 16 == 0;
+  const uintptr_t esz = bf16 ? 2 : 4;
+  const uintptr_t in = reinterpret_cast<uintptr_t>(logits), out = reinterpret_cast<uintptr_t>(dlogits);
+  return ((in ^ out) & 15) == 0 && in % esz == 0 && (((uintptr_t)row_stride * esz) & 15) == (((uintptr_t)out_stride * esz) & 15);
 }
 
 hipError_t weighted_logprob_fused(int64_t n_rows, int vocab, bool bf16, const void* logits, int64_t row_stride,
                                   const int32_t* target, const float* weight, float grad_scale, float* logp, float* lse,
                                   float* loss_acc, void* dlogits, int64_t out_stride, hipStream_t st) {
   if (n_rows == 0) return hipSuccess;
-  const int nvec = vocab / (bf16 ? 8 : 4);
-  const int lds_vecs = std::min(nvec, FUSED_LDS_BYTES / 16);
-  const size_t lds = (size_t)lds_vecs * 16;
   {
     KernelTimer timer(TT_KERNEL_LOSS_FUSED, st);
-    if (bf16) {
-      if (hipError_t e = hipFuncSetAttribute((const void*)row_logprob_dlogits_kernel<__hip_bfloat16>,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, FUSED_LDS_BYTES))
-        return e;
-      row_logprob_dlogits_kernel<__hip_bfloat16><<<(unsigned)n_rows, FUSED_THREADS, lds, st>>>(
-          vocab, (const __hip_bfloat16*)logits, row_stride, target, weight, grad_scale, logp, lse, (__hip_bfloat16*)dlogits,
-          out_stride, lds_vecs);
-    } else {
-      if (hipError_t e = hipFuncSetAttribute((const void*)row_logprob_dlogits_kernel<float>,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, FUSED_LDS_BYTES))
-        return e;
-      row_logprob_dlogits_kernel<float><<<(unsigned)n_rows, FUSED_THREADS, lds, st>>>(
-          vocab, (const float*)logits, row_stride, target, weight, grad_scale, logp, lse, (float*)dlogits, out_stride, lds_vecs);
-    }
+    auto run = [&](auto* z, auto* dz) {
+      using T = std::remove_pointer_t<decltype(dz)>;
+      // (one vector less than the row's bytes say: a row off the 16-byte grid loses one to its head and tail)
+      const bool big = (int64_t)vocab * (int64_t)sizeof(T) / 16 > (int64_t)FUSED_BIG_NREG * FUSED_THREADS;
+      return big ? launch_fused<T, FUSED_BIG_NREG>(n_rows, vocab, z, row_stride, target, weight, grad_scale, logp, lse, dz, out_stride, st)
+                 : launch_fused<T, 0>(n_rows, vocab, z, row_stride, target, weight, grad_scale, logp, lse, dz, out_stride, st);
+    };
+    const hipError_t e = bf16 ? run((const __hip_bfloat16*)logits, (__hip_bfloat16*)dlogits) : run((const float*)logits, (float*)dlogits);
+    if (e != hipSuccess) return e;
   }
-  if (hipError_t e = hipGetLastError()) return e;
   if (loss_acc) {
     KernelTimer timer(TT_KERNEL_LOSS_SUM, st);
     weighted_sum_kernel<<<1, 1024, 0, st>>>(n_rows, logp, weight, target, loss_acc);

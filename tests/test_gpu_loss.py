@@ -307,6 +307,22 @@ def test_fwd_bwd_one_pass_in_place_and_strides():
     _check_fused(logits, target, w[:12], inplace=True, grad_scale=2.0)
 
 
+# Rows off the 16-byte grid and rows kept in registers: 6144 vectors of 16 bytes are the last size without the register
+# part, 6145 the first with it (an off-grid row then has exactly 6144), 10752 fill registers and LDS, beyond that a row is
+# read again; lengths that leave heads and tails of 0 .. 7 (fp32: 0 .. 3) elements.
+@pytest.mark.parametrize("rows,vocab,dtype,inplace", [
+    (9, 32003, "bf16", False), (17, 1001, "bf16", True), (9, 15, "bf16", False), (5, 49152, "bf16", False),
+    (5, 49160, "bf16", False), (9, 49161, "bf16", True), (9, 49167, "bf16", False), (3, 86016, "bf16", True),
+    (9, 86027, "bf16", False), (5, 151935, "bf16", True), (5, 777, "fp32", True), (3, 24576, "fp32", False),
+    (5, 24581, "fp32", False), (5, 43009, "fp32", True), (3, 60002, "fp32", False)])
+def test_fwd_bwd_one_pass_off_grid_and_register_rows(rows, vocab, dtype, inplace):
+    logits, target = W.loss_inputs(rows, vocab, rows + vocab, 2.0, dtype)
+    target = target.clone()
+    target[0], target[1], target[2] = 0, vocab - 1, -1
+    w = (np.random.default_rng(vocab).random(rows) + 0.25).astype(np.float32)
+    _check_fused(logits, target, w, grad_scale=0.5, inplace=inplace)
+
+
 def test_fwd_bwd_one_pass_special_rows_and_chunks():
     V = 4096
     z = torch.zeros(6, V)
