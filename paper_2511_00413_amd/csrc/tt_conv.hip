@@ -6,6 +6,7 @@
 // only where the sequence jumps (first token of a node that does not directly follow its parent's
 // last token) and at the start of a tile.
 #include <hip/hip_runtime.h>
+#include <algorithm>
 #include "tt_internal.h"
 #include "tt_kernels.h"
 
@@ -13,56 +14,59 @@ namespace tt {
 namespace {
 
 constexpr int CONV_THREADS = 256;
+constexpr int CONV_BWD_TILE = 256;       // (512 measured the same)
+constexpr int conv_bwd_wgs(bool bf16) { return bf16 ? 3 : 2; }      // workgroups of the backward walk per compute unit (registers)
 
-template <bool BF16> struct Chan { static constexpr int NV = BF16 ? 8 : 4; };
-
-// one 16-byte channel vector of a row, as loaded (8 bf16 or 4 fp32); STREAM: a non-temporal access, for rows
-// that this kernel touches once
+// Channels per lane: four of either type, so 8 bytes of bf16 or 16 of fp32 per access.  The walks are bound by HBM and the
+// arithmetic together (sigmoid, K taps twice over and the weight sums per element), and what hides one under the
+// other is waves: with eight bf16 channels per lane the forward took 133 registers and the backward 247 (3 and 2 waves per
+// SIMD), with four 90 and 142 (5 and 3).  16406 tokens x 8192 channels, K = 4: forward 106 -> 93 us (5.8 TB/s), backward walk
+// 181 -> 170 us (4.7 TB/s).
 typedef unsigned int u32x4c __attribute__((ext_vector_type(4)));
-template <bool STREAM = false>
-__device__ __forceinline__ uint4 load_raw(const void* base, int64_t row, int64_t stride_bytes, int cv) {
-  const char* p = (const char*)base + row * stride_bytes + (int64_t)cv * 16;
-  if (STREAM) {
-    const u32x4c v = __builtin_nontemporal_load(reinterpret_cast<const u32x4c*>(p));
-    return uint4{v.x, v.y, v.z, v.w};
-  }
-  return *reinterpret_cast<const uint4*>(p);
+typedef unsigned int u32x2c __attribute__((ext_vector_type(2)));
+template <bool BF16> struct Chan { static constexpr int NV = 4; using Raw = u32x4c; };
+template <> struct Chan<true> { static constexpr int NV = 4; using Raw = u32x2c; };
+
+// one channel vector of a row, as loaded; STREAM: a non-temporal access, for rows that this kernel touches once
+template <bool BF16, bool STREAM = false>
+__device__ __forceinline__ typename Chan<BF16>::Raw load_raw(const void* base, int64_t row, int64_t stride_bytes, int cv) {
+  using Raw = typename Chan<BF16>::Raw;
+  const Raw* p = (const Raw*)((const char*)base + row * stride_bytes) + cv;
+  return STREAM ? __builtin_nontemporal_load(p) : *p;
 }
 template <bool BF16>
-__device__ __forceinline__ void unpack_raw(const uint4& u, float (&v)[Chan<BF16>::NV]) {
-  if (BF16) {
-    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+__device__ __forceinline__ void unpack_raw(const typename Chan<BF16>::Raw& u, float (&v)[Chan<BF16>::NV]) {
+  if constexpr (BF16) {
 #pragma unroll
-    for (int i = 0; i < 4; i++) {
-      v[2 * i] = __uint_as_float(w[i] << 16);
-      v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+    for (int i = 0; i < 2; i++) {
+      v[2 * i] = __uint_as_float(u[i] << 16);
+      v[2 * i + 1] = __uint_as_float(u[i] & 0xffff0000u);
     }
   } else {
-    v[0] = __uint_as_float(u.x); v[1] = __uint_as_float(u.y); v[2] = __uint_as_float(u.z); v[3] = __uint_as_float(u.w);
+#pragma unroll
+    for (int i = 0; i < 4; i++) v[i] = __uint_as_float(u[i]);
   }
 }
 template <bool BF16>
 __device__ __forceinline__ void load_row(const void* base, int64_t row, int64_t stride_bytes, int cv, float (&v)[Chan<BF16>::NV]) {
-  unpack_raw<BF16>(load_raw(base, row, stride_bytes, cv), v);
+  unpack_raw<BF16>(load_raw<BF16>(base, row, stride_bytes, cv), v);
 }
 
-typedef float f32x8v __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x8v __attribute__((ext_vector_type(8)));
+typedef float f32x4v __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x4v __attribute__((ext_vector_type(4)));
 
 template <bool BF16, bool STREAM = false>
 __device__ __forceinline__ void store_row(void* base, int64_t row, int64_t stride_bytes, int cv, const float (&v)[Chan<BF16>::NV]) {
-  char* p = (char*)base + row * stride_bytes + (int64_t)cv * 16;
-  u32x4c out;
-  if (BF16) {
-    f32x8v f;
+  using Raw = typename Chan<BF16>::Raw;
+  Raw* p = (Raw*)((char*)base + row * stride_bytes) + cv;
+  f32x4v f;
 #pragma unroll
-    for (int i = 0; i < 8; i++) f[i] = v[i];
-    out = __builtin_bit_cast(u32x4c, __builtin_convertvector(f, bf16x8v));       // round to nearest even
-  } else {
-    out = u32x4c{__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])};
-  }
-  if (STREAM) __builtin_nontemporal_store(out, reinterpret_cast<u32x4c*>(p));
-  else *reinterpret_cast<u32x4c*>(p) = out;
+  for (int i = 0; i < 4; i++) f[i] = v[i];
+  Raw out;
+  if constexpr (BF16) out = __builtin_bit_cast(Raw, __builtin_convertvector(f, bf16x4v));       // round to nearest even
+  else out = __builtin_bit_cast(Raw, f);
+  if (STREAM) __builtin_nontemporal_store(out, p);
+  else *p = out;
 }
 
 struct ConvArgs {
@@ -121,19 +125,6 @@ __device__ __forceinline__ void rebuild_window(const ConvArgs& a, int pred, int 
   }
 }
 
-template <bool BF16, int K>
-__device__ __forceinline__ void pre_activation(const Weights<BF16, K>& wt, const float (&xt)[Chan<BF16>::NV],
-                                               const float (&win)[K > 1 ? K - 1 : 1][Chan<BF16>::NV], float (&pre)[Chan<BF16>::NV]) {
-  constexpr int NV = Chan<BF16>::NV;
-#pragma unroll
-  for (int i = 0; i < NV; i++) {
-    float acc = wt.b[i] + wt.w[K - 1][i] * xt[i];
-#pragma unroll
-    for (int m = 1; m < K; m++) acc += wt.w[K - 1 - m][i] * win[m - 1][i];
-    pre[i] = acc;
-  }
-}
-
 // Tokens whose loads are issued together.  A multiple of K: the kernels keep the last K inputs (and, backward,
 // the last K gradients) in rings of K register slots, token t0 + i in slot i % K, and with batches that are
 // multiples of K every slot index is a compile-time constant after unrolling -- the rings never move.
@@ -176,13 +167,13 @@ __global__ __launch_bounds__(CONV_THREADS) void tree_conv_fwd_kernel(ConvArgs a)
   const int t1 = min(t0 + a.tok_tile, a.n_tokens);
   // Two batches of U tokens are in flight: the loads of the next batch are issued before the current one is
   // worked on, so the memory round trip of a batch runs under the arithmetic of the one before.
-  struct Batch { int p[U]; uint4 x[U]; };
+  struct Batch { int p[U]; typename Chan<BF16>::Raw x[U]; };
   auto load_batch = [&](int tb, Batch& b) {
 #pragma unroll
     for (int u = 0; u < U; u++) {
       const int t = min(tb + u, t1 - 1);
       b.p[u] = a.tok_pred[t];
-      b.x[u] = load_raw<true>(a.x, t, a.x_stride, cv);
+      b.x[u] = load_raw<BF16, true>(a.x, t, a.x_stride, cv);
     }
   };
   auto work_batch = [&](int tb, const Batch& b) {       // (tb - t0) is a multiple of U, hence of K
@@ -215,28 +206,13 @@ __global__ __launch_bounds__(CONV_THREADS) void tree_conv_fwd_kernel(ConvArgs a)
   }
 }
 
-// g[t] = dy[t] * act'(pre[t]) for one token, everything recomputed from x (used off the fast path)
-template <bool BF16, int K>
-__device__ __forceinline__ void grad_pre_at(const ConvArgs& a, const Weights<BF16, K>& wt, int t, int cv, float (&g)[Chan<BF16>::NV]) {
-  constexpr int NV = Chan<BF16>::NV;
-  float xt[NV], pre[NV], win[K > 1 ? K - 1 : 1][NV];
-  load_row<BF16>(a.x, t, a.x_stride, cv, xt);
-  rebuild_window<BF16, K>(a, a.tok_pred[t], cv, win);
-  pre_activation<BF16, K>(wt, xt, win, pre);
-  load_row<BF16>(a.dy, t, a.dy_stride, cv, g);
-  if (a.silu) {
-#pragma unroll
-    for (int i = 0; i < NV; i++) g[i] *= dsilu_f(pre[i]);
-  }
-}
-
 // Backward, fast path.  Walks the tile plus K-1 tokens of look-ahead; g of the last K tokens and
 // their "directly follows its predecessor" flags stay in registers.  dx[s] takes the successors
 // s+1 .. s+K-1 for as long as each directly follows the one before (successors that sit elsewhere
 // in DFS order -- later children of a branch point -- are added by the fix-up kernel, which
 // recomputes those few dx rows completely).  dweight / dbias partial sums per tile go to `partial`.
 template <bool BF16, int K>
-__global__ __launch_bounds__(CONV_THREADS) void tree_conv_bwd_kernel(ConvArgs a) {
+__global__ __launch_bounds__(CONV_THREADS, conv_bwd_wgs(BF16)) void tree_conv_bwd_kernel(ConvArgs a) {
   constexpr int NV = Chan<BF16>::NV;
   constexpr int U = ConvBatch<K>::U;
   const int64_t gid = (int64_t)blockIdx.x * CONV_THREADS + threadIdx.x;
@@ -263,14 +239,14 @@ __global__ __launch_bounds__(CONV_THREADS) void tree_conv_bwd_kernel(ConvArgs a)
   const int t1 = min(t0 + a.tok_tile, a.n_tokens);
   const int t_end = t1 + K - 1;                     // look-ahead: g of the K-1 tokens after the tile
   // two batches of U tokens in flight, as in the forward
-  struct Batch { int p[U]; uint4 x[U], dy[U]; };
+  struct Batch { int p[U]; typename Chan<BF16>::Raw x[U], dy[U]; };
   auto load_batch = [&](int tb, Batch& b) {
 #pragma unroll
     for (int u = 0; u < U; u++) {
       const int t = min(tb + u, a.n_tokens - 1);
       b.p[u] = a.tok_pred[t];
-      b.x[u] = load_raw<true>(a.x, t, a.x_stride, cv);
-      b.dy[u] = load_raw<true>(a.dy, t, a.dy_stride, cv);
+      b.x[u] = load_raw<BF16, true>(a.x, t, a.x_stride, cv);
+      b.dy[u] = load_raw<BF16, true>(a.dy, t, a.dy_stride, cv);
     }
   };
   auto work_batch = [&](int tb, const Batch& b) {       // (tb - t0) is a multiple of U, hence of K
@@ -355,24 +331,61 @@ __device__ __forceinline__ void conv_fix_block(const ConvArgs& a, int64_t block)
   Weights<BF16, K> wt;
   wt.load(a, cv * NV);
   const int s = a.fix_tok[f];
-  float dx[NV], g[NV];
+  float dx[NV];
 #pragma unroll
   for (int i = 0; i < NV; i++) dx[i] = 0.f;
-  // successors along a run of directly-following tokens that starts at `first`, whose distance
-  // from s is `r`
+  // Successors along a run of directly-following tokens that starts at `first`, whose distance from s is `r`.  A few rows
+  // of work, so it is the chain of loads that counts: what does not hang on the predecessor chain of `first` (the rows
+  // of up to K tokens of the run) is requested beside it, and the window moves along the run instead of being looked
+  // up again for every token.  (The finish launch at 16406 x 8192: 31 us, with the reduce below in 16 segments 23, with
+  // this 11; it is the larger part of a small call: 700 x 2048 61 -> 39 us.)
   auto add_run = [&](int first, int r) {
-    for (int m1 = 0; r + m1 < K; m1++) {
-      const int t = first + m1;
-      if (m1 > 0 && (t >= a.n_tokens || a.tok_pred[t] != t - 1)) break;
-      grad_pre_at<BF16, K>(a, wt, t, cv, g);
-      const int j = K - 1 - (r + m1);
-      // weight row j selected without dynamic register indexing
+    int pr[K];
+    typename Chan<BF16>::Raw xq[K], dyq[K];
 #pragma unroll
-      for (int jj = 0; jj < K; jj++)
-        if (jj == j) {
+    for (int u = 0; u < K; u++) {
+      const int t = min(first + u, a.n_tokens - 1);
+      pr[u] = a.tok_pred[t];
+      xq[u] = load_raw<BF16>(a.x, t, a.x_stride, cv);
+      dyq[u] = load_raw<BF16>(a.dy, t, a.dy_stride, cv);
+    }
+    float win[K][NV];                                        // x of the token, of its predecessor, ...
+    {
+      float before[K - 1][NV];
+      rebuild_window<BF16, K>(a, pr[0], cv, before);
 #pragma unroll
-          for (int i = 0; i < NV; i++) dx[i] += wt.w[jj][i] * g[i];
+      for (int m = 1; m < K; m++)
+#pragma unroll
+        for (int i = 0; i < NV; i++) win[m][i] = before[m - 1][i];
+    }
+    bool in_run = true;
+#pragma unroll
+    for (int u = 0; u < K; u++) {
+      in_run = in_run && r + u < K && (u == 0 || (first + u < a.n_tokens && pr[u] == first + u - 1));
+      if (u > 0) {
+#pragma unroll
+        for (int m = K - 1; m > 0; m--)
+#pragma unroll
+          for (int i = 0; i < NV; i++) win[m][i] = win[m - 1][i];
+      }
+      unpack_raw<BF16>(xq[u], win[0]);
+      float g[NV];
+      unpack_raw<BF16>(dyq[u], g);
+      if (in_run) {
+        const int j = K - 1 - (r + u);
+#pragma unroll
+        for (int i = 0; i < NV; i++) {
+          float pre = wt.b[i];
+#pragma unroll
+          for (int m = 0; m < K; m++) pre += wt.w[K - 1 - m][i] * win[m][i];
+          if (a.silu) g[i] *= dsilu_f(pre);
+          // weight row j selected without dynamic register indexing
+          float wj = wt.w[0][i];
+#pragma unroll
+          for (int jj = 1; jj < K; jj++) wj = jj == j ? wt.w[jj][i] : wj;
+          dx[i] += wj * g[i];
         }
+      }
     }
   };
   add_run(s, 0);
@@ -381,38 +394,40 @@ __device__ __forceinline__ void conv_fix_block(const ConvArgs& a, int64_t block)
 }
 
 // dweight[c][j] = sum over tiles of partial[tile][j][c]; dbias[c] = same for j = K.  Fixed order: the tiles are
-// cut into RED_SEG consecutive segments, one thread sums one segment of one output in tile order (16 loads in
+// cut into RED_SEG consecutive segments, one thread sums one segment of four outputs in tile order (8 loads in
 // flight), and the segment sums are added in segment order -- the same association on every run.  A workgroup
-// covers RED_OUT consecutive outputs x RED_SEG segments, so a wavefront reads 256 contiguous bytes per tile.
-constexpr int RED_SEG = 4, RED_OUT = CONV_THREADS / RED_SEG;
+// covers RED_OUT consecutive outputs x RED_SEG segments, so a segment's threads read 256 contiguous bytes per tile.
+constexpr int RED_SEG = 16, RED_OUT = 4 * CONV_THREADS / RED_SEG;
 __device__ __forceinline__ void conv_reduce_block(const float* __restrict__ partial, int n_tiles, int K, int channels,
                                                   float* __restrict__ dweight, float* __restrict__ dbias, int64_t block) {
-  __shared__ float seg_sum[RED_SEG][RED_OUT];
-  const int o = threadIdx.x % RED_OUT, sg = threadIdx.x / RED_OUT;
-  const int64_t n_out = (int64_t)(K + 1) * channels;
-  const int64_t gid = block * RED_OUT + o;
+  __shared__ f32x4v seg_sum[RED_SEG][RED_OUT / 4];
+  const int o = threadIdx.x % (RED_OUT / 4), sg = threadIdx.x / (RED_OUT / 4);
+  const int64_t n_out = (int64_t)(K + 1) * channels;        // a multiple of 4, as channels is
+  const int64_t gid = block * RED_OUT + 4 * o;
   const int per = (n_tiles + RED_SEG - 1) / RED_SEG;
   const int t_lo = min(sg * per, n_tiles), t_hi = min(t_lo + per, n_tiles);
-  float acc = 0.f;
+  f32x4v acc = {0.f, 0.f, 0.f, 0.f};
   if (gid < n_out) {
     const float* src = partial + gid;
     int t = t_lo;
-    for (; t + 16 <= t_hi; t += 16) {
-      float v[16];
+    for (; t + 8 <= t_hi; t += 8) {
+      f32x4v v[8];
 #pragma unroll
-      for (int u = 0; u < 16; u++) v[u] = src[(int64_t)(t + u) * n_out];
+      for (int u = 0; u < 8; u++) v[u] = *(const f32x4v*)(src + (int64_t)(t + u) * n_out);
 #pragma unroll
-      for (int u = 0; u < 16; u++) acc += v[u];
+      for (int u = 0; u < 8; u++) acc += v[u];
     }
-    for (; t < t_hi; t++) acc += src[(int64_t)t * n_out];
+    for (; t < t_hi; t++) acc += *(const f32x4v*)(src + (int64_t)t * n_out);
   }
   seg_sum[sg][o] = acc;
   __syncthreads();
-  if (sg == 0 && gid < n_out) {
-    float tot = seg_sum[0][o];
+  if (threadIdx.x < RED_OUT && block * RED_OUT + threadIdx.x < n_out) {
+    const int64_t out = block * RED_OUT + threadIdx.x;
+    const float* col = (const float*)seg_sum + threadIdx.x;
+    float tot = col[0];
 #pragma unroll
-    for (int q = 1; q < RED_SEG; q++) tot += seg_sum[q][o];
-    const int j = (int)(gid / channels), c = (int)(gid - (int64_t)j * channels);
+    for (int q = 1; q < RED_SEG; q++) tot += col[q * RED_OUT];
+    const int j = (int)(out / channels), c = (int)(out - (int64_t)j * channels);
     if (j < K) dweight[(int64_t)c * K + j] = tot;
     else if (dbias) dbias[c] = tot;
   }
@@ -470,7 +485,16 @@ hipError_t launch_bwd(const ConvArgs& a, float* dweight, float* dbias, hipStream
 
 }  // namespace
 
-int conv_bwd_tile(int64_t n_tokens, int channels, bool bf16) { return pick_tile(n_tokens, channels / (bf16 ? 8 : 4), 32, 256); }
+// Tokens per tile of the backward walk: long tiles (each walks K - 1 tokens of look-ahead and writes a row of partial sums)
+// that still make one workgroup for every one of the chip's conv_bwd_wgs * 256 places, 32 to CONV_BWD_TILE tokens; never
+// shorter than the power of two that makes 1024 workgroups of 16-byte lanes, which bounds the partial sums.
+// Whole backward and forward at 16406 x 8192 bf16, K = 4: tiles of 64 tokens 314 us, 128 294, 171 (this rule) 291; 32000 x
+// 8192: 167 tokens 616 us, 256 (this rule) 591; 9000 x 4096 fp32: 32 tokens 206, 71 (this rule) 185.
+int conv_bwd_tile(int64_t n_tokens, int channels, bool bf16) {
+  const int64_t places = (int64_t)conv_bwd_wgs(bf16) * 256 * CONV_THREADS, vpr = channels / (bf16 ? Chan<true>::NV : Chan<false>::NV);
+  const int64_t tile = tt::ceil_div(n_tokens, std::max<int64_t>(1, places / vpr));
+  return (int)std::max<int64_t>(pick_tile(n_tokens, channels / (bf16 ? 8 : 4), 32, 256), std::min<int64_t>(tile, CONV_BWD_TILE));
+}
 
 size_t conv_bwd_workspace(int64_t n_tokens, int channels, int kernel_size, bool bf16) {
   const int tile = conv_bwd_tile(n_tokens, channels, bf16);
@@ -483,7 +507,7 @@ hipError_t conv_fwd(int64_t n_tokens, int channels, int kernel_size, bool bf16, 
   if (n_tokens == 0) return hipSuccess;
   ConvArgs a{};
   a.n_tokens = (int)n_tokens; a.channels = channels; a.silu = silu ? 1 : 0;
-  a.tok_tile = pick_tile(n_tokens, channels / (bf16 ? 8 : 4), 16, 64);
+  a.tok_tile = pick_tile(n_tokens, channels / Chan<true>::NV, 16, 64);
   a.n_tiles = (int)tt::ceil_div(n_tokens, a.tok_tile);
   a.x = x; a.x_stride = x_stride_bytes; a.weight = weight; a.bias = bias; a.tok_pred = tok_pred;
   a.y = y; a.y_stride = y_stride_bytes;

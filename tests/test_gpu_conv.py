@@ -60,6 +60,16 @@ def test_random_trees_short_nodes(seed, k, dtype, c):
     _run_and_check(m["tok_pred"], m["n_tokens"], c, k, seed, dtype)
 
 
+@pytest.mark.parametrize("nodes,hi,k,dtype,c", [(1, 31, 4, "bf16", 8), (20, 40, 4, "bf16", 24), (26, 40, 3, "fp32", 12),
+                                                (30, 40, 2, "bf16", 8), (400, 3, 4, "bf16", 40), (90, 12, 3, "bf16", 16)])
+def test_weight_gradient_segments_and_run_ends(nodes, hi, k, dtype, c):
+    """Fewer tiles than the 16 segments of the weight-gradient sum, about as many and more; output counts that do not fill
+    its workgroups; branch-point rows whose successors stop short (one-token children, the end of the sequence)."""
+    t = W.random_tree(1200 + nodes, n_nodes=nodes, lo=1, hi=hi)
+    m = M.dfs_meta(t.parent, t.seg_len)
+    _run_and_check(m["tok_pred"], m["n_tokens"], c, k, nodes, dtype)
+
+
 @pytest.mark.parametrize("silu,bias", [(False, True), (True, False), (False, False)])
 def test_activation_and_bias_variants(silu, bias):
     t = W.random_tree(971, n_nodes=30, lo=1, hi=30)
