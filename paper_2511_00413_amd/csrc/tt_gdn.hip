@@ -58,7 +58,8 @@ struct GdnArgs {
   __bf16* o;                         // [N][hv][128]
   // per (chunk, value head) operands
   __bf16* rec;                       // records of REC_ELEMS: -W [64][128], U^T [128][64], scale Q exp(gamma) [64][128],
-                                     // (K exp(gamma_last - gamma))^T [128][64], scale tril((Q K^T) exp(gamma_i - gamma_j)) [64][64]
+                                     // K exp(gamma_last - gamma) [64][128], and in the forward call
+                                     // scale tril((Q K^T) exp(gamma_i - gamma_j)) [64][64]
   float* glast;                      // exp(gamma_last)
   float* slots;                      // [n_slots][hv][128][128] saved node-end states
   // backward pass only
@@ -79,13 +80,16 @@ struct GdnArgs {
 // The operands of one (head, chunk) form one contiguous record, records ordered head-major: a scan
 // workgroup (one head) then streams through memory front to back -- consecutive chunks are
 // adjacent, so address translation and DRAM pages are reused instead of missed on every step.
-constexpr size_t REC_WN = 0, REC_UT = GC * GD, REC_QG = 2 * GC * GD, REC_KDT = 3 * GC * GD, REC_P = 4 * GC * GD;
+constexpr size_t REC_WN = 0, REC_UT = GC * GD, REC_QG = 2 * GC * GD, REC_KD = 3 * GC * GD, REC_P = 4 * GC * GD;
 constexpr size_t REC_ELEMS = 4 * GC * GD + GC * GC;      // bf16 elements per record (72 KB)
-// Record of the reverse walk: Kd = K exp(gamma_last - gamma) [64][128], -W^T [128][64], (scale Q exp(gamma))^T
-// [128][64], P^T [64][64], dO^T [128 value cols][64]
-constexpr size_t REV_KD = 0, REV_WTN = GC * GD, REV_QGT = 2 * GC * GD, REV_PT = 3 * GC * GD, REV_DOT = 3 * GC * GD + GC * GC;
-constexpr size_t REV_ELEMS = 4 * GC * GD + GC * GC;
-static_assert(REC_ELEMS == GDN_REC_ELEMS && REV_ELEMS == GDN_REC_ELEMS && REC_UT == GDN_REC_UT && REV_WTN == GDN_REV_WTN,
+// What only the reverse walk reads, behind that walk's use of the forward record: P^T [64][64], dO^T [128 value cols][64].
+// Both walks take -W, Q exp(gamma) and K exp(gamma_last - gamma) from the same rows, one through row reads, the other
+// through transposing LDS reads: with -W^T, (Q ..)^T and (K ..)^T stored beside them the prepare kernel of the backward
+// wrote 132 KB per chunk and head instead of 100 and spent its time on 2-byte LDS reads to transpose (16406 tokens, 16 / 32
+// heads: 375 us, now 294; the walks are the same to 2 %).
+constexpr size_t REV_PT = 0, REV_DOT = GC * GC;
+constexpr size_t REV_ELEMS = GC * GD + GC * GC;
+static_assert(REC_ELEMS == GDN_REC_ELEMS && REV_ELEMS == GDN_REV_ELEMS && REC_UT == GDN_REC_UT && REC_WN == GDN_REC_WN,
               "record layout shared with the finish kernel");
 __device__ __forceinline__ size_t op_index(const GdnArgs& a, int chunk, int h) { return (size_t)h * a.n_chunks + chunk; }
 
@@ -148,15 +152,15 @@ __global__ __launch_bounds__(G_THREADS) void gdn_prepare_kernel(GdnArgs a) {
     if (tid < GC) a.f32.gam[op * GC + tid] = gam[tid];
   }
 
-  // K and Q rows into LDS (zero rows past the chunk's length); Qg written on the way
+  // K and Q rows into LDS (zero rows past the chunk's length); their decayed forms written on the way
 #pragma unroll
   for (int p = 0; p < NPIECE; p++) {
     const int piece = tid + p * G_THREADS, i = piece >> 4, c8 = (piece & 15) * 8;
     const bf16x8 kv = i < len ? kreg[p] : zero8, qv = i < len ? qreg[p] : zero8;
     *(bf16x8*)&ksm[i][c8] = kv;
     *(bf16x8*)&qsm[i][c8] = qv;
-    if constexpr (!BWD) *(bf16x8*)(a.rec + op * REC_ELEMS + REC_QG + i * GD + c8) = scale_frag(qv, a.scale * __expf(gam[i]));
-    if constexpr (BWD) *(bf16x8*)(a.rev + op * REV_ELEMS + REV_KD + i * GD + c8) = scale_frag(kv, __expf(g_last - gam[i]));
+    *(bf16x8*)(a.rec + op * REC_ELEMS + REC_QG + i * GD + c8) = scale_frag(qv, a.scale * __expf(gam[i]));
+    *(bf16x8*)(a.rec + op * REC_ELEMS + REC_KD + i * GD + c8) = scale_frag(kv, __expf(g_last - gam[i]));
   }
   __syncthreads();
 
@@ -208,17 +212,6 @@ __global__ __launch_bounds__(G_THREADS) void gdn_prepare_kernel(GdnArgs a) {
     }
   }
 
-  // (scale Q exp(gamma)) transposed: one 16-byte piece = 8 consecutive tokens of one dim.  (The same of K exp(gamma_last
-  // - gamma) is written further down, by the waves that would otherwise wait for the triangular inverse.)
-  if constexpr (BWD) {
-    for (int piece = tid; piece < GD * (GC / 8); piece += G_THREADS) {
-      const int d = piece >> 3, i0 = (piece & 7) * 8;
-      float f[8];
-#pragma unroll
-      for (int e = 0; e < 8; e++) f[e] = (float)qsm[i0 + e][d] * a.scale * __expf(gam[i0 + e]);
-      *(bf16x8*)(a.rev + op * REV_ELEMS + REV_QGT + d * GC + i0) = cvt8(f[0], f[1], f[2], f[3], f[4], f[5], f[6], f[7]);
-    }
-  }
   __syncthreads();
   if constexpr (BWD) {
     // dO^T: the rows of dO go through the Q tile's LDS (free now) and leave transposed (further down, beside the
@@ -304,26 +297,16 @@ __global__ __launch_bounds__(G_THREADS) void gdn_prepare_kernel(GdnArgs a) {
     }
     if constexpr (!BWD) stage_v_rows();
   } else {
-    // meanwhile the other three waves write (K exp(gamma_last - gamma)) transposed (K stays in LDS until the second
-    // product) and, in the backward form, dO^T: 8 consecutive tokens of one dim per piece
-    const int t3 = 64 * (w - (w > tw ? 1 : 0)) + lane;
+    // meanwhile the other three waves stage V or, in the backward form, write dO^T: 8 consecutive tokens of one dim per
+    // piece
     if constexpr (BWD) {
-      for (int piece = t3; piece < GD * (GC / 8); piece += G_THREADS - 64) {
-        const int d = piece >> 3, i0 = (piece & 7) * 8;
-        bf16x8 o;
-#pragma unroll
-        for (int e = 0; e < 8; e++) o[e] = qsm[i0 + e][d];
-        *(bf16x8*)(a.rev + op * REV_ELEMS + REV_DOT + d * GC + i0) = o;
+      for (int unit = w - (w > tw ? 1 : 0); unit < (GD / 32) * (GC / 16); unit += G_THREADS / 64 - 1) {
+        const int db = unit >> 2, ks = unit & 3;        // 32 dims x 16 tokens
+        *(bf16x8*)(a.rev + op * REV_ELEMS + REV_DOT + (32 * db + c) * GC + 16 * ks + 8 * hf) =
+            kmajor_frag(&qsm[0][0], GROW, 16 * ks + 8 * hf, 32 * db + 16 * (c >> 4), lane);
       }
     } else {
       stage_v_rows();
-    }
-    for (int piece = t3; piece < GD * (GC / 8); piece += G_THREADS - 64) {
-      const int d = piece >> 3, i0 = (piece & 7) * 8;
-      float f[8];
-#pragma unroll
-      for (int e = 0; e < 8; e++) f[e] = (float)ksm[i0 + e][d] * __expf(g_last - gam[i0 + e]);
-      *(bf16x8*)(a.rec + op * REC_ELEMS + REC_KDT + d * GC + i0) = cvt8(f[0], f[1], f[2], f[3], f[4], f[5], f[6], f[7]);
     }
   }
   if constexpr (BWD) {
@@ -366,14 +349,14 @@ __global__ __launch_bounds__(G_THREADS) void gdn_prepare_kernel(GdnArgs a) {
   // halves of a 16-byte piece together; without it the 32 columns of a wave would start in two banks).
   __bf16* stage_v = &qsm[0][0];
   __bf16* stage_k = &ksm[0][0];
-  auto stage_transposed = [&](__bf16* st, const f32x16 (&ac)[2], float sign) {     // [128 columns][64 tokens]
+  auto stage_transposed = [&](__bf16* st, const f32x16 (&ac)[2]) {                 // [128 columns][64 tokens]
     const int col = 32 * w + c, sw = (col & 7) << 1;
 #pragma unroll
     for (int t = 0; t < 2; t++)
 #pragma unroll
       for (int r4 = 0; r4 < 4; r4++)
         *(bf16x4*)(st + col * GC + (((8 * t + 2 * r4 + hf) ^ sw) << 2)) =
-            cvt4(sign * ac[t][4 * r4], sign * ac[t][4 * r4 + 1], sign * ac[t][4 * r4 + 2], sign * ac[t][4 * r4 + 3]);
+            cvt4(ac[t][4 * r4], ac[t][4 * r4 + 1], ac[t][4 * r4 + 2], ac[t][4 * r4 + 3]);
   };
   auto copy_out_transposed = [&](const __bf16* st, __bf16* dst) {                  // dst [128][64], contiguous
 #pragma unroll
@@ -387,7 +370,7 @@ __global__ __launch_bounds__(G_THREADS) void gdn_prepare_kernel(GdnArgs a) {
   __syncthreads();
   product(qsm, acc);                    // U: rows = tokens, columns = value dims 32 w .. 32 w + 31
   __syncthreads();                      // every wave has read the halves and V
-  stage_transposed(stage_v, acc, 1.f);
+  stage_transposed(stage_v, acc);
   if (w == tw) put_scaled([&](int j) { return bet[j] * __expf(gam[j]); });
   __syncthreads();
   copy_out_transposed(stage_v, a.rec + op * REC_ELEMS + REC_UT);
@@ -399,7 +382,6 @@ __global__ __launch_bounds__(G_THREADS) void gdn_prepare_kernel(GdnArgs a) {
     for (int t = 0; t < 2; t++)
 #pragma unroll
       for (int r = 0; r < 16; r++) stage_k[(32 * t + (r >> 2) * 8 + 4 * hf + (r & 3)) * GD + 32 * w + c] = (__bf16)(-acc[t][r]);
-    if constexpr (BWD) stage_transposed(stage_v, acc, -1.f);      // -W^T for the reverse walk and the finish kernel
   }
   __syncthreads();
 #pragma unroll
@@ -407,7 +389,6 @@ __global__ __launch_bounds__(G_THREADS) void gdn_prepare_kernel(GdnArgs a) {
     const int piece = tid + p * G_THREADS;
     *(bf16x8*)(a.rec + op * REC_ELEMS + REC_WN + (size_t)piece * 8) = *(const bf16x8*)(stage_k + piece * 8);
   }
-  if constexpr (BWD) copy_out_transposed(stage_v, a.rev + op * REV_ELEMS + REV_WTN);
 }
 
 typedef unsigned u32x4n __attribute__((ext_vector_type(4)));      // native vector type (stays in registers)
@@ -421,7 +402,7 @@ typedef unsigned u32x4n __attribute__((ext_vector_type(4)));      // native vect
 struct ScanImage {
   __bf16 wn[GC * GD];           // -W, swizzled tile
   __bf16 qg[GC * GD];           // scale Q exp(gamma), swizzled tile
-  __bf16 kd[GD * GC];           // (K decayed)^T, rows of 64
+  __bf16 kd[GC * GD];           // K exp(gamma_last - gamma), swizzled tile
   __bf16 ut[SCAN_NB * G_DVB * GC];   // U^T, this workgroup's value columns (block after block), rows of 64
   __bf16 p[GC * GC];            // scale tril(Q K^T decay), rows of 64
 };
@@ -447,6 +428,12 @@ __device__ __forceinline__ bf16x8 row64_perm_k(const __bf16* arr, int r, int bas
   return cat4(row64_read4(arr, r, base + 4 * hf), row64_read4(arr, r, base + 8 + 4 * hf));
 }
 
+// Rows r0 .. r0 + 15 of a swizzled tile as an A operand: this lane's row is column 32 db + lane % 32 of the tile, k = the
+// tile rows in accumulator order.
+__device__ __forceinline__ bf16x8 tile_perm_k(const __bf16* tile, const TrBase& tb, int db, int r0) {
+  return cat4(lds_read_tr(tile + r0 * TILE_ROW + (tb.x0 ^ (db << 5))), lds_read_tr(tile + r0 * TILE_ROW + (tb.x1 ^ (db << 5))));
+}
+
 // Copies `rows` rows of 64 elements (contiguous in memory) into a rows-of-64 array; 8 rows per
 // instruction, instructions dealt round-robin to the workgroup's waves (w8 = 0 .. SCAN_NW - 1).
 __device__ __forceinline__ void dma_rows64(const __bf16* src, int rows, __bf16* dst, int w8, int lane) {
@@ -463,7 +450,7 @@ __device__ __forceinline__ void issue_chunk(const GdnArgs& a, int chunk, int h, 
   const __bf16* rec = a.rec + op_index(a, chunk, h) * REC_ELEMS;
   dma_tile64<SCAN_NW>(rec + REC_WN, GD * 2, GC, im.wn, w8, lane);
   if constexpr (!TRAIN) dma_tile64<SCAN_NW>(rec + REC_QG, GD * 2, GC, im.qg, w8, lane);
-  dma_rows64(rec + REC_KDT, GD, im.kd, w8, lane);
+  dma_tile64<SCAN_NW>(rec + REC_KD, GD * 2, GC, im.kd, w8, lane);
   dma_rows64(rec + REC_UT + (size_t)dvb0 * G_DVB * GC, SCAN_NB * G_DVB, im.ut, w8, lane);
   if constexpr (!TRAIN) dma_rows64(rec + REC_P, GC, im.p, w8, lane);
 }
@@ -545,6 +532,7 @@ __device__ __forceinline__ void scan_step(const GdnArgs& a, ScanSmem& sm, ScanIm
       }
     }
   }
+  const TrBase tb = tr_frag_base(lane);
   f32x16 acc;
   if (w < 2) {
 #pragma unroll
@@ -560,7 +548,7 @@ __device__ __forceinline__ void scan_step(const GdnArgs& a, ScanSmem& sm, ScanIm
   for (int jb = 0; jb < 2; jb++)
 #pragma unroll
     for (int t = 0; t < 2; t++) {
-      kfrag[jb][t] = row64_perm_k(im.kd, 32 * w + c, jb * 32 + t * 16, hf);
+      kfrag[jb][t] = tile_perm_k(im.kd, tb, w, jb * 32 + t * 16);
       if constexpr (!TRAIN) pfrag[jb][t] = row64_perm_k(im.p, half * 32 + c, jb * 32 + t * 16, hf);     // used by waves 2, 3 only
     }
   __builtin_amdgcn_sched_barrier(0);
@@ -666,20 +654,17 @@ __global__ __launch_bounds__(SCAN_THREADS, 1) void gdn_scan_kernel(GdnArgs a) {
 // ---- reverse walk of the backward ---------------------------------------------------------------------
 // Per chunk, last to first:  dVn = P^T dO + Kd dS1,  dS0 = EL dS1 + Qg^T dO - W^T dVn  -- the forward step's
 // structure with (-W, S0, U) <-> (Kd, dS1, P^T dO) and (Kd^T, Vn) <-> (-W^T, dVn), plus the Qg^T dO term.  The
-// LDS image is reused with other contents: wn <- Kd (swizzled tile), kd <- -W^T, qg <- Qg^T (rows of 64),
+// LDS image is reused with other contents: wn <- Kd, kd <- -W, qg <- Qg (swizzled tiles, the last two read transposed),
 // p <- P^T, ut <- this workgroup's 32 rows of dO^T.  Saved for the finish kernel: dS1 (bf16, transposed) and dVn
 // (fragments), like the forward walk's S0 and Vn.
-// 8 consecutive elements e0 .. e0+7 (e0 a multiple of 8) of row r of a rows-of-64 array
-__device__ __forceinline__ bf16x8 row64_read8(const __bf16* arr, int r, int e0) {
-  return *(const bf16x8*)(arr + r * GC + (((e0 >> 3) ^ (r & 7)) << 3));
-}
 __device__ __forceinline__ void issue_rev_chunk(const GdnArgs& a, int chunk, int h, int dvb0, ScanImage& im, int w8, int lane) {
-  const __bf16* rec = a.rev + op_index(a, chunk, h) * REV_ELEMS;
-  dma_tile64<SCAN_NW>(rec + REV_KD, GD * 2, GC, im.wn, w8, lane);
-  dma_rows64(rec + REV_WTN, GD, im.kd, w8, lane);
-  dma_rows64(rec + REV_QGT, GD, im.qg, w8, lane);
-  dma_rows64(rec + REV_PT, GC, im.p, w8, lane);
-  dma_rows64(rec + REV_DOT + (size_t)dvb0 * G_DVB * GC, SCAN_NB * G_DVB, im.ut, w8, lane);
+  const __bf16* rec = a.rec + op_index(a, chunk, h) * REC_ELEMS;
+  const __bf16* rev = a.rev + op_index(a, chunk, h) * REV_ELEMS;
+  dma_tile64<SCAN_NW>(rec + REC_KD, GD * 2, GC, im.wn, w8, lane);
+  dma_tile64<SCAN_NW>(rec + REC_WN, GD * 2, GC, im.kd, w8, lane);
+  dma_tile64<SCAN_NW>(rec + REC_QG, GD * 2, GC, im.qg, w8, lane);
+  dma_rows64(rev + REV_PT, GC, im.p, w8, lane);
+  dma_rows64(rev + REV_DOT + (size_t)dvb0 * G_DVB * GC, SCAN_NB * G_DVB, im.ut, w8, lane);
 }
 
 // `later_src`: the source of the chunk that follows in DFS order (handled one step earlier); -2 means that chunk
@@ -732,14 +717,15 @@ __device__ __forceinline__ void rscan_step(const GdnArgs& a, ScanSmem& sm, ScanI
   load_meta(a, max(chunk - 1, c_begin), h, z, meta);
 
   const int half = w & 1;
-  bf16x8 ofrag[GC / 16];              // B operand: column c of dO, k = tokens in plain order
+  const TrBase tb = tr_frag_base(lane);
+  bf16x8 ofrag[GC / 16];              // B operand: column c of dO, k = tokens in accumulator order
 #pragma unroll
-  for (int js = 0; js < GC / 16; js++) ofrag[js] = row64_read8(im.ut + blk * (G_DVB * GC), c, js * 16 + hf * 8);
+  for (int js = 0; js < GC / 16; js++) ofrag[js] = row64_perm_k(im.ut + blk * (G_DVB * GC), c, js * 16, hf);
   bf16x8 wfrag[2][2], qfrag[GC / 16];
 #pragma unroll
   for (int jb = 0; jb < 2; jb++)
 #pragma unroll
-    for (int t = 0; t < 2; t++) wfrag[jb][t] = row64_perm_k(im.kd, 32 * w + c, jb * 32 + t * 16, hf);
+    for (int t = 0; t < 2; t++) wfrag[jb][t] = tile_perm_k(im.kd, tb, w, jb * 32 + t * 16);
   if (w < 2) {
     // rows 32 half .. of dVn
     bf16x8 sfrag[GD / 16], afrag[GD / 16], pfrag[GC / 16];
@@ -750,7 +736,7 @@ __device__ __forceinline__ void rscan_step(const GdnArgs& a, ScanSmem& sm, ScanI
       afrag[ks] = lds_row_frag(im.wn, abase, half, ks);
     }
 #pragma unroll
-    for (int js = 0; js < GC / 16; js++) pfrag[js] = row64_read8(im.p, half * 32 + c, js * 16 + hf * 8);
+    for (int js = 0; js < GC / 16; js++) pfrag[js] = row64_perm_k(im.p, half * 32 + c, js * 16, hf);
     f32x16 acc = zero16();
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -783,7 +769,7 @@ __device__ __forceinline__ void rscan_step(const GdnArgs& a, ScanSmem& sm, ScanI
   // (Qg^T fragments only now: fetched with the others in front of the first product they would push the wave past
   // its register budget at two waves per SIMD; the image is not overwritten before the next step's first barrier)
 #pragma unroll
-  for (int js = 0; js < GC / 16; js++) qfrag[js] = row64_read8(im.qg, 32 * w + c, js * 16 + hf * 8);
+  for (int js = 0; js < GC / 16; js++) qfrag[js] = tile_perm_k(im.qg, tb, w, js * 16);
 
   // dS0 = exp(gamma_last) dS1 - W^T dVn + Qg^T dO, rows 32 w .. 32 w + 31
 #pragma unroll

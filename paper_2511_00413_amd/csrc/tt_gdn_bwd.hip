@@ -15,8 +15,8 @@
 // the chunks has seen them), plus the upstream gradient of a captured state.
 //
 // Kernels (the first three live in tt_gdn.hip with the forward's):
-//   gdn_prepare_kernel<true>   per (chunk, head): the forward walk's bf16 record, the reverse walk's bf16 record
-//                              (Kd, -W^T, Qg^T, P^T, dO^T) and gamma and (I + A)^-1 unrounded
+//   gdn_prepare_kernel<true>   per (chunk, head): the bf16 record of both walks, what the reverse walk needs besides
+//                              (P^T, dO^T), and gamma and (I + A)^-1 unrounded
 //   gdn_scan_kernel<true>      (32 value columns, head): the forward scan without its output; saves S0 and Vn
 //                              of every chunk (bf16)
 //   gdn_rscan_kernel           (32 value columns, head): reverse walk in the forward scan's form (bf16 matrix
@@ -81,7 +81,7 @@ struct FinishSmem {
   // step 1: slabs S0^T, dS1^T [32 columns][128], Vn, dVn [32 columns][64 tokens];  step 2: T as hi and lo halves;  from
   // there on dVb and dKb [token][128];  after step 3 dP scale D in dVb's place, and the closing sums behind it
   __bf16 x[2 * GC * PG];
-  __bf16 r2[GC * PK];                                    // dO, 64 columns; [U | W]^T, 64 columns; dA beta D
+  __bf16 r2[GC * PK];                                    // dO, 64 columns; U^T, 64 rows, then -W, 64 columns; dA beta D
   float gam[GC], bet[GC], eg[GC], el[GC], db_v[GC];
   float dg_row[2][GC], dg_col[2][GC], db_a[2][GC];       // per column / row block
 };
@@ -206,7 +206,7 @@ __global__ __launch_bounds__(BT, 2) void gdn_bwd_finish_kernel(KArgs a) {
     const size_t op = (size_t)h * nc + chunk;
     const __bf16* dvns = (const __bf16*)a.w.sv.dvns + op * (GC * GD);
     const __bf16* ut = (const __bf16*)a.w.sv.fwd_rec + op * GDN_REC_ELEMS + GDN_REC_UT;
-    const __bf16* wtn = (const __bf16*)a.w.sv.rev_rec + op * GDN_REC_ELEMS + GDN_REV_WTN;
+    const __bf16* wn = (const __bf16*)a.w.sv.fwd_rec + op * GDN_REC_ELEMS + GDN_REC_WN;
     const __bf16* vb = (const __bf16*)a.b.v + (size_t)tok0 * vrow + (size_t)h * GD;
 
     // ---- 1. everything that contracts over value columns ----
@@ -320,10 +320,14 @@ __global__ __launch_bounds__(BT, 2) void gdn_bwd_finish_kernel(KArgs a) {
     place();
     // ---- 2. (I + A)^T [dVb | dKb] = [dVn | dW]: X^T = rhs^T T ----
     bf16x8 ur[2][2], vv[4];
-    auto load_uw = [&](int s) {                          // two slabs ahead
-      const __bf16* src = s < 2 ? ut + s * (GC * GC) : wtn + (s - 2) * (GC * GC);
+    // two slabs ahead: 64 rows of U^T (value columns), or 64 columns (key dims) of the rows of -W
+    auto load_uw = [&](int s) {
 #pragma unroll
-      for (int p = 0; p < 2; p++) ur[s & 1][p] = *(const bf16x8*)(src + 8 * (tid + p * BT));
+      for (int p = 0; p < 2; p++) {
+        const int piece = tid + p * BT;
+        ur[s & 1][p] = *(const bf16x8*)(s < 2 ? ut + s * (GC * GC) + 8 * piece
+                                              : wn + (s - 2) * GC + (piece >> 3) * GD + (piece & 7) * 8);
+      }
     };
     const int v_i = tid >> 2, v_c0 = (tid & 3) * 32;     // step 3: this thread's row and columns of dVb
     lds_barrier();                                       // the last slab has been read
@@ -391,9 +395,11 @@ __global__ __launch_bounds__(BT, 2) void gdn_bwd_finish_kernel(KArgs a) {
         for (int r = 0; r < 16; r++) da[r] = -da[r];
       }
 #pragma unroll
-      for (int ss = 0; ss < 4; ss++)
-        da = mfma32(*(const bf16x8*)(sm.x + (s >> 1) * X_KB + (32 * ib + c) * PG + (s & 1) * 64 + 16 * ss + 8 * hf),
-                    kmajor_frag(sm.r2, PK, 16 * ss + 8 * hf, 32 * jb + c16, lane), da);
+      for (int ss = 0; ss < 4; ss++) {
+        const bf16x8 uw = s < 2 ? kmajor_frag(sm.r2, PK, 16 * ss + 8 * hf, 32 * jb + c16, lane)
+                                : *(const bf16x8*)(sm.r2 + (32 * jb + c) * PK + 16 * ss + 8 * hf);
+        da = mfma32(*(const bf16x8*)(sm.x + (s >> 1) * X_KB + (32 * ib + c) * PG + (s & 1) * 64 + 16 * ss + 8 * hf), uw, da);
+      }
       if (s == 0) {
         float dot = 0.f;
         const float b = sm.bet[v_i];
@@ -619,7 +625,7 @@ size_t carve(char* p, int64_t n_tokens, int n_chunks, int n_slots, int n_segment
   t.ops.gam = (float*)take(per * GC * 4);
   t.ops.t = (float*)take(per * GDN_T_ELEMS * 4);
   t.sv.fwd_rec = take(per * GDN_REC_ELEMS * 2);
-  t.sv.rev_rec = take(per * GDN_REC_ELEMS * 2);
+  t.sv.rev_rec = take(per * GDN_REV_ELEMS * 2);
   t.sv.glast = (float*)take(per * 4);
   t.sv.s0t = take(per * GD * GD * 2);
   t.sv.ds1t = take(per * GD * GD * 2);

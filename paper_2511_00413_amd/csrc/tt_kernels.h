@@ -106,12 +106,13 @@ struct GdnChunkOps {
 };
 constexpr size_t GDN_T_ELEMS = 3 * 32 * 32;
 // bf16 operands of the two walks and what they save for the finish kernel:
-constexpr size_t GDN_REC_ELEMS = 4 * 64 * 128 + 64 * 64;     // elements of one walk record (forward and reverse alike)
-constexpr size_t GDN_REC_UT = 64 * 128;      // forward record: U^T [128 value cols][64 tokens], U = (I + A)^-1 (beta V)
-constexpr size_t GDN_REV_WTN = 64 * 128;     // reverse record: -W^T [128 key dims][64 tokens], W = (I + A)^-1 (beta exp(gamma) K)
+constexpr size_t GDN_REC_ELEMS = 4 * 64 * 128 + 64 * 64;     // elements of the record that both walks read
+constexpr size_t GDN_REV_ELEMS = 64 * 128 + 64 * 64;         // elements of the record of the reverse walk alone
+constexpr size_t GDN_REC_WN = 0;             // -W [64 tokens][128 key dims], W = (I + A)^-1 (beta exp(gamma) K)
+constexpr size_t GDN_REC_UT = 64 * 128;      // U^T [128 value cols][64 tokens], U = (I + A)^-1 (beta V)
 struct GdnBwdSaved {
-  void* fwd_rec;     // forward walk records
-  void* rev_rec;     // reverse walk records
+  void* fwd_rec;     // records of both walks
+  void* rev_rec;     // records of the reverse walk
   float* glast;      // exp(gamma_last)
   void* s0t;         // [128 value cols][128 key dims] bf16: state entering the chunk, transposed
   void* ds1t;        // same layout: gradient of the state leaving the chunk
