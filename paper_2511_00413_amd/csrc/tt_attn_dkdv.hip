@@ -84,7 +84,12 @@ constexpr int KV_TARGET_WORK = 768;      // work items (tile chunk x kv head) ai
 constexpr int KV_ITEMS_PER_WG = 2;       // ... and per resident workgroup: with the longest items handed out first two
                                          // per workgroup balance as well as three did in plain order, with 40 % fewer
                                          // partial slots to write and reduce
-constexpr int KV_MIN_CHUNK = 32;         // steps
+// Shortest chunk, in steps.  Small trees have fewer steps than places: there a chunk is what gives every workgroup one
+// item, KV_MIN_CHUNK to KV_SHORT_CHUNK steps, and only what is longer is cut for two per workgroup (an item costs about 10
+// steps' time to start and finish, and its partial slot is written and summed).  Forward + backward at a least chunk of 32 /
+// 16 / 8 / 4: 777 tokens, 32 / 8 heads 129 / 107 / 102 / 124 us, 1024 (chain) 173 / 139 / 132 / 155, 1500 149 / 128 / 152 / 156,
+// 4000, 8 / 8 heads 243 / 226 / 244 / 244.
+constexpr int KV_MIN_CHUNK = 8, KV_SHORT_CHUNK = 16;
 constexpr int KV_SORT_BELOW = 16;        // items per workgroup below which the items are handed out longest first
 constexpr int PLAN_THREADS = 1024;
 constexpr int KV_EPT = KV_BN / 64;       // summary entries per key tile, at most
@@ -248,7 +253,8 @@ kv_plan_kernel(KvPlan pl, const int32_t* __restrict__ kt_max, int n_q, int n_pre
   block_exclusive_scan<false>(my_steps, scratch, &total_steps);       // (its barriers also publish the tile tables)
   const int64_t all = (int64_t)total_steps * hkv;
   const int target = max(1, min(KV_TARGET_WORK, KV_ITEMS_PER_WG * n_workgroups));
-  const int chunk = (int)max((int64_t)KV_MIN_CHUNK, (all + target - 1) / target);
+  const int64_t one_each = (all + n_workgroups - 1) / n_workgroups;
+  const int chunk = (int)max(min((int64_t)KV_SHORT_CHUNK, max((int64_t)KV_MIN_CHUNK, one_each)), (all + target - 1) / target);
 
   // ---- pass 2: chunks per tile; cut tiles are numbered first (their item index is also their slot);
   //      each thread owns consecutive tiles ----
