@@ -177,12 +177,17 @@ __device__ __forceinline__ void dq_tile(const uint32_t (&ra)[8], const uint32_t 
   }
 }
 
-__global__ void __launch_bounds__(NTHREADS, 2)
+// NG: groups of four waves per workgroup, as in the forward kernel: 2 for launches that leave every workgroup a compute
+// unit of its own; the groups take every second key tile and add up their sums at the end.
+// Forward + backward, with the forward's: 4000 tokens, 8 / 8 heads, a chain 267 -> 243 us; 1024, 32 / 8, a chain 179 -> 174.
+template <int NG>
+__global__ void __launch_bounds__(NG * NTHREADS, 2)
 tree_attn_dq_kernel(AttnArgs a, int n_qtiles) {
   extern __shared__ __align__(1024) unsigned char smem_raw[];
-  QSmem& sm = *reinterpret_cast<QSmem*>(smem_raw);
   const int lane = threadIdx.x & 63;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int w_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int grp = NG == 1 ? 0 : w_all / (NTHREADS / 64), w = NG == 1 ? w_all : w_all % (NTHREADS / 64);
+  QSmem& sm = reinterpret_cast<QSmem*>(smem_raw)[grp];
   const int c32 = lane & 31, hf = lane >> 5;
   const int G = a.hq / a.hkv;
   const int bid = blockIdx.x;
@@ -226,7 +231,7 @@ tree_attn_dq_kernel(AttnArgs a, int n_qtiles) {
 #pragma unroll
       for (int e = 0; e < 8; e++) acc = fmaf((float)gf[s][e], (float)of[s][e], acc);
     ndelta = -half_swap_sum(acc);
-    if (q < N && hf == 0) {
+    if (q < N && hf == 0 && grp == 0) {
       a.delta[(int64_t)h * N + q] = ndelta;
       a.neg_lse2[(int64_t)h * N + q] = nlse2;
     }
@@ -253,7 +258,7 @@ tree_attn_dq_kernel(AttnArgs a, int n_qtiles) {
 #define TT_DQ_STEP(FULLFLAG)                                                                            \
   {                                                                                                     \
     int cls_next = KT_FULL;                                                                             \
-    const int u_next = it.next(cls_next);                                                               \
+    const int u_next = next_own(cls_next);                                                              \
     if (u_next >= 0) q_issue_tile(ctx, sm, buf ^ 1, u_next, w, lane);                                   \
     dq_tile<FULLFLAG>(ra, ta, ka, qf, gf, dq_acc, neg_lse2, neg_delta, tile_j0(u_cur), tile_j_last(u_cur), gi, hf, cls_cur); \
     dma_wait_all();                                                                                     \
@@ -271,11 +276,18 @@ tree_attn_dq_kernel(AttnArgs a, int n_qtiles) {
   KTileIter it;
   // as in the forward kernel: tile 0 is nearly always the first tile delivered, so its copy is started before
   // the classification and runs beside it (a wrong guess costs one wasted tile copy)
-  q_issue_tile(ctx, sm, buf, 0, w, lane);
+  if (grp == 0) q_issue_tile(ctx, sm, buf, 0, w, lane);
+  // the next tile of this group; `other`: the tile of the other group passed over last (>= 0 with nothing behind it means
+  // that group 0 has one more tile than group 1)
+  [[maybe_unused]] int other = -1;
+  auto next_own = [&](int& cls) {
+    if constexpr (NG == 2) other = it.next(cls);
+    return it.next(cls);
+  };
   it.fill(&sm.masks, a.kt_max, a.kt_min, 0, u_end, gi_first, gi_last, npt, P, N, w, NTHREADS / 64);
   int cls_cur = KT_FULL;
-  int u_cur = it.next(cls_cur);
-  if (u_cur > 0) {
+  int u_cur = grp == 0 ? it.next(cls_cur) : next_own(cls_cur);
+  if (grp == 0 ? u_cur > 0 : u_cur >= 0) {
     dma_wait_all();
     q_issue_tile(ctx, sm, buf, u_cur, w, lane);
   }
@@ -299,17 +311,35 @@ tree_attn_dq_kernel(AttnArgs a, int n_qtiles) {
     while (u_cur >= 0 && cls_cur == KT_FULL) TT_DQ_STEP(true)
     while (u_cur >= 0) TT_DQ_STEP(false)
     tile0 += 64 * KT_MAX_WIN;
-    if (tile0 >= u_end) break;
+    if (NG == 2 || tile0 >= u_end) break;        // (two groups: the host sees to it that there is one chunk)
     it.fill(&sm.masks, a.kt_max, a.kt_min, tile0, u_end, gi_first, gi_last, npt, P, N, w, NTHREADS / 64);
     u_cur = it.next(cls_cur);
     if (u_cur >= 0) q_issue_tile(ctx, sm, buf, u_cur, w, lane);
   }
 #undef TT_DQ_STEP
 
-  if (q < N) {
-    __bf16* dqp = (__bf16*)a.dq + ((int64_t)q * a.hq + h) * D;
+  if constexpr (NG == 2) {
+    // as in the forward: both groups past their last tile behind the same barrier, then each finishes two column blocks
+    if (grp == 1 && other >= 0) __syncthreads();
+    float* const xch = reinterpret_cast<float*>(&sm);                    // [32 registers][256 lanes]
+    const float* const xin = reinterpret_cast<const float*>(reinterpret_cast<QSmem*>(smem_raw) + (grp ^ 1));
+    const int slot = 64 * w + lane;
 #pragma unroll
-    for (int db = 0; db < 4; db++)
+    for (int db = 0; db < 2; db++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) xch[(16 * db + r) * NTHREADS + slot] = grp == 0 ? dq_acc[2 + db][r] : dq_acc[db][r];
+    __syncthreads();
+#pragma unroll
+    for (int db = 0; db < 2; db++)
+#pragma unroll
+      for (int r = 0; r < 16; r++)
+        dq_acc[db][r] = (grp == 0 ? dq_acc[db][r] : dq_acc[2 + db][r]) + xin[(16 * db + r) * NTHREADS + slot];
+  }
+  constexpr int N_DB = 4 / NG;                   // column blocks that this wave stores, from block N_DB * grp on
+  if (q < N) {
+    __bf16* dqp = (__bf16*)a.dq + ((int64_t)q * a.hq + h) * D + 32 * N_DB * grp;
+#pragma unroll
+    for (int db = 0; db < N_DB; db++)
 #pragma unroll
       for (int r4 = 0; r4 < 4; r4++) {
         const int d0 = db * 32 + r4 * 8 + 4 * hf;
@@ -340,11 +370,13 @@ hipError_t mfma_attn_bwd(const AttnArgs& args, hipStream_t st) {
   // dQ first: its prologue writes the per-row terms the dK/dV pass streams
   {
     const int n_qtiles = (a.n_q + Q_BM - 1) / Q_BM;
-    if (hipError_t e = hipFuncSetAttribute((const void*)tree_attn_dq_kernel,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(QSmem)))
-      return e;
+    const int64_t blocks = (int64_t)n_qtiles * a.hq;
+    const bool two = attn_two_groups(a, blocks);
+    const auto kernel = two ? tree_attn_dq_kernel<2> : tree_attn_dq_kernel<1>;
+    const int lds = (two ? 2 : 1) * (int)sizeof(QSmem);
+    if (hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds)) return e;
     KernelTimer timer(TT_KERNEL_ATTN_DQ, st);
-    tree_attn_dq_kernel<<<(unsigned)((int64_t)n_qtiles * a.hq), NTHREADS, sizeof(QSmem), st>>>(a, n_qtiles);
+    kernel<<<(unsigned)blocks, (two ? 2 : 1) * NTHREADS, lds, st>>>(a, n_qtiles);
     if (hipError_t e = hipGetLastError()) return e;
   }
   return mfma_attn_dkdv(a, st);

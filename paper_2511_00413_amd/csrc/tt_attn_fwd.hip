@@ -207,12 +207,19 @@ __device__ __forceinline__ void process_tile(const uint32_t (&ra)[8], const uint
   l_run += psum;
 }
 
-__global__ void __launch_bounds__(NTHREADS, 2)
+// NG: groups of four waves per workgroup.  2 (launches that leave every workgroup a compute unit of its own): the groups
+// take every second key tile of the same queries, each with its own stages, and add up their sums at the end -- half the
+// chain of tiles, and two waves per SIMD as with two workgroups per compute unit.
+// Kernel and call: 4000 tokens, 8 / 8 heads, a chain 66 -> 56 us; 2000, 16 / 4 22 -> 20; 1024, 32 / 8, a chain 28 -> 26; up to 800
+// tokens of 32 heads the same (a few tiles behind 10 us of start and end).
+template <int NG>
+__global__ void __launch_bounds__(NG * NTHREADS, 2)
 tree_attn_fwd_kernel(AttnArgs a, int n_qtiles) {
   extern __shared__ __align__(1024) unsigned char smem_raw[];
-  Smem& sm = *reinterpret_cast<Smem*>(smem_raw);
   const int lane = threadIdx.x & 63;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int w_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int grp = NG == 1 ? 0 : w_all / (NTHREADS / 64), w = NG == 1 ? w_all : w_all % (NTHREADS / 64);
+  Smem& sm = reinterpret_cast<Smem*>(smem_raw)[grp];
   const int c32 = lane & 31, hf = lane >> 5;
   const int G = a.hq / a.hkv;
   // consecutive workgroups take different kv heads (they land on different XCDs, so each XCD's L2
@@ -263,7 +270,7 @@ tree_attn_fwd_kernel(AttnArgs a, int n_qtiles) {
 #define TT_FWD_STEP(FULLFLAG)                                                                          \
   {                                                                                                    \
     int cls_next = KT_FULL;                                                                            \
-    const int u_next = it.next(cls_next);                                                              \
+    const int u_next = next_own(cls_next);                                                             \
     if (u_next >= 0) issue_tile(ctx, sm, buf ^ 1, u_next, w, lane);                                    \
     process_tile<FULLFLAG>(ra, ta, ka, qf, o_acc, m_run, l_run, neg_m, tile_j0(u_cur), tile_j_last(u_cur), gi, hf, cls_cur); \
     dma_wait_all();                                                                                    \
@@ -283,11 +290,18 @@ tree_attn_fwd_kernel(AttnArgs a, int n_qtiles) {
   // visible to every later query, so tile 0 is nearly always the first tile delivered, and its round trip then runs
   // beside the classification's instead of behind it (and beside the Q fragments').  A wrong guess (several roots,
   // a prefix whose first tile is hidden) costs one wasted tile copy: the right tile is fetched over it.
-  issue_tile(ctx, sm, buf, 0, w, lane);
+  if (grp == 0) issue_tile(ctx, sm, buf, 0, w, lane);
+  // the next tile of this group: of two groups each passes over the other's.  `other` is the tile passed over last: >= 0
+  // with nothing behind it means that group 0 has one more tile than group 1
+  [[maybe_unused]] int other = -1;
+  auto next_own = [&](int& cls) {
+    if constexpr (NG == 2) other = it.next(cls);
+    return it.next(cls);
+  };
   it.fill(&sm.masks, a.kt_max, a.kt_min, 0, u_end, gi_first, gi_last, npt, P, N, w, NTHREADS / 64);
   int cls_cur = KT_FULL;
-  int u_cur = it.next(cls_cur);
-  if (u_cur > 0) {
+  int u_cur = grp == 0 ? it.next(cls_cur) : next_own(cls_cur);
+  if (grp == 0 ? u_cur > 0 : u_cur >= 0) {
     dma_wait_all();                        // this wave's rows of the guessed tile have landed; they are overwritten
     issue_tile(ctx, sm, buf, u_cur, w, lane);
   }
@@ -306,7 +320,7 @@ tree_attn_fwd_kernel(AttnArgs a, int n_qtiles) {
     while (u_cur >= 0 && cls_cur == KT_FULL) TT_FWD_STEP(true)
     while (u_cur >= 0) TT_FWD_STEP(false)
     tile0 += 64 * KT_MAX_WIN;
-    if (tile0 >= u_end) break;
+    if (NG == 2 || tile0 >= u_end) break;        // (two groups: the host sees to it that there is one chunk)
     it.fill(&sm.masks, a.kt_max, a.kt_min, tile0, u_end, gi_first, gi_last, npt, P, N, w, NTHREADS / 64);
     u_cur = it.next(cls_cur);
     if (u_cur >= 0) issue_tile(ctx, sm, buf, u_cur, w, lane);
@@ -314,34 +328,74 @@ tree_attn_fwd_kernel(AttnArgs a, int n_qtiles) {
 #undef TT_FWD_STEP
 
   // ---- epilogue ----
-  const float l_tot = half_swap_sum(l_run);
+  float l_tot = half_swap_sum(l_run);
+  if constexpr (NG == 2) {
+    // Every step ended with a barrier; the group with one tile less makes up for the missing one, so that both are past
+    // their last tile behind the next one and the stages can carry the other group's half of the result: column blocks
+    // 0, 1 are finished by group 0, blocks 2, 3 by group 1.
+    if (grp == 1 && other >= 0) __syncthreads();
+    float* const xch = reinterpret_cast<float*>(&sm);                    // [32 registers][256 lanes], then m and l
+    const float* const xin = reinterpret_cast<const float*>(reinterpret_cast<Smem*>(smem_raw) + (grp ^ 1));
+    const int slot = 64 * w + lane;
+#pragma unroll
+    for (int db = 0; db < 2; db++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) xch[(16 * db + r) * NTHREADS + slot] = grp == 0 ? o_acc[2 + db][r] : o_acc[db][r];
+    xch[32 * NTHREADS + slot] = m_run;
+    xch[33 * NTHREADS + slot] = l_tot;
+    __syncthreads();
+    const float m_in = xin[32 * NTHREADS + slot], l_in = xin[33 * NTHREADS + slot];
+    const float m = fmaxf(m_run, m_in);
+    // a group that has seen no key of this query has sums of zero and no reference
+    const float own = m_run == -INFINITY ? 0.f : fast_exp2(m_run - m), in = m_in == -INFINITY ? 0.f : fast_exp2(m_in - m);
+    l_tot = l_tot * own + l_in * in;
+    m_run = m;
+#pragma unroll
+    for (int db = 0; db < 2; db++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) {
+        const float mine = grp == 0 ? o_acc[db][r] : o_acc[2 + db][r];
+        o_acc[db][r] = mine * own + xin[(16 * db + r) * NTHREADS + slot] * in;
+      }
+  }
+  constexpr int N_DB = 4 / NG;                   // column blocks that this wave stores, from block N_DB * grp on
   const float inv_l = 1.f / l_tot;
   const int q = q0 + 32 * w + c32;
   if (q < N) {
-    __bf16* op = (__bf16*)a.o + ((int64_t)q * a.hq + h) * D;
+    __bf16* op = (__bf16*)a.o + ((int64_t)q * a.hq + h) * D + 32 * N_DB * grp;
 #pragma unroll
-    for (int db = 0; db < 4; db++)
+    for (int db = 0; db < N_DB; db++)
 #pragma unroll
       for (int r4 = 0; r4 < 4; r4++) {
         const bf16x4 ov = cvt4(o_acc[db][r4 * 4 + 0] * inv_l, o_acc[db][r4 * 4 + 1] * inv_l,
                                o_acc[db][r4 * 4 + 2] * inv_l, o_acc[db][r4 * 4 + 3] * inv_l);
         *(bf16x4*)(op + db * 32 + r4 * 8 + 4 * hf) = ov;
       }
-    if (hf == 0) a.lse[(int64_t)h * N + q] = (m_run + log2f(l_tot)) * LN2_F;
+    if (hf == 0 && grp == 0) a.lse[(int64_t)h * N + q] = (m_run + log2f(l_tot)) * LN2_F;
   }
 }
 
 }  // namespace
 
+// Two groups of waves per workgroup where there is no second workgroup for a compute unit to run beside the first, and one
+// chunk of candidate tiles.
+bool attn_two_groups(const AttnArgs& a, int64_t blocks) {
+  int dev = 0, n_cu = 256;
+  if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
+  const int64_t n_ktiles = ((int64_t)a.n_prefix + BN - 1) / BN + ((int64_t)a.n_q + BN - 1) / BN;
+  return blocks <= n_cu && n_ktiles <= 64 * KT_MAX_WIN;
+}
+
 hipError_t mfma_attn_fwd(const AttnArgs& a, hipStream_t st) {
   if (a.n_q == 0) return hipSuccess;
   const int n_qtiles = (a.n_q + BM - 1) / BM;
   const int64_t blocks = (int64_t)n_qtiles * a.hq;
-  if (hipError_t e = hipFuncSetAttribute((const void*)tree_attn_fwd_kernel,
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(Smem)))
-    return e;
+  const bool two = attn_two_groups(a, blocks);
+  const auto kernel = two ? tree_attn_fwd_kernel<2> : tree_attn_fwd_kernel<1>;
+  const int lds = (two ? 2 : 1) * (int)sizeof(Smem);
+  if (hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds)) return e;
   KernelTimer timer(TT_KERNEL_ATTN_FWD, st);
-  tree_attn_fwd_kernel<<<(unsigned)blocks, NTHREADS, sizeof(Smem), st>>>(a, n_qtiles);
+  kernel<<<(unsigned)blocks, (two ? 2 : 1) * NTHREADS, lds, st>>>(a, n_qtiles);
   return hipGetLastError();
 }
 

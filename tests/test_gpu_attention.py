@@ -205,6 +205,18 @@ def test_token_strides_of_a_fused_qkv_buffer():
     assert np.array_equal(f64(o), plain["o"]) and np.array_equal(f64(dk), plain["dk"]) and np.array_equal(f64(dq), plain["dq"])
 
 
+# The forward kernel with two groups of waves (launches of at most one workgroup per compute unit): one key tile (the
+# second group sees none), two, odd and even numbers of them, a second root whose queries see nothing of the first
+# tiles, and both sides of the line (8 and 9 tiles of 128 queries x 32 heads on 256 compute units).
+@pytest.mark.parametrize("segs,parent,hq,hkv", [
+    ([1], [-1], 2, 1), ([64], [-1], 2, 2), ([65], [-1], 4, 2), ([129], [-1], 4, 1), ([64, 63, 66], [-1, 0, 0], 4, 2),
+    ([70, 90, 64], [-1, -1, 1], 8, 2), ([200, 100, 150, 61], [-1, 0, 0, 2], 4, 4), ([400, 300, 324], [-1, 0, 0], 32, 8),
+    ([400, 300, 325], [-1, 0, 0], 32, 8)])
+def test_bf16_forward_two_wave_groups(segs, parent, hq, hkv):
+    t = W._mk(parent, segs, [1] * len(segs), "two-groups")
+    _full_parity(t, W.AttnDims(hq, hkv, 128, "bf16", 0.5), sum(segs), label="two wave groups")
+
+
 @pytest.mark.parametrize("hq,hkv,d", [(2, 2, 64), (6, 2, 128)])
 def test_fp32_matrix_kernels_block_edges(hq, hkv, d):
     """Token counts around the 16-wide blocks and the 128 keys of one round of the waves, nodes that start inside a block,
