@@ -380,8 +380,8 @@ tt_status tt_tree_weighted_logprob_bwd(int64_t n_rows, int32_t vocab, int32_t dt
  *   Arguments as for the two calls; logp and lse [n_rows] fp32 are both required; loss_acc may be
  *   NULL; grad_scale must be known beforehand (it usually is: 1, or 1 / accumulation steps).
  *   dlogits may alias logits when the strides are equal.
- * Alignment: when the logits' and the gradient's rows all start on 16-byte boundaries (aligned
- *   bases, row strides a multiple of 16 bytes) the one-pass kernel runs; otherwise the call runs
+ * Alignment: when every row of the logits and of the gradient is the same distance from a 16-byte
+ *   boundary (aligned bases and equal row strides are), one kernel does both; otherwise the call runs
  *   the two passes one after the other.
  * ------------------------------------------------------------------------------------------ */
 tt_status tt_tree_weighted_logprob_fwd_bwd(int64_t n_rows, int32_t vocab, int32_t dtype,

@@ -71,3 +71,18 @@ def test_agrees_with_library_meta_and_errors():
     with pytest.raises(T.TreeTrainError) as e:
         T.tree_conv_plan([-1, 2, 0], 3)                              # a predecessor must be an earlier token
     assert e.value.status == -3
+
+
+def test_backward_workspace_stays_below_its_bound():
+    """Tiles are never shorter than the power of two (32 .. 256 tokens) that makes 1024 workgroups of 16-byte lanes: what
+    a call of a given shape may need for its partial sums is bounded by that rule, whatever the tile that is used."""
+    rng = np.random.default_rng(5)
+    for _ in range(2000):
+        bf16, k = bool(rng.integers(2)), int(rng.integers(2, 5))
+        lane = 8 if bf16 else 4
+        c, n = lane * int(10 ** rng.uniform(0, 4)), int(10 ** rng.uniform(0, 6.3))
+        tile = 256
+        while tile > 32 and -(-n // tile) * (c // lane) < 1024 * 256:
+            tile //= 2
+        need = T.binding._lib().tt_tree_conv_bwd_workspace(n, c, k, T.binding.DTYPE_BF16 if bf16 else T.binding.DTYPE_FP32)
+        assert 0 < need <= -(-n // tile) * (k + 1) * c * 4 + 256, (n, c, k, bf16)
