@@ -198,8 +198,10 @@ __global__ void __launch_bounds__(64 * NW, 2) f32_fwd_kernel(RefArgs a, int n_qt
   float top = -INFINITY, total = 0.f;
 #pragma unroll
   for (int v = 0; v < NW; v++) top = fmaxf(top, m_s[v][l16]);
+  // (a wave without a reference has a sum of zero if it saw no key, and of NaN if every score it saw was NaN, which the
+  // maximum passes over)
 #pragma unroll
-  for (int v = 0; v < NW; v++) total += m_s[v][l16] == -INFINITY ? 0.f : l_s[v][l16] * expf(m_s[v][l16] - top);
+  for (int v = 0; v < NW; v++) total += m_s[v][l16] == -INFINITY ? l_s[v][l16] : l_s[v][l16] * expf(m_s[v][l16] - top);
   const float f = m == -INFINITY ? 0.f : expf(m - top);
 #pragma unroll
   for (int i = 0; i < D / 16; i++) o[i] *= f;
@@ -208,7 +210,8 @@ __global__ void __launch_bounds__(64 * NW, 2) f32_fwd_kernel(RefArgs a, int n_qt
 #pragma unroll
     for (int i = 0; i < D / 16; i++) o[i] /= total;
     store_row<D>((float*)a.o + ((int64_t)qi * a.hq + h) * D, o, 1.f, g);
-    if (g == 0) a.lse[(int64_t)h * a.n_q + qi] = top + logf(total);
+    // (every score -inf: no distribution, NaN like the row)
+    if (g == 0) a.lse[(int64_t)h * a.n_q + qi] = top == -INFINITY ? NAN : top + logf(total);
   }
 }
 

@@ -244,9 +244,43 @@ def test_fp32_non_finite_values_reach_only_who_sees_them(d):
     k[30, 0, 1] = float("nan")
     q[70, 1, 2] = float("nan")
     do[90, 0, 5] = float("inf")
-    got, ref = (gpu_attention(meta, q, k, v, do, reference_kernels=r) for r in (False, True))
+    _same_where_finite(*(gpu_attention(meta, q, k, v, do, reference_kernels=r) for r in (False, True)))
+
+
+def _same_where_finite(got, ref):
     for key in ("o", "lse", "dq", "dk", "dv"):
         fin = np.isfinite(ref[key])
-        assert np.array_equal(np.isfinite(got[key]), fin), key
+        assert np.array_equal(np.isfinite(got[key]), fin) and np.array_equal(np.isnan(got[key]), np.isnan(ref[key])), key
         # one wave's sums in another order: 1e-5 of the largest entry
         assert fin.any() and not fin.all() and np.abs(got[key][fin] - ref[key][fin]).max() <= 1e-5 * np.abs(ref[key][fin]).max(), key
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("nan_key", [16, 32])
+def test_fp32_nan_of_the_only_key_a_wave_sees(d, nan_key):
+    """A NaN key that opens a 16-key block: for the query of the same token it is the only key of that block, hence of one
+    wave, and its NaN has to survive the join of the waves (LSE, and through it dV of the keys in front); a NaN query makes
+    every wave's scores NaN."""
+    from gpu_util import gpu_attention
+    tree = W._mk([-1, 0], [nan_key + 1, 3], [1, 1], "a chain")
+    meta = T.tree_build_meta(tree.parent, tree.seg_len)
+    n = meta.n_tokens
+    q, k, v, do = W.attn_inputs(n, n, W.AttnDims(2, 2, d, "fp32", 1.0), 4)
+    k[nan_key, 0, 1] = float("nan")
+    q[5, 1, 2] = float("nan")
+    got, ref = (gpu_attention(meta, q, k, v, do, reference_kernels=r) for r in (False, True))
+    assert np.isnan(ref["lse"][0, nan_key:]).all() and np.isnan(ref["lse"][1, 5])
+    _same_where_finite(got, ref)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_row_without_a_finite_score(d):
+    """The only score of query 0 is -inf, which makes its row and its LSE NaN; the other queries see finite keys too."""
+    from gpu_util import gpu_attention
+    meta = T.tree_build_meta([-1, 0], [20, 3])
+    q, k, v, do = W.attn_inputs(23, 23, W.AttnDims(2, 2, d, "fp32", 1.0), 4)
+    q[:, 1, 1] = 0.5
+    k[0, 1, 1] = -float("inf")
+    got, ref = (gpu_attention(meta, q, k, v, do, reference_kernels=r) for r in (False, True))
+    assert np.isnan(ref["lse"][1, 0]) and np.isfinite(ref["lse"][1, 1:]).all()
+    _same_where_finite(got, ref)
