@@ -341,10 +341,15 @@ __global__ void __launch_bounds__(64 * NW, 2) f32_bwd_kernel(RefArgs a, int n_qt
 
 }  // namespace
 
+// Workgroups of a launch.  All of them lie along one grid dimension, and a dimension of a launch holds less than 2^32
+// work-items: calls beyond that (more than 8388607 workgroups) stay with the row kernels, whose grids are two-dimensional.
+static constexpr int64_t f32_workgroups(int64_t n_keys, int64_t heads) { return (n_keys + BLK - 1) / BLK * heads; }
+static constexpr bool f32_grid_fits(int64_t n_keys, int64_t heads) { return f32_workgroups(n_keys, heads) * 64 * NW < (int64_t)1 << 32; }
+static_assert(f32_grid_fits(8388607 * (int64_t)BLK, 1) && !f32_grid_fits(8388607 * (int64_t)BLK + 1, 1), "work-items of a launch");
+static_assert(!f32_grid_fits(1 << 20, 128) && f32_grid_fits(1 << 20, 127), "work-items of a launch");
+
 bool f32_attn_supported(const RefArgs& a) {
-  // (one grid dimension: 2^31 - 1 workgroups)
-  const int64_t tiles = ((int64_t)a.n_prefix + a.n_q + BLK - 1) / BLK;
-  return (a.d == 64 || a.d == 128) && tiles * (a.hq + a.hkv) < INT32_MAX;
+  return (a.d == 64 || a.d == 128) && f32_grid_fits((int64_t)a.n_prefix + a.n_q, (int64_t)a.hq + a.hkv);
 }
 
 hipError_t f32_attn_fwd(const RefArgs& a, hipStream_t st) {
