@@ -412,7 +412,8 @@ hipError_t launch_fused(int64_t n_rows, int vocab, const T* logits, int64_t row_
 
 }  // namespace
 
-bool weighted_logprob_fused_ok(bool bf16, const void* logits, int64_t row_stride, const void* dlogits, int64_t out_stride) {
+bool weighted_logprob_fused_ok(int64_t n_rows, bool bf16, const void* logits, int64_t row_stride, const void* dlogits, int64_t out_stride) {
+  if (n_rows * FUSED_THREADS >= (int64_t)1 << 32) return false;          // a dimension of a launch holds less than 2^32 work-items
   const uintptr_t esz = bf16 ? 2 : 4;
   const uintptr_t in = reinterpret_cast<uintptr_t>(logits), out = reinterpret_cast<uintptr_t>(dlogits);
   return ((in ^ out) & 15) == 0 && in % esz == 0 && (((uintptr_t)row_stride * esz) & 15) == (((uintptr_t)out_stride * esz) & 15);

@@ -359,3 +359,19 @@ def test_fwd_bwd_one_pass_special_rows_and_chunks():
     assert torch.equal(torch.cat(parts), whole[3])
     again = T.tree_weighted_logprob_fwd_bwd(ld, td)
     assert all(torch.equal(a, b) for a, b in zip(whole, again))
+
+
+@pytest.mark.parametrize("vocab", [8, 5])
+def test_fwd_bwd_more_rows_than_one_launch_takes(vocab):
+    """2^23 rows of the one-pass kernel's 512 threads would be 2^32 work-items, which no launch holds: the call runs the
+    two passes, whose workgroups are half as large (rows on the 16-byte grid and off it)."""
+    n = 1 << 23
+    g = torch.Generator(device="cuda").manual_seed(vocab)
+    logits = torch.randn(n, vocab, device="cuda", generator=g).to(torch.bfloat16)
+    target = torch.randint(0, vocab, (n,), device="cuda", generator=g, dtype=torch.int32)
+    logp, lse, _, grad = T.tree_weighted_logprob_fwd_bwd(logits, target)
+    want = torch.log_softmax(logits.float(), 1)
+    assert float((lse - logits.float().logsumexp(1)).abs().max()) <= 4e-6 * max(1.0, np.log(vocab))
+    assert float((logp - want.gather(1, target.long()[:, None])[:, 0]).abs().max()) <= 1e-5
+    want = want.exp_().scatter_add_(1, target.long()[:, None], torch.full((n, 1), -1.0, device="cuda"))
+    assert float((grad.float() - want).abs().max()) <= 2.0 ** -8          # one rounding of values up to 1
