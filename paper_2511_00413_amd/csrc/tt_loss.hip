@@ -28,30 +28,30 @@ struct MS { float m, s; };   // running max (natural units) and sum of exp(z - m
 // several more instructions per element on that range, which made the kernel ALU-bound.
 __device__ __forceinline__ float ex2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// The running maximum starts at the lowest finite number: every difference below is then a number for entries at -inf
+// (masked vocabulary entries, also where a thread sees nothing else), and a sum is only ever scaled, never dropped, so that
+// a NaN, which a maximum passes over, stays in it.
+constexpr float LOWEST = -3.402823466e38f;
+
 __device__ __forceinline__ MS merge(MS a, MS b) {
   const float m = fmaxf(a.m, b.m);
-  // exp2(-inf) = 0 handles empty partners; (-inf) - (-inf) is avoided by the select
-  const float sa = a.m == -INFINITY ? 0.f : a.s * ex2((a.m - m) * LOG2E);
-  const float sb = b.m == -INFINITY ? 0.f : b.s * ex2((b.m - m) * LOG2E);
-  return {m, sa + sb};
+  return {m, a.s * ex2((a.m - m) * LOG2E) + b.s * ex2((b.m - m) * LOG2E)};
 }
 
-__device__ __forceinline__ void push8(MS& st, const float (&z)[8]) {  // z may hold -inf (masked vocabulary entries)
+__device__ __forceinline__ void push8(MS& st, const float (&z)[8]) {
   float vm = fmaxf(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])), fmaxf(fmaxf(z[4], z[5]), fmaxf(z[6], z[7])));
   const float m_new = fmaxf(st.m, vm);
-  const float mref = m_new == -INFINITY ? 0.f : m_new;      // all -inf so far: keep the sum at 0, no NaN
   // the difference is taken before the scaling so that large |z| loses nothing
-  float acc = st.m == -INFINITY ? 0.f : st.s * ex2((st.m - mref) * LOG2E);
+  float acc = st.s * ex2((st.m - m_new) * LOG2E);
 #pragma unroll
-  for (int e = 0; e < 8; e++) acc += ex2((z[e] - mref) * LOG2E);
+  for (int e = 0; e < 8; e++) acc += ex2((z[e] - m_new) * LOG2E);
   st.m = m_new;
   st.s = acc;
 }
 
 __device__ __forceinline__ void push1(MS& st, float z) {
   const float m_new = fmaxf(st.m, z);
-  const float old = st.m == -INFINITY ? 0.f : st.s * ex2((st.m - m_new) * LOG2E);
-  st.s = old + ex2((z - m_new) * LOG2E);
+  st.s = st.s * ex2((st.m - m_new) * LOG2E) + ex2((z - m_new) * LOG2E);
   st.m = m_new;
 }
 
@@ -83,7 +83,7 @@ row_logprob_kernel(int vocab, const T* __restrict__ logits, int64_t row_stride,
   head = head < vocab ? head : vocab;
   const int nvec = (vocab - head) / EPV;
   const int tail0 = head + nvec * EPV;
-  MS st = {-INFINITY, 0.f};
+  MS st = {LOWEST, 0.f};
   const u32x4* vp = reinterpret_cast<const u32x4*>(row + head);
   if constexpr (sizeof(T) == 2) {
     int i = t;
@@ -291,7 +291,7 @@ row_logprob_dlogits_kernel(int vocab, const T* logits, int64_t row_stride, const
   const float w = used ? grad_scale * (weight ? weight[r] : 1.f) : 0.f;
 
   // ---- pass 1: statistics ----
-  MS st = {-INFINITY, 0.f};
+  MS st = {LOWEST, 0.f};
   auto push_vec = [&](const u32x4& v) {
     if constexpr (sizeof(T) == 2) {
       float z[8];

@@ -375,3 +375,35 @@ def test_fwd_bwd_more_rows_than_one_launch_takes(vocab):
     assert float((logp - want.gather(1, target.long()[:, None])[:, 0]).abs().max()) <= 1e-5
     want = want.exp_().scatter_add_(1, target.long()[:, None], torch.full((n, 1), -1.0, device="cuda"))
     assert float((grad.float() - want).abs().max()) <= 2.0 ** -8          # one rounding of values up to 1
+
+
+@pytest.mark.parametrize("vocab", [4096, 1001, 2051, 8195, 60002])
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+def test_masked_entries_and_nan_logits(vocab, dtype):
+    """Entries at -inf anywhere in a row (a thread may see nothing else) count as zero, and one NaN makes the row's LSE
+    NaN: one-pass call and forward call, rows on and off the 16-byte grid."""
+    logits, target = W.loss_inputs(8, vocab, vocab, 2.0, dtype)
+    logits, target = logits.clone(), target.clone()
+    ninf = float("-inf")
+    logits[0, :vocab // 2] = ninf
+    logits[1, vocab // 2:] = ninf
+    logits[2, 1:] = ninf
+    logits[3, ::2] = ninf
+    logits[4, 0] = float("nan")
+    logits[5, vocab - 1] = float("nan")
+    logits[6, 8:24] = float("nan")
+    target[:4] = torch.tensor([vocab - 1, 0, 0, 1])
+    wl, wlse = L.log_softmax_gather(logits[[0, 1, 2, 3, 7]], target[[0, 1, 2, 3, 7]].numpy())
+    for pad in (0, 3):
+        buf = torch.zeros(8, vocab + pad, dtype=logits.dtype, device="cuda")
+        buf[:, :vocab] = logits.cuda()
+        lg, tg = buf[:, :vocab], target.cuda()
+        out = torch.empty_like(buf)[:, :vocab]
+        for logp, lse in (T.tree_weighted_logprob(lg, tg)[:2], T.tree_weighted_logprob_fwd_bwd(lg, tg, out=out)[:2]):
+            logp, lse = (x.cpu().numpy().astype(np.float64) for x in (logp, lse))
+            assert np.isnan(lse[4:7]).all() and np.isnan(logp[4:7]).all()
+            keep = [0, 1, 2, 3, 7]
+            assert np.abs(lse[keep] - wlse).max() <= 4e-6 * np.log(vocab) and np.abs(logp[keep] - wl).max() <= 4e-6 * np.log(vocab)
+        g = out.float().cpu().numpy().astype(np.float64)[:4]
+        want = L.dlogits(logits[:4], target[:4].numpy(), None)
+        assert np.sqrt(((g - want) ** 2).sum()) <= (4e-3 if dtype == "bf16" else 1e-5) * np.sqrt((want ** 2).sum())
