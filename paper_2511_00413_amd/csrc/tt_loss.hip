@@ -257,15 +257,22 @@ row_dlogits_kernel(int vocab, const T* logits, int64_t row_stride, const int32_t
 // kernels.
 constexpr int FUSED_THREADS = 512;
 constexpr int FUSED_LDS_BYTES = 64 * 1024;             // two workgroups per compute unit
-// The register form, for rows longer than 96 KB.  Bound by HBM with the exponentials' issue slots close behind, so two
-// workgroups share a compute unit (one streams in while the other stores), which leaves 128 registers per lane: 12
-// vectors in registers and 72 KB of LDS keep 168 KB of a row.  4096 rows: 151936 bf16 entries 499 -> 474 us, 100352
-// 315 -> 294 us, 40064 fp32 260 -> 244 us; 8 / 16 / 18 / 20 vectors: within 2 % of that, some sizes to either side.  Rows
-// of up to 96 KB measured the same in both forms (65536 bf16: 196 against 198 us) and stay with the first one.
+// The register form.  Bound by HBM with the exponentials' issue slots close behind, so two workgroups share a compute unit
+// (one streams in while the other stores), which leaves 128 registers per lane: 12 vectors in registers and 72 KB of LDS keep
+// 168 KB of a row.  4096 rows: 151936 bf16 entries 499 -> 470 us, 104448 321 -> 290; 8 / 16 / 18 / 20 vectors: within 2 % of that,
+// some sizes to either side.  What it costs is a start with nothing but loads and an end with nothing but stores, so it pays only
+// where the other form reads a good part of the row again.  bf16, us of the first / this form: 4096 rows of 98 KB 141 / 158,
+// 128 KB 178 / 202, 160 KB 231 / 237, 168 KB 253 / 254, 176 KB 270 / 267, 184 KB 282 / 263; with every row on chip at once (512
+// rows) 98 KB 24.1 / 21.8, 112 KB 25.2 / 24.9, 160 KB 37.7 / 33.4; fp32, 512 rows: 112 KB 24.3 / 25.0, 144 KB 32.1 / 30.2, 256 rows of
+// 144 KB 18.7 / 19.4.  With far fewer rows than compute units nothing overlaps either way: 96 rows of 192 KB 20.3 / 22.1, 128
+// of 256 KB 24.1 / 25.0, 192 of 256 KB 31.1 / 25.8.
 // Rows off the 16-byte grid ran the two separate kernels before, the gradient element by element: 32003 bf16 entries
 // 254 -> 114 us, 151935 1127 -> 520 us.
 constexpr int FUSED_BIG_NREG = 12;
 constexpr int FUSED_BIG_LDS_BYTES = 72 * 1024;
+bool fused_in_registers(int64_t n_rows, int64_t row_bytes) {
+  return n_rows >= 192 && row_bytes > (n_rows <= 512 ? 160 * 1024 : 176 * 1024);
+}
 
 template <typename T, int NREG>
 __global__ void __launch_bounds__(FUSED_THREADS, 4)
@@ -304,7 +311,7 @@ row_logprob_dlogits_kernel(int vocab, const T* logits, int64_t row_stride, const
   };
   [[maybe_unused]] u32x4 kept[NREG > 0 ? NREG : 1];
   if constexpr (NREG > 0) {
-    // (the host picks this form only for rows of more than NREG * FUSED_THREADS vectors)
+    // (the host picks this form only for rows of more than NREG * FUSED_THREADS vectors, heads and tails left out)
 #pragma unroll
     for (int j = 0; j < NREG; j++) kept[j] = __builtin_nontemporal_load(vp + j * FUSED_THREADS + t);
 #pragma unroll
@@ -427,8 +434,7 @@ hipError_t weighted_logprob_fused(int64_t n_rows, int vocab, bool bf16, const vo
     KernelTimer timer(TT_KERNEL_LOSS_FUSED, st);
     auto run = [&](auto* z, auto* dz) {
       using T = std::remove_pointer_t<decltype(dz)>;
-      // (one vector less than the row's bytes say: a row off the 16-byte grid loses one to its head and tail)
-      const bool big = (int64_t)vocab * (int64_t)sizeof(T) / 16 > (int64_t)FUSED_BIG_NREG * FUSED_THREADS;
+      const bool big = fused_in_registers(n_rows, (int64_t)vocab * (int64_t)sizeof(T));
       return big ? launch_fused<T, FUSED_BIG_NREG>(n_rows, vocab, z, row_stride, target, weight, grad_scale, logp, lse, dz, out_stride, st)
                  : launch_fused<T, 0>(n_rows, vocab, z, row_stride, target, weight, grad_scale, logp, lse, dz, out_stride, st);
     };

@@ -307,9 +307,8 @@ def test_fwd_bwd_one_pass_in_place_and_strides():
     _check_fused(logits, target, w[:12], inplace=True, grad_scale=2.0)
 
 
-# Rows off the 16-byte grid and rows kept in registers: 6144 vectors of 16 bytes are the last size without the register
-# part, 6145 the first with it (an off-grid row then has exactly 6144), 10752 fill registers and LDS, beyond that a row is
-# read again; lengths that leave heads and tails of 0 .. 7 (fp32: 0 .. 3) elements.
+# Rows off the 16-byte grid and long rows, few of them: lengths that leave heads and tails of 0 .. 7 (fp32: 0 .. 3) elements, around
+# what the LDS copy keeps (4096 vectors of 16 bytes) and what registers and LDS keep together (10752).
 @pytest.mark.parametrize("rows,vocab,dtype,inplace", [
     (9, 32003, "bf16", False), (17, 1001, "bf16", True), (9, 15, "bf16", False), (5, 49152, "bf16", False),
     (5, 49160, "bf16", False), (9, 49161, "bf16", True), (9, 49167, "bf16", False), (3, 86016, "bf16", True),
@@ -407,3 +406,37 @@ def test_masked_entries_and_nan_logits(vocab, dtype):
         g = out.float().cpu().numpy().astype(np.float64)[:4]
         want = L.dlogits(logits[:4], target[:4].numpy(), None)
         assert np.sqrt(((g - want) ** 2).sum()) <= (4e-3 if dtype == "bf16" else 1e-5) * np.sqrt((want ** 2).sum())
+
+
+@pytest.mark.parametrize("rows,vocab,dtype,pad,inplace", [
+    (191, 90000, "bf16", 0, False), (192, 81920, "bf16", 0, False), (192, 81928, "bf16", 0, True), (512, 81923, "bf16", 0, False),
+    (200, 86016, "bf16", 5, True), (200, 86025, "bf16", 0, False), (513, 90112, "bf16", 0, False), (513, 90117, "bf16", 0, True),
+    (192, 40961, "fp32", 0, True), (513, 45057, "fp32", 0, False), (192, 60002, "fp32", 1, False)])
+def test_fwd_bwd_one_pass_rows_in_registers(rows, vocab, dtype, pad, inplace):
+    """Both sides of the lines where the one-pass kernel keeps a row in registers too (192 rows, 160 KB, above 512 rows 176 KB;
+    168 KB fill registers and LDS), on and off the 16-byte grid, against log_softmax in float64."""
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(rows + vocab)
+    buf = torch.randn(rows, vocab + pad, device="cuda", generator=g).mul_(2).to(dt)
+    z = buf[:, :vocab]
+    target = torch.randint(0, vocab, (rows,), device="cuda", generator=g, dtype=torch.int32)
+    target[:3] = torch.tensor([0, vocab - 1, -1])
+    w = torch.rand(rows, device="cuda", generator=g) + 0.25
+    zd = z.double()
+    lse_ref = zd.logsumexp(1)
+    src = buf.clone()[:, :vocab] if inplace else z
+    out = src if inplace else torch.empty_like(buf)[:, :vocab]
+    logp, lse, loss, grad = T.tree_weighted_logprob_fwd_bwd(src, target, w, out=out)
+    used = target >= 0
+    pick = target.clamp(min=0).long()[:, None]
+    logp_ref = torch.where(used, zd.gather(1, pick)[:, 0] - lse_ref, torch.zeros_like(lse_ref))
+    tol = 4e-6 * np.log(vocab)
+    assert float((lse - lse_ref).abs().max()) <= tol and float((logp - logp_ref).abs().max()) <= tol
+    assert abs(float(loss) + float((w * logp_ref).sum())) <= 1e-5 * abs(float(loss))
+    want = zd.sub_(lse_ref[:, None]).exp_().scatter_add_(1, pick, torch.full((rows, 1), -1.0, dtype=torch.float64, device="cuda"))
+    want.mul_(torch.where(used, w, torch.zeros_like(w))[:, None])
+    assert float((grad.double() - want).norm()) <= (4e-3 if dtype == "bf16" else 1e-5) * float(want.norm())
+    # element by element: one rounding to bf16, and 1e-4 of the softmax value for fp32 exponentials of arguments up to 30
+    assert bool(((grad.double() - want).abs() <= (2.0 ** -8 * want.abs() if dtype == "bf16" else 0) + 1e-4 * (want.abs() + 1e-30)).all())
+    if pad and inplace:
+        assert torch.equal(src.as_strided((rows, pad), src.stride(), vocab), buf[:, vocab:])      # nothing past the rows
