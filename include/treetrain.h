@@ -381,8 +381,9 @@ tt_status tt_tree_weighted_logprob_bwd(int64_t n_rows, int32_t vocab, int32_t dt
  *   NULL; grad_scale must be known beforehand (it usually is: 1, or 1 / accumulation steps).
  *   dlogits may alias logits when the strides are equal.
  * Alignment: when every row of the logits and of the gradient is the same distance from a 16-byte
- *   boundary (aligned bases and equal row strides are), one kernel does both; otherwise, and for more
- *   than 8388607 rows, the call runs the two passes one after the other.
+ *   boundary (aligned bases and equal row strides are), one kernel does both; otherwise, for many short
+ *   rows off that grid (more than 1024 rows of less than 2048 entries) and for more than 8388607 rows,
+ *   the call runs the two passes one after the other.
  * ------------------------------------------------------------------------------------------ */
 tt_status tt_tree_weighted_logprob_fwd_bwd(int64_t n_rows, int32_t vocab, int32_t dtype,
                                            const void* logits, int64_t row_stride,

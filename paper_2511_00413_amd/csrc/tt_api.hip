@@ -210,12 +210,12 @@ extern "C" tt_status tt_tree_weighted_logprob_fwd_bwd(int64_t n_rows, int32_t vo
     return fail(TT_ERR_ALIGN, "logits / dlogits is not aligned to its element size");
   const bool bf16 = dtype == TT_DTYPE_BF16;
   hipStream_t st = (hipStream_t)stream;
-  if (tt::weighted_logprob_fused_ok(n_rows, bf16, logits, row_stride, dlogits, dlogits_row_stride))
+  if (tt::weighted_logprob_fused_ok(n_rows, vocab, bf16, logits, row_stride, dlogits, dlogits_row_stride))
     return hip_result(tt::weighted_logprob_fused(n_rows, vocab, bf16, logits, row_stride, target, weight, grad_scale, logp, lse,
                                                  loss_acc, dlogits, dlogits_row_stride, st),
                       "tree_weighted_logprob_fwd_bwd");
-  // logits and gradient rows at different distances from the 16-byte grid, or more rows than one launch of the one-pass
-  // kernel takes: the two passes one after the other
+  // logits and gradient rows at different distances from the 16-byte grid, short ones off it, or more rows than one launch
+  // of the one-pass kernel takes: the two passes one after the other
   if (tt_status s = hip_result(tt::weighted_logprob(n_rows, vocab, bf16, logits, row_stride, target, weight, logp, lse, loss_acc, st),
                                "tree_weighted_logprob_fwd_bwd (forward pass)"))
     return s;

@@ -69,8 +69,9 @@ hipError_t weighted_logprob_bwd(int64_t n_rows, int vocab, bool bf16, const void
                                 void* dlogits, int64_t out_stride, hipStream_t st);
 
 // both in one pass over the logits; weighted_logprob_fused_ok tells whether the pointers and strides allow it (every row
-// of the logits and of the gradient the same distance from a 16-byte boundary) and the rows fit one launch
-bool weighted_logprob_fused_ok(int64_t n_rows, bool bf16, const void* logits, int64_t row_stride, const void* dlogits, int64_t out_stride);
+// of the logits and of the gradient the same distance from a 16-byte boundary), the rows fit one launch and it is the faster way
+bool weighted_logprob_fused_ok(int64_t n_rows, int vocab, bool bf16, const void* logits, int64_t row_stride, const void* dlogits,
+                               int64_t out_stride);
 hipError_t weighted_logprob_fused(int64_t n_rows, int vocab, bool bf16, const void* logits, int64_t row_stride,
                                   const int32_t* target, const float* weight, float grad_scale, float* logp, float* lse,
                                   float* loss_acc, void* dlogits, int64_t out_stride, hipStream_t st);

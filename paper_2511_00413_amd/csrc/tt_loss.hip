@@ -266,8 +266,6 @@ constexpr int FUSED_LDS_BYTES = 64 * 1024;             // two workgroups per com
 // rows) 98 KB 24.1 / 21.8, 112 KB 25.2 / 24.9, 160 KB 37.7 / 33.4; fp32, 512 rows: 112 KB 24.3 / 25.0, 144 KB 32.1 / 30.2, 256 rows of
 // 144 KB 18.7 / 19.4.  With far fewer rows than compute units nothing overlaps either way: 96 rows of 192 KB 20.3 / 22.1, 128
 // of 256 KB 24.1 / 25.0, 192 of 256 KB 31.1 / 25.8.
-// Rows off the 16-byte grid ran the two separate kernels before, the gradient element by element: 32003 bf16 entries
-// 254 -> 114 us, 151935 1127 -> 520 us.
 constexpr int FUSED_BIG_NREG = 12;
 constexpr int FUSED_BIG_LDS_BYTES = 72 * 1024;
 bool fused_in_registers(int64_t n_rows, int64_t row_bytes) {
@@ -419,11 +417,19 @@ hipError_t launch_fused(int64_t n_rows, int vocab, const T* logits, int64_t row_
 
 }  // namespace
 
-bool weighted_logprob_fused_ok(int64_t n_rows, bool bf16, const void* logits, int64_t row_stride, const void* dlogits, int64_t out_stride) {
+// Rows on the 16-byte grid always take the one-pass kernel.  Off it, where the two passes do the gradient element by element,
+// it pays from 2048 entries on, or while its half-empty workgroups are few.  Two passes / one: 65536 rows of 101 bf16 entries 147 /
+// 255 us, 1001 237 / 295, 1501 288 / 307, 2049 357 / 326, 3001 467 / 361, 4096 rows of 32003 253 / 110, of 151935 1127 / 520; 2048
+// rows of 33 11.9 / 12.3, 1024 of 33 10.2 / 9.2, 512 of 101 (fp32) 9.7 / 8.4.
+bool weighted_logprob_fused_ok(int64_t n_rows, int vocab, bool bf16, const void* logits, int64_t row_stride, const void* dlogits,
+                               int64_t out_stride) {
   if (n_rows * FUSED_THREADS >= (int64_t)1 << 32) return false;          // a dimension of a launch holds less than 2^32 work-items
   const uintptr_t esz = bf16 ? 2 : 4;
   const uintptr_t in = reinterpret_cast<uintptr_t>(logits), out = reinterpret_cast<uintptr_t>(dlogits);
-  return ((in ^ out) & 15) == 0 && in % esz == 0 && (((uintptr_t)row_stride * esz) & 15) == (((uintptr_t)out_stride * esz) & 15);
+  const uintptr_t step_in = (uintptr_t)row_stride * esz, step_out = (uintptr_t)out_stride * esz;
+  if (((in | out | step_in | step_out) & 15) == 0) return true;
+  if (n_rows > 1024 && vocab < 2048) return false;
+  return ((in ^ out) & 15) == 0 && in % esz == 0 && (step_in & 15) == (step_out & 15);
 }
 
 hipError_t weighted_logprob_fused(int64_t n_rows, int vocab, bool bf16, const void* logits, int64_t row_stride,

@@ -440,3 +440,13 @@ def test_fwd_bwd_one_pass_rows_in_registers(rows, vocab, dtype, pad, inplace):
     assert bool(((grad.double() - want).abs() <= (2.0 ** -8 * want.abs() if dtype == "bf16" else 0) + 1e-4 * (want.abs() + 1e-30)).all())
     if pad and inplace:
         assert torch.equal(src.as_strided((rows, pad), src.stride(), vocab), buf[:, vocab:])      # nothing past the rows
+
+
+@pytest.mark.parametrize("rows,vocab", [(1024, 37), (1025, 37), (1025, 2047), (1025, 2049)])
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+def test_fwd_bwd_short_rows_off_the_grid(rows, vocab, dtype):
+    """Both sides of the lines between one pass and two for rows off the 16-byte grid (1024 rows, 2048 entries)."""
+    logits, target = W.loss_inputs(rows, vocab, rows + vocab, 2.0, dtype)
+    target = target.clone()
+    target[0], target[1], target[2] = 0, vocab - 1, -1
+    _check_fused(logits, target, (np.random.default_rng(vocab).random(rows) + 0.25).astype(np.float32), grad_scale=0.5)
