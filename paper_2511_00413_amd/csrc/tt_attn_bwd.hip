@@ -179,7 +179,6 @@ __device__ __forceinline__ void dq_tile(const uint32_t (&ra)[8], const uint32_t 
 
 // NG: groups of four waves per workgroup, as in the forward kernel: 2 for launches that leave every workgroup a compute
 // unit of its own; the groups take every second key tile and add up their sums at the end.
-// Forward + backward, with the forward's: 4000 tokens, 8 / 8 heads, a chain 267 -> 243 us; 1024, 32 / 8, a chain 179 -> 174.
 template <int NG>
 __global__ void __launch_bounds__(NG * NTHREADS, 2)
 tree_attn_dq_kernel(AttnArgs a, int n_qtiles) {
@@ -371,7 +370,7 @@ hipError_t mfma_attn_bwd(const AttnArgs& args, hipStream_t st) {
   {
     const int n_qtiles = (a.n_q + Q_BM - 1) / Q_BM;
     const int64_t blocks = (int64_t)n_qtiles * a.hq;
-    const bool two = attn_two_groups(a, blocks);
+    const bool two = attn_two_groups(a, blocks, 32);
     const auto kernel = two ? tree_attn_dq_kernel<2> : tree_attn_dq_kernel<1>;
     const int lds = (two ? 2 : 1) * (int)sizeof(QSmem);
     if (hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds)) return e;

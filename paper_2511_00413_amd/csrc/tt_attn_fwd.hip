@@ -210,8 +210,6 @@ __device__ __forceinline__ void process_tile(const uint32_t (&ra)[8], const uint
 // NG: groups of four waves per workgroup.  2 (launches that leave every workgroup a compute unit of its own): the groups
 // take every second key tile of the same queries, each with its own stages, and add up their sums at the end -- half the
 // chain of tiles, and two waves per SIMD as with two workgroups per compute unit.
-// Kernel and call: 4000 tokens, 8 / 8 heads, a chain 66 -> 56 us; 2000, 16 / 4 22 -> 20; 1024, 32 / 8, a chain 28 -> 26; up to 800
-// tokens of 32 heads the same (a few tiles behind 10 us of start and end).
 template <int NG>
 __global__ void __launch_bounds__(NG * NTHREADS, 2)
 tree_attn_fwd_kernel(AttnArgs a, int n_qtiles) {
@@ -377,20 +375,26 @@ tree_attn_fwd_kernel(AttnArgs a, int n_qtiles) {
 
 }  // namespace
 
-// Two groups of waves per workgroup where there is no second workgroup for a compute unit to run beside the first, and one
-// chunk of candidate tiles.
-bool attn_two_groups(const AttnArgs& a, int64_t blocks) {
+// Two groups of waves per workgroup where there is no second workgroup for a compute unit to run beside the first, one
+// chunk of candidate tiles, and at least `min_tiles` of them: a workgroup whose queries see few tiles pays up to 1 us (forward) or
+// 3 us (dQ) for the second group's start and the exchange at the end, and how many it sees is known on the device alone, so the
+// lines lie where no tree shape loses.  Graph replays, us, one / two groups, shared prefix with short branches / random tree /
+// chain:  forward (from 24 tiles on) 128 tokens of 32 heads 9.6 / 10.5 in all shapes, 256 of 8 11.1 / 12.4, 12.5 / 12.8, 12.5 / 12.5;  1024
+// of 8 13.9 / 15.0, 16.0 / 15.2, 29.0 / 24.1;  1500 of 8 16.7 / 16.6, 16.1 / 15.3, 34.2 / 28.3;  4000 of 8 24.6 / 22.7, 24.4 / 21.2, 65.4 / 53.2;
+// dQ kernel (from 32 tiles on) 1024 of 8 18.9 / 21.4, 21.1 / 21.5, 36.8 / 32.4;  1500 22.5 / 23.1, 21.5 / 21.9, 43.1 / 36.4;  2048 24.1 / 23.9, 23.5 /
+// 23.8, 55.2 / 46.4;  4000 32.2 / 31.1, 32.3 / 29.5, 81.9 / 67.5.
+bool attn_two_groups(const AttnArgs& a, int64_t blocks, int min_tiles) {
   int dev = 0, n_cu = 256;
   if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
   const int64_t n_ktiles = ((int64_t)a.n_prefix + BN - 1) / BN + ((int64_t)a.n_q + BN - 1) / BN;
-  return blocks <= n_cu && n_ktiles <= 64 * KT_MAX_WIN;
+  return blocks <= n_cu && n_ktiles >= min_tiles && n_ktiles <= 64 * KT_MAX_WIN;
 }
 
 hipError_t mfma_attn_fwd(const AttnArgs& a, hipStream_t st) {
   if (a.n_q == 0) return hipSuccess;
   const int n_qtiles = (a.n_q + BM - 1) / BM;
   const int64_t blocks = (int64_t)n_qtiles * a.hq;
-  const bool two = attn_two_groups(a, blocks);
+  const bool two = attn_two_groups(a, blocks, 24);
   const auto kernel = two ? tree_attn_fwd_kernel<2> : tree_attn_fwd_kernel<1>;
   const int lds = (two ? 2 : 1) * (int)sizeof(Smem);
   if (hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds)) return e;

@@ -205,9 +205,8 @@ def test_token_strides_of_a_fused_qkv_buffer():
     assert np.array_equal(f64(o), plain["o"]) and np.array_equal(f64(dk), plain["dk"]) and np.array_equal(f64(dq), plain["dq"])
 
 
-# The forward kernel with two groups of waves (launches of at most one workgroup per compute unit): one key tile (the
-# second group sees none), two, odd and even numbers of them, a second root whose queries see nothing of the first
-# tiles, and both sides of the line (8 and 9 tiles of 128 queries x 32 heads on 256 compute units).
+# Short trees, which take one group of waves per workgroup: one key tile, two, odd and even numbers of them, a second root whose
+# queries see nothing of the first tiles, up to a workgroup for every compute unit and one beyond.
 @pytest.mark.parametrize("segs,parent,hq,hkv", [
     ([1], [-1], 2, 1), ([64], [-1], 2, 2), ([65], [-1], 4, 2), ([129], [-1], 4, 1), ([64, 63, 66], [-1, 0, 0], 4, 2),
     ([70, 90, 64], [-1, -1, 1], 8, 2), ([200, 100, 150, 61], [-1, 0, 0, 2], 4, 4), ([400, 300, 324], [-1, 0, 0], 32, 8),
@@ -215,6 +214,41 @@ def test_token_strides_of_a_fused_qkv_buffer():
 def test_bf16_forward_two_wave_groups(segs, parent, hq, hkv):
     t = W._mk(parent, segs, [1] * len(segs), "two-groups")
     _full_parity(t, W.AttnDims(hq, hkv, 128, "bf16", 0.5), sum(segs), label="two wave groups")
+
+
+# Two groups of waves per workgroup (at most one workgroup per compute unit; forward from 24 key tiles on, dQ from 32): both
+# sides of the lines, and roots of 1, 64, 65, 129 and 224 tokens behind a long one, so that workgroups see one tile (the second
+# group none), two, three and more, odd and even numbers, whole and cut by the mask.
+@pytest.mark.parametrize("segs,parent,hq,hkv", [
+    ([1000, 472], [-1, 0], 4, 2), ([1000, 473], [-1, 0], 4, 2), ([1100, 884], [-1, 0], 2, 2), ([1100, 885], [-1, 0], 2, 1),
+    ([1800, 1, 64, 65, 129, 70, 90, 64], [-1, -1, -1, -1, -1, -1, 5, 5], 4, 2),
+    ([64, 1, 128, 129, 1800, 200, 100], [-1, -1, -1, -1, -1, 4, 4], 8, 8)])
+def test_bf16_two_wave_groups_many_tiles(segs, parent, hq, hkv):
+    t = W._mk(parent, segs, [1] * len(segs), "two-groups")
+    _full_parity(t, W.AttnDims(hq, hkv, 128, "bf16", 0.5), sum(segs), label="two wave groups, many tiles")
+
+
+def test_bf16_two_wave_groups_prefix_and_strides():
+    """Two groups behind a cached prefix whose first tiles are hidden (the tile requested in advance is the wrong one), the
+    largest launch that takes them and the smallest that does not, and token strides of a fused buffer."""
+    from gpu_util import gpu_attention, dev, f64
+    vis = np.ones(2100, dtype=np.uint8)
+    vis[:150] = 0
+    vis[700:1000] = 0
+    _prefix_case("bf16", 23, 2100, vis, W.random_tree(31, n_nodes=5, lo=20, hi=200), 4, 2, 128)
+    for n in (2048, 2049):                               # 256 and 272 workgroups
+        _full_parity(W.random_tree(34, n_nodes=1, lo=n, hi=n), W.AttnDims(16, 2, 128, "bf16", 0.5), 6, label="two wave groups, line")
+    t = W.chain_tree([900, 1200])
+    meta = T.tree_build_meta(t.parent, t.seg_len)
+    q, k, v, do = W.attn_inputs(2100, 2100, W.AttnDims(4, 2, 128, "bf16", 0.5), 10)
+    plain = gpu_attention(meta, q, k, v, do)
+    fused = torch.cat([x.reshape(2100, -1) for x in (q, k, v)], dim=1).to("cuda")
+    qv, kv, vv = (x.unflatten(1, (-1, 128)) for x in fused.split([512, 256, 256], dim=1))
+    mask = tuple(dev(x) for x in (meta.kend, meta.ktile_kend_min, meta.ktile_kend_max))
+    o, lse = T.tree_attn_fwd(qv, kv, vv, *mask)
+    dq, dk, dv = T.tree_attn_bwd(qv, kv, vv, *mask, o, dev(do), lse)
+    for x, key in ((o, "o"), (dq, "dq"), (dk, "dk"), (dv, "dv")):
+        assert np.array_equal(f64(x), plain[key]), key
 
 
 @pytest.mark.parametrize("hq,hkv,d", [(2, 2, 64), (6, 2, 128)])
