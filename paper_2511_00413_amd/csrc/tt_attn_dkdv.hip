@@ -84,12 +84,16 @@ constexpr int KV_TARGET_WORK = 768;      // work items (tile chunk x kv head) ai
 constexpr int KV_ITEMS_PER_WG = 2;       // ... and per resident workgroup: with the longest items handed out first two
                                          // per workgroup balance as well as three did in plain order, with 40 % fewer
                                          // partial slots to write and reduce
-// Shortest chunk, in steps.  Small trees have fewer steps than places: there a chunk is what gives every workgroup one
-// item, KV_MIN_CHUNK to KV_SHORT_CHUNK steps, and only what is longer is cut for two per workgroup (an item costs about 10
-// steps' time to start and finish, and its partial slot is written and summed).  Forward + backward at a least chunk of 32 /
-// 16 / 8 / 4: 777 tokens, 32 / 8 heads 129 / 107 / 102 / 124 us, 1024 (chain) 173 / 139 / 132 / 155, 1500 149 / 128 / 152 / 156,
-// 4000, 8 / 8 heads 243 / 226 / 244 / 244.
-constexpr int KV_MIN_CHUNK = 8, KV_SHORT_CHUNK = 16;
+// Chunks of small trees, in steps.  There a chunk is what gives every workgroup one item, KV_MIN_CHUNK to KV_MAX_SHORT steps, and
+// only what is longer is cut for two items per workgroup (an item costs about 10 steps' time to start and finish, and its
+// partial slot is written and summed).  Two corrections to that:
+//   - below KV_MID_CHUNK steps the chunks come out uneven, and if more of them than workgroups are longer than half a chunk, some
+//     workgroups take two: KV_MID_CHUNK it is then;
+//   - if no tile can have more than KV_UNCUT steps, none is cut: the second item and the sum cost more than they save.
+// Forward + backward, us, at a least chunk of 32 / 16 / 8:  200 tokens of 64 / 8 heads, a random tree 103 / 88 / 79;  800 142 / 119 / 137
+// (here 119);  800, 32 / 8 129 / 104 / 96;  2100, 8 / 8 131 / 108 / 98;  600, 8 / 8, at most 10 steps 75 / 75 / 84 (here 75).  Largest
+// short chunk 16 / 32: 3650 tokens of 32 / 8 heads, a random tree 249 / 226;  5000, 16 / 4, a shared prefix with branches 267 / 233.
+constexpr int KV_MIN_CHUNK = 8, KV_MID_CHUNK = 16, KV_MAX_SHORT = 32, KV_UNCUT = 12;
 constexpr int KV_SORT_BELOW = 16;        // items per workgroup below which the items are handed out longest first
 constexpr int PLAN_THREADS = 1024;
 constexpr int KV_EPT = KV_BN / 64;       // summary entries per key tile, at most
@@ -254,12 +258,24 @@ kv_plan_kernel(KvPlan pl, const int32_t* __restrict__ kt_max, int n_q, int n_pre
   const int64_t all = (int64_t)total_steps * hkv;
   const int target = max(1, min(KV_TARGET_WORK, KV_ITEMS_PER_WG * n_workgroups));
   const int64_t one_each = (all + n_workgroups - 1) / n_workgroups;
-  const int chunk = (int)max(min((int64_t)KV_SHORT_CHUNK, max((int64_t)KV_MIN_CHUNK, one_each)), (all + target - 1) / target);
-
-  // ---- pass 2: chunks per tile; cut tiles are numbered first (their item index is also their slot);
-  //      each thread owns consecutive tiles ----
-  const int per_t = (n_tiles + PLAN_THREADS - 1) / PLAN_THREADS;
+  const int64_t longest = (int64_t)G * ((n_q + KV_BM - 1) / KV_BM);       // no tile has more steps than this
+  const int per_t = (n_tiles + PLAN_THREADS - 1) / PLAN_THREADS;          // each thread owns consecutive tiles
   const int tlo = min(t * per_t, n_tiles), thi = min(tlo + per_t, n_tiles);
+  int chunk = (int)min((int64_t)KV_MAX_SHORT, max((int64_t)KV_MIN_CHUNK, one_each));
+  if (longest <= KV_UNCUT) {
+    chunk = KV_UNCUT;
+  } else if (chunk < KV_MID_CHUNK) {
+    int my_long = 0, n_long;
+    for (int i = tlo; i < thi; i++) {
+      const int steps = tile_nq(i) * G;
+      my_long += steps / chunk + (steps % chunk > chunk / 2 ? 1 : 0);
+    }
+    block_exclusive_scan<false>(my_long, scratch, &n_long);
+    if ((int64_t)n_long * hkv > n_workgroups) chunk = KV_MID_CHUNK;
+  }
+  chunk = (int)max((int64_t)chunk, (all + target - 1) / target);
+
+  // ---- pass 2: chunks per tile; cut tiles are numbered first (their item index is also their slot) ----
   int my_split = 0, my_whole = 0, my_split_tiles = 0;
   for (int i = tlo; i < thi; i++) {
     const int steps = tile_nq(i) * G;

@@ -251,6 +251,16 @@ def test_bf16_two_wave_groups_prefix_and_strides():
         assert np.array_equal(f64(x), plain[key]), key
 
 
+# How the dK / dV pass cuts its key tiles (steps are 64-query tiles x query heads of a kv head): at most 12 steps, nothing is cut;
+# 13 .. 16, in chunks of 8; more chunks of 8 to 16 than compute units, hence of 16; chunks of up to 32 and beyond.
+@pytest.mark.parametrize("segs,parent,hq,hkv", [
+    ([700, 68], [-1, 0], 2, 2), ([700, 69], [-1, 0], 2, 2), ([192], [-1], 4, 1), ([193], [-1], 4, 1), ([30, 20, 50, 60], [-1, 0, 0, 1], 64, 8),
+    ([500, 120, 100, 80], [-1, 0, 0, 2], 64, 8), ([900, 300, 100], [-1, 0, 1], 32, 4), ([1500, 600, 400], [-1, 0, 0], 32, 8)])
+def test_bf16_key_tiles_cut_into_chunks(segs, parent, hq, hkv):
+    t = W._mk(parent, segs, [1] * len(segs), "chunks")
+    _full_parity(t, W.AttnDims(hq, hkv, 128, "bf16", 0.5), sum(segs) + hq, label="chunks")
+
+
 @pytest.mark.parametrize("hq,hkv,d", [(2, 2, 64), (6, 2, 128)])
 def test_fp32_matrix_kernels_block_edges(hq, hkv, d):
     """Token counts around the 16-wide blocks and the 128 keys of one round of the waves, nodes that start inside a block,
