@@ -487,12 +487,23 @@ hipError_t launch_bwd(const ConvArgs& a, float* dweight, float* dbias, hipStream
 
 // Tokens per tile of the backward walk: long tiles (each walks K - 1 tokens of look-ahead and writes a row of partial sums)
 // that still make one workgroup for every one of the chip's conv_bwd_wgs * 256 places, 32 to CONV_BWD_TILE tokens; never
-// shorter than the power of two that makes 1024 workgroups of 16-byte lanes, which bounds the partial sums.
+// shorter than the power of two that makes 1024 workgroups of 16-byte lanes, which bounds the partial sums.  In fp32, where
+// a row takes twice the lanes, the longest tile is reached from 16384 tokens x 6144 channels on; from 8 tokens beyond it on
+// the tokens are cut into equal rounds of all places (a second round of more than a few workgroups costs as much as a full one), and
+// from 128 tokens on a tile is a multiple of the 8 tokens that a turn of the loop takes.
 // Whole backward and forward at 16406 x 8192 bf16, K = 4: tiles of 64 tokens 314 us, 128 294, 171 (this rule) 291; 32000 x
-// 8192: 167 tokens 616 us, 256 (this rule) 591; 9000 x 4096 fp32: 32 tokens 206, 71 (this rule) 185.
+// 8192: 167 tokens 616 us, 256 (this rule) 591;  fp32, tiles of a power of two for 1024 workgroups / one round without the two rules
+// / this: 9000 x 4096 196 / 170 / 170, 16406 x 4096 276 / 292 / 273, 16406 x 6144 450 / 474 / 435, 24000 x 6144 663 / 727 / 620, 20000 x 8192
+// 680 / 729 / 660, 16406 x 8192 642 / 542 / 542.
 int conv_bwd_tile(int64_t n_tokens, int channels, bool bf16) {
-  const int64_t places = (int64_t)conv_bwd_wgs(bf16) * 256 * CONV_THREADS, vpr = channels / (bf16 ? Chan<true>::NV : Chan<false>::NV);
-  const int64_t tile = tt::ceil_div(n_tokens, std::max<int64_t>(1, places / vpr));
+  const int64_t vpr = channels / (bf16 ? Chan<true>::NV : Chan<false>::NV);
+  const int64_t tiles = std::max<int64_t>(1, (int64_t)conv_bwd_wgs(bf16) * 256 * CONV_THREADS / vpr);      // of one round
+  int64_t tile = tt::ceil_div(n_tokens, tiles);
+  if (!bf16) {
+    const int64_t rounds = std::max<int64_t>(1, tt::ceil_div(tile, CONV_BWD_TILE + 8));
+    tile = tt::ceil_div(n_tokens, tiles * rounds);
+    if (tile >= 128) tile = tt::ceil_div(tile, 8) * 8;
+  }
   return (int)std::max<int64_t>(pick_tile(n_tokens, channels / (bf16 ? 8 : 4), 32, 256), std::min<int64_t>(tile, CONV_BWD_TILE));
 }
 

@@ -89,6 +89,38 @@ def test_many_tiles_ragged_tail_and_reproducible():
         assert torch.equal(a, b)
 
 
+# Long tiles of the backward walk (the short ones of 32 tokens are what small shapes get): fp32 in one round of workgroups (tiles of
+# 71 tokens), in one round of the longest tiles and beyond it in two (136), bf16 tiles of 94 and 188 tokens (no multiple of a batch) and of
+# 256, every kernel size.
+@pytest.mark.parametrize("n,c,k,dtype", [(9001, 4096, 3, "fp32"), (9001, 4096, 2, "fp32"), (17003, 4096, 4, "fp32"), (16800, 8192, 4, "fp32"),
+                                         (17003, 8192, 3, "fp32"), (9001, 8192, 3, "bf16"), (18003, 8192, 4, "bf16"), (26001, 8192, 2, "bf16")])
+def test_long_tiles(n, c, k, dtype):
+    """The channels are independent: eight of them (the first and the last lanes of a row) against the oracle."""
+    t = W.random_tree(990 + k, n_nodes=120, lo=1, hi=n // 50)
+    seg = np.maximum(1, np.floor(np.asarray(t.seg_len) * (n / t.n_tokens))).astype(np.int32)
+    seg[-1] += n - seg.sum()
+    pred = M.dfs_meta(t.parent, seg)["tok_pred"]
+    g = torch.Generator(device="cuda").manual_seed(n + c)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    x, dy = (torch.randn((n, c), generator=g, device="cuda").to(tdt) for _ in range(2))
+    w, b = torch.randn((c, k), generator=g, device="cuda") * 0.5, torch.randn(c, generator=g, device="cuda") * 0.1
+    plan = T.tree_conv_plan(pred, k)
+    print(f"[case] tree conv n={n} C={c} K={k} {dtype}, long tiles: {len(plan.fix_tok)} fix-up tokens", flush=True)
+    pred_d = torch.from_numpy(pred).cuda()
+    y = T.tree_conv_fwd(x, w, b, pred_d)
+    dx, dw, db = T.tree_conv_bwd(x, w, b, pred_d, dy, plan)
+    some = [0, 1, 2, 3, c - 4, c - 3, c - 2, c - 1]
+    xs, dys, ws, bs = x[:, some].cpu(), dy[:, some].cpu(), w[some].cpu(), b[some].cpu()
+    want_y, _ = S.tree_conv(xs, ws, bs, pred, "silu")
+    want_dx, want_dw, want_db = S.tree_conv_bwd(xs, ws, bs, pred, dys, "silu")
+    tol = 4e-3 if dtype == "bf16" else 2e-6           # bf16: one rounding of the output (2^-9 relative)
+    got_dx = dx[:, some].float().cpu().numpy()
+    assert rel_l2(y[:, some].float().cpu().numpy(), want_y) <= tol and rel_l2(got_dx, want_dx) <= tol
+    assert np.abs(got_dx - want_dx).max() <= (3e-2 if dtype == "bf16" else 1e-4) * np.abs(want_dx).max()
+    # fp32 sums of n products of independent sign: relative error well below sqrt(n) 2^-24 of the terms' norm
+    assert rel_l2(dw[some].cpu().numpy(), want_dw) <= 2e-5 and rel_l2(db[some].cpu().numpy(), want_db) <= 2e-5
+
+
 def test_strided_rows_and_chain():
     """x and dy as column slices of wider buffers; a plain chain equals a library causal conv1d."""
     n, c, k = 700, 64, 4
