@@ -487,7 +487,8 @@ def _stream_ptr(stream):
     if stream is not None:
         return stream.cuda_stream
     torch = _torch()
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)         # a private name: not every version has to have it
+    return torch.cuda.current_stream().cuda_stream if raw is None else raw(torch.cuda.current_device())
 
 
 def _desc(q, k, v, n_prefix: int, scale, reference_kernels: bool) -> _AttnDesc:

@@ -158,3 +158,13 @@ def test_gdn_backward_workspace_parts():
         want = per * n_chunks * hv + (2 * n * hv * 128 * 4 if split else 0)
         got = lib.tt_tree_gdn_bwd_workspace(n, n_chunks, 0, 0, hk, hv)
         assert want <= got <= want + slack, (n_chunks, hk, hv, got - want)
+
+
+def test_current_stream_without_the_raw_stream_call(monkeypatch):
+    """The stream of a call comes from torch's raw-stream call where that exists and from the Stream object elsewhere."""
+    from types import SimpleNamespace as NS
+    cuda = NS(current_device=lambda: 3, current_stream=lambda: NS(cuda_stream=77))
+    monkeypatch.setattr(T.binding, "_TORCH", NS(_C=NS(), cuda=cuda))
+    assert T.binding._stream_ptr(None) == 77
+    monkeypatch.setattr(T.binding, "_TORCH", NS(_C=NS(_cuda_getCurrentRawStream=lambda dev: 100 + dev), cuda=cuda))
+    assert T.binding._stream_ptr(None) == 103 and T.binding._stream_ptr(NS(cuda_stream=5)) == 5
