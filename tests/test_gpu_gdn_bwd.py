@@ -166,3 +166,46 @@ def test_value_heads_of_a_workgroup(n_nodes, hk, hv):
         outs.append(T.tree_gdn_bwd(*ins, plan, workspace=ws))
     torch.cuda.synchronize()
     assert all(torch.equal(a, b) for a, b in zip(*outs))
+
+
+@pytest.mark.parametrize("rep", [3, 4])
+def test_value_heads_of_a_workgroup_full_chunks(rep):
+    """The same form with full chunks and chunks of 1, 36 and 63 tokens, three and four value heads per key head: some key
+    heads against the oracle; with a state that enters and one that is handed on, against those heads alone (a call of so
+    few pairs takes one value head per workgroup), and over passes of one key head bit for bit."""
+    parent, seg = [-1, 0, 0, 2, 2, 4], [63, 64, 65, 129, 1, 100]
+    hk, hv, n = 40, 40 * rep, sum(seg)
+    q, k, v, g, beta, d_o = _inputs(n, hk, hv, 60 + rep)
+    heads = [0, 17, 39]
+    vheads = [h * rep + r for h in heads for r in range(rep)]
+    plan = T.tree_gdn_plan(parent, seg).to_device()
+    assert plan.n_chunks * hk >= 384 and plan.n_chunks * len(heads) < 384
+    print(f"[case] gdn bwd n={n} hk={hk} hv={hv}: {plan.n_chunks} chunks", flush=True)
+    part = lambda got: [x.float().cpu().numpy()[:, heads if i < 2 else vheads] for i, x in enumerate(got)]      # noqa: E731
+    got = part(T.tree_gdn_bwd(*(x.cuda() for x in (q, k, v, g, beta, d_o)), plan))
+    sub = [x[:, heads] for x in (q, k)] + [x[:, vheads] for x in (v, g, beta, d_o)]
+    want = S.gdn_tree_bwd(*(x.float().numpy() for x in sub[:5]), M.dfs_meta(parent, seg)["tok_pred"], sub[5].float().numpy())
+    for name, a, b in zip(("dq", "dk", "dv", "dg", "dbeta"), got, want):
+        assert rel_l2(a, b) <= 8e-3, (name, rel_l2(a, b))
+    # with the gateway in both directions
+    plan = T.tree_gdn_plan(parent, seg, capture_nodes=[3]).to_device()
+    gen = torch.Generator().manual_seed(rep)
+    init = torch.randn((hv, 128, 128), generator=gen) * 0.1
+    d_state = torch.randn((1, hv, 128, 128), generator=gen) * 0.1
+
+    def run(ins, init, d_state, smallest=False):
+        hk, hv = ins[0].shape[1], ins[2].shape[1]
+        ws = torch.empty(T.tree_gdn_bwd_workspace(n, hk, hv, plan, smallest=smallest), dtype=torch.uint8, device="cuda")
+        return T.tree_gdn_bwd(*(x.contiguous().cuda() for x in ins), plan, initial_state=init.cuda(), d_state_out=d_state.contiguous().cuda(),
+                              want_d_initial_state=True, workspace=ws)
+
+    whole = run((q, k, v, g, beta, d_o), init, d_state)
+    passes = run((q, k, v, g, beta, d_o), init, d_state, smallest=True)
+    alone = run(sub, init[vheads], d_state[:, vheads])
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(whole, passes))
+    for i, (a, b) in enumerate(zip(whole, alone)):
+        a = a[vheads] if i == 5 else a[:, heads if i < 2 else vheads]
+        # the same products; dq and dk summed over the value heads before or after they leave the chip, then rounded to bf16 once
+        e = rel_l2(a.float().cpu().numpy(), b.float().cpu().numpy())
+        assert e <= (2e-3 if a.dtype == torch.bfloat16 else 1e-5), (i, e)
