@@ -141,7 +141,12 @@ extern "C" tt_status tt_tree_attn_bwd(const tt_attn_desc* desc, const void* q, c
   c.a.workspace_bytes = workspace_bytes - delta_bytes(desc);
   hipStream_t st = (hipStream_t)stream;
   if (c.use_mfma) return hip_result(tt::mfma_attn_bwd(c.a, st), "tree_attn_bwd");
-  if (c.use_f32) return hip_result(tt::f32_attn_bwd(c.a, st), "tree_attn_bwd (fp32)");
+  // The fp32 matrix kernels read q, k, v, o and d_o until the end of their one launch.  Gradients that take the place of an
+  // input (dq of o, dk of k, dv of v) need the row kernels, which are through with it before they write.
+  bool in_place = false;
+  for (const void* out : {(const void*)dq, (const void*)dk_own, (const void*)dv_own})
+    for (const void* in : {q, k_own, v_own, o, d_o}) in_place |= out == in;
+  if (c.use_f32 && !in_place) return hip_result(tt::f32_attn_bwd(c.a, st), "tree_attn_bwd (fp32)");
   return hip_result(tt::ref_attn_bwd(c.a, c.bf16, st), "tree_attn_bwd (reference kernels)");
 }
 

@@ -328,3 +328,20 @@ def test_fp32_row_without_a_finite_score(d):
     got, ref = (gpu_attention(meta, q, k, v, do, reference_kernels=r) for r in (False, True))
     assert np.isnan(ref["lse"][1, 0]) and np.isfinite(ref["lse"][1, 1:]).all()
     _same_where_finite(got, ref)
+
+
+@pytest.mark.parametrize("dtype,d", [("fp32", 64), ("fp32", 128), ("bf16", 128)])
+def test_gradients_in_the_place_of_inputs(dtype, d):
+    """dq over o, dk over k and dv over v: every kernel is through with a row before it is overwritten."""
+    from gpu_util import dev, f64
+    t = W.random_tree(95, n_nodes=12, lo=20, hi=200)
+    meta = T.tree_build_meta(t.parent, t.seg_len)
+    n = meta.n_tokens
+    q, k, v, do = (dev(x) for x in W.attn_inputs(n, n, W.AttnDims(4, 2, d, dtype, 1.0), 12))
+    mask = tuple(dev(x) for x in (meta.kend, meta.ktile_kend_min, meta.ktile_kend_max))
+    o, lse = T.tree_attn_fwd(q, k, v, *mask)
+    want = [f64(x) for x in T.tree_attn_bwd(q, k, v, *mask, o, do, lse)]
+    got = [f64(x) for x in T.tree_attn_bwd(q, k, v, *mask, o, do, lse, dq=o, dk=k, dv=v)]
+    for a, b in zip(got, want):
+        # fp32: other kernels, sums in another order (1e-5 of the largest entry); bf16: the same bits
+        assert np.abs(a - b).max() <= (1e-5 * np.abs(b).max() if dtype == "fp32" else 0)
