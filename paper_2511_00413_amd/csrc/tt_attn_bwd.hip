@@ -257,7 +257,8 @@ tree_attn_dq_kernel(AttnArgs a, int n_qtiles) {
 #define TT_DQ_STEP(FULLFLAG)                                                                            \
   {                                                                                                     \
     int cls_next = KT_FULL;                                                                             \
-    const int u_next = next_own(cls_next);                                                              \
+    if constexpr (NG == 2) other = it.next(cls_next);                                                   \
+    const int u_next = it.next(cls_next);                                                               \
     if (u_next >= 0) q_issue_tile(ctx, sm, buf ^ 1, u_next, w, lane);                                   \
     dq_tile<FULLFLAG>(ra, ta, ka, qf, gf, dq_acc, neg_lse2, neg_delta, tile_j0(u_cur), tile_j_last(u_cur), gi, hf, cls_cur); \
     dma_wait_all();                                                                                     \
@@ -276,16 +277,13 @@ tree_attn_dq_kernel(AttnArgs a, int n_qtiles) {
   // as in the forward kernel: tile 0 is nearly always the first tile delivered, so its copy is started before
   // the classification and runs beside it (a wrong guess costs one wasted tile copy)
   if (grp == 0) q_issue_tile(ctx, sm, buf, 0, w, lane);
-  // the next tile of this group; `other`: the tile of the other group passed over last (>= 0 with nothing behind it means
-  // that group 0 has one more tile than group 1)
+  // `other`: the tile of the other group passed over last (>= 0 with nothing behind it means that group 0 has one more
+  // tile than group 1)
   [[maybe_unused]] int other = -1;
-  auto next_own = [&](int& cls) {
-    if constexpr (NG == 2) other = it.next(cls);
-    return it.next(cls);
-  };
   it.fill(&sm.masks, a.kt_max, a.kt_min, 0, u_end, gi_first, gi_last, npt, P, N, w, NTHREADS / 64);
   int cls_cur = KT_FULL;
-  int u_cur = grp == 0 ? it.next(cls_cur) : next_own(cls_cur);
+  if (NG == 2 && grp == 1) other = it.next(cls_cur);
+  int u_cur = it.next(cls_cur);
   if (grp == 0 ? u_cur > 0 : u_cur >= 0) {
     dma_wait_all();
     q_issue_tile(ctx, sm, buf, u_cur, w, lane);

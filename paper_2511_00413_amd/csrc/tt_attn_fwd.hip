@@ -268,7 +268,8 @@ tree_attn_fwd_kernel(AttnArgs a, int n_qtiles) {
 #define TT_FWD_STEP(FULLFLAG)                                                                          \
   {                                                                                                    \
     int cls_next = KT_FULL;                                                                            \
-    const int u_next = next_own(cls_next);                                                             \
+    if constexpr (NG == 2) other = it.next(cls_next);                                                  \
+    const int u_next = it.next(cls_next);                                                              \
     if (u_next >= 0) issue_tile(ctx, sm, buf ^ 1, u_next, w, lane);                                    \
     process_tile<FULLFLAG>(ra, ta, ka, qf, o_acc, m_run, l_run, neg_m, tile_j0(u_cur), tile_j_last(u_cur), gi, hf, cls_cur); \
     dma_wait_all();                                                                                    \
@@ -289,16 +290,14 @@ tree_attn_fwd_kernel(AttnArgs a, int n_qtiles) {
   // beside the classification's instead of behind it (and beside the Q fragments').  A wrong guess (several roots,
   // a prefix whose first tile is hidden) costs one wasted tile copy: the right tile is fetched over it.
   if (grp == 0) issue_tile(ctx, sm, buf, 0, w, lane);
-  // the next tile of this group: of two groups each passes over the other's.  `other` is the tile passed over last: >= 0
-  // with nothing behind it means that group 0 has one more tile than group 1
+  // Of two groups each passes over the other's tiles.  `other` is the tile passed over last: >= 0 with nothing behind it
+  // means that group 0 has one more tile than group 1.  (Written out: as a function for both forms the registers of the
+  // one-group loop came out in another order, which measured 1 % slower.)
   [[maybe_unused]] int other = -1;
-  auto next_own = [&](int& cls) {
-    if constexpr (NG == 2) other = it.next(cls);
-    return it.next(cls);
-  };
   it.fill(&sm.masks, a.kt_max, a.kt_min, 0, u_end, gi_first, gi_last, npt, P, N, w, NTHREADS / 64);
   int cls_cur = KT_FULL;
-  int u_cur = grp == 0 ? it.next(cls_cur) : next_own(cls_cur);
+  if (NG == 2 && grp == 1) other = it.next(cls_cur);
+  int u_cur = it.next(cls_cur);
   if (grp == 0 ? u_cur > 0 : u_cur >= 0) {
     dma_wait_all();                        // this wave's rows of the guessed tile have landed; they are overwritten
     issue_tile(ctx, sm, buf, u_cur, w, lane);
