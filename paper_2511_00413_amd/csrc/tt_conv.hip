@@ -7,6 +7,7 @@
 // last token) and at the start of a tile.
 #include <hip/hip_runtime.h>
 #include <algorithm>
+#include <type_traits>
 #include "tt_internal.h"
 #include "tt_kernels.h"
 
@@ -339,11 +340,13 @@ __device__ __forceinline__ void conv_fix_block(const ConvArgs& a, int64_t block)
   // of up to K tokens of the run) is requested beside it, and the window moves along the run instead of being looked
   // up again for every token.  (The finish launch at 16406 x 8192: 31 us, with the reduce below in 16 segments 23, with
   // this 11; it is the larger part of a small call: 700 x 2048 61 -> 39 us.)
-  auto add_run = [&](int first, int r) {
-    int pr[K];
-    typename Chan<BF16>::Raw xq[K], dyq[K];
+  // (N tokens at most: K from s itself, K - 1 from a listed successor, which is at least one place away.)
+  auto add_run = [&](auto n_tok, int first, int r) {
+    constexpr int N = decltype(n_tok)::value;
+    int pr[N];
+    typename Chan<BF16>::Raw xq[N], dyq[N];
 #pragma unroll
-    for (int u = 0; u < K; u++) {
+    for (int u = 0; u < N; u++) {
       const int t = min(first + u, a.n_tokens - 1);
       pr[u] = a.tok_pred[t];
       xq[u] = load_raw<BF16>(a.x, t, a.x_stride, cv);
@@ -360,7 +363,7 @@ __device__ __forceinline__ void conv_fix_block(const ConvArgs& a, int64_t block)
     }
     bool in_run = true;
 #pragma unroll
-    for (int u = 0; u < K; u++) {
+    for (int u = 0; u < N; u++) {
       in_run = in_run && r + u < K && (u == 0 || (first + u < a.n_tokens && pr[u] == first + u - 1));
       if (u > 0) {
 #pragma unroll
@@ -388,8 +391,8 @@ __device__ __forceinline__ void conv_fix_block(const ConvArgs& a, int64_t block)
       }
     }
   };
-  add_run(s, 0);
-  for (int e = a.fix_off[f]; e < a.fix_off[f + 1]; e++) add_run(a.fix_t[e], a.fix_r[e]);
+  add_run(std::integral_constant<int, K>{}, s, 0);
+  for (int e = a.fix_off[f]; e < a.fix_off[f + 1]; e++) add_run(std::integral_constant<int, K - 1>{}, a.fix_t[e], a.fix_r[e]);
   store_row<BF16>(a.y, s, a.y_stride, cv, dx);
 }
 
