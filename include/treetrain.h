@@ -467,7 +467,7 @@ tt_status tt_tree_conv_bwd(int64_t n_tokens, int32_t channels, int32_t kernel_si
  * library runs on holds one copy from the first use of the library on it until the process ends).
  * The call allocates and frees nothing.
  *   Limit: tt_tree_conv_bwd_workspace(n_tokens, channels, kernel_size, dtype) must not exceed
- *   TT_CONV_BWD_STATIC_SCRATCH_BYTES (e.g. 16 406 tokens x 8192 channels, K = 4, bf16 needs 42 MB);
+ *   TT_CONV_BWD_STATIC_SCRATCH_BYTES (e.g. 16 406 tokens x 8192 channels, K = 4, bf16 needs 15.7 MB);
  *   a larger shape is refused with TT_ERR_WORKSPACE before anything is launched.
  *   The scratch needs no clearing: every call overwrites the part it reads (one row per token tile).
  *   All calls on one GPU share that GPU's array: calls that may overlap in time on one GPU (different
@@ -586,9 +586,9 @@ tt_status tt_tree_gdn_fwd(int64_t n_tokens, int32_t hk, int32_t hv, int32_t dk, 
  * forward (state and state gradient stay fp32); the triangular solves and all element-wise work
  * are fp32.
  * Workspace, 16-byte aligned: tt_tree_gdn_bwd_workspace bytes let all heads run in one pass (about
- * 210 KB per chunk and value head, plus two fp32 [n_tokens][hv][128] arrays, 2 x n_slots saved
- * states per head and, with a schedule, one state gradient per segment and head; n_segments = 0
- * when the call gets no schedule).  The heads are independent up to the sum over the value heads
+ * 210 KB per chunk and value head, 2 x n_slots saved states per head and, with a schedule, one state
+ * gradient per segment and head; n_segments = 0 when the call gets no schedule; plus two fp32
+ * [n_tokens][hv][128] arrays if hv > hk and n_chunks * hk < 384).  The heads are independent up to the sum over the value heads
  * of a key head, so any size from tt_tree_gdn_bwd_workspace_min (one key head with its value heads
  * per pass) upwards is accepted: the call then runs in passes of as many key heads as fit -- less
  * memory for more launches and walks that fill less of the chip; results do not depend on it.

@@ -11,7 +11,7 @@
 // steps a wave instead of one wave per row with serial dot products, and the backward is one launch (dK / dV workgroups
 // first, longest ranges first; they form the row terms <dO, O> themselves).  At large sizes the fp32 matrix rate bounds
 // it.  Operands go from memory to registers: no two waves of a workgroup share a row.
-// Forward + backward, worked tree of 240 tokens, 4 heads of 64: 34 us (the row kernels: 198 us);  agentic tree of
+// Forward + backward, worked tree of 240 tokens, 4 heads of 64: 27 us (the row kernels: 198 us);  agentic tree of
 // 2048 tokens, 4 / 2 heads of 128: 0.28 ms (5.2 ms);  8192 tokens, 32 / 8 heads: 6.9 ms, 37 TFLOP/s (196 ms, 1.3).
 //
 // Layouts of the instruction (lane l: l16 = l % 16, g = l / 16): A [16 x 4] row l16, k = g;  B [4 x 16] k = g, column

@@ -375,13 +375,15 @@ tree_attn_fwd_kernel(AttnArgs a, int n_qtiles) {
 }  // namespace
 
 // Two groups of waves per workgroup where there is no second workgroup for a compute unit to run beside the first, one
-// chunk of candidate tiles, and at least `min_tiles` of them: a workgroup whose queries see few tiles pays up to 1 us (forward) or
-// 3 us (dQ) for the second group's start and the exchange at the end, and how many it sees is known on the device alone, so the
-// lines lie where no tree shape loses.  Graph replays, us, one / two groups, shared prefix with short branches / random tree /
-// chain:  forward (from 24 tiles on) 128 tokens of 32 heads 9.6 / 10.5 in all shapes, 256 of 8 11.1 / 12.4, 12.5 / 12.8, 12.5 / 12.5;  1024
-// of 8 13.9 / 15.0, 16.0 / 15.2, 29.0 / 24.1;  1500 of 8 16.7 / 16.6, 16.1 / 15.3, 34.2 / 28.3;  4000 of 8 24.6 / 22.7, 24.4 / 21.2, 65.4 / 53.2;
-// dQ kernel (from 32 tiles on) 1024 of 8 18.9 / 21.4, 21.1 / 21.5, 36.8 / 32.4;  1500 22.5 / 23.1, 21.5 / 21.9, 43.1 / 36.4;  2048 24.1 / 23.9, 23.5 /
-// 23.8, 55.2 / 46.4;  4000 32.2 / 31.1, 32.3 / 29.5, 81.9 / 67.5.
+// chunk of candidate tiles, and at least `min_tiles` of them: a workgroup whose queries see few tiles pays up to 1.3 us
+// (forward) or 3 us (dQ) for the second group's start and the exchange at the end, and how many it sees is known on the
+// device alone, so the lines lie where a shared prefix with short branches no longer loses (a forest of roots of one or two
+// tiles each still pays 0.2 to 0.6 of 10 to 15 us).
+// us, one / two groups, shared prefix with branches; random tree; chain.  Forward (from 24 tiles on), graph replays: 128 tokens
+// of 32 heads 9.6 / 10.5 in all shapes;  256 of 8 11.1 / 12.4; 12.5 / 12.8; 12.5 / 12.5;  1024 of 8 13.9 / 15.0; 16.0 / 15.2; 29.0 / 24.1;
+// 1500 of 8 16.7 / 16.6; 16.1 / 15.3; 34.2 / 28.3;  4000 of 8 24.6 / 22.7; 24.4 / 21.2; 65.4 / 53.2.  dQ kernel (from 32 tiles on), between
+// events: 1024 of 8 18.9 / 21.4; 21.1 / 21.5; 36.8 / 32.4;  1500 22.5 / 23.1; 21.5 / 21.9; 43.1 / 36.4;  2048 24.1 / 23.9; 23.5 / 23.8; 55.2 / 46.4;
+// 4000 32.2 / 31.1; 32.3 / 29.5; 81.9 / 67.5.
 bool attn_two_groups(const AttnArgs& a, int64_t blocks, int min_tiles) {
   int dev = 0, n_cu = 256;
   if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);

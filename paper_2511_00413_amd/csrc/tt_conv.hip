@@ -1,7 +1,7 @@
 // Tree-correct depthwise causal convolution (Section "Implementation", paragraph "SSM Layers (GDN)",
 // item (ii); Appendix "Tree-Correct Causal Convolution"): every token's window holds the K-1 tokens
 // that precede it on its own root-to-token sequence, found through tok_pred, not the K-1 tokens that
-// precede it in DFS order.  HBM-bound: one lane owns one 16-byte channel vector and walks a tile of
+// precede it in DFS order.  HBM-bound: one lane owns four channels and walks a tile of
 // consecutive tokens with the window in registers; the window is rebuilt from the predecessor chain
 // only where the sequence jumps (first token of a node that does not directly follow its parent's
 // last token) and at the start of a tile.
@@ -21,7 +21,7 @@ constexpr int conv_bwd_wgs(bool bf16) { return bf16 ? 3 : 2; }      // workgroup
 // Channels per lane: four of either type, so 8 bytes of bf16 or 16 of fp32 per access.  The walks are bound by HBM and the
 // arithmetic together (sigmoid, K taps twice over and the weight sums per element), and what hides one under the
 // other is waves: with eight bf16 channels per lane the forward took 133 registers and the backward 247 (3 and 2 waves per
-// SIMD), with four 90 and 142 (5 and 3).  16406 tokens x 8192 channels, K = 4: forward 106 -> 93 us (5.8 TB/s), backward walk
+// SIMD), with four 90 and 142 (5 and 3).  16406 tokens x 8192 channels, K = 4: forward 106 -> 97 us (5.5 TB/s), backward walk
 // 181 -> 170 us (4.7 TB/s).
 typedef unsigned int u32x4c __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2c __attribute__((ext_vector_type(2)));

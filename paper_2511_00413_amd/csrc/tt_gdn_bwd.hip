@@ -68,9 +68,11 @@ __device__ __forceinline__ int tile_row(int r, int hf) { return (r >> 2) * 8 + 4
 //   4. K K^T and Q K^T again (K and Q stay in LDS for all heads; cheaper than 32 KB of A0 and P per head out and in):
 //      row and column sums of dP o P + dA o A in registers, dP scale D and dA beta D as bf16 to LDS
 //   5. dq += (dP scale D) K;  dk += (dP scale D)^T Q + (dA beta D) K + (dA beta D)^T K + beta eg dKb
-// LDS 80 KB: two workgroups per compute unit, one's loads beside the other's products.  16406 tokens, 16 / 32 heads: 0.49
-// ms at 2.3 GB (4.7 TB/s; a large copy reaches 5.1).  With one value head per workgroup, fp32 dq / dk through memory,
-// A0 and P from memory and S0, dS1, dO, Vn read once per product it was 0.86 ms at 4.9 GB and 0.12 ms for the sum.
+// LDS 80 KB: two workgroups per compute unit, one's loads beside the other's products.  16406 tokens, 16 / 32 heads: 0.50
+// ms at 2.3 GB (4.6 TB/s; a large copy reaches 4.8).  The loop over the heads spills 24 registers (76 bytes per lane and
+// head out and in again): 0.18 of the 0.46 GB that the kernel writes at that size, 8 % of its traffic.  With one value head
+// per workgroup, fp32 dq / dk through memory, A0 and P from memory and S0, dS1, dO, Vn read once per product it was 0.86 ms
+// at 4.9 GB and 0.12 ms for the sum.
 // Register r of a wave's tile (row block t, column block w) of a 64 x 128 result: row 32 t + tile_row(r), column
 // 32 w + lane % 32; of a 64 x 64 result: row block w & 1, column block w >> 1.
 constexpr int PG = GD + 8;                               // LDS pitches (elements): rows 16-byte aligned, 8 elements of
