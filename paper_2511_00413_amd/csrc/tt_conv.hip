@@ -16,12 +16,13 @@ namespace {
 
 constexpr int CONV_THREADS = 256;
 constexpr int CONV_BWD_TILE = 256;       // (512 measured the same)
+constexpr int CONV_SUM_RUN = 48;         // tokens; a multiple of two batches of every kernel size
 constexpr int conv_bwd_wgs(bool bf16) { return bf16 ? 3 : 2; }      // workgroups of the backward walk per compute unit (registers)
 
 // Channels per lane: four of either type, so 8 bytes of bf16 or 16 of fp32 per access.  The walks are bound by HBM and the
 // arithmetic together (sigmoid, K taps twice over and the weight sums per element), and what hides one under the
 // other is waves: with eight bf16 channels per lane the forward took 133 registers and the backward 247 (3 and 2 waves per
-// SIMD), with four 90 and 142 (5 and 3).  16406 tokens x 8192 channels, K = 4: forward 106 -> 97 us (5.5 TB/s), backward walk
+// SIMD), with four 90 and 162 (5 and 3).  16406 tokens x 8192 channels, K = 4: forward 106 -> 97 us (5.5 TB/s), backward walk
 // 181 -> 170 us (4.7 TB/s).
 typedef unsigned int u32x4c __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2c __attribute__((ext_vector_type(2)));
@@ -227,13 +228,25 @@ __global__ __launch_bounds__(CONV_THREADS, conv_bwd_wgs(BF16)) void tree_conv_bw
   // predecessor" flags
   float xr[K][NV], gq[K][NV];
   bool lk[K];
-  float dw[K][NV], db[NV];
+  // dweight, dbias: the running sums of at most CONV_SUM_RUN tokens, and the sum of the runs that are complete (a tile is longer
+  // than a single fp32 chain of additions should be: 2.6e-7 from the exact bf16 dweight at 16406 x 8192, K = 4, with 256 tokens
+  // in a chain, 1.7e-7 with these runs, at the same time: 283 and 277 us for forward and backward)
+  float dw[K][NV], db[NV], dw_runs[K][NV], db_runs[NV];
 #pragma unroll
   for (int i = 0; i < NV; i++) {
-    db[i] = 0.f;
+    db[i] = db_runs[i] = 0.f;
 #pragma unroll
-    for (int j = 0; j < K; j++) { dw[j][i] = 0.f; gq[j][i] = 0.f; xr[j][i] = 0.f; }
+    for (int j = 0; j < K; j++) { dw[j][i] = dw_runs[j][i] = 0.f; gq[j][i] = 0.f; xr[j][i] = 0.f; }
   }
+  auto end_run = [&]() {
+#pragma unroll
+    for (int i = 0; i < NV; i++) {
+      db_runs[i] += db[i];
+      db[i] = 0.f;
+#pragma unroll
+      for (int j = 0; j < K; j++) { dw_runs[j][i] += dw[j][i]; dw[j][i] = 0.f; }
+    }
+  };
 #pragma unroll
   for (int j = 0; j < K; j++) lk[j] = false;
   const int t0 = (int)tile * a.tok_tile;
@@ -303,19 +316,26 @@ __global__ __launch_bounds__(CONV_THREADS, conv_bwd_wgs(BF16)) void tree_conv_bw
   };
   Batch ba, bb;
   load_batch(t0, ba);
+  static_assert(CONV_SUM_RUN % (2 * U) == 0);
+  int turns = 0;
   for (int tb = t0; tb < t_end; tb += 2 * U) {
     load_batch(tb + U, bb);
     work_batch(tb, ba);
     load_batch(tb + 2 * U, ba);
     work_batch(tb + U, bb);
+    if (++turns == CONV_SUM_RUN / (2 * U)) {
+      turns = 0;
+      end_run();
+    }
   }
+  end_run();
   float* part = a.partial + (int64_t)tile * (K + 1) * a.channels + cv * NV;
 #pragma unroll
   for (int j = 0; j < K; j++)
 #pragma unroll
-    for (int i = 0; i < NV; i++) part[(int64_t)j * a.channels + i] = dw[j][i];
+    for (int i = 0; i < NV; i++) part[(int64_t)j * a.channels + i] = dw_runs[j][i];
 #pragma unroll
-  for (int i = 0; i < NV; i++) part[(int64_t)K * a.channels + i] = db[i];
+  for (int i = 0; i < NV; i++) part[(int64_t)K * a.channels + i] = db_runs[i];
 }
 
 // Backward, fix-up: dx of the tokens that have a successor outside the "directly follows" chain.

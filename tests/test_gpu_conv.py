@@ -117,8 +117,10 @@ def test_long_tiles(n, c, k, dtype):
     got_dx = dx[:, some].float().cpu().numpy()
     assert rel_l2(y[:, some].float().cpu().numpy(), want_y) <= tol and rel_l2(got_dx, want_dx) <= tol
     assert np.abs(got_dx - want_dx).max() <= (3e-2 if dtype == "bf16" else 1e-4) * np.abs(want_dx).max()
-    # fp32 sums of n products of independent sign: relative error well below sqrt(n) 2^-24 of the terms' norm
-    assert rel_l2(dw[some].cpu().numpy(), want_dw) <= 2e-5 and rel_l2(db[some].cpu().numpy(), want_db) <= 2e-5
+    # fp32 sums: 48 tokens to a chain of additions (one rounding of 2^-25 sqrt(k) of the terms' norm at its k-th, about 1.2e-7 of
+    # the sum), then a few sums of such chains; one chain per tile of 256 tokens comes to 3e-7
+    errs = rel_l2(dw[some].cpu().numpy(), want_dw), rel_l2(db[some].cpu().numpy(), want_db)
+    assert errs[0] <= 2.4e-7 and errs[1] <= 2.8e-7
 
 
 def test_strided_rows_and_chain():
