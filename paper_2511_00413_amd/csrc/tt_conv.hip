@@ -16,7 +16,7 @@ namespace {
 
 constexpr int CONV_THREADS = 256;
 constexpr int CONV_BWD_TILE = 256;       // (512 measured the same)
-constexpr int CONV_SUM_RUN = 48;         // tokens; a multiple of two batches of every kernel size
+constexpr int CONV_SUM_RUN = 24;         // tokens; a multiple of two batches of every kernel size (48 and 96 take the same time)
 constexpr int conv_bwd_wgs(bool bf16) { return bf16 ? 3 : 2; }      // workgroups of the backward walk per compute unit (registers)
 
 // Channels per lane: four of either type, so 8 bytes of bf16 or 16 of fp32 per access.  The walks are bound by HBM and the
@@ -228,9 +228,10 @@ __global__ __launch_bounds__(CONV_THREADS, conv_bwd_wgs(BF16)) void tree_conv_bw
   // predecessor" flags
   float xr[K][NV], gq[K][NV];
   bool lk[K];
-  // dweight, dbias: the running sums of at most CONV_SUM_RUN tokens, and the sum of the runs that are complete (a tile is longer
-  // than a single fp32 chain of additions should be: 2.6e-7 from the exact bf16 dweight at 16406 x 8192, K = 4, with 256 tokens
-  // in a chain, 1.7e-7 with these runs, at the same time: 283 and 277 us for forward and backward)
+  // dweight, dbias: the running sums of at most CONV_SUM_RUN tokens, and the sum of the runs that are complete.  A tile is longer
+  // than a single fp32 chain of additions should be: dweight of 16406 x 8192, K = 4, is 2.6e-7 from the exact one (bf16; fp32
+  // 3.1e-7) with one chain per tile, 1.7e-7 with runs of 48, 1.5e-7 with 24 (both types), all three at 280 us (bf16, both
+  // directions); at 300 - 2500 tokens 1.35 - 1.49e-7 with 48 and 1.19 - 1.39e-7 with 24
   float dw[K][NV], db[NV], dw_runs[K][NV], db_runs[NV];
 #pragma unroll
   for (int i = 0; i < NV; i++) {
