@@ -1,28 +1,12 @@
-// Gated delta rule with tree state routing, forward (Section "Implementation", paragraph "SSM Layers
-// (GDN)" (i); Appendix "Tree-Aware SSM State Routing"): the recurrent state at a node's first token
-// is the end state of its parent node, not of the previous node in DFS order.
+// Gated delta rule with tree state routing: per-chunk operands and the two walks of the backward (Section "Implementation",
+// paragraph "SSM Layers (GDN)" (i); Appendix "Tree-Aware SSM State Routing").  The forward is in tt_gdn_fwd.hip.
 //
 // Chunked form, 64 tokens per chunk, chunks never cross a node boundary.  With gamma_i the running
 // sum of the log-decays inside a chunk, beta the write strengths and S0 the state entering the chunk:
 //     A  = strictly-lower( beta_i (k_i . k_j) exp(gamma_i - gamma_j) )
 //     U  = (I + A)^-1 (beta * V)                 W = (I + A)^-1 (beta * exp(gamma) * K)
 //     Vn = U - W S0
-//     O  = scale (Q * exp(gamma)) S0 + scale tril( (Q K^T) * exp(gamma_i - gamma_j) ) Vn
 //     S1 = exp(gamma_last) S0 + (K * exp(gamma_last - gamma))^T Vn
-// which is the token recurrence  S <- e^g S + beta k (v - (e^g S)^T k)^T,  o = scale S^T q  written
-// per chunk.  Two kernels:
-//   gdn_prepare_kernel  (chunk, value head): everything that does not depend on S0 -- K K^T and
-//       Q K^T on MFMA, the inverse T = (I + A)^-1 by forward substitution on the identity (one wave, one
-//       lane per column, no synchronisation inside), U and W as products with T on MFMA, operands
-//       written in the layouts the second kernel's MFMA fragments want;
-//   gdn_scan_kernel  (64 value columns, value head): walks the chunks in DFS order with the state
-//       in MFMA accumulators (the columns of S evolve independently, so a head is cut into four
-//       independent blocks of 32 columns, four wavefronts each; two blocks form a workgroup and share
-//       the LDS copy of the chunk's operands); state routing = where a chunk takes S0 from (registers when it
-//       continues the previous chunk's sequence, a saved node-end state, or zero).
-// The backward pass (tt_gdn_bwd.hip) reuses both: the prepare kernel in a form that also writes the reverse walk's
-// operands, the scan in a form that saves every chunk's entering state and Vn instead of writing the output, and
-// gdn_rscan_kernel, the reverse walk, built like the scan.
 #include <hip/hip_runtime.h>
 #include "tt_internal.h"
 #include "tt_kernels.h"
@@ -838,14 +822,7 @@ __global__ __launch_bounds__(G_THREADS) void gdn_root_grad_kernel(const float* _
   }
 }
 
-size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
-
 }  // namespace
-
-size_t gdn_workspace(int n_chunks, int n_slots, int hv) {
-  const size_t per = (size_t)n_chunks * hv;
-  return align256(per * REC_ELEMS * 2) + align256(per * 4) + align256((size_t)n_slots * hv * GD * GD * 4) + 256;
-}
 
 // Walks the chunk program forward: one launch for everything without a schedule, else one launch per dependency
 // level with the level's segments side by side (blockIdx.y).
@@ -864,31 +841,6 @@ static hipError_t launch_scan(GdnArgs& a, const tt_gdn_schedule* sched, hipStrea
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   }
   return hipSuccess;
-}
-
-hipError_t gdn_fwd(int64_t n_tokens, int hk, int hv, float scale, const void* q, const void* k, const void* v, const float* g,
-                   const float* beta, int n_chunks, const int32_t* chunk_tok0, const int32_t* chunk_len, const int32_t* chunk_src,
-                   const int32_t* chunk_dst, int n_slots, const int32_t* chunk_cap, const tt_gdn_schedule* sched,
-                   const float* initial_state, float* state_out, void* o, void* workspace, hipStream_t st) {
-  if (n_chunks == 0) return hipSuccess;
-  GdnArgs a{};
-  a.n_tokens = (int)n_tokens; a.hk = hk; a.hv = hv; a.hv_n = hv; a.n_chunks = n_chunks; a.scale = scale;
-  a.q = (const __bf16*)q; a.k = (const __bf16*)k; a.v = (const __bf16*)v; a.g = g; a.beta = beta;
-  a.chunk_tok0 = chunk_tok0; a.chunk_len = chunk_len; a.chunk_src = chunk_src; a.chunk_dst = chunk_dst;
-  a.chunk_cap = chunk_cap; a.initial_state = initial_state; a.state_out = state_out;
-  a.o = (__bf16*)o;
-  const size_t per = (size_t)n_chunks * hv;
-  char* p = (char*)workspace;
-  a.rec = (__bf16*)p; p += align256(per * REC_ELEMS * 2);
-  a.glast = (float*)p; p += align256(per * 4);
-  a.slots = (float*)p;
-  {
-    KernelTimer t(TT_KERNEL_GDN_PREPARE, st);
-    gdn_prepare_kernel<false><<<gdn_group_order_grid(n_chunks, hv, hv / hk), G_THREADS, 0, st>>>(a);
-  }
-  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-  KernelTimer t(TT_KERNEL_GDN_SCAN, st);
-  return launch_scan<false>(a, sched, st);
 }
 
 hipError_t gdn_bwd_prepare_and_walks(const GdnBwdArgs& b, const GdnChunkOps& ops, const GdnBwdSaved& sv, hipStream_t st) {

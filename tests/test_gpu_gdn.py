@@ -99,6 +99,28 @@ def test_larger_tree_sampled_heads():
     _check(t, 4, 8, 11, heads_checked=[0, 5])
 
 
+@pytest.mark.parametrize("hk,hv", [(3, 3), (8, 8), (8, 24), (1, 5)])
+def test_head_layouts_and_chunk_lengths(hk, hv):
+    """One, three and five value heads per key head (whole and unfinished rounds of the prepare kernel), key head counts that
+    are and are not a multiple of eight (the workgroup order differs), chunks of 1, 31, 32, 33, 63, 64 tokens.  Operands and
+    the state are rounded to bf16 once each and meet in sums of up to 128 products: 2^-9 per operand, 8e-3 for o."""
+    seg = [63, 64, 33, 32, 31, 1, 65, 97, 128, 2]
+    parent = [-1, 0, 0, 1, 1, 2, 4, 4, 0, 8]
+    t = W._mk(parent, seg, [1] * len(seg), "lengths")
+    n = sum(seg)
+    q, k, v, g, beta = _inputs(n, hk, hv, 70 + hv)
+    pred, rep = M.dfs_meta(parent, seg)["tok_pred"], hv // hk
+    o = T.tree_gdn_fwd(q.cuda(), k.cuda(), v.cuda(), g.cuda(), beta.cuda(), T.tree_gdn_plan(t.parent, t.seg_len)).float().cpu().numpy()
+    for h in range(hv):
+        want = S.gdn_tree(q[:, h // rep:h // rep + 1], k[:, h // rep:h // rep + 1], v[:, h:h + 1], g[:, h:h + 1], beta[:, h:h + 1], pred)
+        assert rel_l2(o[:, h], want[:, 0]) <= 8e-3, h
+
+
+def test_more_chunks_than_a_wave_holds_scalars_of():
+    """A node of 66 chunks: the scalars of 64 consecutive chunks lie in the lanes of a wave and are fetched again behind them."""
+    _check(W._mk([-1, 0, 0], [65 * 64 + 7, 40, 70], [1] * 3, "long"), 1, 1, 3)
+
+
 def test_errors():
     q = torch.zeros((4, 1, 64), dtype=torch.bfloat16, device="cuda")
     v = torch.zeros((4, 1, 64), dtype=torch.bfloat16, device="cuda")
