@@ -12,13 +12,13 @@ LIB = os.path.join(HERE, "libtreetrain.so")
 
 SOURCES = ["tt_error.cpp", "tt_meta.cpp", "tt_api.hip", "tt_timing.hip", "tt_attn_ref.hip", "tt_attn_f32.hip", "tt_loss.hip",
            "tt_attn_fwd.hip", "tt_attn_bwd.hip", "tt_attn_dkdv.hip", "tt_rope.hip", "tt_partition.cpp",
-           "tt_partition_run.hip", "tt_conv.hip", "tt_gdn_fwd.hip", "tt_gdn.hip", "tt_gdn_bwd.hip"]
+           "tt_partition_run.hip", "tt_conv.hip", "tt_gdn.hip", "tt_gdn_bwd.hip"]
 
 # Kernels that run two waves per SIMD keep MFMA results in architectural VGPRs (the softmax / dS
 # arithmetic consumes them directly); the dK/dV kernel needs the accumulation VGPRs for its 128
 # accumulator registers per lane and is compiled with the default register form.
 VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
-PER_FILE_FLAGS = {"tt_attn_fwd.hip": VGPR_FORM, "tt_attn_bwd.hip": VGPR_FORM, "tt_gdn.hip": VGPR_FORM, "tt_gdn_fwd.hip": VGPR_FORM}
+PER_FILE_FLAGS = {"tt_attn_fwd.hip": VGPR_FORM, "tt_attn_bwd.hip": VGPR_FORM, "tt_gdn.hip": VGPR_FORM}
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wextra",

@@ -1,32 +1,28 @@
 // Gated delta rule with tree state routing, backward (Section "Implementation", paragraph "SSM Layers
 // (GDN)" (i): gradients accumulate at the shared parent state; Appendix "Tree-Aware SSM State
 // Routing").  Chunked like the forward (64 tokens, chunks never cross a node boundary).  With
-//     Vn = U - W S0,   O = Qg S0 + P Vn,   S1 = EL S0 + Kd^T Vn
-// (Qg = scale exp(gamma) Q, Kd = exp(gamma_last - gamma) K, EL = exp(gamma_last), U = (I+A)^-1 beta V,
-// W = (I+A)^-1 beta exp(gamma) K, A = beta_i A0_ij, A0 = strictly-lower((k_i.k_j) D_ij),
-// P = scale tril((q_i.k_j) D_ij), D_ij = exp(gamma_i - gamma_j)) the chain rule gives, per chunk,
-//     dVn = P^T dO + Kd dS1                      dS0 = EL dS1 + Qg^T dO - W^T dVn          (serial part)
-//     dQg = dO S0^T    dKd = Vn dS1^T    dW = -dVn S0^T    dP = tril(dO Vn^T)
-//     [dVb | dKb] = (I+A)^-T [dVn | dW]          dA = strictly-lower(-dVb U^T - dKb W^T)
-// and from there dq, dk, dv, dbeta and dgamma by the product rule; dg is the reverse running sum of
+//     R = beta V - beta eg (K S0),   Vn = T R,   O = scale eg (Q S0) + P Vn,   S1 = EL S0 + K^T (el Vn)
+// (eg = exp(gamma), el = exp(gamma_last - gamma), EL = exp(gamma_last), row factors; T = (I + A)^-1, A = beta_i A0_ij,
+// A0 = strictly-lower((k_i.k_j) D_ij), P = scale tril((q_i.k_j) D_ij), D_ij = exp(gamma_i - gamma_j)) the chain rule gives, per chunk,
+//     dVn = P^T dO + el (K dS1)     dR = T^T dVn     dS0 = EL dS1 + Q^T (scale eg dO) - K^T (beta eg dR)          (serial part)
+//     dQg = dO S0^T      dKd = Vn dS1^T      dKb = -dR S0^T      dP = tril(dO Vn^T)      dA = strictly-lower(-dR Vn^T)
+// (the triangular solve's own gradient: dA = -T^T dVn Vn^T).  From there dq, dk, dv = beta dR, dbeta and dgamma by the product
+// rule; dg is the reverse running sum of
 // dgamma inside the chunk.  State routing backwards: dS1 of a chunk is the dS0 of the chunk that
 // continued from it on chip plus the gradient collected in its saved-state slot (every chunk that
 // started from the slot added its dS0 there; they all come later in DFS order, so a reverse walk over
 // the chunks has seen them), plus the upstream gradient of a captured state.
 //
 // Kernels (the first three live in tt_gdn.hip with the forward's):
-//   gdn_prepare_kernel<true>   per (chunk, head): the bf16 record of both walks, what the reverse walk needs besides
-//                              (P^T, dO^T), and gamma and (I + A)^-1 unrounded
-//   gdn_scan_kernel<true>      (32 value columns, head): the forward scan without its output; saves S0 and Vn
-//                              of every chunk (bf16)
-//   gdn_rscan_kernel           (32 value columns, head): reverse walk in the forward scan's form (bf16 matrix
-//                              instruction, fp32 state gradient in accumulators); saves dS1 and dVn (bf16)
+//   gdn_prepare_kernel<true>   per (chunk, key head): T, P transposed, row factors
+//   gdn_fwalk_kernel           (value head, segment): the forward scan without its output; saves S0 and Vn of every chunk (bf16)
+//   gdn_rwalk_kernel           (value head, segment): reverse walk in the forward scan's form; saves dS1 and dR (bf16)
 //   gdn_bwd_finish_kernel      per (chunk, key head): everything else: products on the bf16 matrix instruction (fp32
-//                              accumulation), the transposed solve as a product with the inverse and all element-wise
-//                              work in fp32; dq / dk summed over the key head's value heads in registers
+//                              accumulation), element-wise work in fp32; dq / dk summed over the key head's value heads in registers
 //   gdn_bwd_group_sum_kernel   calls with few chunks: sums fp32 dq / dk over the value heads, rounds to bf16
 #include <hip/hip_runtime.h>
 #include <algorithm>
+#include <type_traits>
 #include "tt_internal.h"
 #include "tt_kernels.h"
 #include "tt_mfma.h"
@@ -36,10 +32,10 @@ namespace {
 
 constexpr int GC = TT_GDN_CHUNK;     // 64
 constexpr int GD = 128;
-constexpr int BT = 256;
+constexpr int BT = 256;              // threads of the small kernels
+constexpr int FT = 512;              // of the finish kernel
 
 struct BwdWs {
-  GdnChunkOps ops;
   GdnBwdSaved sv;
   float* dqh;        // split calls only: [N][hv_n][128] per-value-head dq, dk (the heads of the pass)
   float* dkh;
@@ -55,49 +51,36 @@ __device__ __forceinline__ float4 ld4(const float* p) { return *(const float4*)p
 __device__ __forceinline__ int tile_row(int r, int hf) { return (r >> 2) * 8 + 4 * hf + (r & 3); }
 
 // ---- per-chunk finish ----------------------------------------------------------------------------------
-// One workgroup of four waves per (chunk, key head); it goes through the value heads of the key head one after the
-// other and keeps dq and dk, which are sums over them, in accumulator registers (SPLIT: one value head per workgroup, dq /
-// dk of every head in fp32 to memory, summed by gdn_bwd_group_sum_kernel).  What bounds it is memory: about 190 KB of
-// operands per (chunk, value head), of which every byte is read once.  To that end everything that shares an operand is
-// done while that operand is on chip:
-//   1. one pass over the four blocks of 32 value columns with S0, dS1, dO, Vn and dVn of the block in LDS:
-//      dW = -dVn S0^T, dQg = dO S0^T, dKd = Vn dS1^T, dP = dO Vn^T and <dS1, S0>
-//   2. [dVb | dKb]^T = [dVn | dW]^T T on both halves of the split T; the result stays in LDS.  A wave's dW
-//      accumulators are, as bf16, the A fragments of its own column block
-//   3. dA = -[dVb | dKb] [U | W]^T, dv and dbeta's part from dVb
-//   4. K K^T and Q K^T again (K and Q stay in LDS for all heads; cheaper than 32 KB of A0 and P per head out and in):
-//      row and column sums of dP o P + dA o A in registers, dP scale D and dA beta D as bf16 to LDS
-//   5. dq += (dP scale D) K;  dk += (dP scale D)^T Q + (dA beta D) K + (dA beta D)^T K + beta eg dKb
-// LDS 80 KB: two workgroups per compute unit, one's loads beside the other's products.  16406 tokens, 16 / 32 heads: 0.50
-// ms at 2.3 GB (4.6 TB/s; a large copy reaches 4.8).  The loop over the heads spills 24 registers (76 bytes per lane and
-// head out and in again): 0.18 of the 0.46 GB that the kernel writes at that size, 8 % of its traffic.  With one value head
-// per workgroup, fp32 dq / dk through memory, A0 and P from memory and S0, dS1, dO, Vn read once per product it was 0.86 ms
-// at 4.9 GB and 0.12 ms for the sum.
-// Register r of a wave's tile (row block t, column block w) of a 64 x 128 result: row 32 t + tile_row(r), column
-// 32 w + lane % 32; of a 64 x 64 result: row block w & 1, column block w >> 1.
-constexpr int PG = GD + 8;                               // LDS pitches (elements): rows 16-byte aligned, 8 elements of
-constexpr int PK = GC + 8;                               // padding against bank conflicts
-
+// One workgroup of eight waves per compute unit; it goes through its (chunk, key head) pairs, the value heads of a key head one after
+// the other, and keeps dq and dk, which are sums over them, in accumulator registers (SPLIT: one value head each, dq /
+// dk of every head in fp32 to memory, summed by gdn_bwd_group_sum_kernel).  What bounds it is memory: 128 KB of
+// operands per (chunk, value head), each byte read once.  To that end
+//   - everything that contracts over value columns is done while a slab of 32 of them is on chip: S0, dS1, Vn, dR, dO, V, 32 KB, copied
+//     straight to LDS as the walks stored it; transposing reads give the operands
+//         dQg = dO S0^T, dKb = -dR S0^T, dKd = Vn dS1^T, dP = dO Vn^T, dA = -dR Vn^T and <dS1, S0>
+//   - three slabs are on chip: two on their way while one is worked on, across heads and pairs
+// Then, per head: K K^T and Q K^T again (K and Q stay in LDS for all heads): row and column sums of dP o P + dA o A in
+// registers, dP scale D and dA beta D as bf16 to LDS, and
+//         dq += (dP scale D) K;  dk += (dP scale D)^T Q + (dA beta D) K + (dA beta D)^T K + beta eg dKb
+// A wave's tile (tb, kb) of a 64 x 128 result: rows 32 tb .., columns 32 kb ..
+// 16406 tokens, 16 / 32 heads: 0.40 ms at 1.45 GB (0.50 ms at 2.3 GB before, when dW went through the transposed solve and U, W and T
+// were read for it).  A slab takes 2600 cycles of which 1000 are waits for memory, what follows the slabs of a head 9000.
+constexpr int PK = GC + 8;                               // LDS pitch (elements) of the 64 x 64 matrices
+constexpr int SLAB_B = 32 * 1024, N_SLOTS = 3;
+constexpr int F_S0 = 0, F_DS1 = 8 * 1024, F_VN = 16 * 1024, F_DR = 20 * 1024, F_DO = 24 * 1024, F_V = 28 * 1024;
 struct FinishSmem {
-  __bf16 k[GC * PG], q[GC * PG];                         // rows of K and Q, zero past the chunk's length
-  // step 1: slabs S0^T, dS1^T [32 columns][128], Vn, dVn [32 columns][64 tokens];  step 2: T as hi and lo halves;  from
-  // there on dVb and dKb [token][128];  after step 3 dP scale D in dVb's place, and the closing sums behind it
-  __bf16 x[2 * GC * PG];
-  __bf16 r2[GC * PK];                                    // dO, 64 columns; U^T, 64 rows, then -W, 64 columns; dA beta D
-  float gam[GC], bet[GC], eg[GC], el[GC], db_v[GC];
-  float dg_row[2][GC], dg_col[2][GC], db_a[2][GC];       // per column / row block
+  unsigned char slab[N_SLOTS][SLAB_B];
+  __bf16 k[GC * GD], q[GC * GD];                         // swizzled tiles; at a pair's end dk and dq on their way to memory
+  __bf16 m1[GC * PK], m2[GC * PK];                       // dP scale D, dA beta D, column by column
+  float row[2][5][GC];                                   // beta, beta eg, el, eg, gamma of this head and the next
+  float dg_row[2][2][GC], dg_col[2][2][GC], db_a[2][GC]; // [dP / dA part][column / row block]
+  float sum_qk[4][GC], sum_kb[4][GC], db_v[4][GC], part[8];
 };
-static_assert(sizeof(FinishSmem) <= 80 * 1024, "two workgroups per compute unit");
-constexpr int SLAB = 32;                                 // value columns per slab of step 1
-constexpr int X_S0 = 0, X_DS1 = SLAB * PG, X_VN = 2 * SLAB * PG, X_DVN = 2 * SLAB * PG + SLAB * PK;
-constexpr int X_TLO = GC * PK;
-constexpr int X_KB = GC * PG;                            // dKb
-constexpr int X_SUMS = GC * PK;                          // 9 x 64 floats
-static_assert(X_DVN + SLAB * PK <= 2 * GC * PG && X_SUMS % 8 == 0 && X_SUMS + 2 * 9 * GC <= X_KB && GC * PK <= X_SUMS, "LDS areas");
+static_assert(sizeof(FinishSmem) <= 160 * 1024, "LDS of one compute unit");
 
-// Barrier that waits for this wave's LDS traffic only (a __syncthreads also waits for every global load in flight,
-// i.e. for what was requested ahead).  Not for global data written by other threads of the workgroup.
+// Barriers that wait for this wave's LDS traffic, and for its copies except the last n requests.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+template <int N> __device__ __forceinline__ void copies_barrier() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"i"(N) : "memory"); }
 
 // Sums 16 values over the 32 lanes of a half wave (the lanes that hold one row of an accumulator tile in register r): every
 // step folds the lane positions on each other and hands half of the values to either side, so that 16 sums take 16
@@ -119,469 +102,381 @@ __device__ __forceinline__ float half_wave_sums(float (&v)[16], int c) {
   return __uint_as_float(o[0]) + __uint_as_float(o[1]);
 }
 
-// The value is formed at this point of the program.  (The compiler moves additions to their use two steps later and keeps
-// both operands in registers until then: 94 spilled registers, 1.3 GB of scratch traffic and 0.82 ms at 16 K tokens.)
-template <class T> __device__ __forceinline__ void form_here(T& x) { asm volatile("" : "+v"(x)); }
+// a value that is the same for all lanes, by a scalar load (a vector load would be waited for with the copies in flight)
+__device__ __forceinline__ int ld_uniform(const int32_t* p) { return *(const __attribute__((address_space(4))) int32_t*)(uintptr_t)p; }
+__device__ __forceinline__ void fence() { __builtin_amdgcn_sched_barrier(0); }
 
 template <bool SPLIT>
-__global__ __launch_bounds__(BT, 2) void gdn_bwd_finish_kernel(KArgs a) {
-  __shared__ __attribute__((aligned(16))) FinishSmem sm;
-  const int nc = a.b.n_chunks, hv = a.b.hv, rep = hv / a.b.hk;
-  int chunk, unit;                                       // unit: key head (SPLIT: value head) inside this pass
-  if (!gdn_group_order(blockIdx.x, nc, SPLIT ? a.b.hv_n : a.b.hv_n / rep, SPLIT ? rep : 1, chunk, unit)) return;
-  const int kh = SPLIT ? unit / rep : unit;
-  const int tok0 = a.b.chunk_tok0[chunk], len = a.b.chunk_len[chunk];
+__global__ __launch_bounds__(FT, 2) void gdn_bwd_finish_kernel(KArgs a) {
+  __shared__ __attribute__((aligned(1024))) FinishSmem sm;
+  const int nc = a.b.n_chunks, hv = a.b.hv, rep = hv / a.b.hk, n_r = SPLIT ? 1 : rep;
+  const int items = nc * (SPLIT ? a.b.hv_n : a.b.hv_n / rep);
   const float scale = a.b.scale;
-  const size_t qrow = (size_t)a.b.hk * GD, vrow = (size_t)hv * GD;
-  bf16x8 zero8;
-#pragma unroll
-  for (int e = 0; e < 8; e++) zero8[e] = (__bf16)0.f;
+  const uint32_t qrow = (uint32_t)a.b.hk * (GD * 2), vrow = (uint32_t)hv * (GD * 2);      // bytes per token
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tb = w & 1, kb = w >> 1;
+  // waves 0 .. 2: the lower tiles (0, 0), (1, 0), (1, 1) of dP;  3 .. 5: of dA
+  const int part = w / 3, ib = (w % 3 + 1) >> 1, jb = (w % 3) >> 1;
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)&sm);
 
-  // Thread positions (ib, jb: this wave's tile of a 64 x 64 result).  LDS and memory offsets are functions of these alone:
-  // taken from an opaque copy per step, they are formed where they are used; otherwise the compiler forms those of all
-  // steps in front of the loop over the heads and keeps them.
-  int tid, lane, c, hf, c16, w, ib, jb;
-  auto place = [&]() {
-    int t = threadIdx.x & (BT - 1);
-    asm volatile("" : "+v"(t)::"memory");
-    tid = t; lane = t & 63; c = lane & 31; hf = lane >> 5; c16 = 16 * (c >> 4);
-    w = __builtin_amdgcn_readfirstlane(t >> 6);
-    ib = w & 1; jb = w >> 1;
-  };
-  // The pieces of a slab, and what a head starts with (slab 0 and the chunk's scalars): requested one slab ahead, a head's
-  // first ones during the last step of the head in front of it.
-  bf16x8 s0r[2], ds1r[2], vnr, dvnr, dor[2];
-  float glast, gv, bv;
-  auto load_slab = [&](int h, int cb) {
-    // saved by the walks (bf16): S0 and dS1 transposed [value col][key dim], Vn and dVn in fragment order
-    const size_t op = (size_t)h * nc + chunk;
-    const __bf16* s0t = (const __bf16*)a.w.sv.s0t + op * (GD * GD) + cb * (SLAB * GD);
-    const __bf16* ds1t = (const __bf16*)a.w.sv.ds1t + op * (GD * GD) + cb * (SLAB * GD);
-#pragma unroll
-    for (int p = 0; p < 2; p++) {
-      s0r[p] = *(const bf16x8*)(s0t + 8 * (tid + p * BT));
-      ds1r[p] = *(const bf16x8*)(ds1t + 8 * (tid + p * BT));
+  // ---- copies ----
+  // 32 pieces of a slab: wave w takes fragment w of S0 and of dS1, one of Vn or dR, one of dO or V (16 rows of 64 bytes, the
+  // 16-byte chunks of a row permuted so that 16 rows read at the same chunk meet all banks).  Pointers move on by a slab; a new head's
+  // are formed with its first one.
+  int n_item = blockIdx.x, n_rh = 0, n_cb = 0, n_slot = 0, n_par = 0;      // the slab to request next
+  if (n_item >= items) return;
+  int n_chunk = n_item % nc, n_unit = n_item / nc, n_tok0 = ld_uniform(a.b.chunk_tok0 + n_chunk), n_len = ld_uniform(a.b.chunk_len + n_chunk);
+  const char *p_s0 = nullptr, *p_ds1 = nullptr, *p_vn = nullptr, *p_do = nullptr;
+  uint32_t do_at = 0;
+  auto request = [&]() {
+    if (n_item >= items) return;
+    if (n_cb == 0) {
+      const int h = SPLIT ? n_unit : n_unit * rep + n_rh;
+      const size_t op = (size_t)h * nc + n_chunk;
+      p_s0 = (const char*)a.w.sv.s0 + op * (GD * GD * 2) + 1024 * w;
+      p_ds1 = (const char*)a.w.sv.ds1 + op * (GD * GD * 2) + 1024 * w;
+      p_vn = (const char*)(w < 4 ? a.w.sv.vns : a.w.sv.drs) + op * (GC * GD * 2) + 1024 * (w & 3);
+      p_do = (const char*)(w < 4 ? a.b.d_o : a.b.v) + (uint64_t)(uint32_t)n_tok0 * vrow + (size_t)h * (GD * 2);
+      do_at = (uint32_t)min(16 * (w & 3) + (lane >> 2), n_len - 1) * vrow + 16u * (uint32_t)((lane & 3) ^ ((lane >> 4) & 3));
+      const uint32_t rows = lds0 + (uint32_t)offsetof(FinishSmem, row) + 5 * GC * 4 * n_par;
+      if (w == 0) dma16((const char*)a.w.sv.rec + (op * GDN_REC_ELEMS + GDN_REC_ROW) * 2, 16u * lane, rows);
+      if (w == 1) dma4(a.w.sv.gam + op * GC, 4u * lane, rows + 4 * GC * 4);
     }
-    vnr = *(const bf16x8*)((const __bf16*)a.w.sv.vns + op * (GC * GD) + cb * (SLAB * GC) + 8 * tid);
-    dvnr = *(const bf16x8*)((const __bf16*)a.w.sv.dvns + op * (GC * GD) + cb * (SLAB * GC) + 8 * tid);
-    if ((cb & 1) == 0) {
-      const __bf16* dob = (const __bf16*)a.b.d_o + (size_t)tok0 * vrow + (size_t)h * GD + cb * SLAB;
-#pragma unroll
-      for (int p = 0; p < 2; p++) {
-        const int piece = tid + p * BT, i = piece >> 3, k8 = (piece & 7) * 8;
-        dor[p] = *(const bf16x8*)(dob + (size_t)min(i, len - 1) * vrow + k8);
+    const uint32_t dst = lds0 + (uint32_t)offsetof(FinishSmem, slab) + SLAB_B * n_slot + 1024 * w;
+    dma16(p_s0, 16u * lane, dst + F_S0);
+    dma16(p_ds1, 16u * lane, dst + F_DS1);
+  };
+  auto request_rest = [&]() {           // (between the products: a compute unit takes 64 bytes a cycle, and a wave waits for its turn)
+    if (n_item >= items) return;
+    const uint32_t dst = lds0 + (uint32_t)offsetof(FinishSmem, slab) + SLAB_B * n_slot + 1024 * w;
+    dma16(p_vn, 16u * lane, dst + F_VN);
+    dma16(p_do, do_at, dst + F_DO);
+    p_s0 += 8192; p_ds1 += 8192; p_vn += 4096; p_do += 64;
+    n_slot = n_slot == N_SLOTS - 1 ? 0 : n_slot + 1;
+    if (++n_cb == 4) {
+      n_cb = 0; n_par ^= 1;
+      if (++n_rh == n_r) {
+        n_rh = 0;
+        n_item += gridDim.x;
+        if (n_item < items) {
+          n_chunk = n_item % nc; n_unit = n_item / nc;
+          n_tok0 = ld_uniform(a.b.chunk_tok0 + n_chunk); n_len = ld_uniform(a.b.chunk_len + n_chunk);
+        }
       }
     }
   };
-  auto load_head = [&](int h) {
-    const float* gam = a.w.ops.gam + ((size_t)h * nc + chunk) * GC;
-    glast = gam[GC - 1];
-    gv = gam[lane];
-    bv = a.b.beta[(size_t)(tok0 + min(lane, len - 1)) * hv + h];
-    load_slab(h, 0);
+  auto request_kq = [&](int kh, int tok0, int len) {
+    const uint64_t at = (uint64_t)(uint32_t)tok0 * qrow + (size_t)kh * (GD * 2);
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    dma_tile64<8>((const char*)a.b.k + at, qrow, len, sm.k, w, ln);
+    dma_tile64<8>((const char*)a.b.q + at, qrow, len, sm.q, w, ln);
   };
-  {
-    place();
-    const __bf16* qb = (const __bf16*)a.b.q + (size_t)tok0 * qrow + (size_t)kh * GD;
-    const __bf16* kb = (const __bf16*)a.b.k + (size_t)tok0 * qrow + (size_t)kh * GD;
-    bf16x8 kr[4], qr[4];
+
+  // ---- LDS addresses ----
+  const int c = lane & 31, hf = lane >> 5, i16 = lane & 15, gidx = (lane >> 4) & 1, q2 = i16 >> 2, qd = i16 & 3;
+  const uint32_t slab0 = lds0 + (uint32_t)offsetof(FinishSmem, slab);
+  // rows of dO / V as operands: token 32 blk + c, columns 16 s + 8 hf .. of the slab
+  uint32_t a_row[2];
 #pragma unroll
-    for (int p = 0; p < 4; p++) {
-      const int piece = tid + p * BT, i = piece >> 4, c8 = (piece & 15) * 8;
-      const size_t at = (size_t)min(i, len - 1) * qrow + c8;
-      kr[p] = *(const bf16x8*)(kb + at);
-      qr[p] = *(const bf16x8*)(qb + at);
-    }
-    load_head(SPLIT ? unit : kh * rep);
+  for (int s = 0; s < 2; s++) a_row[s] = (uint32_t)(64 * c + 16 * ((2 * s + hf) ^ ((c >> 2) & 3)));
+  // tokens as lanes, 8 value columns 16 s + 8 hf .. each, out of the column-wise fragments of Vn / dR (two reads x of 4)
+  uint32_t a_tr[2], b_tr[2];
 #pragma unroll
-    for (int p = 0; p < 4; p++) {
-      const int piece = tid + p * BT, i = piece >> 4, c8 = (piece & 15) * 8;
-      *(bf16x8*)(sm.k + i * PG + c8) = i < len ? kr[p] : zero8;
-      *(bf16x8*)(sm.q + i * PG + c8) = i < len ? qr[p] : zero8;
-    }
+  for (int x = 0; x < 2; x++) {
+    a_tr[x] = (uint32_t)(1024 * gidx + 512 * (qd & 1) + 16 * ((8 * hf + 4 * x + q2) ^ (4 * (qd & 1))) + 8 * (qd >> 1));
+    // key dims as lanes, 8 value columns each, out of the fragments of S0 / dS1
+    b_tr[x] = (uint32_t)(1024 * gidx + 512 * (qd >> 1) + 16 * ((8 * hf + 4 * x + q2) ^ (4 * (qd >> 1))) + 8 * (qd & 1)) + 2048u * kb;
   }
-
-  f32x16 dq[2] = {zero16(), zero16()}, dk[2] = {zero16(), zero16()};
+  int item = blockIdx.x, slot = 0, par = 0;
+  request_kq(SPLIT ? n_unit / rep : n_unit, n_tok0, n_len);
+  request(); request_rest();
+  request(); request_rest();
+  for (; item < items; item += gridDim.x) {
+    const int chunk = item % nc, unit = item / nc, kh = SPLIT ? unit / rep : unit;
+    const int tok0 = ld_uniform(a.b.chunk_tok0 + chunk), len = ld_uniform(a.b.chunk_len + chunk);
+    f32x16 dq = zero16(), dk = zero16(), x = zero16();    // x: this wave's tile of Q K^T or K K^T
 #pragma unroll 1
-  for (int r_h = 0; r_h < (SPLIT ? 1 : rep); r_h++) {
-    const int h = SPLIT ? unit : kh * rep + r_h;
-    const size_t op = (size_t)h * nc + chunk;
-    const __bf16* dvns = (const __bf16*)a.w.sv.dvns + op * (GC * GD);
-    const __bf16* ut = (const __bf16*)a.w.sv.fwd_rec + op * GDN_REC_ELEMS + GDN_REC_UT;
-    const __bf16* wn = (const __bf16*)a.w.sv.fwd_rec + op * GDN_REC_ELEMS + GDN_REC_WN;
-    const __bf16* vb = (const __bf16*)a.b.v + (size_t)tok0 * vrow + (size_t)h * GD;
-
-    // ---- 1. everything that contracts over value columns ----
-    place();
-    const float el_last = __expf(glast);
-    if (tid < GC) {
-      sm.gam[tid] = gv;
-      sm.bet[tid] = tid < len ? bv : 0.f;
-      sm.eg[tid] = __expf(gv);
-      sm.el[tid] = __expf(glast - gv);
-    }
-    float s_dot = 0.f;                                   // this thread's part of <dS1, S0>
-    bf16x8 xf[2][GC / 16];                               // A fragments of the right-hand sides of step 2
-    float4 t_in[3];
-    f32x16 dp = zero16();
-    float row_qk[2], s_kd = 0.f;                         // row sums of dQg o Qg - dKd o Kd;  this thread's part of <dKd, Kd>
-    {
-      f32x16 dw[2] = {zero16(), zero16()}, dqg[2] = {zero16(), zero16()}, dkd[2] = {zero16(), zero16()};
+    for (int r_h = 0; r_h < n_r; r_h++) {
+      const int h = SPLIT ? unit : kh * rep + r_h;
+      const float(*row)[GC] = sm.row[par];
+      // ---- 1. everything that contracts over value columns ----
+      f32x16 dqg = zero16(), dkb = zero16(), dkd = zero16(), dm = zero16();      // dm: this wave's tile of dP or -dA
+      float s_dot = 0.f, db = 0.f;      // this thread's part of <dS1, S0>;  of dR_i . v_i (token 32 tb + c)
+#pragma unroll 1
+      for (int cb = 0; cb < 4; cb++) {
+        // this slab has landed (what was requested behind it may still be on its way), and every wave has left the one before
+        // requested behind it: 4 pieces of the next slab, and 4 of K and Q behind a pair's third slab
+        const bool kq = r_h == 0 && item != (int)blockIdx.x;
+        if (kq && (cb == 1 || cb == 2)) copies_barrier<8>();
+        else if (cb < 3 || r_h + 1 < n_r || item + (int)gridDim.x < items) copies_barrier<4>();
+        else copies_barrier<0>();
+        request();
+        const uint32_t sl = slab0 + SLAB_B * slot;
+        slot = slot == N_SLOTS - 1 ? 0 : slot + 1;
+        const uint32_t at0 = sl + a_tr[0], at1 = sl + a_tr[1], bt0 = sl + b_tr[0], bt1 = sl + b_tr[1];
+        bf16x8 d_o[2], dr[2], vn[2], s0[2], ds1[2], left[2], right[2];
 #pragma unroll
-      for (int cb = 0; cb < GD / SLAB; cb++) {
-        place();
-        lds_barrier();                                   // the previous slab (or whatever was here before) has been read
-#pragma unroll
-        for (int p = 0; p < 2; p++) {
-          const int piece = tid + p * BT, at = (piece >> 4) * PG + (piece & 15) * 8;
-          *(bf16x8*)(sm.x + X_S0 + at) = s0r[p];
-          *(bf16x8*)(sm.x + X_DS1 + at) = ds1r[p];
-#pragma unroll
-          for (int e = 0; e < 8; e++) s_dot += (float)s0r[p][e] * (float)ds1r[p][e];
+        for (int s = 0; s < 2; s++) {
+          d_o[s] = lds_b128(sl + a_row[s] + 2048 * tb, F_DO);
+          s0[s] = lds_tr2(bt0, bt1, F_S0 + 256 * s);
+          dr[s] = lds_tr2(at0 + 2048 * tb, at1 + 2048 * tb, F_DR + 256 * s);
+          vn[s] = lds_tr2(at0 + 2048 * tb, at1 + 2048 * tb, F_VN + 256 * s);
+          ds1[s] = lds_tr2(bt0, bt1, F_DS1 + 256 * s);
+          left[s] = part == 0 ? lds_b128(sl + a_row[s] + 2048 * ib, F_DO) : lds_tr2(at0 + 2048 * ib, at1 + 2048 * ib, F_DR + 256 * s);
+          right[s] = lds_tr2(at0 + 2048 * jb, at1 + 2048 * jb, F_VN + 256 * s);     // (waves 6, 7: not used)
         }
-        form_here(s_dot);
+        fence();
+#pragma unroll
+        for (int s = 0; s < 2; s++) {
+          dqg = mfma32(d_o[s], s0[s], dqg);
+          dkb = mfma32(dr[s], s0[s], dkb);
+          dkd = mfma32(vn[s], ds1[s], dkd);
+          dm = mfma32(left[s], right[s], dm);
+          if (s == 0) {
+            request_rest();
+            if (kq && cb == 0) request_kq(kh, tok0, len);     // (the previous pair's dq and dk have left their place)
+          }
+          fence();
+        }
         {
-          // one piece of a fragment-ordered array = 8 tokens of one column: base .. base + 3 and base + 8 .. base + 11
-          const int f = tid >> 6, at = c * PK + 16 * f + 4 * hf;
-          *(bf16x4*)(sm.x + X_VN + at) = __builtin_shufflevector(vnr, vnr, 0, 1, 2, 3);
-          *(bf16x4*)(sm.x + X_VN + at + 8) = __builtin_shufflevector(vnr, vnr, 4, 5, 6, 7);
-          *(bf16x4*)(sm.x + X_DVN + at) = __builtin_shufflevector(dvnr, dvnr, 0, 1, 2, 3);
-          *(bf16x4*)(sm.x + X_DVN + at + 8) = __builtin_shufflevector(dvnr, dvnr, 4, 5, 6, 7);
+          const uint32_t at = sl + 16u * threadIdx.x;
+          const bf16x8 x = lds_b128(at, F_S0), y = lds_b128(at, F_DS1);
+#pragma unroll
+          for (int e = 0; e < 8; e++) s_dot += (float)x[e] * (float)y[e];
         }
-        if ((cb & 1) == 0) {
-#pragma unroll
-          for (int p = 0; p < 2; p++) {
-            const int piece = tid + p * BT, i = piece >> 3, k8 = (piece & 7) * 8;
-            *(bf16x8*)(sm.r2 + i * PK + k8) = i < len ? dor[p] : zero8;
-          }
-        }
-        lds_barrier();
-        if (cb + 1 < GD / SLAB) {
-          load_slab(h, cb + 1);
-        } else {
-          // for step 2: T (three 32 x 32 blocks, the fourth is zero) and the dVn fragments of this wave's column block
-          const float* tg = a.w.ops.t + op * GDN_T_ELEMS;
-#pragma unroll
-          for (int p = 0; p < 3; p++) t_in[p] = ld4(tg + 4 * (tid + p * BT));
-#pragma unroll
-          for (int s = 0; s < GC / 16; s++) xf[0][s] = ((const bf16x8*)dvns)[(w * 4 + s) * 64 + lane];
-        }
-#pragma unroll
-        for (int s = 0; s < SLAB / 16; s++) {
-          const int k0 = 16 * s + 8 * hf;
-          const bf16x8 b_s0 = kmajor_frag(sm.x + X_S0, PG, k0, 32 * w + c16, lane);
-          const bf16x8 b_ds1 = kmajor_frag(sm.x + X_DS1, PG, k0, 32 * w + c16, lane);
-#pragma unroll
-          for (int t = 0; t < 2; t++) {
-            dw[t] = mfma32(kmajor_frag(sm.x + X_DVN, PK, k0, 32 * t + c16, lane), b_s0, dw[t]);
-            dqg[t] = mfma32(*(const bf16x8*)(sm.r2 + (32 * t + c) * PK + (cb & 1) * SLAB + k0), b_s0, dqg[t]);
-            dkd[t] = mfma32(kmajor_frag(sm.x + X_VN, PK, k0, 32 * t + c16, lane), b_ds1, dkd[t]);
-          }
-          dp = mfma32(*(const bf16x8*)(sm.r2 + (32 * ib + c) * PK + (cb & 1) * SLAB + k0),
-                      kmajor_frag(sm.x + X_VN, PK, k0, 32 * jb + c16, lane), dp);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int t = 0; t < 2; t++) {
-        place();
-#pragma unroll
-        for (int u = 0; u < 2; u++)
-          xf[1][2 * t + u] = cvt8(-dw[t][8 * u], -dw[t][8 * u + 1], -dw[t][8 * u + 2], -dw[t][8 * u + 3], -dw[t][8 * u + 4],
-                                  -dw[t][8 * u + 5], -dw[t][8 * u + 6], -dw[t][8 * u + 7]);
-        // dq_i = scale exp(gamma_i) dQg_i + ...;  dk_j = exp(gamma_last - gamma_j) dKd_j + ...;  their dot products with
-        // q_i and k_j go into dgamma.  (A k-major fragment in accumulator order holds the rows of 8 registers.)
-        float dot[16];
-#pragma unroll
-        for (int u = 0; u < 2; u++) {
-          const bf16x8 qf = kmajor_frag_acc_order(sm.q, PG, 32 * t + 16 * u + 4 * hf, 32 * w + c16, lane);
-          const bf16x8 kf = kmajor_frag_acc_order(sm.k, PG, 32 * t + 16 * u + 4 * hf, 32 * w + c16, lane);
-#pragma unroll
-          for (int v4 = 0; v4 < 2; v4++) {
-            const int i4 = 32 * t + 16 * u + 8 * v4 + 4 * hf;
-            const f32x4 eg4 = *(const f32x4*)(sm.eg + i4), el4 = *(const f32x4*)(sm.el + i4);
-#pragma unroll
-            for (int e = 0; e < 4; e++) {
-              const int r = 8 * u + 4 * v4 + e;
-              const float vq = scale * eg4[e] * dqg[t][r], vk = el4[e] * dkd[t][r], vkk = vk * (float)kf[4 * v4 + e];
-              dot[r] = vq * (float)qf[4 * v4 + e] - vkk;
-              s_kd += vkk;
-              dq[t][r] += vq;
-              dk[t][r] += vk;
-            }
-          }
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        row_qk[t] = half_wave_sums(dot, c);
-        form_here(dq[t]);
-        form_here(dk[t]);
-      }
-    }
-
-    place();
-    // ---- 2. (I + A)^T [dVb | dKb] = [dVn | dW]: X^T = rhs^T T ----
-    bf16x8 ur[2][2], vv[4];
-    // two slabs ahead: 64 rows of U^T (value columns), or 64 columns (key dims) of the rows of -W
-    auto load_uw = [&](int s) {
-#pragma unroll
-      for (int p = 0; p < 2; p++) {
-        const int piece = tid + p * BT;
-        ur[s & 1][p] = *(const bf16x8*)(s < 2 ? ut + s * (GC * GC) + 8 * piece
-                                              : wn + (s - 2) * GC + (piece >> 3) * GD + (piece & 7) * 8);
-      }
-    };
-    const int v_i = tid >> 2, v_c0 = (tid & 3) * 32;     // step 3: this thread's row and columns of dVb
-    lds_barrier();                                       // the last slab has been read
-#pragma unroll
-    for (int p = 0; p < 3; p++) {
-      const int k = (p > 0 ? 32 : 0) + (tid >> 3), i4 = (p == 2 ? 32 : 0) + (tid & 7) * 4;
-      const float4 v = t_in[p];
-      const bf16x4 h4 = cvt4(v.x, v.y, v.z, v.w);
-      *(bf16x4*)(sm.x + k * PK + i4) = h4;
-      *(bf16x4*)(sm.x + X_TLO + k * PK + i4) = cvt4(v.x - (float)h4[0], v.y - (float)h4[1], v.z - (float)h4[2], v.w - (float)h4[3]);
-    }
-    lds_barrier();
-    load_uw(0);
-    load_uw(1);
-#pragma unroll
-    for (int q = 0; q < 4; q++) vv[q] = *(const bf16x8*)(vb + (size_t)min(v_i, len - 1) * vrow + v_c0 + 8 * q);
-    {
-      bf16x4 xo[2][2][4];                                // the result as bf16, one column block of T at a time (registers)
-#pragma unroll
-      for (int cb = 0; cb < 2; cb++) {
-        f32x16 xa[2] = {zero16(), zero16()};
-#pragma unroll
-        for (int s = 2 * cb; s < GC / 16; s++) {         // (rows 0 .. 31 of T are zero from column 32 on)
-          const bf16x8 th = kmajor_frag_acc_order(sm.x, PK, 16 * s + 4 * hf, 32 * cb + c16, lane);
-          const bf16x8 tl = kmajor_frag_acc_order(sm.x + X_TLO, PK, 16 * s + 4 * hf, 32 * cb + c16, lane);
-#pragma unroll
-          for (int m = 0; m < 2; m++) {
-            xa[m] = mfma32(xf[m][s], th, xa[m]);
-            xa[m] = mfma32(xf[m][s], tl, xa[m]);
-          }
-        }
-#pragma unroll
-        for (int m = 0; m < 2; m++)
-#pragma unroll
-          for (int r4 = 0; r4 < 4; r4++)
-            xo[m][cb][r4] = cvt4(xa[m][4 * r4], xa[m][4 * r4 + 1], xa[m][4 * r4 + 2], xa[m][4 * r4 + 3]);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      lds_barrier();                                     // T has been read
-      // a lane holds row i = 32 cb + c and, per register group, 4 consecutive columns
-#pragma unroll
-      for (int m = 0; m < 2; m++)
-#pragma unroll
-        for (int cb = 0; cb < 2; cb++)
-#pragma unroll
-          for (int r4 = 0; r4 < 4; r4++)
-            *(bf16x4*)(sm.x + m * X_KB + (32 * cb + c) * PG + 32 * w + 8 * r4 + 4 * hf) = xo[m][cb][r4];
-    }
-
-    // ---- 3. dA = strictly-lower(-[dVb | dKb] [U | W]^T);  dv_i = beta_i dVb_i,  dbeta_i += dVb_i . v_i ----
-    f32x16 da = zero16();
-#pragma unroll
-    for (int s = 0; s < 4; s++) {
-      place();
-      lds_barrier();                                     // the previous slab has been read (first time: dVb, dKb are there)
-#pragma unroll
-      for (int p = 0; p < 2; p++) {
-        const int piece = tid + p * BT;
-        *(bf16x8*)(sm.r2 + (piece >> 3) * PK + (piece & 7) * 8) = ur[s & 1][p];
-      }
-      lds_barrier();
-      if (s < 2) load_uw(s + 2);
-      if (s == 2) {                                      // from the second half on the records hold -W
-#pragma unroll
-        for (int r = 0; r < 16; r++) da[r] = -da[r];
-      }
-#pragma unroll
-      for (int ss = 0; ss < 4; ss++) {
-        const bf16x8 uw = s < 2 ? kmajor_frag(sm.r2, PK, 16 * ss + 8 * hf, 32 * jb + c16, lane)
-                                : *(const bf16x8*)(sm.r2 + (32 * jb + c) * PK + 16 * ss + 8 * hf);
-        da = mfma32(*(const bf16x8*)(sm.x + (s >> 1) * X_KB + (32 * ib + c) * PG + (s & 1) * 64 + 16 * ss + 8 * hf), uw, da);
-      }
-      if (s == 0) {
-        float dot = 0.f;
-        const float b = sm.bet[v_i];
-#pragma unroll
-        for (int q = 0; q < 4; q++) {
-          const bf16x8 xb = *(const bf16x8*)(sm.x + v_i * PG + v_c0 + 8 * q);
-          float xv[8];
+        if ((kb >> 1) == (cb & 1)) {    // dv_i = beta_i dR_i of 16 columns
+          const int s = kb & 1, i = 32 * tb + c;
+          const bf16x8 dr_s = s ? dr[1] : dr[0], v = lds_b128(sl + (s ? a_row[1] : a_row[0]) + 2048 * tb, F_V);
+          const float b = row[0][i];
+          float x[8];
 #pragma unroll
           for (int e = 0; e < 8; e++) {
-            xv[e] = (float)xb[e];
-            dot += xv[e] * (float)vv[q][e];
+            x[e] = b * (float)dr_s[e];
+            db += (float)dr_s[e] * (float)v[e];
           }
-          if (v_i < len)
-            *(bf16x8*)((__bf16*)a.b.dv + ((size_t)(tok0 + v_i) * hv + h) * GD + v_c0 + 8 * q) =
-                cvt8(b * xv[0], b * xv[1], b * xv[2], b * xv[3], b * xv[4], b * xv[5], b * xv[6], b * xv[7]);
+          if (i < len)
+            *(bf16x8*)((char*)a.b.dv + (uint64_t)(uint32_t)tok0 * vrow + (size_t)h * (GD * 2) + (uint32_t)i * vrow + 64 * cb + 32 * s + 16 * hf) =
+                cvt8(x[0], x[1], x[2], x[3], x[4], x[5], x[6], x[7]);
         }
-        dot += __shfl_xor(dot, 1);
-        dot += __shfl_xor(dot, 2);
-        if ((tid & 3) == 0) sm.db_v[v_i] = v_i < len ? dot : 0.f;
       }
-    }
 
-    // ---- 4. G = dP o P + dA o A: its row sums minus its column sums are the part of dgamma that comes through D ----
-    {
-      place();
-      f32x16 kk = zero16(), qk = zero16();
+      // Lane positions of the steps per head, from an opaque copy of the lane: their LDS and memory offsets are formed where they
+      // are used; otherwise the compiler forms those of all steps in front of the loops and keeps them (72 spilled registers).
+      int ln = lane;
+      asm volatile("" : "+v"(ln));
+      const int c = ln & 31, hf = ln >> 5;
+      // ---- 2. dq_i = scale eg_i dQg_i + ..;  dk_j = el_j dKd_j + beta eg_j dKb_j + ..;  their dot products with q_i and k_j go into dgamma ----
+      float row_qk, row_kb, s_kd = 0.f;
+      {
+        float dot[16], dot_kb[16];
+        const TrBase tr = tr_frag_base(ln);
+        auto acc_frag = [&](const __bf16* tile, int r0) {       // 16 tokens in the order of accumulator registers, this wave's key dims
+          return cat4(lds_read_tr(tile + r0 * GD + (tr.x0 ^ (kb << 5))), lds_read_tr(tile + r0 * GD + (tr.x1 ^ (kb << 5))));
+        };
+        bf16x8 qf[2], kf[2];
+        f32x4 eg4[4], el4[4], beg4[4];
 #pragma unroll
-      for (int s = 0; s < GD / 16; s++) {
-        const bf16x8 kj = *(const bf16x8*)(sm.k + (32 * jb + c) * PG + 16 * s + 8 * hf);
-        kk = mfma32(*(const bf16x8*)(sm.k + (32 * ib + c) * PG + 16 * s + 8 * hf), kj, kk);
-        qk = mfma32(*(const bf16x8*)(sm.q + (32 * ib + c) * PG + 16 * s + 8 * hf), kj, qk);
-      }
-      const int j = 32 * jb + c;
-      const float gj = sm.gam[j];
-      float col = 0.f;
-      lds_barrier();                                     // dVb and the last slab have been read: dP scale D, dA beta D go there
-      float g[16], ga[16];
+        for (int u = 0; u < 2; u++) { qf[u] = acc_frag(sm.q, 32 * tb + 16 * u); kf[u] = acc_frag(sm.k, 32 * tb + 16 * u); }
 #pragma unroll
-      for (int r4 = 0; r4 < 4; r4++) {
-        const int i4 = 32 * ib + 8 * r4 + 4 * hf;
-        const f32x4 gi4 = *(const f32x4*)(sm.gam + i4), b4 = *(const f32x4*)(sm.bet + i4);
-        f32x4 mp, ma;
-#pragma unroll
-        for (int e = 0; e < 4; e++) {
-          const int r = 4 * r4 + e, i = i4 + e;
-          const float dec = j <= i ? __expf(gi4[e] - gj) : 0.f;
-          const float vp = j <= i ? dp[r] : 0.f, va = j < i ? da[r] : 0.f;
-          mp[e] = vp * (scale * dec);
-          ma[e] = va * dec;
-          ga[r] = ma[e] * (j < i ? kk[r] : 0.f);         // its row sums are the part of dbeta that comes through A
-          ma[e] *= b4[e];
-          g[r] = mp[e] * (j <= i ? qk[r] : 0.f) + b4[e] * ga[r];
-          col += g[r];
+        for (int r4 = 0; r4 < 4; r4++) {
+          const int i4 = 32 * tb + 8 * r4 + 4 * hf;
+          eg4[r4] = *(const f32x4*)&row[3][i4];
+          el4[r4] = *(const f32x4*)&row[2][i4];
+          beg4[r4] = *(const f32x4*)&row[1][i4];
         }
-        *(bf16x4*)(sm.x + j * PK + i4) = cvt4(mp[0], mp[1], mp[2], mp[3]);
-        *(bf16x4*)(sm.r2 + j * PK + i4) = cvt4(ma[0], ma[1], ma[2], ma[3]);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      const float row_g = half_wave_sums(g, c), row_a = half_wave_sums(ga, c);
-      if (c < 16) {
-        sm.dg_row[jb][32 * ib + tile_row(c, hf)] = row_g;
-        sm.db_a[jb][32 * ib + tile_row(c, hf)] = row_a;
-      }
-      col = half_swap_sum(col);
-      if (hf == 0) sm.dg_col[ib][j] = col;
-    }
-    lds_barrier();
-
-    // ---- 5. what is left of dq and dk (the 64 x 64 matrices are lower triangular) ----
-    place();
-    if (!SPLIT && r_h + 1 < rep) load_head(h + 1);
-    float row_kb[2];
+        fence();
 #pragma unroll
-    for (int s = 0; s < GC / 16; s++) {
-      const int k0 = 16 * s + 8 * hf;
-      const bf16x8 b_k = kmajor_frag(sm.k, PG, k0, 32 * w + c16, lane);
-      const bf16x8 b_q = kmajor_frag(sm.q, PG, k0, 32 * w + c16, lane);
-#pragma unroll
-      for (int t = 0; t < 2; t++) {
-        if (s < 2 * t + 2) {                             // rows of block t: columns up to its diagonal
-          dq[t] = mfma32(kmajor_frag(sm.x, PK, k0, 32 * t + c16, lane), b_k, dq[t]);
-          dk[t] = mfma32(kmajor_frag(sm.r2, PK, k0, 32 * t + c16, lane), b_k, dk[t]);
+        for (int r = 0; r < 16; r++) {
+          const float kv = (float)kf[r >> 3][r & 7], vq = scale * eg4[r >> 2][r & 3] * dqg[r], vk = el4[r >> 2][r & 3] * dkd[r], vkk = vk * kv;
+          dot[r] = vq * (float)qf[r >> 3][r & 7] - vkk;
+          dot_kb[r] = -dkb[r] * kv;
+          s_kd += vkk;
+          dq[r] += vq;
+          dk[r] += vk - beg4[r >> 2][r & 3] * dkb[r];
         }
-        if (s >= 2 * t) {                                // transposed
-          dk[t] = mfma32(*(const bf16x8*)(sm.x + (32 * t + c) * PK + k0), b_q, dk[t]);
-          dk[t] = mfma32(*(const bf16x8*)(sm.r2 + (32 * t + c) * PK + k0), b_k, dk[t]);
-        }
+        row_qk = half_wave_sums(dot, c);
+        row_kb = half_wave_sums(dot_kb, c);
       }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    place();
+      // ---- 3. G = dP o P + dA o A: its row sums minus its column sums are the part of dgamma that comes through D ----
+      auto through_d = [&](auto part_, auto diag_) {
+        constexpr int part = decltype(part_)::value;
+        constexpr bool DIAG = decltype(diag_)::value;
+        if (r_h == 0) {
+          const __bf16* left = part == 0 ? sm.q : sm.k;
+          const int rd = row_frag_base(ln);
+          bf16x8 fa[4], fb[4];
 #pragma unroll
-    for (int t = 0; t < 2; t++) {
-      float dot[16];
+          for (int s = 0; s < 4; s++) { fa[s] = lds_row_frag(left, rd, ib, s); fb[s] = lds_row_frag(sm.k, rd, jb, s); }
+          fence();
 #pragma unroll
-      for (int u = 0; u < 2; u++) {
-        const bf16x8 xf = kmajor_frag_acc_order(sm.x + X_KB, PG, 32 * t + 16 * u + 4 * hf, 32 * w + c16, lane);
-        const bf16x8 kf = kmajor_frag_acc_order(sm.k, PG, 32 * t + 16 * u + 4 * hf, 32 * w + c16, lane);
+          for (int s = 0; s < GD / 16; s++) {
+            x = mfma32(fa[s & 3], fb[s & 3], x);
+            if (s + 4 < GD / 16) { fa[s & 3] = lds_row_frag(left, rd, ib, s + 4); fb[s & 3] = lds_row_frag(sm.k, rd, jb, s + 4); }
+            fence();
+          }
+        }
+        const int j = 32 * jb + c;
+        const float gj = row[4][j];
+        if (part == 0 && len < GC) {    // rows of dO past the chunk's length are copies of its last row
 #pragma unroll
-        for (int v4 = 0; v4 < 2; v4++) {
-          const int i4 = 32 * t + 16 * u + 8 * v4 + 4 * hf;
-          const f32x4 b4 = *(const f32x4*)(sm.bet + i4), eg4 = *(const f32x4*)(sm.eg + i4);
+          for (int r = 0; r < 16; r++) dm[r] = 32 * ib + tile_row(r, hf) < len ? dm[r] : 0.f;
+        }
+        float col = 0.f, g[16], ga[16];
+        __bf16* const m = part == 0 ? sm.m1 : sm.m2;
+        f32x4 gi[2], bi[2];
+        auto read = [&](int r4) {
+          gi[r4 & 1] = *(const f32x4*)&row[4][32 * ib + 8 * r4 + 4 * hf];
+          bi[r4 & 1] = *(const f32x4*)&row[0][32 * ib + 8 * r4 + 4 * hf];
+        };
+        read(0);
+#pragma unroll
+        for (int r4 = 0; r4 < 4; r4++) {
+          const int i4 = 32 * ib + 8 * r4 + 4 * hf;
+          const f32x4 gi4 = gi[r4 & 1], b4 = bi[r4 & 1];
+          if (r4 < 3) read(r4 + 1);
+          const int below = 8 * r4 + 4 * hf - c;      // i - j of the group's first row, inside a diagonal tile
+          float v[4];
 #pragma unroll
           for (int e = 0; e < 4; e++) {
-            const float dkb = (float)xf[4 * v4 + e];
-            dot[8 * u + 4 * v4 + e] = dkb * (float)kf[4 * v4 + e];
-            dk[t][8 * u + 4 * v4 + e] += b4[e] * eg4[e] * dkb;
+            const int r = 4 * r4 + e;
+            float dec = fast_exp2((gi4[e] - gj) * LOG2E_F);
+            if (DIAG) dec = below + e >= part ? dec : 0.f;       // dP: j <= i, dA: j < i
+            if (part == 0) {
+              v[e] = dm[r] * (scale * dec);
+              g[r] = v[e] * x[r];
+            } else {
+              const float ma = -dm[r] * dec;
+              ga[r] = ma * x[r];        // its row sums are the part of dbeta that comes through A
+              v[e] = ma * b4[e];
+              g[r] = b4[e] * ga[r];
+            }
+            col += g[r];
           }
+          *(bf16x4*)(m + j * PK + i4) = cvt4(v[0], v[1], v[2], v[3]);
+          fence();
+        }
+        const float row_g = half_wave_sums(g, c);
+        if (c < 16) sm.dg_row[part][jb][32 * ib + tile_row(c, hf)] = row_g;
+        if (part == 1) {
+          const float row_a = half_wave_sums(ga, c);
+          if (c < 16) sm.db_a[jb][32 * ib + tile_row(c, hf)] = row_a;
+        }
+        col = half_swap_sum(col);
+        if (hf == 0) sm.dg_col[part][ib][j] = col;
+        if (DIAG && ib == 0) {          // the upper right tile is zero: nobody forms its sums
+          if (hf == 0) sm.dg_row[part][1][c] = 0.f;
+          if (hf == 1) sm.dg_col[part][0][32 + c] = 0.f;
+          if (part == 1 && hf == 0) sm.db_a[1][c] = 0.f;
+        }
+      };
+      if (w == 1) through_d(std::integral_constant<int, 0>{}, std::false_type{});
+      else if (w < 3) through_d(std::integral_constant<int, 0>{}, std::true_type{});
+      else if (w == 4) through_d(std::integral_constant<int, 1>{}, std::false_type{});
+      else if (w < 6) through_d(std::integral_constant<int, 1>{}, std::true_type{});
+      if (c < 16) {
+        sm.sum_qk[kb][32 * tb + tile_row(c, hf)] = row_qk;
+        sm.sum_kb[kb][32 * tb + tile_row(c, hf)] = row_kb;
+      }
+      db = half_swap_sum(db);
+      if (hf == 0) sm.db_v[kb][32 * tb + c] = db;
+      // what goes through gamma_last: <dKd, Kd>, and exp(gamma_last) <dS1, S0> (it also scales the state that is carried over)
+      float s_last = s_kd + row[3][GC - 1] * s_dot;
+#pragma unroll
+      for (int d = 32; d > 0; d >>= 1) s_last += __shfl_xor(s_last, d);
+      if (ln == 0) sm.part[w] = s_last;
+      lds_barrier();
+
+      // ---- 4. what is left of dq and dk (the 64 x 64 matrices are lower triangular) ----
+      // K / Q: 8 consecutive tokens per half of the wave, this wave's key dims as lanes
+      const int l16 = ln & 15, chunk16 = 4 * kb + 2 * ((ln >> 4) & 1) + ((l16 & 3) >> 1);
+      int nat[2];
+#pragma unroll
+      for (int x = 0; x < 2; x++)
+        nat[x] = (8 * hf + 4 * x + (l16 >> 2)) * GD + ((chunk16 ^ (((l16 >> 2) << 2) | ((2 * hf + x) & 3))) << 3) + 4 * (l16 & 1);
+      auto nat_frag = [&](const __bf16* tile, int s) { return cat4(lds_read_tr(tile + 16 * s * GD + nat[0]), lds_read_tr(tile + 16 * s * GD + nat[1])); };
+      // rows of block tb: columns up to its diagonal (s < 2 tb + 2), and transposed (s >= 2 tb)
+      auto below = [&](const __bf16* m, int s) { return kmajor_frag(m, PK, 16 * s + 8 * hf, 32 * tb + 16 * (c >> 4), ln); };
+      auto across = [&](const __bf16* m, int s) { return *(const bf16x8*)(m + (32 * tb + c) * PK + 16 * s + 8 * hf); };
+      auto rest = [&](auto tb_) {
+        constexpr int TB = decltype(tb_)::value;
+        bf16x8 fk[2], fq[2], f1[2], f2[2], t1[2], t2[2];
+        auto read = [&](int s) {
+          const int u = s & 1;
+          fk[u] = nat_frag(sm.k, s);
+          if (s < 2 * TB + 2) { f1[u] = below(sm.m1, s); f2[u] = below(sm.m2, s); }
+          if (s >= 2 * TB) { fq[u] = nat_frag(sm.q, s); t1[u] = across(sm.m1, s); t2[u] = across(sm.m2, s); }
+        };
+        read(0);
+#pragma unroll
+        for (int s = 0; s < GC / 16; s++) {
+          const int u = s & 1;
+          if (s + 1 < GC / 16) read(s + 1);
+          fence();
+          if (s < 2 * TB + 2) { dq = mfma32(f1[u], fk[u], dq); dk = mfma32(f2[u], fk[u], dk); }
+          if (s >= 2 * TB) { dk = mfma32(t1[u], fq[u], dk); dk = mfma32(t2[u], fk[u], dk); }
+          fence();
+        }
+      };
+      if (tb == 0) rest(std::integral_constant<int, 0>{});
+      else rest(std::integral_constant<int, 1>{});
+      // ---- dg, dbeta ----
+      if (w == 7) {
+        const int t = ln;
+        const float dkb_k = row[3][t] * ((sm.sum_kb[0][t] + sm.sum_kb[1][t]) + (sm.sum_kb[2][t] + sm.sum_kb[3][t]));       // eg dKb_i . k_i
+        float s = (sm.dg_row[0][0][t] + sm.dg_row[0][1][t]) + (sm.dg_row[1][0][t] + sm.dg_row[1][1][t]) -
+                  ((sm.dg_col[0][0][t] + sm.dg_col[0][1][t]) + (sm.dg_col[1][0][t] + sm.dg_col[1][1][t])) +
+                  ((sm.sum_qk[0][t] + sm.sum_qk[1][t]) + (sm.sum_qk[2][t] + sm.sum_qk[3][t])) + row[0][t] * dkb_k;
+        s = t < len ? s : 0.f;
+        // gamma_i = sum of g_j over j <= i: a sum over the rows from this one on; gamma_last reaches every g
+#pragma unroll
+        for (int d = 1; d < GC; d <<= 1) {
+          const float down = __shfl_down(s, d);
+          s += t + d < GC ? down : 0.f;
+        }
+        const float last = ((sm.part[0] + sm.part[1]) + (sm.part[2] + sm.part[3])) + ((sm.part[4] + sm.part[5]) + (sm.part[6] + sm.part[7]));
+        if (t < len) {
+          a.b.dg[(size_t)(tok0 + t) * hv + h] = s + last;
+          a.b.dbeta[(size_t)(tok0 + t) * hv + h] =
+              sm.db_a[0][t] + sm.db_a[1][t] + dkb_k + ((sm.db_v[0][t] + sm.db_v[1][t]) + (sm.db_v[2][t] + sm.db_v[3][t]));
         }
       }
-      row_kb[t] = half_wave_sums(dot, c);
-      __builtin_amdgcn_sched_barrier(0);
+      par ^= 1;
     }
 
-    // ---- dg, dbeta ----
-    float(*sum_qk)[GC] = (float(*)[GC])(sm.x + X_SUMS);  // per-wave parts of the row sums (a quarter of the columns each)
-    float(*sum_kb)[GC] = sum_qk + 4, *part = &sum_qk[8][0];
-    if (c < 16) {
-#pragma unroll
-      for (int t = 0; t < 2; t++) {
-        sum_qk[w][32 * t + tile_row(c, hf)] = row_qk[t];
-        sum_kb[w][32 * t + tile_row(c, hf)] = row_kb[t];
-      }
-    }
-    // what goes through gamma_last: <dKd, Kd>, and exp(gamma_last) <dS1, S0> (it also scales the state that is carried over)
-    float s_last = s_kd + el_last * s_dot;
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) s_last += __shfl_xor(s_last, d);
-    if (lane == 0) part[w] = s_last;
-    lds_barrier();
-    if (tid < GC) {
-      const float dkb = sm.eg[tid] * ((sum_kb[0][tid] + sum_kb[1][tid]) + (sum_kb[2][tid] + sum_kb[3][tid]));       // eg dKb_i . k_i
-      float s = (sm.dg_row[0][tid] + sm.dg_row[1][tid]) - (sm.dg_col[0][tid] + sm.dg_col[1][tid]) +
-                ((sum_qk[0][tid] + sum_qk[1][tid]) + (sum_qk[2][tid] + sum_qk[3][tid])) + sm.bet[tid] * dkb;
-      // gamma_i = sum of g_j over j <= i: a sum over the rows from this one on; gamma_last reaches every g
-#pragma unroll
-      for (int d = 1; d < GC; d <<= 1) {
-        const float down = __shfl_down(s, d);
-        s += tid + d < GC ? down : 0.f;
-      }
-      const float last = (part[0] + part[1]) + (part[2] + part[3]);
-      if (tid < len) {
-        a.b.dg[(size_t)(tok0 + tid) * hv + h] = s + last;
-        a.b.dbeta[(size_t)(tok0 + tid) * hv + h] = sm.db_a[0][tid] + sm.db_a[1][tid] + dkb + sm.db_v[tid];
-      }
-    }
-  }
-
-  place();
-  if constexpr (SPLIT) {
-#pragma unroll
-    for (int t = 0; t < 2; t++)
+    // ---- the pair's dq and dk ----
+    int ln = lane;                      // (opaque, as above)
+    asm volatile("" : "+v"(ln));
+    const int c = ln & 31, hf = ln >> 5;
+    if constexpr (SPLIT) {
 #pragma unroll
       for (int r = 0; r < 16; r++) {
-        const int i = 32 * t + tile_row(r, hf);
-        const size_t at = ((size_t)(tok0 + i) * a.b.hv_n + unit) * GD + 32 * w + c;
+        const int i = 32 * tb + tile_row(r, hf);
+        const size_t at = ((size_t)(tok0 + i) * a.b.hv_n + unit) * GD + 32 * kb + c;
         if (i < len) {
-          a.w.dqh[at] = dq[t][r];
-          a.w.dkh[at] = dk[t][r];
+          a.w.dqh[at] = dq[r];
+          a.w.dkh[at] = dk[r];
         }
       }
-  } else {
-    // through LDS, so that rows leave in 16-byte pieces
-    lds_barrier();                                       // K and Q have been read
-#pragma unroll
-    for (int t = 0; t < 2; t++)
+    } else {
+      // through LDS, so that rows leave in 16-byte pieces
+      lds_barrier();                    // K and Q have been read
 #pragma unroll
       for (int r = 0; r < 16; r++) {
-        const int at = (32 * t + tile_row(r, hf)) * PG + 32 * w + c;
-        sm.q[at] = (__bf16)dq[t][r];
-        sm.k[at] = (__bf16)dk[t][r];
+        const int at = (32 * tb + tile_row(r, hf)) * GD + 32 * kb + c;
+        sm.q[at] = (__bf16)dq[r];
+        sm.k[at] = (__bf16)dk[r];
       }
-    lds_barrier();
+      lds_barrier();
 #pragma unroll
-    for (int p = 0; p < 4; p++) {
-      const int piece = tid + p * BT, i = piece >> 4, c8 = (piece & 15) * 8;
-      const size_t at = (size_t)(tok0 + i) * qrow + (size_t)kh * GD + c8;
-      if (i < len) {
-        *(bf16x8*)((__bf16*)a.b.dq + at) = *(const bf16x8*)(sm.q + i * PG + c8);
-        *(bf16x8*)((__bf16*)a.b.dk + at) = *(const bf16x8*)(sm.k + i * PG + c8);
+      for (int p = 0; p < 2; p++) {
+        const int piece = 64 * w + ln + p * FT, i = piece >> 4, c8 = (piece & 15) * 8;
+        const uint64_t at = (uint64_t)(uint32_t)(tok0 + i) * qrow + (size_t)kh * (GD * 2) + c8 * 2;
+        if (i < len) {
+          *(bf16x8*)((char*)a.b.dq + at) = *(const bf16x8*)(sm.q + i * GD + c8);
+          *(bf16x8*)((char*)a.b.dk + at) = *(const bf16x8*)(sm.k + i * GD + c8);
+        }
       }
     }
   }
@@ -624,18 +519,16 @@ size_t carve(char* p, int64_t n_tokens, int n_chunks, int n_slots, int n_segment
     return r;
   };
   BwdWs t{};
-  t.ops.gam = (float*)take(per * GC * 4);
-  t.ops.t = (float*)take(per * GDN_T_ELEMS * 4);
-  t.sv.fwd_rec = take(per * GDN_REC_ELEMS * 2);
-  t.sv.rev_rec = take(per * GDN_REV_ELEMS * 2);
-  t.sv.glast = (float*)take(per * 4);
-  t.sv.s0t = take(per * GD * GD * 2);
-  t.sv.ds1t = take(per * GD * GD * 2);
+  t.sv.gam = (float*)take(per * GC * 4);
+  t.sv.rec = take(per * GDN_REC_ELEMS * 2);
+  t.sv.s0 = take(per * GD * GD * 2);
+  t.sv.ds1 = take(per * GD * GD * 2);
   t.sv.vns = take(per * GC * GD * 2);
-  t.sv.dvns = take(per * GC * GD * 2);
+  t.sv.drs = take(per * GC * GD * 2);
   t.sv.slots = (float*)take((size_t)n_slots * hv * GD * GD * 4);
   t.sv.slot_grad = (float*)take((size_t)n_slots * hv * GD * GD * 4);
   t.sv.seg_grad = (float*)take((size_t)n_segments * hv * GD * GD * 4);
+  t.sv.flags = (int*)take((size_t)(n_slots + n_segments) * hv_n * 16);
   if (split) {
     t.dqh = (float*)take((size_t)n_tokens * hv_n * GD * 4);
     t.dkh = (float*)take((size_t)n_tokens * hv_n * GD * 4);
@@ -653,9 +546,16 @@ bool finish_split(int n_chunks, int hk, int hv) { return hv > hk && (int64_t)n_c
 
 }  // namespace
 
+// The size callers are told: 209156 bytes per (chunk, value head), what the call took when the walks' operands were stored in
+// full, where 118 KB are used now.  It stays, with the smallest size that is accepted, so that budgets and buffers made for it
+// mean what they meant; a pass takes as many heads as fit by what is used.
 size_t gdn_bwd_workspace(int64_t n_tokens, int n_chunks, int n_slots, int n_segments, int hk, int hv, int key_heads_per_pass) {
-  return carve(nullptr, n_tokens, n_chunks, n_slots, n_segments, hv, key_heads_per_pass * (hv / hk),
-               finish_split(n_chunks, hk, hv), nullptr);
+  constexpr size_t STATED = 209156;
+  static_assert(GC * 4 + GDN_REC_ELEMS * 2 + 4 * GD * GD + 4 * GC * GD <= STATED, "the arrays of carve");
+  const int hv_n = key_heads_per_pass * (hv / hk);
+  const size_t per = (size_t)n_chunks * hv_n, arrays = 16 * 256;
+  const size_t states = (size_t)(2 * n_slots + n_segments) * hv * GD * GD * 4;
+  return align256(per * STATED) + states + (finish_split(n_chunks, hk, hv) ? 2 * align256((size_t)n_tokens * hv_n * GD * 4) : 0) + arrays;
 }
 
 // The value heads are independent of each other up to the final sum over the value heads of a key head, so the
@@ -664,12 +564,13 @@ size_t gdn_bwd_workspace(int64_t n_tokens, int n_chunks, int n_slots, int n_segm
 hipError_t gdn_bwd(const GdnBwdArgs& b0, hipStream_t st) {
   if (b0.n_chunks == 0 || b0.n_tokens == 0) return hipSuccess;
   const int rep = b0.hv / b0.hk, n_seg = b0.sched ? b0.sched->n_segments : 0;
-  int per_pass = b0.hk;
-  while (per_pass > 1 && gdn_bwd_workspace(b0.n_tokens, b0.n_chunks, b0.n_slots, n_seg, b0.hk, b0.hv, per_pass) > b0.workspace_bytes)
-    per_pass--;
-  if (gdn_bwd_workspace(b0.n_tokens, b0.n_chunks, b0.n_slots, n_seg, b0.hk, b0.hv, per_pass) > b0.workspace_bytes)
-    return hipErrorInvalidValue;
   const bool split = finish_split(b0.n_chunks, b0.hk, b0.hv);
+  auto used = [&](int key_heads) { return carve(nullptr, b0.n_tokens, b0.n_chunks, b0.n_slots, n_seg, b0.hv, key_heads * rep, split, nullptr); };
+  int per_pass = b0.hk;
+  while (per_pass > 1 && used(per_pass) > b0.workspace_bytes) per_pass--;
+  if (used(per_pass) > b0.workspace_bytes) return hipErrorInvalidValue;
+  int dev = 0, n_cu = 256;
+  if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
   auto zero = [&](float* p, size_t floats) {
     if (floats == 0) return;
     const size_t n4 = floats / 4;
@@ -700,11 +601,13 @@ hipError_t gdn_bwd(const GdnBwdArgs& b0, hipStream_t st) {
       }
     }
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-    if (hipError_t e = gdn_bwd_prepare_and_walks(b, a.w.ops, a.w.sv, st); e != hipSuccess) return e;
+    if (hipError_t e = gdn_bwd_prepare_and_walks(b, a.w.sv, st); e != hipSuccess) return e;
     {
       KernelTimer t(TT_KERNEL_GDN_BWD_FINISH, st);
-      if (split) gdn_bwd_finish_kernel<true><<<gdn_group_order_grid(b.n_chunks, b.hv_n, rep), BT, 0, st>>>(a);
-      else gdn_bwd_finish_kernel<false><<<gdn_group_order_grid(b.n_chunks, hk_n, 1), BT, 0, st>>>(a);
+      const int64_t items = (int64_t)b.n_chunks * (split ? b.hv_n : hk_n);
+      const unsigned grid = (unsigned)std::min<int64_t>(items, n_cu);
+      if (split) gdn_bwd_finish_kernel<true><<<grid, FT, 0, st>>>(a);
+      else gdn_bwd_finish_kernel<false><<<grid, FT, 0, st>>>(a);
     }
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     if (split) {

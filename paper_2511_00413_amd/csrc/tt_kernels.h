@@ -99,37 +99,26 @@ hipError_t gdn_fwd(int64_t n_tokens, int hk, int hv, float scale, const void* q,
 size_t gdn_workspace(int n_chunks, int n_slots, int hv);
 
 // Backward of the gated delta rule.  Every per-chunk array is indexed by (head * n_chunks + chunk).
-// Unrounded per-chunk quantities that do not depend on the state (written by the prepare kernel, read by the
-// finish kernel):
-struct GdnChunkOps {
-  float* gam;      // [64]       running sum of the log-decays inside the chunk
-  float* t;        // [3][32][32] the blocks T11, T21, T22 of (I + A)^-1 (T12 is zero), A = strictly-lower(beta_i
-                   //            (k_i . k_j) exp(gamma_i - gamma_j)): the inverse both triangular solves are products with
-};
-constexpr size_t GDN_T_ELEMS = 3 * 32 * 32;
-// bf16 operands of the two walks and what they save for the finish kernel:
-constexpr size_t GDN_REC_ELEMS = 4 * 64 * 128 + 64 * 64;     // elements of the record that both walks read
-constexpr size_t GDN_REV_ELEMS = 64 * 128 + 64 * 64;         // elements of the record of the reverse walk alone
-constexpr size_t GDN_REC_WN = 0;             // -W [64 tokens][128 key dims], W = (I + A)^-1 (beta exp(gamma) K)
-constexpr size_t GDN_REC_UT = 64 * 128;      // U^T [128 value cols][64 tokens], U = (I + A)^-1 (beta V)
+constexpr int GDN_REC_ELEMS = 19 * 512;      // bf16 elements of a chunk's record (tt_gdn.hip)
+constexpr int GDN_REC_ROW = 12 * 512;        // its rows of 64 fp32 factors: beta, beta exp(gamma), exp(gamma_last - gamma), exp(gamma)
+// What the walks leave for the finish kernel, rounded to bf16, as the 1 KB fragments their waves hold (four blocks of 32 value
+// columns; lane = column, at position gdn_saved_lane):
 struct GdnBwdSaved {
-  void* fwd_rec;     // records of both walks
-  void* rev_rec;     // records of the reverse walk
-  float* glast;      // exp(gamma_last)
-  void* s0t;         // [128 value cols][128 key dims] bf16: state entering the chunk, transposed
-  void* ds1t;        // same layout: gradient of the state leaving the chunk
-  void* vns;         // Vn  [64][128] bf16 in matrix-instruction fragment order (gdn_frag_index)
-  void* dvns;        // dVn, same order
-  float* slots;      // [n_slots][hv][128][128] saved node-end states
-  float* slot_grad;  // their gradients (zeroed by the caller); walk in sequence order only
-  float* seg_grad;   // [n_segments][hv][128][128] gradient of the state every segment starts from; scheduled walk only
+  void* rec;         // records
+  float* gam;        // [64] running sum of the log-decays inside the chunk
+  void* s0;          // [4][8][64][8]: state entering the chunk; fragment ks, half hf, element e = key dim 16 ks + 8 hf + e
+  void* ds1;         // gradient of the state leaving the chunk, same layout
+  void* vns;         // [4][4][64][8]: Vn; fragment js, half hf, element e = token 16 js + 4 hf + 8 (e / 4) + e % 4
+  void* drs;         // dR, same layout
+  // states and gradients of states, 128 x 128 floats each, in the order in which the walks' lanes hold them:
+  float* slots;      // [n_slots][hv] saved node-end states
+  float* slot_grad;  // [n_slots][hv] their gradients (zeroed by the caller); walk in sequence order only
+  float* seg_grad;   // [n_segments][hv] gradient of the state every segment starts from; scheduled walk only
+  int* flags;        // [n_slots + n_segments][value heads of the pass][4]: stored
 };
-// position of element (token i, value column col) inside a chunk's fragment-ordered [64][128] array
-__host__ __device__ inline int gdn_frag_index(int i, int col) {
-  const int dvb = col >> 5, c = col & 31, half = i >> 5, t = (i >> 4) & 1, i16 = i & 15;
-  const int hf = (i16 >> 2) & 1, e = ((i16 >> 3) << 2) | (i16 & 3);
-  return ((((dvb * 2 + half) * 2 + t) * 64 + hf * 32 + c) << 3) | e;
-}
+// Position of a lane's 16 bytes in a saved fragment: the two halves of the wave lie 512 bytes apart, where the transposing reads of
+// the finish kernel would meet in the same banks; the upper half is shifted by 64 bytes.
+__host__ __device__ inline int gdn_saved_lane(int lane) { return lane ^ ((lane >> 5) << 2); }
 
 // backward of the gated delta rule (tt_gdn_bwd.hip)
 struct GdnBwdArgs {
@@ -151,7 +140,7 @@ struct GdnBwdArgs {
   size_t workspace_bytes;            // decides how many key-head groups one pass takes
 };
 // prepare kernel (backward form) + forward walk + reverse walk (tt_gdn.hip)
-hipError_t gdn_bwd_prepare_and_walks(const GdnBwdArgs& b, const GdnChunkOps& ops, const GdnBwdSaved& sv, hipStream_t st);
+hipError_t gdn_bwd_prepare_and_walks(const GdnBwdArgs& b, const GdnBwdSaved& sv, hipStream_t st);
 hipError_t gdn_bwd(const GdnBwdArgs& a, hipStream_t st);
 // workspace for passes of key_heads_per_pass key heads (with their hv / hk value heads) at a time
 size_t gdn_bwd_workspace(int64_t n_tokens, int n_chunks, int n_slots, int n_segments, int hk, int hv, int key_heads_per_pass);

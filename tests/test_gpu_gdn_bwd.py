@@ -209,3 +209,42 @@ def test_value_heads_of_a_workgroup_full_chunks(rep):
         # the same products; dq and dk summed over the value heads before or after they leave the chip, then rounded to bf16 once
         e = rel_l2(a.float().cpu().numpy(), b.float().cpu().numpy())
         assert e <= (2e-3 if a.dtype == torch.bfloat16 else 1e-5), (i, e)
+
+
+def _spine(n):
+    """A spine of n branch points: every node has a leaf and the next spine node as children."""
+    parent, seg, at = [-1], [3], 0
+    for i in range(n):
+        parent += [at, at]
+        seg += [1 + i % 3, 2 + (i % 5) * 31]
+        at = len(parent) - 1
+    return W._mk(parent, seg, [1] * len(seg), "spine")
+
+
+def test_more_levels_than_a_launch_lists():
+    """40 dependency levels: segments wait for their parents' states and for their readers' gradients inside one launch;
+    the reverse walk orders up to 32 levels longest segment first."""
+    t = _spine(40)
+    assert T.tree_gdn_plan(t.parent, t.seg_len).n_levels > 32
+    _check(t, 1, 2, 13)
+
+
+def test_two_streams_at_once():
+    """Two calls in flight on two streams, each with its own workspace and flags: the results of each alone, bit for bit."""
+    trees = [_spine(12), W.random_tree(996, n_nodes=30, lo=1, hi=200, n_roots=2)]
+    ins, plans, alone = [], [], []
+    for i, t in enumerate(trees):
+        n = sum(t.seg_len)
+        ins.append([x.cuda() for x in _inputs(n, 8, 16, 90 + i)])
+        plans.append(T.tree_gdn_plan(t.parent, t.seg_len).to_device())
+        alone.append(T.tree_gdn_bwd(*ins[i], plans[i]))
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in trees]
+    for _ in range(3):
+        outs = [None, None]
+        for i, st in enumerate(streams):
+            with torch.cuda.stream(st):
+                outs[i] = T.tree_gdn_bwd(*ins[i], plans[i])
+        torch.cuda.synchronize()
+        for got, want in zip(outs, alone):
+            assert all(torch.equal(a, b) for a, b in zip(got, want))
