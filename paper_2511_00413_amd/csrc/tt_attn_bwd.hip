@@ -30,7 +30,7 @@ constexpr int NTHREADS = 256;
 // ------------------------------------------------------------------------------------------------
 // dQ
 // ------------------------------------------------------------------------------------------------
-constexpr int Q_BM = 128;          // queries per workgroup
+constexpr int Q_BM = 128;          // queries per workgroup, over all its heads
 constexpr int Q_BN = 64;           // keys per tile (= TT_KTILE)
 constexpr int Q_TILE_ELEMS = Q_BN * TILE_ROW;
 
@@ -179,7 +179,7 @@ __device__ __forceinline__ void dq_tile(const uint32_t (&ra)[8], const uint32_t 
 
 // NG: groups of four waves per workgroup, as in the forward kernel: 2 for launches that leave every workgroup a compute
 // unit of its own; the groups take every second key tile and add up their sums at the end.
-template <int NG>
+template <int NG, int LG_HEADS>
 __global__ void __launch_bounds__(NG * NTHREADS, 2)
 tree_attn_dq_kernel(AttnArgs a, int n_qtiles) {
   extern __shared__ __align__(1024) unsigned char smem_raw[];
@@ -192,17 +192,20 @@ tree_attn_dq_kernel(AttnArgs a, int n_qtiles) {
   const int bid = blockIdx.x;
   const int kvh = bid % a.hkv;
   const int rest = bid / a.hkv;
-  const int h = kvh * G + rest % G;
-  const int qt = n_qtiles - 1 - rest / G;
-  const int q0 = qt * Q_BM;
+  constexpr int HEADS = 1 << LG_HEADS;
+  const int hg = rest % (G / HEADS);                 // query heads and queries of a wave: as in the forward kernel
+  const int h = kvh * G + hg * HEADS + w % HEADS;
+  const int qt = n_qtiles - 1 - rest / (G / HEADS);
+  constexpr int QUERIES = Q_BM / HEADS;
+  const int q0 = qt * QUERIES;
   const int P = a.n_prefix, N = a.n_q;
-  const int q_hi = min(q0 + Q_BM, N);
+  const int q_hi = min(q0 + QUERIES, N);
   const int gi_first = P + q0, gi_last = P + q_hi - 1;
   const int npt = (P + Q_BN - 1) / Q_BN;
   const int u_end = npt + (q_hi - 1) / Q_BN + 1;
   const QCtx ctx{a, kvh, P, N, npt};
 
-  const int q = q0 + 32 * w + c32;
+  const int q = q0 + 32 * (w / HEADS) + c32;
   const int my_q = min(q, N - 1);
   const int gi = P + q;
   bf16x8 qf[8], gf[8];
@@ -366,10 +369,11 @@ hipError_t mfma_attn_bwd(const AttnArgs& args, hipStream_t st) {
   a.workspace_bytes -= stat;
   // dQ first: its prologue writes the per-row terms the dK/dV pass streams
   {
-    const int n_qtiles = (a.n_q + Q_BM - 1) / Q_BM;
-    const int64_t blocks = (int64_t)n_qtiles * a.hq;
+    const int lg = attn_lg_heads(a), bm = Q_BM >> lg, n_qtiles = (a.n_q + bm - 1) / bm;
+    const int64_t blocks = (int64_t)n_qtiles * (a.hq >> lg);
     const bool two = attn_two_groups(a, blocks, 32);
-    const auto kernel = two ? tree_attn_dq_kernel<2> : tree_attn_dq_kernel<1>;
+    const auto kernel = two ? (lg == 0 ? tree_attn_dq_kernel<2, 0> : lg == 1 ? tree_attn_dq_kernel<2, 1> : tree_attn_dq_kernel<2, 2>)
+                          : (lg == 0 ? tree_attn_dq_kernel<1, 0> : lg == 1 ? tree_attn_dq_kernel<1, 1> : tree_attn_dq_kernel<1, 2>);
     const int lds = (two ? 2 : 1) * (int)sizeof(QSmem);
     if (hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds)) return e;
     KernelTimer timer(TT_KERNEL_ATTN_DQ, st);

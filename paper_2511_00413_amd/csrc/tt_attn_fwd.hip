@@ -5,7 +5,7 @@
 // kend, which is all that is needed to skip a tile (nothing visible), run it unmasked (everything
 // visible) or apply the per-element test (boundary tile).
 //
-// One workgroup = 128 queries x one query head, 4 wavefronts x 32 queries, two workgroups per
+// One workgroup = 128 / g queries x g query heads of one kv head (attn_lg_heads), 4 wavefronts x 32 queries, two workgroups per
 // compute unit.  Scores are produced transposed, S^T[key, query] = K Q^T, so that a lane owns one
 // query: the softmax statistics are per-lane scalars (plus one exchange with the lane holding the
 // other half of the column), and P^T is already in B-operand layout for
@@ -19,7 +19,7 @@ namespace tt {
 namespace {
 
 constexpr int D = 128;
-constexpr int BM = 128;            // queries per workgroup
+constexpr int BM = 128;            // queries per workgroup, over all its heads
 constexpr int BN = 64;             // keys per tile (= TT_KTILE)
 constexpr int NTHREADS = 256;
 constexpr int TILE_ELEMS = BN * TILE_ROW;
@@ -210,7 +210,7 @@ __device__ __forceinline__ void process_tile(const uint32_t (&ra)[8], const uint
 // NG: groups of four waves per workgroup.  2 (launches that leave every workgroup a compute unit of its own): the groups
 // take every second key tile of the same queries, each with its own stages, and add up their sums at the end -- half the
 // chain of tiles, and two waves per SIMD as with two workgroups per compute unit.
-template <int NG>
+template <int NG, int LG_HEADS>
 __global__ void __launch_bounds__(NG * NTHREADS, 2)
 tree_attn_fwd_kernel(AttnArgs a, int n_qtiles) {
   extern __shared__ __align__(1024) unsigned char smem_raw[];
@@ -225,19 +225,22 @@ tree_attn_fwd_kernel(AttnArgs a, int n_qtiles) {
   const int bid = blockIdx.x;
   const int kvh = bid % a.hkv;
   const int rest = bid / a.hkv;
-  const int h = kvh * G + rest % G;
-  const int qt = n_qtiles - 1 - rest / G;
-  const int q0 = qt * BM;
+  constexpr int HEADS = 1 << LG_HEADS;
+  const int hg = rest % (G / HEADS);                 // this workgroup's HEADS query heads of the kv head, one per wave
+  const int h = kvh * G + hg * HEADS + w % HEADS;
+  const int qt = n_qtiles - 1 - rest / (G / HEADS);
+  constexpr int QUERIES = BM / HEADS;
+  const int q0 = qt * QUERIES, wq = w / HEADS;
   const int P = a.n_prefix, N = a.n_q;
-  const int q_hi = min(q0 + BM, N);                  // one past the last valid query
+  const int q_hi = min(q0 + QUERIES, N);                  // one past the last valid query
   const int gi_first = P + q0, gi_last = P + q_hi - 1;
   const int npt = (P + BN - 1) / BN;                 // prefix tiles
   const int u_end = npt + (q_hi - 1) / BN + 1;       // own tiles up to the diagonal
   const Ctx ctx{a, kvh, P, N, npt};
 
   // ---- Q fragments (B operand: column = query, k = d) straight from global memory ----
-  const int my_q = min(q0 + 32 * w + c32, N - 1);
-  const int gi = P + q0 + 32 * w + c32;              // unified index of this lane's query
+  const int my_q = min(q0 + 32 * wq + c32, N - 1);
+  const int gi = P + q0 + 32 * wq + c32;             // unified index of this lane's query
   bf16x8 qf[8];
   {
     const __bf16* qp = (const __bf16*)a.q + (int64_t)my_q * a.q_stride + (int64_t)h * D + 8 * hf;
@@ -357,7 +360,7 @@ tree_attn_fwd_kernel(AttnArgs a, int n_qtiles) {
   }
   constexpr int N_DB = 4 / NG;                   // column blocks that this wave stores, from block N_DB * grp on
   const float inv_l = 1.f / l_tot;
-  const int q = q0 + 32 * w + c32;
+  const int q = q0 + 32 * wq + c32;
   if (q < N) {
     __bf16* op = (__bf16*)a.o + ((int64_t)q * a.hq + h) * D + 32 * N_DB * grp;
 #pragma unroll
@@ -372,6 +375,13 @@ tree_attn_fwd_kernel(AttnArgs a, int n_qtiles) {
   }
 }
 
+int compute_units() {
+  int dev = 0, n_cu = 256;
+  if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
+  return n_cu;
+}
+int64_t attn_key_tiles(const AttnArgs& a) { return ((int64_t)a.n_prefix + BN - 1) / BN + ((int64_t)a.n_q + BN - 1) / BN; }
+
 }  // namespace
 
 // Two groups of waves per workgroup where there is no second workgroup for a compute unit to run beside the first, one
@@ -385,18 +395,32 @@ tree_attn_fwd_kernel(AttnArgs a, int n_qtiles) {
 // events: 1024 of 8 18.9 / 21.4; 21.1 / 21.5; 36.8 / 32.4;  1500 22.5 / 23.1; 21.5 / 21.9; 43.1 / 36.4;  2048 24.1 / 23.9; 23.5 / 23.8; 55.2 / 46.4;
 // 4000 32.2 / 31.1; 32.3 / 29.5; 81.9 / 67.5.
 bool attn_two_groups(const AttnArgs& a, int64_t blocks, int min_tiles) {
-  int dev = 0, n_cu = 256;
-  if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
-  const int64_t n_ktiles = ((int64_t)a.n_prefix + BN - 1) / BN + ((int64_t)a.n_q + BN - 1) / BN;
+  const int n_cu = compute_units();
+  const int64_t n_ktiles = attn_key_tiles(a);
   return blocks <= n_cu && n_ktiles >= min_tiles && n_ktiles <= 64 * KT_MAX_WIN;
+}
+
+// log2 of the query heads of a kv head that share a workgroup, one wave or two each.  A workgroup's waves all take every tile
+// that one of its queries sees, so 32 queries of 4 heads ask for fewer tiles than 128 queries of one (16406 tokens in a tree of
+// 4 levels: 28.6 instead of 29.9), and for fewer that need the per-element test (13.7 % instead of 19.7 %).  us, 1 / 2 / 4 heads, forward:
+// 777 tokens of 32 / 8 heads 16.5 / - / 14.9; 4000 of 16 / 4 29.9 / 28.0 / 28.0; chain of 4000 of 32 / 8 132.1 / 131.0 / 129.5; 16384 of 32 / 8 716 / - / 685.
+// Launches that leave compute units over: 2 and 4 are alike, but for 300 to 700 tokens, where 2 is better (chain of 300 of 16 / 4 13.6 / 14.0 / 14.3;
+// trees of 300 of 32 / 8 13.3 / 13.0 / 13.5, 1000 of 16 / 4 14.5 / 12.7 / 13.3).  Those of less than half a chip with few tiles have nothing to
+// win by it and lose up to 4 % (300 tokens of 16 / 4); in chains of 700 of 32 / 8 all of 22.8 / 23.5 / 23.7 stays (trees there 18.4 / - / 16.7).
+int attn_lg_heads(const AttnArgs& a) {
+  const int G = a.hq / a.hkv, n_cu = compute_units();
+  const int64_t blocks = (int64_t)((a.n_q + BM - 1) / BM) * a.hq;
+  const int most = blocks > n_cu ? 2 : 2 * blocks < n_cu && attn_key_tiles(a) < 8 ? 0 : 1;
+  return most == 2 && G % 4 == 0 ? 2 : most >= 1 && G % 2 == 0 ? 1 : 0;
 }
 
 hipError_t mfma_attn_fwd(const AttnArgs& a, hipStream_t st) {
   if (a.n_q == 0) return hipSuccess;
-  const int n_qtiles = (a.n_q + BM - 1) / BM;
-  const int64_t blocks = (int64_t)n_qtiles * a.hq;
+  const int lg = attn_lg_heads(a), bm = BM >> lg, n_qtiles = (a.n_q + bm - 1) / bm;
+  const int64_t blocks = (int64_t)n_qtiles * (a.hq >> lg);
   const bool two = attn_two_groups(a, blocks, 24);
-  const auto kernel = two ? tree_attn_fwd_kernel<2> : tree_attn_fwd_kernel<1>;
+  const auto kernel = two ? (lg == 0 ? tree_attn_fwd_kernel<2, 0> : lg == 1 ? tree_attn_fwd_kernel<2, 1> : tree_attn_fwd_kernel<2, 2>)
+                          : (lg == 0 ? tree_attn_fwd_kernel<1, 0> : lg == 1 ? tree_attn_fwd_kernel<1, 1> : tree_attn_fwd_kernel<1, 2>);
   const int lds = (two ? 2 : 1) * (int)sizeof(Smem);
   if (hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds)) return e;
   KernelTimer timer(TT_KERNEL_ATTN_FWD, st);

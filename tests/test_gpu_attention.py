@@ -345,3 +345,19 @@ def test_gradients_in_the_place_of_inputs(dtype, d):
     for a, b in zip(got, want):
         # fp32: other kernels, sums in another order (1e-5 of the largest entry); bf16: the same bits
         assert np.abs(a - b).max() <= (1e-5 * np.abs(b).max() if dtype == "fp32" else 0)
+
+
+@pytest.mark.parametrize("hq,hkv", [(12, 2), (3, 1), (64, 8), (72, 12)])
+@pytest.mark.parametrize("n", [33, 95, 129, 577])
+def test_bf16_query_heads_that_share_a_workgroup(hq, hkv, n):
+    """1, 2 or 4 query heads of a kv head share a workgroup: 4 where a launch has more blocks of 128 queries than the chip has
+    compute units (577 tokens of 64 heads), 2 below that, 1 in the smallest launches (33 tokens) and for odd groups of
+    heads; last blocks of 1 .. 65 queries, with and without a prefix."""
+    parent, segs = [-1, 0, 0, 1, 1], [n // 3, n // 5, n // 4, 1, 0]
+    segs[4] = n - sum(segs)
+    t = W._mk(parent, segs, [1] * 5, "packed")
+    _full_parity(t, W.AttnDims(hq, hkv, 128, "bf16", 0.5), n + hq, label="packed")
+    if n == 577:
+        vis = np.ones(70, dtype=np.uint8)
+        vis[5:9] = 0
+        _prefix_case("bf16", hq, 70, vis, t, hq, hkv, 128)
