@@ -624,7 +624,7 @@ tt_status tt_tree_gdn_bwd(int64_t n_tokens, int32_t hk, int32_t hv, int32_t dk, 
 #define TT_KERNEL_LOSS_SUM    5   /* weighted sum over rows                              */
 #define TT_KERNEL_REF_FWD     6   /* fp32-arithmetic kernels                             */
 #define TT_KERNEL_REF_BWD     7
-#define TT_KERNEL_ATTN_PLAN   8   /* work decomposition of the dK/dV pass                */
+#define TT_KERNEL_ATTN_PLAN   8   /* (now part of the dQ launch: always 0)                */
 #define TT_KERNEL_ATTN_REDUCE 9   /* sum of dK/dV partials of key tiles that were cut    */
 #define TT_KERNEL_LOSS_BWD    10  /* gradient of the loss with respect to the logits     */
 #define TT_KERNEL_ROPE        11  /* rotary position embedding                           */

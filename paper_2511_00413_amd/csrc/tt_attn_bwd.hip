@@ -7,7 +7,8 @@
 // in fp32 to caller-owned accumulators (Appendix "Float32 Gradient Accumulation").
 //
 // Kernels, no atomics (results are bit-reproducible); the dK/dV pass lives in tt_attn_dkdv.hip and runs
-// after the dQ pass, whose prologue also produces the per-row terms D_i and LSE_i log2 e:
+// after the dQ pass, whose prologue also produces the per-row terms D_i and LSE_i log2 e and whose first workgroup plans the work
+// of the dK/dV pass (tt_attn_plan.h):
 //   dkdv      column-parallel: one work item = a key tile of up to 256 keys x one kv head, 8 wavefronts
 //             x 32 keys; loops over the query heads of the group and over the 64-query steps that can
 //             see the keys -- a contiguous range [first key, max kend) because in DFS order a subtree
@@ -18,6 +19,7 @@
 //             query per lane, dQ^T[d,q] += K^T[d,key] dS^T[key,q].
 #include <hip/hip_runtime.h>
 #include <algorithm>
+#include "tt_attn_plan.h"
 #include "tt_kernels.h"
 #include "tt_mfma.h"
 
@@ -40,6 +42,8 @@ struct QSmem {
   int32_t kend[2][Q_BN];
   KTileMasks masks;
 };
+
+static_assert(sizeof(PlanSmem) <= sizeof(QSmem), "the planner takes the place of the tiles");
 
 struct QCtx {
   const AttnArgs& a;
@@ -181,15 +185,19 @@ __device__ __forceinline__ void dq_tile(const uint32_t (&ra)[8], const uint32_t 
 // unit of its own; the groups take every second key tile and add up their sums at the end.
 template <int NG, int LG_HEADS>
 __global__ void __launch_bounds__(NG * NTHREADS, 2)
-tree_attn_dq_kernel(AttnArgs a, int n_qtiles) {
+tree_attn_dq_kernel(AttnArgs a, int n_qtiles, KvPlan plan, int kv_workgroups) {
   extern __shared__ __align__(1024) unsigned char smem_raw[];
+  if (blockIdx.x == 0) {                             // (the first workgroup plans the dK/dV pass)
+    kv_plan<NG * NTHREADS>(*reinterpret_cast<PlanSmem*>(smem_raw), plan, a.kt_max, a.n_q, a.n_prefix, a.hq / a.hkv, a.hkv, kv_workgroups);
+    return;
+  }
   const int lane = threadIdx.x & 63;
   const int w_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int grp = NG == 1 ? 0 : w_all / (NTHREADS / 64), w = NG == 1 ? w_all : w_all % (NTHREADS / 64);
   QSmem& sm = reinterpret_cast<QSmem*>(smem_raw)[grp];
   const int c32 = lane & 31, hf = lane >> 5;
   const int G = a.hq / a.hkv;
-  const int bid = blockIdx.x;
+  const int bid = blockIdx.x - 1;
   const int kvh = bid % a.hkv;
   const int rest = bid / a.hkv;
   constexpr int HEADS = 1 << LG_HEADS;
@@ -376,8 +384,10 @@ hipError_t mfma_attn_bwd(const AttnArgs& args, hipStream_t st) {
                           : (lg == 0 ? tree_attn_dq_kernel<1, 0> : lg == 1 ? tree_attn_dq_kernel<1, 1> : tree_attn_dq_kernel<1, 2>);
     const int lds = (two ? 2 : 1) * (int)sizeof(QSmem);
     if (hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds)) return e;
+    KvPlan plan;
+    if (kv_plan_layout(a.workspace, a.n_q, a.n_prefix, a.hkv, &plan) > a.workspace_bytes) return hipErrorInvalidValue;
     KernelTimer timer(TT_KERNEL_ATTN_DQ, st);
-    kernel<<<(unsigned)blocks, (two ? 2 : 1) * NTHREADS, lds, st>>>(a, n_qtiles);
+    kernel<<<(unsigned)blocks + 1, (two ? 2 : 1) * NTHREADS, lds, st>>>(a, n_qtiles, plan, kv_workgroups(plan, a.hkv));
     if (hipError_t e = hipGetLastError()) return e;
   }
   return mfma_attn_dkdv(a, st);
