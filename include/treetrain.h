@@ -516,7 +516,7 @@ tt_status tt_tree_conv_bwd_static(int64_t n_tokens, int32_t channels, int32_t ke
  *   it depends only on the segment that saved the slot its first chunk loads.  Level 0 holds the
  *   segments that start from the initial state, level l + 1 those whose slot a level-l segment
  *   saves: sibling subtrees land in one level and are walked by different workgroups at the same
- *   time, one launch per level.  Outputs, segments in level order (inside a level the longest
+ *   time.  Outputs, segments in level order (inside a level the longest
  *   first, ties in chunk order):
  *     seg_chunk0, seg_chunk1 [n_segments]  first chunk and one past the last chunk
  *     level_off [n_levels + 1]             segments of level l: level_off[l] .. level_off[l+1]-1
