@@ -57,7 +57,7 @@ hipError_t mfma_attn_bwd(const AttnArgs& a, hipStream_t st);
 bool attn_two_groups(const AttnArgs& a, int64_t blocks, int min_tiles);      // whether forward or dQ run two groups of waves
 int attn_lg_heads(const AttnArgs& a);                                            // log2 of the query heads per workgroup of both
 size_t mfma_attn_workspace(int n_q, int n_prefix, int hq, int hkv, int d, bool backward);
-// dK/dV pass of the backward (tt_attn_dkdv.hip); a.workspace must hold mfma_attn_dkdv_workspace bytes
+// dK/dV pass of the backward (tt_attn_dkdv.hip); a.workspace must hold mfma_attn_dkdv_workspace bytes and the plan that the dQ launch wrote there
 hipError_t mfma_attn_dkdv(const AttnArgs& a, hipStream_t st);
 size_t mfma_attn_dkdv_workspace(int n_q, int n_prefix, int hkv);
 
