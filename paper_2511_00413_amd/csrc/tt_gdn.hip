@@ -26,6 +26,7 @@
 //     dS0 = exp(gamma_last) dS1 + Q^T (scale exp(gamma) * dO) - K^T (beta exp(gamma) * dR)
 #include <hip/hip_runtime.h>
 #include <algorithm>
+#include "tt_gdn_order.h"
 #include "tt_internal.h"
 #include "tt_kernels.h"
 #include "tt_mfma.h"
@@ -50,6 +51,16 @@ constexpr int REC_ELEMS = REC_P + 6 * FRAG;                      // 19 KB
 __device__ __forceinline__ int t_piece(int lane, int f) { return lane ^ (lane >> 5 << 2) ^ ((f & 1) << 3); }
 static_assert(REC_ELEMS == GDN_REC_ELEMS && REC_ROW == GDN_REC_ROW && REC_ELEMS * 2 == 19 * 1024, "whole 1 KB pieces; shared with the finish kernel");
 
+// What scheduled walks synchronise with, per value head and saved state, or gradient of a segment: whether the waves that hold its four
+// blocks of columns have stored it; and, in those of state 0 and segment 0, how many workgroups of a column of the grid have started
+// (a head has one column, or two).  16 bytes each: hundreds of waves look at the flags of one state, and with 4 bytes for a head, all
+// heads in one line of memory, the forward walks took 6 us longer (16406 tokens of 16 / 32 heads).
+struct WalkSync {
+  uint8_t stored[4];
+  int started[2], unused;
+};
+static_assert(sizeof(WalkSync) == 16, "as the workspaces count them");
+
 constexpr int WALK_LEVELS = 32;
 struct GdnArgs {
   int hk, hv, n_chunks;              // hk, hv: heads of the tensors (their strides)
@@ -60,11 +71,13 @@ struct GdnArgs {
   const int32_t *chunk_tok0, *chunk_len, *chunk_src, *chunk_dst;
   const int32_t* chunk_cap;          // nullptr, or per chunk: -1 / index into state_out
   const int32_t *seg_chunk0, *seg_chunk1;   // nullptr (one segment: all chunks), or the chunk ranges of the segments
-  int seg_base, n_segments;          // first segment of this launch (blockIdx.y counts from it, in level order), segments in all
+  int seg_base, n_segments;          // place of this launch's first workgroups (blockIdx.y counts from it), segments in all
   int n_levels, level_off[WALK_LEVELS + 1];       // reverse walk: the levels' first segments, or n_levels = 0 (more than WALK_LEVELS)
   int hv_n;                          // value heads of this launch
-  int* flags;                        // scheduled walks: [n_slots][hv_n][4] states saved, then [n_segments][hv_n][4] gradients stored, by wave
-  int n_flags, seg_flags;            // cleared by the prepare kernel; where the second part begins
+  WalkSync *slot_sync, *seg_sync;    // scheduled walks: [n_slots][hv_n], [n_segments][hv_n] behind it
+  int n_sync;                        // cleared by the prepare kernel, from slot_sync on
+  WalkSync* tickets;                 // nullptr (no segment waits for another), or whose `started` this walk counts in
+  int max_polls;                     // after which a wait gives up
   const float* initial_state;        // nullptr (zero) or [hv][128][128]: the state roots start from
   float* state_out;                  // [n_capture][hv][128][128]
   __bf16* o;                         // [N][hv][128]
@@ -105,7 +118,7 @@ struct PrepSmem {
 template <bool BWD>
 __global__ __launch_bounds__(G_THREADS, 3) void gdn_prepare_kernel(GdnArgs a) {
   __shared__ __attribute__((aligned(1024))) PrepSmem sm;
-  for (int i = (int)blockIdx.x * G_THREADS + (int)threadIdx.x; i < a.n_flags; i += (int)gridDim.x * G_THREADS) a.flags[i] = 0;
+  for (int i = (int)blockIdx.x * G_THREADS + (int)threadIdx.x; i < a.n_sync; i += (int)gridDim.x * G_THREADS) a.slot_sync[i] = WalkSync{};
   const int rep = a.hv / a.hk;
   int chunk, kh;
   if (!gdn_group_order(blockIdx.x, a.n_chunks, a.hk_n, 1, chunk, kh)) return;
@@ -298,6 +311,25 @@ __device__ __forceinline__ int walk_head(const GdnArgs& a, int id) {
   const int rep = a.hv / a.hk;
   return a.hk_n % 8 == 0 ? ((id >> 3) / rep * 8 + (id & 7)) * rep + (id >> 3) % rep : id;
 }
+// Which segment a workgroup takes: its place in the walk's order is its ticket, the number of workgroups of its column (blockIdx.x) that
+// have started before it.  The order in which the hardware starts workgroups is not documented, and with walks of two streams on the
+// chip the first one that is not finished may not have been started at all: 4 heads' workgroups of one walk wait on XCD 0 for one
+// that has no room on XCD 1, where those of the other walk wait for one that has none on XCD 0.  (16406 tokens of 16 / 32 heads, places
+// from block ids / from tickets: forward 257.8 / 257.7 us, backward 913.7 / 914.4.)
+template <bool REVERSE>
+__device__ __forceinline__ void walk_start(const GdnArgs& a, int half, int lane, ChunkMeta& meta, int& seg, int& c_begin, int& c_end) {
+  __shared__ int place_of_all;
+  if (a.tickets) {
+    if (threadIdx.x == 0)
+      place_of_all = __hip_atomic_fetch_add(&a.tickets[(int)blockIdx.x - half * a.hv_n].started[half], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+  }
+  const int place = __builtin_amdgcn_readfirstlane(a.tickets ? place_of_all : a.seg_base + (int)blockIdx.y);
+  seg = REVERSE ? reverse_walk_segment(place, a.n_segments, a.n_levels, a.level_off) : place;
+  c_begin = __builtin_amdgcn_readfirstlane(a.seg_chunk0 ? a.seg_chunk0[seg] : 0);
+  c_end = __builtin_amdgcn_readfirstlane(a.seg_chunk1 ? a.seg_chunk1[seg] : a.n_chunks);
+  meta.load(a, REVERSE ? max(c_end - 64, 0) : c_begin, lane);
+}
 __device__ __forceinline__ void walk_barrier() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 __device__ __forceinline__ void fence() { __builtin_amdgcn_sched_barrier(0); }
 
@@ -488,8 +520,9 @@ struct ScanState {
   // where a chunk does not continue the previous one: a saved node-end state, or the state handed in for the roots
   __device__ __forceinline__ void enter(const GdnArgs& a, int src, int h, int lane, int w) {
     if (src >= 0) {
-      if (a.seg_chunk0) wait_for(a, 0, src, h, w);
+      const bool saved = !a.seg_chunk0 || wait_for(a, a.slot_sync, src, h, w);
       get<true>(a.slots + ((size_t)src * a.hv + h) * (GD * GD), lane, w);
+      if (!saved) spoil();
     } else if (a.initial_state) {
       get<false>(a.initial_state + (size_t)h * (GD * GD), lane, w);
     } else {
@@ -500,26 +533,37 @@ struct ScanState {
   __device__ __forceinline__ void leave(const GdnArgs& a, int dst, int cap, int h, int lane, int w) const {
     if (dst >= 0) {
       put<true>(a.slots + ((size_t)dst * a.hv + h) * (GD * GD), lane, w);
-      publish(a, 0, dst, h, lane, w);
+      publish(a, a.slot_sync, dst, h, lane, w);
     }
     if (cap >= 0) put<false>(a.state_out + ((size_t)cap * a.hv + h) * (GD * GD), lane, w);
   }
   // What a segment starts from comes from segments of earlier levels, of the same launch: a flag per state and wave (a wave needs
   // the columns that its like in the other workgroup holds).  The stores have reached memory when the flag is set.
-  __device__ static __forceinline__ void publish(const GdnArgs& a, int base, int i, int h, int lane, int w) {
+  __device__ static __forceinline__ void publish(const GdnArgs& a, WalkSync* sync, int i, int h, int lane, int w) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if (lane == 0 && a.seg_chunk0) __hip_atomic_store(a.flags + base + (i * a.hv_n + h) * 4 + w, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane == 0 && a.seg_chunk0) __hip_atomic_store(&sync[(size_t)i * a.hv_n + h].stored[w], (uint8_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  // Every wait ends: workgroups start in the order of their ids on every XCD, and a workgroup waits only for ones with smaller ids, so
-  // of those running the first has nothing left to wait for.  (With a schedule that is not one of this program, whose levels
-  // do not hold, it ends after some seconds.)
-  __device__ static __forceinline__ void wait_for(const GdnArgs& a, int base, int i, int h, int w) {
-    const int* flag = a.flags + base + (i * a.hv_n + h) * 4 + w;
-    for (int n = 0; n < (1 << 22); n++) {
-      if (__builtin_amdgcn_readfirstlane(__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) break;
+  // Every wait ends: the workgroups of a column of the grid (a head's, or half a head's) take their segments by ticket (walk_start), so
+  // that whoever is waited for, being of the same column and earlier in the order, has a smaller ticket and is running, whatever the
+  // order in which workgroups are started and whatever else is on the chip; of those running the first has nothing left to wait for.
+  // With a schedule that is not one of this program (a state that no segment saves) the wait gives up after a time that no
+  // walk takes, 75 times a step for every chunk of the call, and what depends on it becomes NaN.
+  __device__ static __forceinline__ bool wait_for(const GdnArgs& a, const WalkSync* sync, int i, int h, int w) {
+    const uint8_t* flag = &sync[(size_t)i * a.hv_n + h].stored[w];
+    bool there = false;
+    for (int n = 0; n < a.max_polls; n++) {
+      there = __builtin_amdgcn_readfirstlane(__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+      if (there) break;
       __builtin_amdgcn_s_sleep(4);
     }
     asm volatile("" ::: "memory");
+    return there;
+  }
+  __device__ __forceinline__ void spoil() {
+#pragma unroll
+    for (int kt = 0; kt < 4; kt++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) s[kt][r] = __builtin_nanf("");
   }
 };
 
@@ -671,14 +715,13 @@ __global__ __launch_bounds__(G_THREADS, 1) void gdn_scan_kernel(GdnArgs a) {
   __shared__ __attribute__((aligned(1024))) unsigned char sm[SCAN_LDS];
   const int lane = threadIdx.x & 63, c = lane & 31, hf = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int h = walk_head(a, blockIdx.x), seg = a.seg_base + blockIdx.y;
-  const int c_begin = __builtin_amdgcn_readfirstlane(a.seg_chunk0 ? a.seg_chunk0[seg] : 0);
-  const int c_end = __builtin_amdgcn_readfirstlane(a.seg_chunk1 ? a.seg_chunk1[seg] : a.n_chunks);
+  const int h = walk_head(a, blockIdx.x);
+  ChunkMeta meta;
+  int seg, c_begin, c_end;
+  walk_start<false>(a, 0, lane, meta, seg, c_begin, c_end);
   ScanAddr ad;
   ad.set(__builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)&sm), lane, w);
   const uint32_t o_at[2] = {(uint32_t)c * (uint32_t)a.hv * (GD * 2) + 16u * hf, (uint32_t)(32 + c) * (uint32_t)a.hv * (GD * 2) + 16u * hf};
-  ChunkMeta meta;
-  meta.load(a, c_begin, lane);
   ChunkCopy<WALK_FWD, 4> copy;
   copy.start(a, h, ad.rec);
   copy.point(c_begin, meta.get(meta.tok0, c_begin), meta.get(meta.len, c_begin) & 255, w, lane);
@@ -821,13 +864,12 @@ __global__ __launch_bounds__(64 * WAVES, 1) void gdn_fwalk_kernel(GdnArgs a) {
   const int lane = threadIdx.x & 63;
   const int half = WAVES < 4 ? (int)blockIdx.x / a.hv_n : 0;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) + WAVES * half;
-  const int h = walk_head(a, blockIdx.x - half * a.hv_n), seg = a.seg_base + blockIdx.y;
-  const int c_begin = __builtin_amdgcn_readfirstlane(a.seg_chunk0 ? a.seg_chunk0[seg] : 0);
-  const int c_end = __builtin_amdgcn_readfirstlane(a.seg_chunk1 ? a.seg_chunk1[seg] : a.n_chunks);
+  const int h = walk_head(a, blockIdx.x - half * a.hv_n);
+  ChunkMeta meta;
+  int seg, c_begin, c_end;
+  walk_start<false>(a, half, lane, meta, seg, c_begin, c_end);
   ScanAddr ad;
   ad.set(__builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)&sm), lane, w);
-  ChunkMeta meta;
-  meta.load(a, c_begin, lane);
   ChunkCopy<WALK_SAVE, WAVES> copy;
   copy.start(a, h, ad.rec);
   copy.point(c_begin, meta.get(meta.tok0, c_begin), meta.get(meta.len, c_begin) & 255, w % WAVES, lane);
@@ -1007,16 +1049,12 @@ __global__ __launch_bounds__(64 * WAVES, 1) void gdn_rwalk_kernel(GdnArgs a) {
   const int half = WAVES < 4 ? (int)blockIdx.x / a.hv_n : 0;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) + WAVES * half;
   const int h = walk_head(a, blockIdx.x - half * a.hv_n);
-  // last level first, a level's segments in their order (the longest first)
-  int seg = a.n_segments - 1 - (a.seg_base + (int)blockIdx.y);
-  for (int l = 0; l < a.n_levels; l++)
-    if (seg >= a.level_off[l] && seg < a.level_off[l + 1]) { seg = a.level_off[l] + a.level_off[l + 1] - 1 - seg; break; }
-  const int c_begin = __builtin_amdgcn_readfirstlane(a.seg_chunk0 ? a.seg_chunk0[seg] : 0);
-  const int last = __builtin_amdgcn_readfirstlane(a.seg_chunk1 ? a.seg_chunk1[seg] : a.n_chunks) - 1;
+  ChunkMeta meta;
+  int seg, c_begin, c_end;
+  walk_start<true>(a, half, lane, meta, seg, c_begin, c_end);
+  const int last = c_end - 1;
   ScanAddr ad;
   ad.set(__builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)&sm), lane, w);
-  ChunkMeta meta;
-  meta.load(a, max(last - 63, 0), lane);
   ChunkCopy<WALK_REV, WAVES> copy;
   copy.start(a, h, ad.rec);
   copy.point(last, meta.get(meta.tok0, last), meta.get(meta.len, last) & 255, w % WAVES, lane);
@@ -1042,8 +1080,9 @@ __global__ __launch_bounds__(64 * WAVES, 1) void gdn_rwalk_kernel(GdnArgs a) {
           const int k1 = a.slot_cons_off[dst + 1];
           for (int k = a.slot_cons_off[dst]; k < k1; k++) {
             const int reader = a.slot_cons[k];
-            ScanState::wait_for(a, a.seg_flags, reader, h, w);
+            const bool stored = ScanState::wait_for(a, a.seg_sync, reader, h, w);
             st.add<true>(a.sv.seg_grad + ((size_t)reader * a.hv + h) * (GD * GD), lane, w);
+            if (!stored) st.spoil();
           }
         } else {
           st.add<true>(a.sv.slot_grad + ((size_t)dst * a.hv + h) * (GD * GD), lane, w);
@@ -1066,7 +1105,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void gdn_rwalk_kernel(GdnArgs a) {
         // scheduled walk: this is the first chunk of segment `seg`; its entering state's gradient is stored in the
         // segment's own array -- the slot's saver, or the sum over the roots, picks it up
         st.put<true>(a.sv.seg_grad + ((size_t)seg * a.hv + h) * (GD * GD), lane, w);
-        ScanState::publish(a, a.seg_flags, seg, h, lane, w);
+        ScanState::publish(a, a.seg_sync, seg, h, lane, w);
       } else if (src >= 0) {
         float* g = a.sv.slot_grad + ((size_t)src * a.hv + h) * (GD * GD);
         st.add<true>(g, lane, w);
@@ -1109,7 +1148,7 @@ size_t gdn_workspace(int n_chunks, int n_slots, int hv) {
 }
 
 // Walks the chunk program: one workgroup per head and segment, segments in level order (without a schedule one segment).  The
-// levels are kept by the flags, not by launches: a launch per level cost 3 to 5 us each, and short segments stood still for the
+// levels are kept by the flags and tickets, not by launches: a launch per level cost 3 to 5 us each, and short segments stood still for the
 // longest of their level (16406 tokens of 16 / 32 heads, 4 levels: forward 286 -> 254 us, backward 959 -> 918; 1500 tokens in 8
 // levels, 4 / 8 heads: backward 280 -> 256).
 //
@@ -1143,6 +1182,15 @@ static hipError_t launch_walk(Kernel kernel4, Kernel kernel2, GdnArgs& a, const 
   return hipSuccess;
 }
 
+// (Without saved states nobody waits, and no places are counted.)
+static void set_sync(GdnArgs& a, void* sync, int n_slots, int n_segments, const tt_gdn_schedule* sched) {
+  a.slot_sync = (WalkSync*)sync;
+  a.seg_sync = a.slot_sync + (size_t)n_slots * a.hv_n;
+  a.n_sync = sched ? (n_slots + n_segments) * a.hv_n : 0;
+  a.tickets = sched && n_slots > 0 ? a.slot_sync : nullptr;
+  a.max_polls = (1 << 18) + 256 * a.n_chunks;       // (a poll takes 1 us and more)
+}
+
 hipError_t gdn_fwd(int64_t n_tokens, int hk, int hv, float scale, const void* q, const void* k, const void* v, const float* g,
                    const float* beta, int n_chunks, const int32_t* chunk_tok0, const int32_t* chunk_len, const int32_t* chunk_src,
                    const int32_t* chunk_dst, int n_slots, const int32_t* chunk_cap, const tt_gdn_schedule* sched,
@@ -1156,8 +1204,8 @@ hipError_t gdn_fwd(int64_t n_tokens, int hk, int hv, float scale, const void* q,
   a.o = (__bf16*)o;
   a.rec = (__bf16*)workspace;
   a.slots = (float*)((char*)workspace + align256((size_t)n_chunks * hv * REC_ELEMS * 2));
-  a.flags = (int*)((char*)a.slots + align256((size_t)n_slots * hv * GD * GD * 4));
-  a.hv_n = hv; a.n_flags = n_slots * hv * 4;
+  a.hv_n = hv;
+  set_sync(a, (char*)a.slots + align256((size_t)n_slots * hv * GD * GD * 4), n_slots, 0, sched);
   {
     KernelTimer t(TT_KERNEL_GDN_PREPARE, st);
     gdn_prepare_kernel<false><<<gdn_group_order_grid(n_chunks, hk, 1), G_THREADS, 0, st>>>(a);
@@ -1176,10 +1224,8 @@ hipError_t gdn_bwd_prepare_and_walks(const GdnBwdArgs& b, const GdnBwdSaved& sv,
   a.initial_state = b.initial_state;
   a.rec = (__bf16*)sv.rec; a.slots = sv.slots; a.sv = sv; a.d_o = (const __bf16*)b.d_o;
   a.d_state_out = b.d_state_out; a.d_initial_state = b.d_initial_state;
-  a.flags = sv.flags;
   a.hv_n = b.hv_n;
-  a.seg_flags = b.n_slots * b.hv_n * 4;
-  a.n_flags = a.seg_flags + (b.sched ? b.sched->n_segments : 0) * b.hv_n * 4;
+  set_sync(a, sv.sync, b.n_slots, b.sched ? b.sched->n_segments : 0, b.sched);
   {
     KernelTimer t(TT_KERNEL_GDN_PREPARE, st);
     gdn_prepare_kernel<true><<<gdn_group_order_grid(b.n_chunks, a.hk_n, 1), G_THREADS, 0, st>>>(a);
@@ -1190,6 +1236,7 @@ hipError_t gdn_bwd_prepare_and_walks(const GdnBwdArgs& b, const GdnBwdSaved& sv,
     if (hipError_t e = launch_walk(gdn_fwalk_kernel<4>, gdn_fwalk_kernel<2>, a, b.sched, st); e != hipSuccess) return e;
   }
   a.chunk_cap = b.d_state_out ? b.chunk_cap : nullptr;
+  if (a.tickets) a.tickets = a.seg_sync;
   KernelTimer t(TT_KERNEL_GDN_BWD_RSCAN, st);
   if (b.sched) { a.slot_cons_off = b.sched->slot_cons_off; a.slot_cons = b.sched->slot_cons; }
   if (hipError_t e = launch_walk(gdn_rwalk_kernel<4>, gdn_rwalk_kernel<2>, a, b.sched, st); e != hipSuccess) return e;

@@ -528,7 +528,7 @@ size_t carve(char* p, int64_t n_tokens, int n_chunks, int n_slots, int n_segment
   t.sv.slots = (float*)take((size_t)n_slots * hv * GD * GD * 4);
   t.sv.slot_grad = (float*)take((size_t)n_slots * hv * GD * GD * 4);
   t.sv.seg_grad = (float*)take((size_t)n_segments * hv * GD * GD * 4);
-  t.sv.flags = (int*)take((size_t)(n_slots + n_segments) * hv_n * 16);
+  t.sv.sync = take((size_t)(n_slots + n_segments) * hv_n * 16);
   if (split) {
     t.dqh = (float*)take((size_t)n_tokens * hv_n * GD * 4);
     t.dkh = (float*)take((size_t)n_tokens * hv_n * GD * 4);

@@ -115,7 +115,7 @@ struct GdnBwdSaved {
   float* slots;      // [n_slots][hv] saved node-end states
   float* slot_grad;  // [n_slots][hv] their gradients (zeroed by the caller); walk in sequence order only
   float* seg_grad;   // [n_segments][hv] gradient of the state every segment starts from; scheduled walk only
-  int* flags;        // [n_slots + n_segments][value heads of the pass][4]: stored
+  void* sync;        // [n_slots + n_segments][value heads of the pass] of 16 bytes: what the walks synchronise with
 };
 // Position of a lane's 16 bytes in a saved fragment: the two halves of the wave lie 512 bytes apart, where the transposing reads of
 // the finish kernel would meet in the same banks; the upper half is shifted by 64 bytes.

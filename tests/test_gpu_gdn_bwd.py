@@ -248,3 +248,53 @@ def test_two_streams_at_once():
         torch.cuda.synchronize()
         for got, want in zip(outs, alone):
             assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+@pytest.mark.parametrize("hk,hv", [(1, 2), (2, 4), (3, 12), (10, 20)])
+def test_two_streams_at_once_rows_of_any_length(hk, hv):
+    """Rows of the walks' grids that are no multiple of eight workgroups: a segment and the one it waits for then run on different
+    XCDs.  Forward and backward of two trees in flight on two streams: the results of each alone, bit for bit."""
+    trees = [_spine(12), W.random_tree(996, n_nodes=30, lo=1, hi=200, n_roots=2)]
+    ins, plans, alone = [], [], []
+
+    def both(i):
+        return (T.tree_gdn_fwd(*ins[i][:5], plans[i]),) + T.tree_gdn_bwd(*ins[i], plans[i])
+
+    for i, t in enumerate(trees):
+        ins.append([x.cuda() for x in _inputs(sum(t.seg_len), hk, hv, 190 + i)])
+        plans.append(T.tree_gdn_plan(t.parent, t.seg_len).to_device())
+        alone.append(both(i))
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in trees]
+    for _ in range(3):
+        outs = [None, None]
+        for i, st in enumerate(streams):
+            with torch.cuda.stream(st):
+                outs[i] = both(i)
+        torch.cuda.synchronize()
+        for got, want in zip(outs, alone):
+            assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+def test_a_wait_that_gives_up_leaves_nan():
+    """A chunk program that does not fit its schedule: a state that no segment saves, a gradient that no reader stores.  The walks'
+    bounded waits end, what depends on them is NaN and the rest is as it should be."""
+    seg = [70, 30, 40]
+    ins = [x.cuda() for x in _inputs(sum(seg), 1, 2, 5)]
+    plan = T.tree_gdn_plan([-1, 0, 0], seg).to_device()
+    o, (dq, dk, dv, dg, db) = T.tree_gdn_fwd(*ins[:5], plan), T.tree_gdn_bwd(*ins, plan)
+    torch.cuda.synchronize()
+    saved = plan.device["chunk_dst"].clone()
+    plan.device["chunk_dst"].fill_(-1)                # the root's segment saves nothing: its children wait in vain
+    print("[case] gdn: nobody saves the children's state", flush=True)
+    o2, (dq2, dk2, dv2, dg2, db2) = T.tree_gdn_fwd(*ins[:5], plan), T.tree_gdn_bwd(*ins, plan)
+    torch.cuda.synchronize()
+    assert torch.equal(o2[:70], o[:70]) and torch.equal(dq2[:70], dq[:70])
+    assert all(x[70:].isnan().all() for x in (o2, dq2, dg2, db2))
+    plan.device["chunk_dst"].copy_(saved)
+    plan.device["chunk_src"].clamp_(max=-1)           # the children start from zero and store no gradient: the root waits in vain
+    print("[case] gdn: nobody stores the root's gradient", flush=True)
+    dq3, dk3, dv3, dg3, db3 = T.tree_gdn_bwd(*ins, plan)
+    torch.cuda.synchronize()
+    assert all(x[70:].isfinite().all() for x in (dq3, dk3, dv3, dg3, db3))
+    assert torch.equal(dq3[:70], dq[:70]) and all(x[:70].isnan().all() for x in (dk3, dv3, dg3, db3))
