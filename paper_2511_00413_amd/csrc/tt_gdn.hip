@@ -26,6 +26,7 @@
 //     dS0 = exp(gamma_last) dS1 + Q^T (scale exp(gamma) * dO) - K^T (beta exp(gamma) * dR)
 #include <hip/hip_runtime.h>
 #include <algorithm>
+#include <type_traits>
 #include "tt_gdn_order.h"
 #include "tt_internal.h"
 #include "tt_kernels.h"
@@ -330,17 +331,19 @@ __device__ __forceinline__ void walk_start(const GdnArgs& a, int half, int lane,
   c_end = __builtin_amdgcn_readfirstlane(a.seg_chunk1 ? a.seg_chunk1[seg] : a.n_chunks);
   meta.load(a, REVERSE ? max(c_end - 64, 0) : c_begin, lane);
 }
+__device__ __forceinline__ void walker_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }      // (of waves that copy nothing)
 __device__ __forceinline__ void walk_barrier() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 __device__ __forceinline__ void fence() { __builtin_amdgcn_sched_barrier(0); }
 
 // The copies of one chunk's operands, pieces of 1 KB per wave.  They are requested one by one between the products of the
 // chunk before (piece): a wave that requests them all at once stands still for 2000 of a step's 7000 cycles.
 // WALK_FWD: Q, K, V and the record (17 pieces); WALK_SAVE: K, V and the record up to the row factors (12); WALK_REV: Q, K, dO
-// in V's place and the record (17).
+// in V's place and the record (17).  A piece is copied by the four waves of a workgroup, or by two in two turns.
 enum { WALK_FWD, WALK_SAVE, WALK_REV };
+struct NoCopy { static constexpr int N = 0; };           // somebody else's
 template <int WALK, int WAVES>
 struct ChunkCopy {
-  static constexpr int TURNS = 4 / WAVES;   // a piece is copied by four waves, or by two in two turns
+  static constexpr int TURNS = 4 / WAVES;
   static constexpr int REC_KB = WALK == WALK_SAVE ? REC_P * 2 / 1024 : REC_B / 1024, N = (WALK == WALK_SAVE ? 8 : 12) + (REC_KB + 3) / 4;
   const char *k0, *q0, *v0, *rec0;      // of token 0 / chunk 0: K and Q of the key head, V of the value head, the records of the head
   uint32_t k_row, v_row;                // bytes per token
@@ -753,16 +756,18 @@ __global__ __launch_bounds__(G_THREADS, 1) void gdn_scan_kernel(GdnArgs a) {
 // ---- forward walk of the backward: the scan without its output; S0 and Vn of every chunk are saved, rounded -----------
 // Bound by memory where the chip is full (93 KB in and out per chunk and head), by a step's own instructions and LDS round trips where it is not:
 // 182 us at 16406 tokens of 32 heads (235 in the form before).
-template <int WAVES>
-__device__ __forceinline__ void fwalk_step(const GdnArgs& a, ScanState& st, const ScanAddr& ad, const ChunkCopy<WALK_SAVE, WAVES>& copy, bool has_next,
+template <class Copy>
+__device__ __forceinline__ void fwalk_step(const GdnArgs& a, ScanState& st, const ScanAddr& ad, const Copy& copy, bool has_next,
                                            size_t op, int w, int lane) {
   const int c = lane & 31;
   f32x16(&s)[4] = st.s;
   bf16x8(&sb)[8] = st.sb;
   auto copies = [&](int p, int n) {
-    if (has_next) {
+    if constexpr (Copy::N > 0) {
+      if (has_next) {
 #pragma unroll
-      for (int i = p; i < p + n; i++) copy.piece(i, w % WAVES, lane);
+        for (int i = p; i < p + n; i++) copy.piece(i, w, lane);
+      }
     }
   };
   auto read_row = [&](int i) { return lds_b128(ad.row[i >> 1], L_K + (i & 1) * 32 * TILE_ROW * 2); };
@@ -858,23 +863,55 @@ __device__ __forceinline__ void fwalk_step(const GdnArgs& a, ScanState& st, cons
   sb[4] = cvt_regs(s[2], 0); sb[5] = cvt_regs(s[2], 8);
 }
 
+// The two-wave forms of the walks have two waves more that copy the operands of both: on its SIMD nothing but a walking wave's own chain
+// counts, and the copies, twice as many per wave there, are out of it (and so is the wait for its stores at a step's end).  Backward of chains of
+// 1500 / 4000 / 8000 tokens of 8 heads 227 -> 197 / 367 -> 308 / 588 -> 512 us; and with a pause of 128 cycles behind every piece, so that
+// they don't take the LDS from the walking waves' first reads, 197 / 304 / 485.
+template <int WALK>
+__device__ __forceinline__ void walk_copies(const GdnArgs& a, ChunkMeta& meta, uint32_t lds, int h, int first, int n, int w, int lane) {
+  constexpr int STEP = WALK == WALK_REV ? -1 : 1;
+  ChunkCopy<WALK, 2> copy;
+  copy.start(a, h, lds);
+  int sign = 1;
+  for (int i = 0, chunk = first; i < n; i++, chunk += STEP) {      // the operands of step i, into the image that step i - 2 has left
+    if (STEP > 0 && chunk - meta.first == 64) meta.load(a, chunk, lane);
+    if (STEP < 0 && chunk < meta.first) meta.load(a, max(chunk - 63, 0), lane);
+    copy.point(chunk, meta.get(meta.tok0, chunk), meta.get(meta.len, chunk) & 255, w, lane);
+#pragma unroll
+    for (int p = 0; p < copy.N; p++) {
+      copy.piece(p, w, lane);
+      __builtin_amdgcn_s_sleep(2);
+    }
+    walk_barrier();                     // (the one in front of step i)
+    copy.other_image(sign);
+    sign = -sign;
+  }
+}
+
 template <int WAVES>
-__global__ __launch_bounds__(64 * WAVES, 1) void gdn_fwalk_kernel(GdnArgs a) {
+__global__ __launch_bounds__(G_THREADS, 1) void gdn_fwalk_kernel(GdnArgs a) {
   __shared__ __attribute__((aligned(1024))) unsigned char sm[SCAN_LDS];
-  const int lane = threadIdx.x & 63;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int half = WAVES < 4 ? (int)blockIdx.x / a.hv_n : 0;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) + WAVES * half;
+  const int w = wave + WAVES * half;
   const int h = walk_head(a, blockIdx.x - half * a.hv_n);
   ChunkMeta meta;
   int seg, c_begin, c_end;
   walk_start<false>(a, half, lane, meta, seg, c_begin, c_end);
+  const uint32_t lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)&sm);
+  if (WAVES < 4 && wave >= WAVES) {
+    walk_copies<WALK_SAVE>(a, meta, lds, h, c_begin, c_end - c_begin, wave - WAVES, lane);
+    return;
+  }
   ScanAddr ad;
-  ad.set(__builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)&sm), lane, w);
-  ChunkCopy<WALK_SAVE, WAVES> copy;
-  copy.start(a, h, ad.rec);
-  copy.point(c_begin, meta.get(meta.tok0, c_begin), meta.get(meta.len, c_begin) & 255, w % WAVES, lane);
+  ad.set(lds, lane, w);
+  std::conditional_t<WAVES == 4, ChunkCopy<WALK_SAVE, 4>, NoCopy> copy;
+  if constexpr (WAVES == 4) {
+    copy.start(a, h, ad.rec);
+    copy.point(c_begin, meta.get(meta.tok0, c_begin), meta.get(meta.len, c_begin) & 255, w, lane);
 #pragma unroll
-  for (int p = 0; p < copy.N; p++) copy.piece(p, w % WAVES, lane);
+    for (int p = 0; p < copy.N; p++) copy.piece(p, w, lane);
+  }
   ScanState st;
   st.zero();
   int sign = 1;                         // where the other image lies
@@ -884,10 +921,14 @@ __global__ __launch_bounds__(64 * WAVES, 1) void gdn_fwalk_kernel(GdnArgs a) {
     const bool has_next = chunk + 1 < c_end;
     if (has_next) {
       if (chunk + 1 - meta.first == 64) meta.load(a, chunk + 1, lane);
-      copy.point(chunk + 1, meta.get(meta.tok0, chunk + 1), meta.get(meta.len, chunk + 1) & 255, w % WAVES, lane);
+      if constexpr (WAVES == 4) copy.point(chunk + 1, meta.get(meta.tok0, chunk + 1), meta.get(meta.len, chunk + 1) & 255, w, lane);
     }
-    walk_barrier();
-    copy.other_image(sign);
+    if constexpr (WAVES == 4) {
+      walk_barrier();
+      copy.other_image(sign);
+    } else {
+      walker_barrier();
+    }
     fwalk_step(a, st, ad, copy, has_next, op_index(a, chunk, h), w, lane);
     if (bits & ChunkMeta::LEAVES) st.leave(a, dst, -1, h, lane, w);         // (nothing is captured here)
     ad.other_image(sign);
@@ -900,16 +941,18 @@ __global__ __launch_bounds__(64 * WAVES, 1) void gdn_fwalk_kernel(GdnArgs a) {
 // The state's gradient in the place of the state, last chunk of a segment to first; the leaving state's gradient dS1 and dR of
 // every chunk are saved, rounded.  The scan's structure: K dS1 -> dVn -> dR is the chain, Q^T dO beside it.  257 us at 16406 tokens of
 // 32 heads (303 in the form before, which left the transposed solve to the finish kernel).
-template <int WAVES>
-__device__ __forceinline__ void rwalk_step(const GdnArgs& a, ScanState& st, const ScanAddr& ad, const ChunkCopy<WALK_REV, WAVES>& copy, bool has_next,
+template <class Copy>
+__device__ __forceinline__ void rwalk_step(const GdnArgs& a, ScanState& st, const ScanAddr& ad, const Copy& copy, bool has_next,
                                            size_t op, int len, int w, int lane) {
   const int c = lane & 31, hf = lane >> 5;
   f32x16(&s)[4] = st.s;
   bf16x8(&sb)[8] = st.sb;
   auto copies = [&](int p, int n) {
-    if (has_next) {
+    if constexpr (Copy::N > 0) {
+      if (has_next) {
 #pragma unroll
-      for (int i = p; i < p + n; i++) copy.piece(i, w % WAVES, lane);
+        for (int i = p; i < p + n; i++) copy.piece(i, w, lane);
+      }
     }
   };
   auto read_row = [&](int i) { return lds_b128(ad.row[i >> 1], L_K + (i & 1) * 32 * TILE_ROW * 2); };
@@ -1043,23 +1086,30 @@ __device__ __forceinline__ void rwalk_step(const GdnArgs& a, ScanState& st, cons
 }
 
 template <int WAVES>
-__global__ __launch_bounds__(64 * WAVES, 1) void gdn_rwalk_kernel(GdnArgs a) {
+__global__ __launch_bounds__(G_THREADS, 1) void gdn_rwalk_kernel(GdnArgs a) {
   __shared__ __attribute__((aligned(1024))) unsigned char sm[SCAN_LDS];
-  const int lane = threadIdx.x & 63;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int half = WAVES < 4 ? (int)blockIdx.x / a.hv_n : 0;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) + WAVES * half;
+  const int w = wave + WAVES * half;
   const int h = walk_head(a, blockIdx.x - half * a.hv_n);
   ChunkMeta meta;
   int seg, c_begin, c_end;
   walk_start<true>(a, half, lane, meta, seg, c_begin, c_end);
   const int last = c_end - 1;
+  const uint32_t lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)&sm);
+  if (WAVES < 4 && wave >= WAVES) {
+    walk_copies<WALK_REV>(a, meta, lds, h, last, c_end - c_begin, wave - WAVES, lane);
+    return;
+  }
   ScanAddr ad;
-  ad.set(__builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)&sm), lane, w);
-  ChunkCopy<WALK_REV, WAVES> copy;
-  copy.start(a, h, ad.rec);
-  copy.point(last, meta.get(meta.tok0, last), meta.get(meta.len, last) & 255, w % WAVES, lane);
+  ad.set(lds, lane, w);
+  std::conditional_t<WAVES == 4, ChunkCopy<WALK_REV, 4>, NoCopy> copy;
+  if constexpr (WAVES == 4) {
+    copy.start(a, h, ad.rec);
+    copy.point(last, meta.get(meta.tok0, last), meta.get(meta.len, last) & 255, w, lane);
 #pragma unroll
-  for (int p = 0; p < copy.N; p++) copy.piece(p, w % WAVES, lane);
+    for (int p = 0; p < copy.N; p++) copy.piece(p, w, lane);
+  }
   // The gradient of the state a segment's last chunk leaves starts from zero; so does, walking all chunks in sequence, that of a
   // chunk whose successor in the sequence did not continue from it.
   ScanState st;
@@ -1094,10 +1144,14 @@ __global__ __launch_bounds__(64 * WAVES, 1) void gdn_rwalk_kernel(GdnArgs a) {
     const bool has_next = chunk > c_begin;
     if (has_next) {
       if (chunk == meta.first) meta.load(a, max(chunk - 64, 0), lane);
-      copy.point(chunk - 1, meta.get(meta.tok0, chunk - 1), meta.get(meta.len, chunk - 1) & 255, w % WAVES, lane);
+      if constexpr (WAVES == 4) copy.point(chunk - 1, meta.get(meta.tok0, chunk - 1), meta.get(meta.len, chunk - 1) & 255, w, lane);
     }
-    walk_barrier();
-    copy.other_image(sign);
+    if constexpr (WAVES == 4) {
+      walk_barrier();
+      copy.other_image(sign);
+    } else {
+      walker_barrier();
+    }
     rwalk_step(a, st, ad, copy, has_next, op_index(a, chunk, h), bits & 255, w, lane);
     fresh = src != -2;
     if (src >= 0 || (src == -1 && a.d_initial_state)) {
@@ -1152,11 +1206,13 @@ size_t gdn_workspace(int n_chunks, int n_slots, int hv) {
 // longest of their level (16406 tokens of 16 / 32 heads, 4 levels: forward 286 -> 254 us, backward 959 -> 918; 1500 tokens in 8
 // levels, 4 / 8 heads: backward 280 -> 256).
 //
-// The backward's walks put a head on two workgroups of two waves where every level leaves most compute units idle:
-// a wave shares the LDS with one other instead of three.  Chains of 1500 / 8000 tokens of 8 heads 251 -> 243 / 586 -> 578 us, 16384
-// tokens of 32 heads 1574 -> 1470 (in the form before: 225, 550, 1843; deep chains of few heads lose, see gdn_scan_kernel); levels of 32 segments
-// of 8 heads (256 walks) are 2 to 3 % slower with it, and so is the scan everywhere.
-constexpr int NARROW_WALKS = 64;       // widest level, in walks (segments x heads)
+// The backward's walks put a head on two workgroups of two waves, and two that copy for them (walk_copies), as long as the walks of the
+// widest level all run side by side like that: a wave shares the LDS with one other instead of three.  Against the form before (a head on two
+// workgroups of eight waves that exchange the state through LDS) / two waves that copy for themselves / this: chains of 1500, 4000, 8000 tokens of
+// 8 heads 198 / 227 / 197, 314 / 367 / 304, 508 / 588 / 485 us; 16384 tokens of 32 heads 1752 / 1485 / 1441.  Four waves / this in levels of
+// 104 walks 224 / 197, of 128 371 / 337 and 203 / 186.  (Levels of 256 walks were 2 to 3 % slower with two waves, and so is the
+// scan everywhere.)
+constexpr int NARROW_WALKS = 128;      // widest level, in walks (segments x heads)
 template <class Kernel>
 static hipError_t launch_walk(Kernel kernel4, Kernel kernel2, GdnArgs& a, const tt_gdn_schedule* sched, hipStream_t st) {
   int widest = 1;
@@ -1167,7 +1223,7 @@ static hipError_t launch_walk(Kernel kernel4, Kernel kernel2, GdnArgs& a, const 
   a.seg_base = 0;
   if (!sched) {
     a.seg_chunk0 = a.seg_chunk1 = nullptr; a.n_segments = 1; a.n_levels = 0;
-    kernel<<<dim3(heads, 1), 64 * waves, 0, st>>>(a);
+    kernel<<<dim3(heads, 1), G_THREADS, 0, st>>>(a);
     return hipGetLastError();
   }
   a.seg_chunk0 = sched->seg_chunk0; a.seg_chunk1 = sched->seg_chunk1; a.n_segments = sched->n_segments;
@@ -1176,7 +1232,7 @@ static hipError_t launch_walk(Kernel kernel4, Kernel kernel2, GdnArgs& a, const 
   constexpr int MAX_Y = 65535;          // blocks of a launch along y
   for (; a.seg_base < a.n_segments; a.seg_base += MAX_Y) {
     const int n = a.n_segments - a.seg_base;
-    kernel<<<dim3(heads, (unsigned)(n < MAX_Y ? n : MAX_Y)), 64 * waves, 0, st>>>(a);
+    kernel<<<dim3(heads, (unsigned)(n < MAX_Y ? n : MAX_Y)), G_THREADS, 0, st>>>(a);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   }
   return hipSuccess;

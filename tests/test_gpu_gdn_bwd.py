@@ -298,3 +298,29 @@ def test_a_wait_that_gives_up_leaves_nan():
     torch.cuda.synchronize()
     assert all(x[70:].isfinite().all() for x in (dq3, dk3, dv3, dg3, db3))
     assert torch.equal(dq3[:70], dq[:70]) and all(x[:70].isnan().all() for x in (dk3, dv3, dg3, db3))
+
+
+def test_walks_of_two_and_of_four_waves():
+    """Levels of up to 128 walks (segments x heads) run with two waves per workgroup and two that copy for them, wider ones with four:
+    levels of 2 segments of 64 and of 65 heads, a node of more chunks than a wave holds scalars of, chunks of 1, 7, 40 and 64 tokens.
+    A head's arithmetic is the same in both, so its results are, bit for bit, those of that head alone; which are the oracle's."""
+    parent, seg = [-1, 0, 0, 1, 1], [65 * 64 + 7, 40, 70, 1, 129]
+    tree = W._mk(parent, seg, [1] * 5, "long")
+    _check(tree, 1, 1, 21)
+    plan = T.tree_gdn_plan(parent, seg, capture_nodes=[1]).to_device()
+    gen = torch.Generator().manual_seed(8)
+    ins = list(_inputs(sum(seg), 65, 65, 22)) + [torch.randn((65, 128, 128), generator=gen) * 0.1, torch.randn((1, 65, 128, 128), generator=gen) * 0.1]
+
+    def run(lo, hi):
+        x = [t[lo:hi] if i == 6 else t[:, lo:hi] for i, t in enumerate(ins)]
+        x = [t.contiguous().cuda() for t in x]
+        return T.tree_gdn_bwd(*x[:6], plan, initial_state=x[6], d_state_out=x[7], want_d_initial_state=True)
+
+    wide, narrow = run(0, 65), {h: run(h, h + 1) for h in (0, 37, 64)}
+    both = run(0, 64)
+    torch.cuda.synchronize()
+    for h, alone in narrow.items():
+        for i, (a, b, c) in enumerate(zip(wide, both, alone)):
+            cut = (lambda t, h=h, i=i: t[h:h + 1] if i == 5 else t[:, h:h + 1])
+            assert torch.equal(cut(a), c), (h, i)
+            assert h == 64 or torch.equal(cut(b), c), (h, i)
