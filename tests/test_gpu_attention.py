@@ -236,7 +236,7 @@ def test_bf16_two_wave_groups_prefix_and_strides():
     vis[:150] = 0
     vis[700:1000] = 0
     _prefix_case("bf16", 23, 2100, vis, W.random_tree(31, n_nodes=5, lo=20, hi=200), 4, 2, 128)
-    for n in (2048, 2049):                               # 256 and 272 workgroups
+    for n in (2048, 2049):               # 256 workgroups of two heads (and the planner's in dQ) and 260 of four
         _full_parity(W.random_tree(34, n_nodes=1, lo=n, hi=n), W.AttnDims(16, 2, 128, "bf16", 0.5), 6, label="two wave groups, line")
     t = W.chain_tree([900, 1200])
     meta = T.tree_build_meta(t.parent, t.seg_len)
@@ -361,3 +361,13 @@ def test_bf16_query_heads_that_share_a_workgroup(hq, hkv, n):
         vis = np.ones(70, dtype=np.uint8)
         vis[5:9] = 0
         _prefix_case("bf16", hq, 70, vis, t, hq, hkv, 128)
+
+
+def test_bf16_two_wave_groups_of_four_heads():
+    """Two groups of waves and four query heads per workgroup: more blocks of 128 queries x one head than compute units (288),
+    but not of 32 queries x four heads (252), and 44 key tiles, most of them a cached prefix with hidden runs."""
+    vis = np.ones(2100, dtype=np.uint8)
+    vis[:70] = 0
+    vis[900:1300] = 0
+    parent, segs = [-1, 0, 0, 2], [200, 141, 250, 50]
+    _prefix_case("bf16", 25, 2100, vis, W._mk(parent, segs, [1] * 4, "four heads"), 48, 4, 128)
