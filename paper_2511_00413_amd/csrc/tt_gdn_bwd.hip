@@ -537,11 +537,13 @@ size_t carve(char* p, int64_t n_tokens, int n_chunks, int n_slots, int n_segment
   return off + 256;
 }
 
-// One value head per workgroup of the finish kernel where a call has few (chunk, key head) pairs (the chip holds 512
-// workgroups): there the value heads side by side are worth more than the fp32 dq / dk saved.  Whole backward, two value
-// heads per key head, one by one / in one workgroup: 164 pairs 200 / 208 us, 328 pairs 221 / 225, 332 pairs (longer walk)
-// 317 / 316, 408 pairs 279 / 265, 664 pairs 443 / 430, 1328 pairs 636 / 610.  The whole call decides, not the pass: results do not depend on how much workspace there is.
-constexpr int64_t FINISH_SPLIT_BELOW = 384;
+// One value head per workgroup of the finish kernel where a call has so few (chunk, key head) pairs that two value heads each have a
+// compute unit of their own (the kernel holds one): beyond that the fp32 dq / dk, written and read again, cost more than a shorter last round
+// saves.  Whole backward, value heads one by one / in one workgroup, two value heads per key head: 74 pairs 99 / 103 us, 115 125 / 127, 140
+// 148 / 141, 237 211 / 200, 280 157.5 / 154.5, 366 202 / 193, 504 195 / 170, 1076 411 / 355;  three: 180 149 / 136, 280 195 / 193;  four: 74
+// 121 / 128, 115 148 / 153, 140 173 / 167, 345 258 / 227.  The whole call decides, not the pass: results do not depend on how much
+// workspace there is.
+constexpr int64_t FINISH_SPLIT_BELOW = 128;
 bool finish_split(int n_chunks, int hk, int hv) { return hv > hk && (int64_t)n_chunks * hk < FINISH_SPLIT_BELOW; }
 
 }  // namespace

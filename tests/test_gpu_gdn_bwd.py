@@ -148,9 +148,9 @@ def test_chunk_boundary_lengths():
     _check(W._mk(parent, seg, [1] * len(seg), "boundaries"), 1, 2, 77)
 
 
-@pytest.mark.parametrize("n_nodes,hk,hv", [(11, 32, 64), (12, 32, 64), (16, 32, 96), (3, 171, 171)])
+@pytest.mark.parametrize("n_nodes,hk,hv", [(3, 42, 84), (4, 32, 64), (11, 32, 64), (12, 32, 64), (16, 32, 96), (1, 127, 381), (3, 171, 171)])
 def test_value_heads_of_a_workgroup(n_nodes, hk, hv):
-    """From 384 (chunk, key head) pairs on, one workgroup takes all value heads of a key head and sums dq and dk on chip;
+    """From 128 (chunk, key head) pairs on, one workgroup takes all value heads of a key head and sums dq and dk on chip;
     below, every value head has a workgroup of its own.  Both sides of that line, two and three value heads per key head
     and one; passes over a part of the key heads give the same bits."""
     parent = [-1] + [(i - 1) // 2 for i in range(1, n_nodes)]
@@ -179,7 +179,7 @@ def test_value_heads_of_a_workgroup_full_chunks(rep):
     heads = [0, 17, 39]
     vheads = [h * rep + r for h in heads for r in range(rep)]
     plan = T.tree_gdn_plan(parent, seg).to_device()
-    assert plan.n_chunks * hk >= 384 and plan.n_chunks * len(heads) < 384
+    assert plan.n_chunks * hk >= 128 and plan.n_chunks * len(heads) < 128
     print(f"[case] gdn bwd n={n} hk={hk} hv={hv}: {plan.n_chunks} chunks", flush=True)
     part = lambda got: [x.float().cpu().numpy()[:, heads if i < 2 else vheads] for i, x in enumerate(got)]      # noqa: E731
     got = part(T.tree_gdn_bwd(*(x.cuda() for x in (q, k, v, g, beta, d_o)), plan))

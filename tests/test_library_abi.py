@@ -152,9 +152,9 @@ def test_gdn_backward_workspace_parts():
     lib = T.binding._lib()
     per = 64 * 4 + 3 * 32 * 32 * 4 + (4 * 64 * 128 + 64 * 64) * 2 + (64 * 128 + 64 * 64) * 2 + 4 + 2 * 128 * 128 * 2 + 2 * 64 * 128 * 2
     slack = 16 * 256 + 256                              # every array starts on 256 bytes
-    for n_chunks, hk, hv in [(269, 16, 32), (40, 16, 32), (12, 32, 64), (11, 32, 64), (50, 8, 8)]:
+    for n_chunks, hk, hv in [(269, 16, 32), (40, 16, 32), (12, 32, 64), (11, 32, 64), (4, 32, 64), (3, 42, 84), (50, 8, 8)]:
         n = 64 * n_chunks
-        split = hv > hk and n_chunks * hk < 384
+        split = hv > hk and n_chunks * hk < 128
         want = per * n_chunks * hv + (2 * n * hv * 128 * 4 if split else 0)
         got = lib.tt_tree_gdn_bwd_workspace(n, n_chunks, 0, 0, hk, hv)
         assert want <= got <= want + slack, (n_chunks, hk, hv, got - want)
