@@ -585,9 +585,9 @@ tt_status tt_tree_gdn_fwd(int64_t n_tokens, int32_t hk, int32_t hv, int32_t dk, 
  * start from.  Arithmetic: matrix products use bf16 operands with fp32 accumulation, like the
  * forward (state and state gradient stay fp32); the triangular solves and all element-wise work
  * are fp32.
- * Workspace, 16-byte aligned: tt_tree_gdn_bwd_workspace bytes let all heads run in one pass (stated as
- * 210 KB per chunk and value head, of which about 120 KB are used, 2 x n_slots saved states per head
- * and, with a schedule, one state gradient per segment and head; n_segments = 0 when the call gets no schedule; plus two fp32
+ * Workspace, 16-byte aligned: tt_tree_gdn_bwd_workspace bytes let all heads run in one pass (118 KB
+ * per chunk and value head, 2 x n_slots saved states per head and, with a schedule, one state gradient
+ * per segment and head; n_segments = 0 when the call gets no schedule; plus two fp32
  * [n_tokens][hv][128] arrays if hv > hk and n_chunks * hk < 128).  The heads are independent up to the sum over the value heads
  * of a key head, so any size from tt_tree_gdn_bwd_workspace_min (one key head with its value heads
  * per pass) upwards is accepted: the call then runs in passes of as many key heads as fit -- less

@@ -548,16 +548,17 @@ bool finish_split(int n_chunks, int hk, int hv) { return hv > hk && (int64_t)n_c
 
 }  // namespace
 
-// The size callers are told: 209156 bytes per (chunk, value head), what the call took when the walks' operands were stored in
-// full, where 118 KB are used now.  It stays, with the smallest size that is accepted, so that budgets and buffers made for it
-// mean what they meant; a pass takes as many heads as fit by what is used.
+// What carve takes, at most: 118 KB per (chunk, value head), the states, and the words that the walks synchronise with counted for as
+// many slots and segments as there are chunks (a program has no more), so that a segment adds its gradient and nothing else.
+// (It was 209156 bytes per chunk and head, what the call took when the walks' operands were stored in full: 0.8 GB of 1.9 at 16406
+// tokens of 16 / 32 heads were never touched.)
 size_t gdn_bwd_workspace(int64_t n_tokens, int n_chunks, int n_slots, int n_segments, int hk, int hv, int key_heads_per_pass) {
-  constexpr size_t STATED = 209156;
-  static_assert(GC * 4 + GDN_REC_ELEMS * 2 + 4 * GD * GD + 4 * GC * GD <= STATED, "the arrays of carve");
+  constexpr size_t PER_CHUNK = GC * 4 + GDN_REC_ELEMS * 2 + 4 * GD * GD + 4 * GC * GD;
   const int hv_n = key_heads_per_pass * (hv / hk);
-  const size_t per = (size_t)n_chunks * hv_n, arrays = 16 * 256;
-  const size_t states = (size_t)(2 * n_slots + n_segments) * hv * GD * GD * 4;
-  return align256(per * STATED) + states + (finish_split(n_chunks, hk, hv) ? 2 * align256((size_t)n_tokens * hv_n * GD * 4) : 0) + arrays;
+  const size_t arrays = 16 * 256;
+  const size_t sync = ((size_t)n_chunks + std::max(n_chunks, n_slots)) * hv_n * 16;
+  const size_t states = (size_t)(2 * (size_t)n_slots + n_segments) * hv * GD * GD * 4;
+  return align256((size_t)n_chunks * hv_n * PER_CHUNK + sync) + states + (finish_split(n_chunks, hk, hv) ? 2 * align256((size_t)n_tokens * hv_n * GD * 4) : 0) + arrays;
 }
 
 // The value heads are independent of each other up to the final sum over the value heads of a key head, so the
