@@ -212,7 +212,7 @@ __device__ __forceinline__ void process_tile(const uint32_t (&ra)[8], const uint
 // chain of tiles, and two waves per SIMD as with two workgroups per compute unit.
 template <int NG, int LG_HEADS>
 __global__ void __launch_bounds__(NG * NTHREADS, 2)
-tree_attn_fwd_kernel(AttnArgs a, int n_qtiles) {
+tree_attn_fwd_kernel(AttnArgs a, int n_qtiles, int n_alone) {
   extern __shared__ __align__(1024) unsigned char smem_raw[];
   const int lane = threadIdx.x & 63;
   const int w_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -221,18 +221,20 @@ tree_attn_fwd_kernel(AttnArgs a, int n_qtiles) {
   const int c32 = lane & 31, hf = lane >> 5;
   const int G = a.hq / a.hkv;
   // consecutive workgroups take different kv heads (they land on different XCDs, so each XCD's L2
-  // keeps serving the same K/V head); heavy (late) query tiles are issued first
-  const int bid = blockIdx.x;
+  // keeps serving the same K/V head); heavy (late) query tiles are issued first; of several heads per workgroup the first
+  // n_alone workgroups take one head each of the last queries, those behind the n_qtiles blocks (attn_last_alone)
+  const bool alone = LG_HEADS > 0 && (int)blockIdx.x < n_alone;
+  const int bid = LG_HEADS > 0 && !alone ? blockIdx.x - n_alone : blockIdx.x;
   const int kvh = bid % a.hkv;
   const int rest = bid / a.hkv;
   constexpr int HEADS = 1 << LG_HEADS;
   const int hg = rest % (G / HEADS);                 // this workgroup's HEADS query heads of the kv head, one per wave
-  const int h = kvh * G + hg * HEADS + w % HEADS;
-  const int qt = n_qtiles - 1 - rest / (G / HEADS);
+  const int h = kvh * G + (alone ? rest : hg * HEADS + w % HEADS);
+  const int qt = alone ? n_qtiles : n_qtiles - 1 - rest / (G / HEADS);
   constexpr int QUERIES = BM / HEADS;
-  const int q0 = qt * QUERIES, wq = w / HEADS;
+  const int q0 = qt * QUERIES, wq = alone ? w : w / HEADS;
   const int P = a.n_prefix, N = a.n_q;
-  const int q_hi = min(q0 + QUERIES, N);                  // one past the last valid query
+  const int q_hi = alone ? N : min(q0 + QUERIES, N);   // one past the last valid query
   const int gi_first = P + q0, gi_last = P + q_hi - 1;
   const int npt = (P + BN - 1) / BN;                 // prefix tiles
   const int u_end = npt + (q_hi - 1) / BN + 1;       // own tiles up to the diagonal
@@ -406,7 +408,7 @@ bool attn_two_groups(const AttnArgs& a, int64_t blocks, int min_tiles) {
 // 777 tokens of 32 / 8 heads 16.5 / - / 14.9; 4000 of 16 / 4 29.9 / 28.0 / 28.0; chain of 4000 of 32 / 8 132.1 / 131.0 / 129.5; 16384 of 32 / 8 716 / - / 685.
 // Launches that leave compute units over: 2 and 4 are alike, but for 300 to 700 tokens, where 2 is better (chain of 300 of 16 / 4 13.6 / 14.0 / 14.3;
 // trees of 300 of 32 / 8 13.3 / 13.0 / 13.5, 1000 of 16 / 4 14.5 / 12.7 / 13.3).  Those of less than half a chip with few tiles have nothing to
-// win by it and lose up to 4 % (300 tokens of 16 / 4); in chains of 700 of 32 / 8 all of 22.8 / 23.5 / 23.7 stays (trees there 18.4 / - / 16.7).
+// win by it and lose up to 4 % (300 tokens of 16 / 4).  (What chains lost by it attn_last_alone gives back.)
 int attn_lg_heads(const AttnArgs& a) {
   const int G = a.hq / a.hkv, n_cu = compute_units();
   const int64_t blocks = (int64_t)((a.n_q + BM - 1) / BM) * a.hq;
@@ -414,17 +416,40 @@ int attn_lg_heads(const AttnArgs& a) {
   return most == 2 && G % 4 == 0 ? 2 : most >= 1 && G % 2 == 0 ? 1 : 0;
 }
 
+// Where the last queries' workgroups take one head each again (first such query; n_q: nowhere): two waves of 32 queries instead of four.  In a
+// chain the last queries see the most keys, and a workgroup of two waves takes a tile 10 % faster.  Until this rule, sharing cost chains
+// whose last 128 queries are half empty up to 9 %.  us, one head per workgroup / shared / shared but for the last: chains of 316 tokens of 64 / 8 heads
+// 12.8 / 14.0 / 12.8, 444 and 700 of 32 / 8 15.1 / 16.2 / 15.0 and 21.1 / 22.1 / 21.0, 956 of 16 / 4 24.9 / 26.2 / 24.9 (and 500 of 32 / 8, whose last 128
+// are not, 18.3 / 18.1 / 17.0), trees of 444 and 700 12.7 / 12.4 / 12.5 and 14.6 / 12.9 / 12.9.  That is two heads per workgroup, where all
+// workgroups have a compute unit.  Four heads, launches that are on the chip all at once, and only if the last 128 are half empty: chains of 572 and 700 of 64 / 8
+// 20.8 / 22.0 / 21.0 and 23.9 / 24.6 / 23.9, 1084 of 32 / 8 28.6 / 29.5 / 28.6, trees of 700 of 64 / 8 17.1 / 16.7 / 15.8, 1084 of 32 / 8 17.1 / 15.2 / 15.4.
+// (Longer: 16406 of 32 / 8 335 / 312 / 315, a chain of 4140 134 / 128 / 133.)
+static int attn_last_alone(const AttnArgs& a, int lg) {
+  const int n_cu = compute_units();
+  if (lg == 1) {
+    const int64_t blocks = (int64_t)((a.n_q + 63) / 64) * (a.hq / 2);
+    if (blocks + a.hq / 2 <= n_cu) return (a.n_q - 1) / 64 * 64;
+  } else if (lg == 2 && (a.n_q - 1) % 128 < 64) {
+    const int from = (a.n_q - 1) / 128 * 128;
+    const int64_t blocks = (int64_t)((a.n_q + 31) / 32) * (a.hq / 4);
+    if (blocks > n_cu && (int64_t)(from / 32) * (a.hq / 4) + a.hq <= 2 * n_cu) return from;
+  }
+  return a.n_q;
+}
+
 hipError_t mfma_attn_fwd(const AttnArgs& a, hipStream_t st) {
   if (a.n_q == 0) return hipSuccess;
-  const int lg = attn_lg_heads(a), bm = BM >> lg, n_qtiles = (a.n_q + bm - 1) / bm;
-  const int64_t blocks = (int64_t)n_qtiles * (a.hq >> lg);
+  const int lg = attn_lg_heads(a), bm = BM >> lg;
+  const int alone_from = attn_last_alone(a, lg), n_alone = alone_from < a.n_q ? a.hq : 0;
+  const int n_qtiles = (alone_from + bm - 1) / bm;
+  const int64_t blocks = (int64_t)n_qtiles * (a.hq >> lg) + n_alone;
   const bool two = attn_two_groups(a, blocks, 24);
   const auto kernel = two ? (lg == 0 ? tree_attn_fwd_kernel<2, 0> : lg == 1 ? tree_attn_fwd_kernel<2, 1> : tree_attn_fwd_kernel<2, 2>)
                           : (lg == 0 ? tree_attn_fwd_kernel<1, 0> : lg == 1 ? tree_attn_fwd_kernel<1, 1> : tree_attn_fwd_kernel<1, 2>);
   const int lds = (two ? 2 : 1) * (int)sizeof(Smem);
   if (hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds)) return e;
   KernelTimer timer(TT_KERNEL_ATTN_FWD, st);
-  kernel<<<(unsigned)blocks, (two ? 2 : 1) * NTHREADS, lds, st>>>(a, n_qtiles);
+  kernel<<<(unsigned)blocks, (two ? 2 : 1) * NTHREADS, lds, st>>>(a, n_qtiles, n_alone);
   return hipGetLastError();
 }
 

@@ -371,3 +371,17 @@ def test_bf16_two_wave_groups_of_four_heads():
     vis[900:1300] = 0
     parent, segs = [-1, 0, 0, 2], [200, 141, 250, 50]
     _prefix_case("bf16", 25, 2100, vis, W._mk(parent, segs, [1] * 4, "four heads"), 48, 4, 128)
+
+
+@pytest.mark.parametrize("hq,hkv,n", [(12, 2, 64), (12, 2, 65), (12, 2, 129), (12, 2, 257), (32, 8, 700), (64, 8, 512), (64, 8, 513), (64, 8, 545),
+                                      (64, 8, 576), (64, 8, 577)])
+def test_bf16_last_queries_one_head_per_workgroup(hq, hkv, n):
+    """Where heads share workgroups the last queries' may take one head each: the last 1 .. 64 in launches of two heads that leave
+    compute units over (the whole of 64 tokens among them), the last 1 .. 64 of 128 in those of four, and not from 65 on (577: 5 blocks of 64
+    heads are more than the compute units).  A line and a tree, and behind a prefix of 24 key tiles and more with two groups of waves."""
+    for parent, segs in (([-1], [n]), ([-1, 0, 0], [n // 3, n // 2, n - n // 3 - n // 2])):
+        _full_parity(W._mk(parent, segs, [1] * len(segs), "last alone"), W.AttnDims(hq, hkv, 128, "bf16", 0.5), n + hq, label="last alone")
+    if n in (65, 129):
+        vis = np.ones(1600, dtype=np.uint8)
+        vis[64:200] = 0
+        _prefix_case("bf16", hq + n, 1600, vis, W._mk([-1], [n], [1], "last alone"), hq, hkv, 128)
