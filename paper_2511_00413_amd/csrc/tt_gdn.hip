@@ -121,8 +121,7 @@ __global__ __launch_bounds__(G_THREADS, 3) void gdn_prepare_kernel(GdnArgs a) {
   __shared__ __attribute__((aligned(1024))) PrepSmem sm;
   for (int i = (int)blockIdx.x * G_THREADS + (int)threadIdx.x; i < a.n_sync; i += (int)gridDim.x * G_THREADS) a.slot_sync[i] = WalkSync{};
   const int rep = a.hv / a.hk;
-  int chunk, kh;
-  if (!gdn_group_order(blockIdx.x, a.n_chunks, a.hk_n, 1, chunk, kh)) return;
+  const int chunk = (int)blockIdx.x % a.n_chunks, kh = (int)blockIdx.x / a.n_chunks;
   const int lane = threadIdx.x & 63, c = lane & 31, hf = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int tok0 = a.chunk_tok0[chunk], len = a.chunk_len[chunk];
@@ -1264,7 +1263,7 @@ hipError_t gdn_fwd(int64_t n_tokens, int hk, int hv, float scale, const void* q,
   set_sync(a, (char*)a.slots + align256((size_t)n_slots * hv * GD * GD * 4), n_slots, 0, sched);
   {
     KernelTimer t(TT_KERNEL_GDN_PREPARE, st);
-    gdn_prepare_kernel<false><<<gdn_group_order_grid(n_chunks, hk, 1), G_THREADS, 0, st>>>(a);
+    gdn_prepare_kernel<false><<<(unsigned)n_chunks * (unsigned)hk, G_THREADS, 0, st>>>(a);
   }
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   KernelTimer t(TT_KERNEL_GDN_SCAN, st);
@@ -1284,7 +1283,7 @@ hipError_t gdn_bwd_prepare_and_walks(const GdnBwdArgs& b, const GdnBwdSaved& sv,
   set_sync(a, sv.sync, b.n_slots, b.sched ? b.sched->n_segments : 0, b.sched);
   {
     KernelTimer t(TT_KERNEL_GDN_PREPARE, st);
-    gdn_prepare_kernel<true><<<gdn_group_order_grid(b.n_chunks, a.hk_n, 1), G_THREADS, 0, st>>>(a);
+    gdn_prepare_kernel<true><<<(unsigned)b.n_chunks * (unsigned)a.hk_n, G_THREADS, 0, st>>>(a);
   }
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   {

@@ -72,14 +72,6 @@ __device__ __forceinline__ bf16x8 kmajor_frag(const __bf16* slab, int pitch, int
   return cat4(lds_read_tr(p), lds_read_tr(p + 4 * pitch));
 }
 
-// The same for 8 k in the order in which an accumulator's registers enumerate rows: k0 .. k0 + 3 and k0 + 8 .. k0 + 11
-// (k0 = 16 s + 4 hf of k-step s) -- the B operand that matches an A operand taken straight from accumulator registers.
-__device__ __forceinline__ bf16x8 kmajor_frag_acc_order(const __bf16* slab, int pitch, int k0, int n0, int lane) {
-  const int i = lane & 15;
-  const __bf16* p = slab + (k0 + (i >> 2)) * pitch + n0 + 4 * (i & 3);
-  return cat4(lds_read_tr(p), lds_read_tr(p + 8 * pitch));
-}
-
 // max / sum of a value with the lane 32 positions away (the other half of the same column)
 __device__ __forceinline__ float half_swap_max(float x) {
   auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
@@ -277,24 +269,5 @@ struct KTileIter {
     return tile0 + (win - 1) * 64 + b;
   }
 };
-
-// Workgroup order of the gated delta rule's per-(chunk, value head) kernels.  The value heads of one key head read the
-// same q and k rows; workgroups are dealt to the chip's 8 XCDs (each with its own L2) round-robin by their linear id,
-// so the `group` members of a (chunk, key head) pair get ids that differ by multiples of 8 and follow each other
-// directly on their XCD: they run at the same time behind the same L2.  The grid is padded to whole rounds of 8
-// pairs; a workgroup past the last pair gets `false` and returns.
-constexpr unsigned GDN_XCDS = 8;
-inline unsigned gdn_group_order_grid(int n_chunks, int hv_n, int group) {
-  const unsigned pairs = (unsigned)n_chunks * (unsigned)(hv_n / group);
-  return (pairs + GDN_XCDS - 1) / GDN_XCDS * GDN_XCDS * (unsigned)group;
-}
-__device__ __forceinline__ bool gdn_group_order(unsigned id, int n_chunks, int hv_n, int group, int& chunk, int& h) {
-  const unsigned xcd = id % GDN_XCDS, t = id / GDN_XCDS;
-  const unsigned member = t % (unsigned)group, pair = t / (unsigned)group * GDN_XCDS + xcd;
-  if (pair >= (unsigned)n_chunks * (unsigned)(hv_n / group)) return false;
-  chunk = (int)(pair % (unsigned)n_chunks);
-  h = (int)(pair / (unsigned)n_chunks) * group + (int)member;
-  return true;
-}
 
 }  // namespace tt
