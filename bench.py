@@ -449,9 +449,10 @@ def leg_gdn(c):
         gt = T.kernel_timing_read()
         T.kernel_timing_enable(False)
         p_ms, s_ms = gt["gdn_prepare"][0] / n_it, gt["gdn_scan"][0] / n_it
-        # MFMA flop actually needed per 64-token chunk and head: K K^T, Q K^T (lower halves count in full here),
-        # W S0, Q S0, P Vn, K^T Vn
-        chunk_flop = 2.0 * (2 * 64 * 64 * 128 + 2 * 64 * 128 * 128 + 64 * 64 * 128 + 128 * 64 * 128)
+        # MFMA flop actually needed per 64-token chunk and value head: K K^T, Q K^T (once per key head; lower halves count in
+        # full here), K S0, Q S0, K^T Vn, T R, P Vn
+        pair_flop = 2 * 64 * 64 * 128 * ghk / ghv
+        chunk_flop = 2.0 * (pair_flop + 3 * 64 * 128 * 128 + 2 * 64 * 64 * 128)
         gdn = {"hk": ghk, "hv": ghv, "dk": 128, "dv": 128, "n_chunks": gplan.n_chunks, "saved_states": gplan.n_slots,
                "ms_prepare": round(p_ms, 4), "ms_scan": round(s_ms, 4), "ms_fwd": round(p_ms + s_ms, 4),
                "tokens_per_s": round(N / ((p_ms + s_ms) * 1e-3), 1),
@@ -474,12 +475,12 @@ def leg_gdn(c):
             ev[1].synchronize()
             bt = T.kernel_timing_read()
             T.kernel_timing_enable(False)
-            # multiply-adds per chunk and head of the backward as written (the forward walk it recomputes included)
-            bwd_flop = 2.0 * (2 * 64 * 64 * 128                       # prepare: K K^T, Q K^T
-                              + 64 * 128 * 128 * 2                    # forward walk: W S0, Kd^T Vn
-                              + 64 * 64 * 128 + 64 * 128 * 128 * 3    # reverse walk: P^T dO, Kd dS1, Qg^T dO, W^T dVn
-                              + 64 * 128 * 128 * 3 + 64 * 64 * 256 + 64 * 64 * 128   # finish: dW, dQg, dKd, dA, dP
-                              + 64 * 64 * 128 * 3 + 64 * 64 * 128)    # products with dP and dA, the two triangular solves
+            # multiply-adds per chunk and value head of the backward as written (the forward walk it recomputes included)
+            bwd_flop = 2.0 * (2 * pair_flop                              # K K^T, Q K^T in the prepare and in the finish kernel
+                              + 2 * 64 * 128 * 128 + 64 * 64 * 128       # forward walk: K S0, K^T Vn, T R
+                              + 3 * 64 * 128 * 128 + 2 * 64 * 64 * 128   # reverse walk: K dS1, Q^T dO, K^T dR, P^T dO, T^T dVn
+                              + 3 * 64 * 128 * 128 + 2 * 64 * 64 * 128   # finish: dQg, dKb, dKd, dP, dA
+                              + 4 * 64 * 64 * 128)                       # dP K, dP^T Q, dA K, dA^T K
             b_ms = ev[0].elapsed_time(ev[1]) / n_it
             gdn.update({"ms_bwd": round(b_ms, 4),
                         "ms_bwd_kernels": {"prepare": round(bt["gdn_prepare"][0] / n_it, 4), "forward_walk": round(bt["gdn_bwd_fscan"][0] / n_it, 4),
