@@ -516,8 +516,7 @@ tt_status tt_tree_conv_bwd_static(int64_t n_tokens, int32_t channels, int32_t ke
  *   it depends only on the segment that saved the slot its first chunk loads.  Level 0 holds the
  *   segments that start from the initial state, level l + 1 those whose slot a level-l segment
  *   saves: sibling subtrees land in one level and are walked by different workgroups at the same
- *   time.  Outputs, segments in level order (inside a level the longest
- *   first, ties in chunk order):
+ *   time.  Outputs, segments in level order (inside a level the longest first, ties in chunk order):
  *     seg_chunk0, seg_chunk1 [n_segments]  first chunk and one past the last chunk
  *     level_off [n_levels + 1]             segments of level l: level_off[l] .. level_off[l+1]-1
  *     slot_cons_off [n_slots + 1], slot_cons [n_consumers]   per slot, the segments that start
@@ -525,6 +524,9 @@ tt_status tt_tree_conv_bwd_static(int64_t n_tokens, int32_t channels, int32_t ke
  *                                          gradients in this order)
  *   The device calls take the schedule as tt_gdn_schedule (level_off stays a host array, the
  *   others are device copies); NULL = one set of workgroups walks all chunks in sequence order.
+ *   A schedule must be the one of the chunk arrays it is given with: the segments wait for each other on
+ *   the device, and where a state or gradient that one waits for is never stored, the wait ends after a
+ *   bounded time and what depends on it is NaN.
  * tt_tree_gdn_fwd (device): q, k [n_tokens][hk][128], v, o [n_tokens][hv][128] bf16 contiguous;
  *   g, beta [n_tokens][hv] fp32 (g <= 0: log of the decay); the chunk arrays are device
  *   copies of the plan (chunk_cap may be NULL = nothing captured).  initial_state [hv][128][128]
@@ -583,8 +585,10 @@ tt_status tt_tree_gdn_fwd(int64_t n_tokens, int32_t hk, int32_t hv, int32_t dk, 
  * (what the child partitions' d_initial_state returned; needs chunk_cap);
  * d_initial_state [hv][128][128] fp32, overwritten with the gradient of the state the roots
  * start from.  Arithmetic: matrix products use bf16 operands with fp32 accumulation, like the
- * forward (state and state gradient stay fp32); the triangular solves and all element-wise work
- * are fp32.
+ * forward (state and state gradient stay fp32); all element-wise work is fp32.  The inverse T of a
+ * chunk's triangular system is formed in fp32; the products with T - I, here and in the forward, take it
+ * as two bf16 halves (relative error 2^-17) and the right-hand sides rounded to bf16, and add the
+ * right-hand sides themselves in fp32.
  * Workspace, 16-byte aligned: tt_tree_gdn_bwd_workspace bytes let all heads run in one pass (118 KB
  * per chunk and value head, 2 x n_slots saved states per head and, with a schedule, one state gradient
  * per segment and head; n_segments = 0 when the call gets no schedule; plus two fp32
@@ -592,7 +596,7 @@ tt_status tt_tree_gdn_fwd(int64_t n_tokens, int32_t hk, int32_t hv, int32_t dk, 
  * of a key head, so any size from tt_tree_gdn_bwd_workspace_min (one key head with its value heads
  * per pass) upwards is accepted: the call then runs in passes of as many key heads as fit -- less
  * memory for more launches and walks that fill less of the chip; results do not depend on it.
- * With a schedule the reverse walk also runs level by level (last level first): every segment
+ * With a schedule the reverse walk too takes the segments by level (last level first): every segment
  * stores the gradient of the state it started from, and the chunk that saved a slot adds the
  * gradients of the slot's readers in the order of slot_cons -- a fixed order, no atomics.
  * Errors: as tt_tree_gdn_fwd.

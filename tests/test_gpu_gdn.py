@@ -1,5 +1,5 @@
 """GPU parity: gated delta rule with tree state routing (forward) against the fp64 token recurrence.
-Tolerance: the chunked kernel rounds its per-chunk operands (U, W, decayed Q / K, the entering
+Tolerance: the chunked kernel rounds its per-chunk operands (R, Vn, the decayed Q K^T, the entering
 state) to bf16 once each (2^-9 relative) and accumulates in fp32; rel-L2 <= 2e-2 on o, measured a
 few 1e-3."""
 import numpy as np
@@ -74,7 +74,7 @@ def test_routing_figure_and_reproducible():
 
 @pytest.mark.parametrize("seed", range(3))
 def test_level_schedule_equals_sequence_order(seed):
-    """Sibling subtrees walked side by side (one launch per dependency level of the chunk program) give bit-identical
+    """Sibling subtrees walked side by side (all dependency levels of the chunk program in one launch) give bit-identical
     outputs and captured states to one walk over all chunks in sequence order: every chunk does the same arithmetic
     on the same entering state, only when and where it runs differs."""
     t = W.random_tree(930 + seed, n_nodes=10 + 8 * seed, lo=1, hi=160, n_roots=1 + seed % 2, p_zero=0.15)

@@ -1,7 +1,7 @@
 """GPU parity: backward of the gated delta rule with tree state routing against the fp64 reverse recurrence.
 Like the forward, the kernels round the operands of their matrix products to bf16 once each (per-chunk
-operands, entering state, Vn, gradient of the leaving state, dVn, the solved right-hand sides) and accumulate in
-fp32; solves and element-wise work are fp32; dq, dk, dv are rounded to bf16 at the end (dq, dk after the fp32 sum
+operands, entering state, R, Vn, gradient of the leaving state, dVn, dR) and accumulate in
+fp32; the inverse of a chunk's triangular system and element-wise work are fp32; dq, dk, dv are rounded to bf16 at the end (dq, dk after the fp32 sum
 over the value heads of a key head).  Tolerance: rel-L2 <= 8e-3 on every output (a product of two or three
 operands rounded to bf16, fp32 sums; measured 2.3e-3 .. 3.4e-3)."""
 import numpy as np
@@ -50,7 +50,7 @@ def _check(tree, hk, hv, seed):
 
 @pytest.mark.parametrize("seed", range(3))
 def test_level_schedule_against_sequence_order(seed):
-    """The backward with the level schedule (forward walk and reverse walk one launch per dependency level, sibling
+    """The backward with the level schedule (forward walk and reverse walk one launch each over all levels, sibling
     subtrees side by side; state gradients of a slot's readers stored per segment and added in list order) against
     the walk over all chunks in sequence order.  dv and the per-chunk work are identical; where several readers'
     gradients meet, the two walks add them in a different association, so the comparison is to fp32 rounding of the
