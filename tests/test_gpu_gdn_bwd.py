@@ -324,3 +324,27 @@ def test_walks_of_two_and_of_four_waves():
             cut = (lambda t, h=h, i=i: t[h:h + 1] if i == 5 else t[:, h:h + 1])
             assert torch.equal(cut(a), c), (h, i)
             assert h == 64 or torch.equal(cut(b), c), (h, i)
+
+
+def test_more_segments_than_a_launch_has_rows():
+    """70 roots, 65500 branches of the first and what is below one of them: 65572 segments in three levels, walked by two launches whose
+    places go on where the first one's ended.  Against the walk over all chunks in sequence order: the same bits, but for the gradients of
+    the first root's three tokens.  There 65500 readers' gradients are added in another order: sqrt(65500) 2^-24 = 1.5e-5 of the
+    sum, by which one in 250 of its entries is rounded to the other bf16 neighbour (2^-8) on its way into the products: 2.5e-4 in them,
+    1e-3 behind another rounding to bf16.  Bounds: four times that."""
+    parent = [-1] * 70 + [0] * 65500 + [70, 70, 71]
+    seg = [3] * 70 + [1] * 65500 + [2, 66, 5]
+    plan = T.tree_gdn_plan(parent, seg).to_device()
+    assert plan.n_segments > 65535 and plan.n_levels == 3
+    ins = [x.cuda() for x in _inputs(sum(seg), 1, 1, 17)]
+    print(f"[case] gdn {plan.n_segments} segments", flush=True)
+    got = (T.tree_gdn_fwd(*ins[:5], plan),) + T.tree_gdn_bwd(*ins, plan)
+    torch.cuda.synchronize()
+    plan.parallel = False
+    print("[case] gdn in sequence", flush=True)
+    want = (T.tree_gdn_fwd(*ins[:5], plan),) + T.tree_gdn_bwd(*ins, plan)
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], want[0])
+    for a, b in zip(got[1:], want[1:]):
+        assert torch.equal(a[3:], b[3:])
+        assert rel_l2(a[:3].float().cpu().numpy(), b[:3].float().cpu().numpy()) <= (4e-3 if a.dtype == torch.bfloat16 else 1e-3)
